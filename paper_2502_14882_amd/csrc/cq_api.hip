@@ -343,14 +343,16 @@ int cq_quantize_kv(const cq_layout_t* L, const void* k_f16, const void* v_f16,
   const int rows = L->batch * L->n_kv_heads;
   if (do_k) {
     hipError_t e = (path != CQ_PATH_GENERIC && k_tuned)
-        ? cq::launch_quantize_tuned(k_f16, *k_out, rows, L->n_vis, L->bits, L->k_axis, L->k_group, s)
+        ? cq::launch_quantize_tuned(k_f16, *k_out, rows, L->n_vis, L->head_dim, L->bits, L->k_axis,
+                                    L->k_group, s)
         : cq::launch_quantize_generic(k_f16, *k_out, rows, L->n_vis, L->head_dim, L->bits,
                                       L->k_axis, L->k_group, s);
     if (e != hipSuccess) return hip_fail(e, "quantize keys");
   }
   if (do_v) {
     hipError_t e = (path != CQ_PATH_GENERIC && v_tuned)
-        ? cq::launch_quantize_tuned(v_f16, *v_out, rows, L->n_vis, L->bits, L->v_axis, L->v_group, s)
+        ? cq::launch_quantize_tuned(v_f16, *v_out, rows, L->n_vis, L->head_dim, L->bits, L->v_axis,
+                                    L->v_group, s)
         : cq::launch_quantize_generic(v_f16, *v_out, rows, L->n_vis, L->head_dim, L->bits,
                                       L->v_axis, L->v_group, s);
     if (e != hipSuccess) return hip_fail(e, "quantize values");

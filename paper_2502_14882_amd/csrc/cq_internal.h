@@ -107,10 +107,13 @@ hipError_t launch_tau_search(const DecodeShape& s, const void* q, const void* k_
                              double* mse_out, float* workspace, const TauWorkspace& wl,
                              hipStream_t stream);
 
-// Register-resident tile quantizer for head_dim 128, b in {1,2,4,8}, n_vis a multiple of 128,
-// groups of 32/64/128 or (channel axis) the whole sequence, which adds an extrema pass.
+// Register-resident tile quantizer (quantize_tile.h): head_dim 64, 128 or 256, b in {1,2,4,8}, any
+// channel-wise group of tokens, channel groups of 32 to 256, any n_vis.
 bool quantize_tuned_supported(int n_vis, int d, int bits, int axis, int group);
 hipError_t launch_quantize_tuned(const void* x_f16, const cq_qtensor_t& out, int rows, int n_vis,
+                                 int d, int bits, int axis, int group, hipStream_t stream);
+// its head dimensions other than 128
+hipError_t launch_quantize_heads(const void* x_f16, const cq_qtensor_t& out, size_t n_tokens, int d,
                                  int bits, int axis, int group, hipStream_t stream);
 
 // Merge the per-chunk partials [n_rows][n_chunks][d + 2] of the online softmax into out.

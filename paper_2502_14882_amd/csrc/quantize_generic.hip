@@ -5,8 +5,8 @@
 // their products with 2^b-1 <= 255 fit 53 bits); the single rounding is the fp64 division, whose
 // quotient is further from a half-integer than its rounding error unless it is an exact tie,
 // so round-to-nearest-even of it equals exact rational rounding with ties to even.
-// The tuned kernels replace this by per-group fp16 thresholds; these stay as the reference
-// path for every other shape.
+// The tile kernels (quantize_tile.h) replace this by per-group fp16 thresholds for head_dim 64, 128
+// and 256; these stay as the reference path, and for the other head dimensions.
 #include <hip/hip_fp16.h>
 
 #include "cq_internal.h"

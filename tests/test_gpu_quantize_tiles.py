@@ -1,0 +1,39 @@
+"""The tile quantizer away from round sizes: head dimensions 64 and 256, token counts that leave a
+short tile, groups of any size.  Codes, scale bits and minimum bits against the oracle, bit for bit."""
+import pytest
+import torch
+
+from oracle import cq_oracle as O
+from paper_2502_14882_amd import binding as cq
+from paper_2502_14882_amd import synth
+import helpers as H
+
+pytestmark = pytest.mark.gpu
+
+# (axis, group, n_vis): a last tile of 32 tokens; long groups one token over a tile, just under two
+# tiles, and a multiple of neither; two long groups per row; groups that are one short tile each;
+# a last tile of 1 and of 127 tokens
+SIZES = [(0, 32, 160), (0, 64, 192), (0, 129, 129), (0, 255, 510), (0, 1003, 1003), (0, 7, 21),
+         (0, 127, 127), (1, 32, 129), (1, 64, 255)]
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("bits", [1, 2, 4, 8])
+def test_short_tiles_and_any_group(d, bits):
+    prev = cq.cq_bench_set_kernel_path(cq.CQ_PATH_TUNED)      # no fallback to the shape-agnostic kernels
+    try:
+        for axis, group, n_vis in SIZES + [(1, d, 257)]:
+            what = "d %d bits %d axis %d group %d n_vis %d" % (d, bits, axis, group, n_vis)
+            print(what, flush=True)
+            w = synth.WORKLOADS[4].replace(batch=3, n_kv_heads=1, n_q_heads=1, head_dim=d, n_vis=n_vis,
+                                           seed=n_vis + d)
+            k = synth.make_inputs(w, "cpu", parts=("k",))["k"]
+            k[0, 0, :, 1] = 0.25                               # a constant channel
+            k[1, 0, n_vis - 1, 2] = -900.0                     # an extremum in the last token
+            k[2, 0, 0, d - 1] = 900.0                          # and in the first
+            lay = cq.make_layout(3, 1, 1, d, n_vis, bits, axis, axis, group, group)
+            got, _ = cq.cq_quantize_kv(lay, k.cuda(), None)
+            torch.cuda.synchronize()
+            H.assert_qtensor_equal(got, O.quantize_tensor(k.numpy(), bits, axis, group), what)
+    finally:
+        cq.cq_bench_set_kernel_path(prev)
