@@ -130,9 +130,11 @@ struct DecodeCall {
   float softmax_scale;
   bool tuned;               // the tuned kernels run (else the shape-agnostic ones)
   bool streamed;            // tuned, split rows: the streaming kernels with logits kept in scratch
+  bool tiled;               // not tuned: the tile kernels run (else the shape-agnostic ones)
   cq::FusedPlan plan;       // valid when tuned
   cq::StreamPlan stream;    // valid when streamed
-  cq::Workspace generic_ws; // valid when !tuned
+  cq::TilePlan tile;        // valid when tiled
+  cq::Workspace generic_ws; // valid when neither tuned nor tiled
   size_t ws_bytes;          // scratch the selected kernels touch
 };
 
@@ -175,9 +177,15 @@ int select_kernels(const cq_layout_t* L, int n_text, int n_text_cap, size_t scra
     call->stream = cq::make_stream_plan(call->shape, g_decode_chunks);
     call->streamed = call->stream.ok && call->stream.ws_bytes <= scratch_limit;
   }
+  call->tiled = false;
+  if (!call->tuned && g_kernel_path == CQ_PATH_AUTO) {
+    call->tile = cq::make_tile_plan(call->shape);
+    call->tiled = call->tile.ok && call->tile.ws_bytes <= scratch_limit;
+  }
   call->generic_ws = cq::workspace_layout(L->batch, L->n_q_heads, L->head_dim, L->n_vis, n_text);
   call->ws_bytes = call->streamed ? call->stream.ws_bytes
                    : call->tuned  ? call->plan.ws_bytes
+                   : call->tiled  ? call->tile.ws_bytes
                                   : call->generic_ws.total_bytes;
   return CQ_OK;
 }
@@ -230,6 +238,10 @@ int launch_decode(const DecodeCall& call, const void* q_f16, const cq_qtensor_t*
       ? cq::launch_decode_fused(call.shape, call.plan, q_f16, kq, vq, k_text_f16, v_text_f16,
                                 n_text_dev, call.calib, call.softmax_scale, out_f16,
                                 static_cast<float*>(workspace), st)
+      : call.tiled
+      ? cq::launch_decode_tile(call.shape, call.tile, q_f16, kq, vq, k_text_f16, v_text_f16,
+                               n_text_dev, call.calib, call.softmax_scale, out_f16,
+                               static_cast<float*>(workspace), st)
       : cq::launch_decode_generic(call.shape, q_f16, kq, vq, k_text_f16, v_text_f16, n_text_dev,
                                   call.calib, call.softmax_scale, out_f16,
                                   static_cast<float*>(workspace), call.generic_ws, st);

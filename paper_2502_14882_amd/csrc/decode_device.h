@@ -130,20 +130,10 @@ __device__ inline float lane_value(float v, int lane) {     // wave-uniform copy
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
 }
 
-// Additive post-scaling term of one key group, sum_c q'[h][c] * min[c] for the four heads.  Every
-// lane brings two channels (q' already carries the softmax scale and the lane's operand weight
-// w, which inv_w = 1/w takes out again, per channel).  A transposing butterfly leaves lane (.., b1, b0) with head
-// 2*b0 + b1 after two steps, the remaining steps add lanes that hold the same head; the result
-// lane of head kb = lane / 16 then fetches its head.
-// off0/off1: what the operand bytes leave out per channel (128 * scale for 8-bit codes, else 0).
-__device__ inline float group_bias(const float (&qv0)[kHeads], const float (&qv1)[kHeads],
-                                   uint16_t m0, uint16_t m1, float off0, float off1, float inv_w0,
-                                   float inv_w1, int lane) {
-  const float f0 = (__half2float(__ushort_as_half(m0)) + off0) * inv_w0;
-  const float f1 = (__half2float(__ushort_as_half(m1)) + off1) * inv_w1;
-  float part[kHeads];
-#pragma unroll
-  for (int h = 0; h < kHeads; ++h) part[h] = fmaf(qv0[h], f0, qv1[h] * f1);
+// Sum over the wave of the four heads' parts, head kb = lane / 16 in every lane of row kb.  A
+// transposing butterfly leaves lane (.., b1, b0) with head 2*b0 + b1 after two steps, the remaining
+// steps add lanes that hold the same head; the rows then exchange heads.
+__device__ inline float head_sums(const float (&part)[kHeads], int lane) {
   const bool b0 = lane & 1, b1 = lane & 2;
   float u0 = b0 ? part[2] : part[0], u1 = b0 ? part[3] : part[1];
   const float g0 = b0 ? part[0] : part[2], g1 = b0 ? part[1] : part[3];
@@ -168,6 +158,21 @@ __device__ inline float group_bias(const float (&qv0)[kHeads], const float (&qv1
   const float s13 = float_of(o[0]) + float_of(o[1]);            // head 1 | head 3
   const auto t = __builtin_amdgcn_permlane16_swap(bits_of(s02), bits_of(s13), false, false);
   return float_of(t[0]) + float_of(t[1]);                       // rows 0..3: heads 0, 1, 2, 3
+}
+
+// Additive post-scaling term of one key group, sum_c q'[h][c] * min[c] for the four heads.  Every
+// lane brings two channels (q' already carries the softmax scale and the lane's operand weight
+// w, which inv_w = 1/w takes out again, per channel).
+// off0/off1: what the operand bytes leave out per channel (128 * scale for 8-bit codes, else 0).
+__device__ inline float group_bias(const float (&qv0)[kHeads], const float (&qv1)[kHeads],
+                                   uint16_t m0, uint16_t m1, float off0, float off1, float inv_w0,
+                                   float inv_w1, int lane) {
+  const float f0 = (__half2float(__ushort_as_half(m0)) + off0) * inv_w0;
+  const float f1 = (__half2float(__ushort_as_half(m1)) + off1) * inv_w1;
+  float part[kHeads];
+#pragma unroll
+  for (int h = 0; h < kHeads; ++h) part[h] = fmaf(qv0[h], f0, qv1[h] * f1);
+  return head_sums(part, lane);
 }
 
 // Fixed-point operands are |x| < 2^29, four signed base-256 digits.  The wide range is needed

@@ -8,8 +8,9 @@
 //   combine  merge the chunk partials of the joint softmax and round to fp16
 //
 // Works for every layout the ABI accepts (any head_dim, group, axis, b in {1,2,4,8}) by
-// dequantizing element by element (code * scale + min, Sec. 2.2).  The tuned kernels are the fast
-// path; this one is the fallback and the on-device cross-check.
+// dequantizing element by element (code * scale + min, Sec. 2.2).  The fused, streaming and tile
+// kernels are the fast paths; this one takes what is left (token-wise keys, several value groups per
+// token, other head dimensions) and is the on-device cross-check.
 #include <hip/hip_fp16.h>
 
 #include <cfloat>

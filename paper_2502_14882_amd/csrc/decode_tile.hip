@@ -1,0 +1,759 @@
+// Decode attention over the packed cache for the layouts that the fused and the streaming kernels do
+// not take (gfx950): head_dim 64, 128 or 256, 1-, 2-, 4- or 8-bit codes, channel-wise keys in groups
+// of any number of tokens (Sec. 3.1 as printed: the whole sequence, whatever its length), values
+// token-wise with one group per token or channel-wise in groups of any number of tokens, any
+// number of query heads per KV head.
+//
+//   logits pass   (row, head set, chunk of the visual tokens) or (row, chunk of the fp16 tail) per
+//                 workgroup of 4 waves: raw logits in fp32 and the extrema of the chunk to the workspace
+//   values pass   the same division of the tokens into chunks of their own: g of Sec. 3.2 from the row's
+//                 extrema, weights, one partial (m, l, acc[D]) of the joint softmax per (head, chunk)
+//   combine       the shared kernel of decode_generic.hip
+//
+// Both contractions over packed codes run on the int8 matrix cores as in decode_fused.hip (codes
+// picked out of a word by AND masks, the other operand as four signed base-256 digits of a 29-bit
+// fixed-point number, 4 query heads = 16 matrix rows), here for any head_dim that is a multiple of 64.
+// A wave works for itself: it owns whole blocks of up to 128 tokens of one key group (logits) or a
+// run of 64-token tiles (values); groups and the row's end cut blocks and tiles short, a short one
+// reads its last token again and the surplus is neither stored nor weighted.
+//
+// Nothing is pipelined by hand: with 4-wave workgroups of at most 128 registers 16 waves share a CU
+// and hide each other's latency.  Bound: issue of vector instructions and, on small calls, the three
+// launches.  Against the shape-agnostic kernels, which dequantize element by element: 64 rows x 3003
+// tokens, 2 bits, whole-sequence keys and values 618 -> 21.6 us; 64 rows x 3328 tokens of 64
+// channels, 1 bit, 422 -> 18.9 us.  Over key and value groups from 1 to 48 tokens, head_dim 64 to 256
+// and 1 and 8 bits they are 1.8 (value groups of one token) to 26 times as fast, so they take every
+// layout they can.
+#include <hip/hip_fp16.h>
+
+#include <cfloat>
+
+#include "cq_internal.h"
+#include "decode_device.h"
+
+namespace cq {
+namespace {
+
+constexpr int kWaves = 4;
+constexpr int kThreads = kWaves * 64;
+constexpr int kKeyBlock = 128;       // most tokens per key block (8 tiles of 16)
+constexpr int kValTile = 64;         // tokens per value tile
+constexpr int kTextBlock = 256;      // tokens of the fp16 tail per workgroup and round: 64 per wave
+constexpr int kMaxRun = 1024;        // value tiles between two folds of the int32 digit sums (2^20 each)
+
+struct TileArgs {
+  const __half* q;
+  const uint32_t* k_codes; const float* k_scale; const uint16_t* k_min;
+  const uint32_t* v_codes; const float* v_scale; const uint16_t* v_min;
+  const __half* k_text; const __half* v_text;
+  int g, sets, n_vis, n_text, n_text_cap;    // sets = ceil(g / 4)
+  const int32_t* n_text_dev;   // NULL, or the tail length in device memory (n_text is then its bound)
+  int k_group, k_bpg;          // tokens per key group, blocks per group
+  int v_group, v_tpg;          // tokens per value group (token-wise: n_vis), tiles per group
+  int ca, ca_base, ca_rem;     // logits pass: chunks per row, in key blocks
+  int cb, cb_base, cb_rem;     // values pass: chunks per row, in value tiles
+  int ct, ct_tokens;           // chunks of the fp16 tail per row, tokens per chunk
+  float* ws_logits;            // [B*Hq][n_vis + n_text]
+  float* ws_minmax;            // [B*Hq][ca + ct][2]
+  float* ws_partial;           // [B*Hq][cb + ct][D + 2]
+  int calib_mode; float tau1, tau2, gamma, delta, softmax_scale;
+};
+
+// How the codes of a token become the operand registers of a lane.  A matrix product takes 64 codes,
+// 16 per lane (4 registers of 4 bytes); a token of D codes fills D / 64 products.  Lane row kb holds
+// `words` consecutive words of its token, register p is variant p % kV of word p / kV.  One-bit
+// codes of 64 channels are the exception: two words for four lane rows, so a lane row holds half
+// a word, shifted down by 4 where it is the upper half of every byte.
+template <int D, int BITS>
+struct Operand {
+  static constexpr int kProducts = D / 64;
+  static constexpr int kV = 8 / BITS;                       // variants (codes per byte)
+  static constexpr bool kHalf = D * BITS < 128;             // half a word per lane row
+  static constexpr int kWords = kHalf ? 1 : D * BITS / 128; // words per lane
+  static constexpr int kRowWords = D * BITS / 32;           // words per token
+  __device__ static int first_word(int kb) { return kHalf ? kb >> 1 : kb * kWords; }
+  __device__ static int shift(int kb) { return kHalf ? 4 * (kb & 1) : 0; }
+  // channel and variant of operand byte y of register p in lane row kb
+  __device__ static int channel(int kb, int p, int y) {
+    const int e = kHalf ? 0 : p / kV, v = kHalf ? p + 4 * (kb & 1) : p % kV;
+    return (32 / BITS) * (first_word(kb) + e) + code_in_word<BITS>(y, v);
+  }
+  __device__ static int variant(int p) { return kHalf ? p : p % kV; }
+  __device__ static int reg(const uint32_t (&w)[kWords], int p, int sh) {
+    return operand_variant<BITS>(kHalf ? w[0] >> sh : w[p / kV], variant(p));
+  }
+};
+
+template <int N>
+__device__ inline void load_words(uint32_t (&w)[N], const uint32_t* p) {
+  if constexpr (N == 1) {
+    w[0] = *p;
+  } else if constexpr (N == 2) {
+    const v2i t = *reinterpret_cast<const v2i*>(p);
+    w[0] = (uint32_t)t[0];
+    w[1] = (uint32_t)t[1];
+  } else {
+#pragma unroll
+    for (int e = 0; e < N / 4; ++e) {
+      const v4i t = reinterpret_cast<const v4i*>(p)[e];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) w[4 * e + u] = (uint32_t)t[u];
+    }
+  }
+}
+
+// min and max of the workgroup's waves for the 16 heads of a text workgroup or the 4 of a head set:
+// lane h of wave 0 stores head h
+__device__ inline void store_extrema(float (*red)[16][2], int n_heads, float* mm, size_t pitch) {
+  __syncthreads();
+  const int h = threadIdx.x;
+  if (h < n_heads) {
+    float lo = FLT_MAX, hi = -FLT_MAX;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      lo = fminf(lo, red[w][h][0]);
+      hi = fmaxf(hi, red[w][h][1]);
+    }
+    mm[h * pitch] = lo;
+    mm[h * pitch + 1] = hi;
+  }
+}
+
+// ===================================================================================== logits pass
+// A workgroup's share of the fp16 tail: all query heads of the KV head, 16 at a time, on the fp16
+// matrix cores (products of fp16 numbers are exact in fp32).  keys: the row's first text key.
+template <int D>
+__device__ inline void text_logits(const TileArgs& a, size_t row, int chunk, float (*red)[16][2]) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n16 = lane & 15, kb = lane >> 4;
+  const int n_text = a.n_text_dev ? min(max(*a.n_text_dev, 0), a.n_text) : a.n_text;
+  const int t0 = chunk * a.ct_tokens, t1 = min(t0 + a.ct_tokens, n_text);
+  const size_t n_all = (size_t)a.n_vis + a.n_text;
+  const __half* keys = a.k_text + row * (size_t)a.n_text_cap * D;
+  for (int h0 = 0; h0 < a.g; h0 += 16) {
+    const int nh = min(16, a.g - h0);
+    const size_t head0 = row * a.g + h0;
+    v8h A[D / 32];
+#pragma unroll
+    for (int s = 0; s < D / 32; ++s) {
+      const v8h z = {0, 0, 0, 0, 0, 0, 0, 0};
+      A[s] = n16 < nh ? *reinterpret_cast<const v8h*>(a.q + (head0 + n16) * D + 32 * s + 8 * kb) : z;
+    }
+    float mn[4], mx[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) { mn[r] = FLT_MAX; mx[r] = -FLT_MAX; }
+    for (int t = t0 + 16 * wave; t < t1; t += 16 * kWaves) {
+      const int tok = t + n16;
+      const __half* kp = keys + (size_t)min(tok, t1 - 1) * D + 8 * kb;
+      v4f c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < D / 32; ++s)
+        c = __builtin_amdgcn_mfma_f32_16x16x32_f16(A[s], *reinterpret_cast<const v8h*>(kp + 32 * s), c, 0, 0, 0);
+      if (tok < t1) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {          // result rows 4 kb + r are heads
+          if (4 * kb + r < nh) {
+            const float s = c[r] * a.softmax_scale;
+            a.ws_logits[(head0 + 4 * kb + r) * n_all + a.n_vis + tok] = s;
+            mn[r] = fminf(mn[r], s);
+            mx[r] = fmaxf(mx[r], s);
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float lo = row_min(mn[r]), hi = row_max(mx[r]);
+      if (n16 == 0) {
+        red[wave][4 * kb + r][0] = lo;
+        red[wave][4 * kb + r][1] = hi;
+      }
+    }
+    const size_t pitch = (size_t)(a.ca + a.ct) * 2;
+    store_extrema(red, nh, a.ws_minmax + head0 * pitch + (size_t)(a.ca + chunk) * 2, pitch);
+    __syncthreads();
+  }
+}
+
+// grid: rows * ct text workgroups, then rows * ca * sets visual ones
+template <int D, int BITS>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(D == 256 ? 2 : 4)))
+tile_logits_kernel(const TileArgs a, int n_text_wg) {
+  using Op = Operand<D, BITS>;
+  constexpr int NP = Op::kProducts;
+  __shared__ __align__(16) uint8_t s_x[kWaves][NP * 1024];     // query operand of a wave's key group
+  __shared__ float red[kWaves][16][2];
+  if ((int)blockIdx.x < n_text_wg) {
+    const unsigned row = blockIdx.x / (unsigned)a.ct;
+    text_logits<D>(a, row, (int)(blockIdx.x - row * (unsigned)a.ct), red);
+    return;
+  }
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n16 = lane & 15, kb = lane >> 4;
+  const unsigned piece = (blockIdx.x - n_text_wg) / (unsigned)a.sets;
+  const int set = (int)(blockIdx.x - n_text_wg - piece * (unsigned)a.sets);
+  const size_t row = piece / (unsigned)a.ca;
+  const int chunk = (int)(piece - row * a.ca);
+  const int b0 = chunk_first(a.ca_base, a.ca_rem, chunk), b1 = chunk_first(a.ca_base, a.ca_rem, chunk + 1);
+  const int gh = min(kHeads, a.g - set * kHeads);              // live heads of the set
+  const size_t head0 = row * a.g + (size_t)set * kHeads;
+  const size_t n_all = (size_t)a.n_vis + a.n_text;
+
+  // Writer of the query operand: lane l writes row l of every product (lane row l / 16, register
+  // (l / 4) % 4, byte l % 4), one channel each; together the lanes cover every channel once.
+  int ch[NP];
+  float inv_w[NP], qv[NP][kHeads];
+  float qmax = 0.f;
+#pragma unroll
+  for (int i = 0; i < NP; ++i) {
+    const int p = 4 * i + ((lane >> 2) & 3);
+    ch[i] = Op::channel(kb, p, lane & 3);
+    const float wgt = variant_weight<BITS>(Op::variant(p));
+    inv_w[i] = 1.f / wgt;                                      // exact: powers of two
+#pragma unroll
+    for (int h = 0; h < kHeads; ++h) {
+      const float qf = h < gh ? __half2float(a.q[(head0 + h) * D + ch[i]]) : 0.f;
+      qmax = fmaxf(qmax, fabsf(qf));
+      qv[i][h] = qf * (a.softmax_scale * wgt);
+    }
+  }
+  qmax = wave_max_nonneg(qmax) * a.softmax_scale;
+
+  uint8_t* xb = s_x[wave];
+  const uint8_t* x_rd = xb + (kb * 16 + (n16 >> 1)) * 16 + (n16 & 1) * 8;
+  const uint32_t* kc = a.k_codes + row * (size_t)a.n_vis * Op::kRowWords + Op::first_word(kb);
+  const int sh = Op::shift(kb);
+  const int n_groups = a.n_vis / a.k_group;
+  const size_t meta0 = row * (size_t)n_groups * D;
+  float* out = a.ws_logits + (head0 + min(kb, gh - 1)) * n_all;     // result lane: head kb, token n16
+  const bool live = kb < gh;
+
+  v4i A[NP];
+  float bias = 0.f, inv_f = 0.f, inv_f16 = 0.f, mn = FLT_MAX, mx = -FLT_MAX;
+  int have = -1;                                               // key group of the operand in A
+  for (int blk = b0 + wave; blk < b1; blk += kWaves) {
+    const int grp = a.k_bpg == 1 ? blk : blk / a.k_bpg;
+    const int t0 = grp * a.k_group + (blk - grp * a.k_bpg) * kKeyBlock;
+    const int t1 = min(t0 + kKeyBlock, (grp + 1) * a.k_group);
+    uint32_t w[2][Op::kWords];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      load_words<Op::kWords>(w[u], kc + (size_t)min(t0 + 16 * u + n16, t1 - 1) * Op::kRowWords);
+    if (grp != have) {                                         // wave-uniform
+      have = grp;
+      float s[NP], m[NP], smax = 0.f;
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
+        s[i] = a.k_scale[meta0 + (size_t)grp * D + ch[i]];
+        m[i] = __half2float(__ushort_as_half(a.k_min[meta0 + (size_t)grp * D + ch[i]]));
+        smax = fmaxf(smax, s[i]);
+      }
+      const int F = fixed_point_shift(qmax * wave_max_nonneg(smax));
+      float part[kHeads] = {0.f, 0.f, 0.f, 0.f};
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
+        const float sf = ldexpf(s[i], F);
+        v4i x;
+#pragma unroll
+        for (int h = 0; h < kHeads; ++h) x[h] = product_digits(qv[i][h], sf);
+        *reinterpret_cast<v4i*>(xb + i * 1024 + lane * 16) = x;
+        // 8-bit operand bytes are code - 128: the 128 comes back with the minimum
+        const float f = (m[i] + (BITS == 8 ? 128.f * s[i] : 0.f)) * inv_w[i];
+#pragma unroll
+        for (int h = 0; h < kHeads; ++h) part[h] = fmaf(qv[i][h], f, part[h]);
+      }
+      lds_publish();
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
+        const v2i lo = lds_read_tr8(x_rd + i * 1024), hi = lds_read_tr8(x_rd + i * 1024 + 128);
+        A[i] = (v4i){lo[0], lo[1], hi[0], hi[1]};
+      }
+      bias = head_sums(part, lane);
+      inv_f = ldexpf(1.f, -F);
+      inv_f16 = ldexpf(1.f, 16 - F);
+      __builtin_amdgcn_wave_barrier();
+    }
+    for (int t = t0; t < t1; t += 32) {                        // two tiles at a time
+      uint32_t wn[2][Op::kWords];
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+        load_words<Op::kWords>(wn[u], kc + (size_t)min(t + 32 + 16 * u + n16, t1 - 1) * Op::kRowWords);
+      v4i c[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
+        v4i B[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) B[u][v] = Op::reg(w[u], 4 * i + v, sh);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) c[u] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A[i], B[u], c[u], 0, 0, 0);
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int lo = c[u][0] + (c[u][1] << 8), hi = c[u][2] + (c[u][3] << 8);
+        const float s = fmaf((float)hi, inv_f16, fmaf((float)lo, inv_f, bias));
+        const int tok = t + 16 * u + n16;
+        if (tok < t1) {
+          if (live) out[tok] = s;
+          mn = fminf(mn, s);
+          mx = fmaxf(mx, s);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int e = 0; e < Op::kWords; ++e) w[u][e] = wn[u][e];
+    }
+  }
+  mn = row_min(mn);
+  mx = row_max(mx);
+  if (n16 == 0) {
+    red[wave][kb][0] = mn;
+    red[wave][kb][1] = mx;
+  }
+  const size_t pitch = (size_t)(a.ca + a.ct) * 2;
+  store_extrema(red, gh, a.ws_minmax + head0 * pitch + (size_t)chunk * 2, pitch);
+}
+
+// ===================================================================================== values pass
+// the workgroup's partial of the joint softmax for the heads of a set, from per-wave sums in LDS
+template <int D>
+__device__ inline void store_partial(const TileArgs& a, size_t head0, int gh, int slot, const float* m_ref,
+                                     const float (*s_part)[kHeads][D], const float (*s_lm)[kHeads][2]) {
+  __syncthreads();
+  for (int e = threadIdx.x; e < gh * D; e += kThreads) {
+    const int h = e / D, c = e % D;
+    float num = 0.f, den = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      num += s_part[w][h][c] + s_lm[w][h][1];
+      den += s_lm[w][h][0];
+    }
+    float* out = a.ws_partial + ((head0 + h) * (size_t)(a.cb + a.ct) + slot) * (D + 2);
+    if (c == 0) { out[0] = m_ref[h]; out[1] = den; }
+    out[2 + c] = num;
+  }
+}
+
+// A chunk of the fp16 tail: weights in fp32 (lane = token), then lane = (token slot, channel octet).
+template <int D>
+__device__ inline void text_values(const TileArgs& a, size_t row, int set, int chunk, float (*s_p)[kHeads],
+                                   float (*s_part)[kHeads][D], float (*s_lm)[kHeads][2]) {
+  constexpr int kOct = D / 8, kSlots = 64 / kOct;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n_text = a.n_text_dev ? min(max(*a.n_text_dev, 0), a.n_text) : a.n_text;
+  const int t0 = chunk * a.ct_tokens, t1 = min(t0 + a.ct_tokens, n_text);
+  const int gh = min(kHeads, a.g - set * kHeads);
+  const size_t head0 = row * a.g + (size_t)set * kHeads;
+  const size_t n_all = (size_t)a.n_vis + a.n_text;
+  const __half* vals = a.v_text + row * (size_t)a.n_text_cap * D;
+  float m_ref[kHeads], l[kHeads], acc[kHeads][8];
+#pragma unroll
+  for (int h = 0; h < kHeads; ++h) {
+    const float* mm = a.ws_minmax + (head0 + min(h, gh - 1)) * (size_t)(a.ca + a.ct) * 2;
+    m_ref[h] = t1 > t0 ? mm[(a.ca + chunk) * 2 + 1] : -FLT_MAX;   // an empty chunk has weight 0
+    l[h] = 0.f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc[h][j] = 0.f;
+  }
+  const int c8 = lane & (kOct - 1), ts = lane / kOct;
+  for (int t = t0 + 64 * wave; t < t1; t += 64 * kWaves) {
+    const int nt = min(64, t1 - t);
+    v4f p = {0.f, 0.f, 0.f, 0.f};
+    if (lane < nt) {
+#pragma unroll
+      for (int h = 0; h < kHeads; ++h)
+        if (h < gh)
+          p[h] = __builtin_amdgcn_exp2f((a.ws_logits[(head0 + h) * n_all + a.n_vis + t + lane] - m_ref[h]) * kLog2e);
+    }
+#pragma unroll
+    for (int h = 0; h < kHeads; ++h) l[h] += p[h];
+    __builtin_amdgcn_wave_barrier();
+    *reinterpret_cast<v4f*>(s_p[64 * wave + lane]) = p;
+    lds_publish();
+#pragma unroll 4
+    for (int i = 0; i < 64 / kSlots; ++i) {
+      if (i * kSlots >= nt) break;             // wave-uniform
+      const int j = i * kSlots + ts;           // past the end: the last token with weight 0
+      const v8h v = *reinterpret_cast<const v8h*>(vals + (size_t)(t + min(j, nt - 1)) * D + 8 * c8);
+      const v4f w = *reinterpret_cast<const v4f*>(s_p[64 * wave + j]);
+#pragma unroll
+      for (int h = 0; h < kHeads; ++h)
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc[h][u] = fmaf(w[h], (float)v[u], acc[h][u]);
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+#pragma unroll
+  for (int h = 0; h < kHeads; ++h) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+#pragma unroll
+      for (int o = kOct; o <= 32; o <<= 1) acc[h][u] += __shfl_xor(acc[h][u], o);
+      if (ts == 0) s_part[wave][h][8 * c8 + u] = acc[h][u];
+    }
+    const float lw = wave_sum(l[h]);
+    if (lane == 0) { s_lm[wave][h][0] = lw; s_lm[wave][h][1] = 0.f; }
+  }
+  store_partial<D>(a, head0, gh, a.cb + chunk, m_ref, s_part, s_lm);
+}
+
+// grid: rows * ct * sets text workgroups, then rows * cb * sets visual ones
+template <int D, int BITS, bool VCH>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(D == 256 || BITS == 8 ? 2 : 4)))
+tile_values_kernel(const TileArgs a, int n_text_wg) {
+  constexpr int CB = D * BITS / 8;                             // code bytes per token
+  constexpr int kV = 8 / BITS;
+  constexpr int kBlocks = CB >= 16 ? CB / 16 : 1;              // 16-byte column blocks (8 bytes: half of one)
+  constexpr int NACC = kBlocks * kV;
+  constexpr int SW = CB < 128 ? CB : 128;                      // bytes per token staged at a time
+  constexpr int kPasses = CB / SW;
+  constexpr int kPitch = SW >= 64 ? SW + 16 : SW;              // spreads the transposing reads over the banks
+  constexpr int kPieces = SW >= 16 ? SW / 16 : 1;              // 16-byte (8-byte) loads per lane and pass
+  constexpr int kPieceBytes = SW >= 16 ? 16 : 8;
+  struct Stage { uint8_t x[1024]; uint8_t codes[64 * kPitch]; };
+  union Mem {
+    Stage stage[kWaves];
+    float part[kWaves][kHeads][D];
+  };
+  __shared__ __align__(16) Mem mem;
+  __shared__ __align__(16) float s_lm[kWaves][kHeads][2];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool is_text = (int)blockIdx.x < n_text_wg;
+  const unsigned bid = is_text ? blockIdx.x : blockIdx.x - n_text_wg;
+  const unsigned piece = bid / (unsigned)a.sets, per_row = (unsigned)(is_text ? a.ct : a.cb);
+  const int set = (int)(bid - piece * (unsigned)a.sets);
+  const size_t row = piece / per_row;
+  const int chunk = (int)(piece - row * per_row);
+  if (is_text) {
+    __shared__ __align__(16) float s_tp[kWaves * 64][kHeads];
+    text_values<D>(a, row, set, chunk, s_tp, mem.part, s_lm);
+    return;
+  }
+  const int n16 = lane & 15, kb = lane >> 4;
+  const int gh = min(kHeads, a.g - set * kHeads);
+  const size_t head0 = row * a.g + (size_t)set * kHeads;
+  const size_t n_all = (size_t)a.n_vis + a.n_text;
+
+  // ---- calibration line and reference point per head (Sec. 3.2): lane 16 h + c folds chunks c,
+  // c + 16, ... of head h
+  float a2[kHeads], c2[kHeads], m_ref[kHeads];
+  {
+    const float* mm = a.ws_minmax + (head0 + min(kb, gh - 1)) * (size_t)(a.ca + a.ct) * 2;
+    float lo_l = FLT_MAX, hi_l = -FLT_MAX;
+    for (int c = n16; c < a.ca; c += 16) {
+      lo_l = fminf(lo_l, mm[2 * c]);
+      hi_l = fmaxf(hi_l, mm[2 * c + 1]);
+    }
+    lo_l = row_min(lo_l);
+    hi_l = row_max(hi_l);
+#pragma unroll
+    for (int h = 0; h < kHeads; ++h) {
+      const float lo = lane_value(lo_l, 16 * h), hi = lane_value(hi_l, 16 * h);
+      float slope = 1.f, gam = 0.f, shift = 0.f;               // s' = slope * (s - gam) + shift
+      if (a.calib_mode != CQ_CALIB_NONE) {
+        const float glo = a.calib_mode == CQ_CALIB_DYNAMIC ? lo : a.gamma;
+        const float ghi = a.calib_mode == CQ_CALIB_DYNAMIC ? hi : a.delta;
+        const float width = ghi - glo;
+        slope = width == 0.f ? 1.f : (width + a.tau1 - a.tau2) / width;
+        gam = glo;
+        shift = glo - a.tau1;
+      }
+      // the map is monotone: an end of the row's range is its maximum, every weight is <= 1
+      const float M = fmaxf(slope * (lo - gam) + shift, slope * (hi - gam) + shift);
+      m_ref[h] = M;
+      a2[h] = h < gh ? slope * kLog2e : 0.f;
+      c2[h] = h < gh ? (shift - slope * gam - M) * kLog2e : -200.f;     // no head: weight 0
+    }
+  }
+
+  // the wave's run of tiles
+  const int u0 = chunk_first(a.cb_base, a.cb_rem, chunk), u1 = chunk_first(a.cb_base, a.cb_rem, chunk + 1);
+  const int per = (u1 - u0) / kWaves, rem = (u1 - u0) % kWaves;
+  const int k0 = u0 + chunk_first(per, rem, wave), k1 = u0 + chunk_first(per, rem, wave + 1);
+
+  const uint8_t* vc = reinterpret_cast<const uint8_t*>(a.v_codes) + row * (size_t)a.n_vis * CB;
+  const float* vs = a.v_scale + row * (size_t)a.n_vis;         // token-wise
+  const uint16_t* vm = a.v_min + row * (size_t)a.n_vis;
+  const size_t meta0 = VCH ? row * (size_t)(a.n_vis / a.v_group) * D : 0;
+  const float* lg[kHeads];
+#pragma unroll
+  for (int h = 0; h < kHeads; ++h) lg[h] = a.ws_logits + (head0 + min(h, gh - 1)) * n_all;
+  uint8_t* xbuf = mem.stage[wave].x;
+  uint8_t* cbuf = mem.stage[wave].codes;
+  const uint8_t* x_rd = xbuf + (kb * 16 + (n16 >> 1)) * 16 + (n16 & 1) * 8;
+  // (8-byte tokens: the upper eight columns repeat the lower eight and are dropped at the end)
+  const uint8_t* v_rd = cbuf + (kb * 16 + (n16 >> 1)) * kPitch + (CB >= 16 ? (n16 & 1) * 8 : 0);
+  // channel of accumulator p (column block cb, variant v) in this lane
+  auto channel = [&](int p) {
+    const int tb = 16 * (p / kV) + (CB >= 16 ? n16 : n16 & 7);
+    return (32 / BITS) * (tb >> 2) + code_in_word<BITS>(tb & 3, p % kV);
+  };
+
+  v4i acc[NACC], acc_w = {0, 0, 0, 0};
+  float facc[NACC], lsum[kHeads], msum[kHeads];
+#pragma unroll
+  for (int p = 0; p < NACC; ++p) { acc[p] = (v4i){0, 0, 0, 0}; facc[p] = 0.f; }
+#pragma unroll
+  for (int h = 0; h < kHeads; ++h) lsum[h] = msum[h] = 0.f;
+  int F = 90;                                                  // token-wise: running fixed-point shift
+  float fit_below = ldexpf(1.f, 29 - 90);
+  int run = 0;
+
+  v4i piece_r[kPieces];
+  float lgv[kHeads], sc = 0.f;
+  uint16_t mi = 0;
+  auto tile_at = [&](int k, int& grp, int& tok0, int& nt) {
+    grp = a.v_tpg == 1 ? k : k / a.v_tpg;
+    const int sub = k - grp * a.v_tpg;
+    tok0 = grp * a.v_group + sub * kValTile;
+    nt = min(kValTile, a.v_group - sub * kValTile);
+  };
+  auto load_pieces = [&](int tok0, int nt, int pass) {
+    const uint8_t* base = vc + (size_t)tok0 * CB + pass * SW;
+#pragma unroll
+    for (int e = 0; e < kPieces; ++e) {
+      const int o = 64 * kPieceBytes * e + kPieceBytes * lane;
+      const uint8_t* p = base + (size_t)min(o / SW, nt - 1) * CB + o % SW;
+      if constexpr (kPieceBytes == 16) {
+        piece_r[e] = *reinterpret_cast<const v4i*>(p);
+      } else {
+        const v2i t = *reinterpret_cast<const v2i*>(p);
+        piece_r[e] = (v4i){t[0], t[1], 0, 0};
+      }
+    }
+  };
+  auto load_tile = [&](int k) {
+    int grp, tok0, nt;
+    tile_at(k, grp, tok0, nt);
+    const int j = tok0 + min(lane, nt - 1);
+#pragma unroll
+    for (int h = 0; h < kHeads; ++h) lgv[h] = lg[h][j];
+    if constexpr (!VCH) {
+      sc = vs[j];
+      mi = vm[j];
+    }
+    load_pieces(tok0, nt, 0);
+  };
+  if (k0 < k1) load_tile(k0);
+  for (int k = k0; k < k1; ++k) {
+    int grp, tok0, nt;
+    tile_at(k, grp, tok0, nt);
+    const bool have = lane < nt;
+    float vsf = 536870912.f, vmf = 0.f;                        // channel-wise: weights p * 2^29
+    if constexpr (!VCH) {
+      // the largest scale so far sets the shift; when it drops, bank the digit sums in fp32 first
+      // (the four digit sums of a value cannot be shifted one by one)
+      if (__builtin_amdgcn_ballot_w64(sc >= fit_below) != 0 || run == kMaxRun) {
+        const float w_old = ldexpf(1.f, -F);
+#pragma unroll
+        for (int p = 0; p < NACC; ++p) {
+          facc[p] = fmaf(digits_to_float(acc[p]), w_old, facc[p]);
+          acc[p] = (v4i){0, 0, 0, 0};
+        }
+        run = 0;
+        F = min(F, fixed_point_shift(wave_max_nonneg(sc)));
+        fit_below = ldexpf(1.f, 29 - F);
+      }
+      vsf = ldexpf(sc, F);
+      vmf = __half2float(__ushort_as_half(mi)) + (BITS == 8 ? 128.f * sc : 0.f);
+    }
+    v4i xs;
+#pragma unroll
+    for (int h = 0; h < kHeads; ++h) {
+      const float e = __builtin_amdgcn_exp2f(fmaf(lgv[h], a2[h], c2[h]));
+      const float p = have ? e : 0.f;
+      lsum[h] += p;
+      if constexpr (!VCH) msum[h] = fmaf(p, vmf, msum[h]);
+      xs[h] = product_digits(p, vsf);
+    }
+    const bool fold = VCH && (k + 1 == k1 || (k + 1 - grp * a.v_tpg) == a.v_tpg || run + 1 == kMaxRun);
+    float gs[VCH ? NACC : 1], gm[VCH ? NACC : 1];
+    if constexpr (VCH) {
+      if (fold) {                                              // wave-uniform
+#pragma unroll
+        for (int p = 0; p < NACC; ++p) {
+          const size_t at = meta0 + (size_t)grp * D + channel(p);
+          gs[p] = a.v_scale[at];
+          gm[p] = __half2float(__ushort_as_half(a.v_min[at]));
+        }
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+    *reinterpret_cast<v4i*>(xbuf + 16 * lane) = xs;
+    v4i A;
+#pragma unroll
+    for (int pass = 0; pass < kPasses; ++pass) {
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int e = 0; e < kPieces; ++e) {
+        const int o = 64 * kPieceBytes * e + kPieceBytes * lane;
+        uint8_t* dst = cbuf + (o / SW) * kPitch + o % SW;
+        if constexpr (kPieceBytes == 16) *reinterpret_cast<v4i*>(dst) = piece_r[e];
+        else *reinterpret_cast<v2i*>(dst) = (v2i){piece_r[e][0], piece_r[e][1]};
+      }
+      lds_publish();
+      if (pass == 0) {
+        const v2i lo = lds_read_tr8(x_rd), hi = lds_read_tr8(x_rd + 128);
+        A = (v4i){lo[0], lo[1], hi[0], hi[1]};
+      }
+      // the next loads go out under the products
+      if (pass + 1 < kPasses) load_pieces(tok0, nt, pass + 1);
+      else if (k + 1 < k1) load_tile(k + 1);
+      constexpr int kPassBlocks = SW >= 16 ? SW / 16 : 1;
+#pragma unroll
+      for (int cbl = 0; cbl < kPassBlocks; ++cbl) {
+        const v2i lo = lds_read_tr8(v_rd + 16 * cbl), hi = lds_read_tr8(v_rd + 16 * cbl + 8 * kPitch);
+        const v4i raw = {lo[0], lo[1], hi[0], hi[1]};
+#pragma unroll
+        for (int v = 0; v < kV; ++v) {
+          v4i B;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) B[u] = operand_variant<BITS>((uint32_t)raw[u], v);
+          const int p = (pass * kPassBlocks + cbl) * kV + v;
+          acc[p] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A, B, acc[p], 0, 0, 0);
+        }
+      }
+    }
+    ++run;
+    if constexpr (VCH) {
+      const v4i ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
+      acc_w = __builtin_amdgcn_mfma_i32_16x16x64_i8(A, ones, acc_w, 0, 0, 0);
+      if (fold) {
+        const float wsum = digits_to_float(acc_w) * 0x1p-29f;
+        acc_w = (v4i){0, 0, 0, 0};
+#pragma unroll
+        for (int p = 0; p < NACC; ++p) {
+          const float s = gs[p] * variant_weight<BITS>(p % kV);
+          const float add = gm[p] + (BITS == 8 ? 128.f * gs[p] : 0.f);
+          facc[p] = fmaf(digits_to_float(acc[p]) * 0x1p-29f, s, fmaf(wsum, add, facc[p]));
+          acc[p] = (v4i){0, 0, 0, 0};
+        }
+        run = 0;
+      }
+    }
+  }
+  __syncthreads();                                             // the stages become the partial sums
+  const float inv_f = ldexpf(1.f, -F);
+#pragma unroll
+  for (int p = 0; p < NACC; ++p) {
+    const float v = VCH ? facc[p]
+                        : fmaf(digits_to_float(acc[p]), inv_f, facc[p]) * variant_weight<BITS>(p % kV);
+    if (CB >= 16 || n16 < 8) mem.part[wave][kb][channel(p)] = v;
+  }
+#pragma unroll
+  for (int h = 0; h < kHeads; ++h) {
+    const float l = wave_sum(lsum[h]), m = wave_sum(msum[h]);
+    if (lane == 0) { s_lm[wave][h][0] = l; s_lm[wave][h][1] = m; }
+  }
+  store_partial<D>(a, head0, gh, chunk, m_ref, mem.part, s_lm);
+}
+
+using LogitsKernel = void (*)(const TileArgs, int);
+
+template <int D>
+LogitsKernel logits_kernel(int bits) {
+  switch (bits) {
+    case 1: return tile_logits_kernel<D, 1>;
+    case 2: return tile_logits_kernel<D, 2>;
+    case 4: return tile_logits_kernel<D, 4>;
+    case 8: return tile_logits_kernel<D, 8>;
+    default: return nullptr;
+  }
+}
+template <int D>
+LogitsKernel values_kernel(int bits, bool vch) {
+  switch (bits * 2 + (vch ? 1 : 0)) {
+    case 2: return tile_values_kernel<D, 1, false>;
+    case 3: return tile_values_kernel<D, 1, true>;
+    case 4: return tile_values_kernel<D, 2, false>;
+    case 5: return tile_values_kernel<D, 2, true>;
+    case 8: return tile_values_kernel<D, 4, false>;
+    case 9: return tile_values_kernel<D, 4, true>;
+    case 16: return tile_values_kernel<D, 8, false>;
+    case 17: return tile_values_kernel<D, 8, true>;
+    default: return nullptr;
+  }
+}
+
+}  // namespace
+
+TilePlan make_tile_plan(const DecodeShape& s) {
+  TilePlan p;
+  if (s.d != 64 && s.d != 128 && s.d != 256) return p;
+  if (s.bits != 1 && s.bits != 2 && s.bits != 4 && s.bits != 8) return p;
+  if (s.k_axis != CQ_AXIS_CHANNEL) return p;
+  if (s.v_axis != CQ_AXIS_CHANNEL && s.v_group != s.d) return p;
+  const long long rows = (long long)s.B * s.Hkv, sets = (s.g + kHeads - 1) / kHeads;
+  auto clamp = [](long long v, long long lo, long long hi) { return (int)(v < lo ? lo : v > hi ? hi : v); };
+  if (s.n_vis > 0) {
+    const long long blocks = (long long)(s.n_vis / s.k_group) * ceil_div(s.k_group, kKeyBlock);
+    const long long tiles = s.v_axis == CQ_AXIS_CHANNEL
+                                ? (long long)(s.n_vis / s.v_group) * ceil_div(s.v_group, kValTile)
+                                : ceil_div(s.n_vis, kValTile);
+    // four workgroups per CU, of at least one key block (two value tiles) per wave
+    const long long want = (1024 + rows * sets - 1) / (rows * sets);
+    p.ca = clamp(want, 1, clamp((blocks + kWaves - 1) / kWaves, 1, 64));
+    p.cb = clamp(want, 1, clamp((tiles + 2 * kWaves - 1) / (2 * kWaves), 1, 64));
+  }
+  // the tail does not change how the visual tokens are divided: a workspace for a longer tail serves
+  // a shorter one
+  p.ct_tokens = kTextBlock * ceil_div(ceil_div(s.n_text, kTextBlock), 64);
+  if (s.n_text > 0) p.ct = ceil_div(s.n_text, p.ct_tokens);
+  const size_t heads = (size_t)s.B * s.Hq;
+  auto align64 = [](size_t x) { return (x + 63) / 64 * 64; };
+  p.ws_minmax_floats = align64(heads * ((size_t)s.n_vis + s.n_text));
+  p.ws_partial_floats = align64(p.ws_minmax_floats + heads * (size_t)(p.ca + p.ct) * 2);
+  const size_t floats = p.ws_partial_floats + heads * (size_t)(p.cb + p.ct) * (s.d + 2);
+  p.ws_bytes = (floats * sizeof(float) + 255) / 256 * 256;
+  const long long most = rows * (sets > 0 ? sets : 1) * (64 + 64);
+  p.ok = most < 0x7fffffffLL;
+  return p;
+}
+
+hipError_t launch_decode_tile(const DecodeShape& s, const TilePlan& plan, const void* q,
+                              const cq_qtensor_t& k, const cq_qtensor_t& v, const void* k_text,
+                              const void* v_text, const int32_t* n_text_dev, const Calib& calib,
+                              float softmax_scale, void* out, float* workspace, hipStream_t stream) {
+  if (!plan.ok) return hipErrorInvalidValue;
+  TileArgs a{};
+  a.q = static_cast<const __half*>(q);
+  a.k_codes = k.codes; a.k_scale = k.scale; a.k_min = k.min;
+  a.v_codes = v.codes; a.v_scale = v.scale; a.v_min = v.min;
+  a.k_text = static_cast<const __half*>(k_text);
+  a.v_text = static_cast<const __half*>(v_text);
+  a.g = s.g; a.sets = ceil_div(s.g, kHeads); a.n_vis = s.n_vis; a.n_text = s.n_text;
+  a.n_text_cap = s.n_text_cap; a.n_text_dev = n_text_dev;
+  const bool vch = s.v_axis == CQ_AXIS_CHANNEL;
+  a.k_group = s.k_group; a.k_bpg = ceil_div(s.k_group, kKeyBlock);
+  a.v_group = vch ? s.v_group : s.n_vis; a.v_tpg = ceil_div(a.v_group, kValTile);
+  a.ca = plan.ca; a.cb = plan.cb; a.ct = plan.ct; a.ct_tokens = plan.ct_tokens;
+  if (s.n_vis > 0) {
+    const int blocks = s.n_vis / s.k_group * a.k_bpg, tiles = s.n_vis / a.v_group * a.v_tpg;
+    a.ca_base = blocks / a.ca; a.ca_rem = blocks % a.ca;
+    a.cb_base = tiles / a.cb; a.cb_rem = tiles % a.cb;
+  }
+  a.ws_logits = workspace;
+  a.ws_minmax = workspace + plan.ws_minmax_floats;
+  a.ws_partial = workspace + plan.ws_partial_floats;
+  a.calib_mode = calib.mode; a.tau1 = calib.tau1; a.tau2 = calib.tau2;
+  a.gamma = calib.gamma; a.delta = calib.delta; a.softmax_scale = softmax_scale;
+  const LogitsKernel kern_a = s.d == 64 ? logits_kernel<64>(s.bits)
+                              : s.d == 128 ? logits_kernel<128>(s.bits) : logits_kernel<256>(s.bits);
+  const LogitsKernel kern_b = s.d == 64 ? values_kernel<64>(s.bits, vch)
+                              : s.d == 128 ? values_kernel<128>(s.bits, vch) : values_kernel<256>(s.bits, vch);
+  if (!kern_a || !kern_b) return hipErrorInvalidValue;
+  const unsigned rows = (unsigned)(s.B * s.Hkv), sets = (unsigned)a.sets;
+  const unsigned text_a = rows * (unsigned)a.ct, text_b = text_a * sets;
+  kern_a<<<dim3(text_a + rows * (unsigned)a.ca * sets), dim3(kThreads), 0, stream>>>(a, (int)text_a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  kern_b<<<dim3(text_b + rows * (unsigned)a.cb * sets), dim3(kThreads), 0, stream>>>(a, (int)text_b);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  return launch_combine(s.B * s.Hq, plan.cb + plan.ct, s.d, a.ws_partial, out, stream);
+}
+
+}  // namespace cq

@@ -1,0 +1,61 @@
+"""Decode attention on the tile kernels (head dimensions 64 and 256, token counts and groups of any
+size, wide codes with channel-wise values) against the fp64 oracle, at the sizes where blocks, tiles,
+head sets and chunks end."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import cq_oracle as O
+from paper_2502_14882_amd import binding as cq
+from paper_2502_14882_amd import synth
+
+import helpers as H
+
+pytestmark = pytest.mark.gpu
+
+# (n_vis, k_group, v_axis, v_group (0: head_dim), q heads of 1 KV head, n_text, calibration)
+# whole sequences one token over a block, one under two, long and ragged; groups of 64 in a row that is
+# not a multiple of 64 per wave; a group no block or tile size divides; 4, 5 and 9 heads (head sets);
+# tails of 0, 1, a block and more; text only; a falling calibration line
+CASES = [(129, 129, 0, 129, 4, 1, "dynamic"), (255, 255, 1, 0, 1, 0, "none"),
+         (3003, 3003, 0, 3003, 5, 77, "dynamic"), (2112, 64, 0, 64, 4, 256, "dynamic"),
+         (1000, 40, 0, 200, 9, 257, "fixed"), (4160, 32, 1, 0, 3, 600, "dynamic"),
+         (0, 32, 1, 0, 4, 300, "none"), (17, 17, 0, 17, 2, 3, "falling")]
+MODES = {"none": (cq.CQ_CALIB_NONE, 0, 0, 0, 0), "dynamic": (cq.CQ_CALIB_DYNAMIC, 1, 2, 0, 0),
+         "fixed": (cq.CQ_CALIB_FIXED, 3, 1, -9, 9), "falling": (cq.CQ_CALIB_FIXED, 0, 3, -1, 1)}
+
+
+def _check(out, ref, what):
+    got = out.cpu().numpy().astype(np.float64)
+    assert np.isfinite(got).all(), what
+    err = O.rel_l2(got, ref)
+    assert err <= H.REGRESSION_TOL, "%s: rel L2 %.3e" % (what, err)
+    H.assert_elementwise_close(got, ref, what)
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("bits", [1, 2, 4, 8])
+def test_tile_decode(d, bits):
+    for n_vis, kg, vax, vg, g, n_text, calib in CASES:
+        vg = vg or d
+        what = "d %d bits %d n_vis %d kg %d v %d/%d g %d n_text %d %s" % (d, bits, n_vis, kg, vax, vg, g, n_text, calib)
+        print(what, flush=True)
+        w = synth.WORKLOADS[2].replace(batch=2, n_kv_heads=2, n_q_heads=2 * g, head_dim=d, n_vis=n_vis,
+                                       n_text=n_text + 2, seed=n_vis + d + bits)
+        x_cpu = synth.make_inputs(w, "cpu")
+        lay = cq.make_layout(2, 2 * g, 2, d, n_vis, bits, 0, vax, kg, vg)
+        x = H.to_device(x_cpu)
+        kq, vq = H.oracle_quantize(x_cpu, lay)
+        kd, vd = cq.cq_quantize_kv(lay, x["k"], x["v"]) if n_vis else (None, None)
+        args = MODES[calib]
+        ref = O.decode_attn(x_cpu["q"].numpy(), kq, vq, x_cpu["k_text"].numpy(), x_cpu["v_text"].numpy(),
+                            n_text, *args, 0.0)
+        out = cq.cq_decode_attn(lay, x["q"], kd, vd, x["k_text"], x["v_text"], n_text, cq.make_calib(*args))
+        torch.cuda.synchronize()
+        _check(out, ref, what)
+        # the tail length on the device, its bound two tokens longer
+        n_dev = torch.tensor([n_text], dtype=torch.int32, device="cuda")
+        out = cq.cq_decode_attn_devlen(lay, x["q"], kd, vd, x["k_text"], x["v_text"], n_dev, n_text + 2,
+                                       cq.make_calib(*args))
+        torch.cuda.synchronize()
+        _check(out, ref, what + " length on the device")
