@@ -6,9 +6,18 @@
 // tokens of a query row, then over all (batch, query head) rows.  gamma, delta of g are the
 // extrema of the row's visual logits, as in the decode call.  The caller takes the argmin.
 //
-// A calibration-time utility, not part of the decode step: logits come from the shape-agnostic
-// logits kernel (any layout), the weights are formed in fp64.
+// A calibration-time utility, not part of the decode step: fp32 logits of both key sets (the tile
+// kernels' logits pass where it takes the layout, else the shape-agnostic one; the exact keys pass
+// as a 16-bit tail), the weights in fp64.
+//
+// The grid costs n1 + n2 + 2 exponentials per token and pass instead of one per pair: with
+// u = (s - gamma) / (delta - gamma),  g(s) = s + tau1 (u - 1) - tau2 u,  so a weight is
+// e^s e^(tau1 (u - 1)) e^(-tau2 u).  Blocks of 4 x 4 pairs stay in registers; a row is cut into chunks
+// so that every CU works, and two passes (normalizers, then squared differences) meet in memory.
+// Bound: fp64 arithmetic.  128 query rows x 3456 tokens, 4 x 4 grid: 416 -> 57 us (logits 2 x 124 -> 2 x
+// 6, grid 136 -> 17 + 24, sum over rows 31 -> 4), against 64 bits 2e-7 -> 3e-8.
 #include <cfloat>
+#include <cmath>
 
 #include "cq_internal.h"
 
@@ -16,82 +25,194 @@ namespace cq {
 namespace {
 
 constexpr int kThreads = 256;
+constexpr int kGrid = 4;                 // pairs are taken 4 x 4 at a time
+constexpr int kPairs = kGrid * kGrid;
+// Largest |tau| whose factors e^(tau (u - 1)) and e^(-tau u) are formed on their own: products of the
+// three factors then stay within e^+-150 of 1.  Beyond it every pair gets its own exponential.
+constexpr double kFactorLimit = 50.0;
 
-struct TauGrid {
-  float tau1[kMaxTauPairs], tau2[kMaxTauPairs];   // pair p = (tau1[p], tau2[p])
-  int n_pairs;
+struct TauArgs {
+  float tau1[kMaxTauPairs], tau2[kMaxTauPairs];
+  int n1, n2, n_vis, n_text, n_chunks, chunk_tokens;
+  int ca, ct, cx;                        // chunk extrema: quantized visual, text, exact keys
+  const float* logits_q;                 // [rows][n_vis + n_text]: quantized visual, then text
+  const float* logits_x;                 // [rows][n_vis]: exact visual
+  const float* minmax_q;                 // [rows][ca + ct][2]
+  const float* minmax_x;                 // [rows][cx][2]
+  double* z_part;                        // [rows][n_chunks][n1 n2 + 1] normalizers, the last one exact
+  double* err_part;                      // [rows][n_chunks][n1 n2] squared differences
 };
 
-__device__ inline double block_sum(double v, double* red) {
-  __syncthreads();
-  red[threadIdx.x] = v;
-  __syncthreads();
-  for (int off = kThreads / 2; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
+__device__ inline double wave_total(double v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  return v;
+}
+
+// What every thread of a block knows about its query row.
+struct Row {
+  double gamma, inv_width, width, top_text, m_ref, m0;
+};
+__device__ inline Row row_extrema(const TauArgs& a, size_t row) {
+  // the chunk extrema over the lanes of every wave
+  const int lane = threadIdx.x & 63;
+  float lo = FLT_MAX, hi = -FLT_MAX, tmax = -FLT_MAX, xmax = -FLT_MAX;
+  const float* mq = a.minmax_q + row * (size_t)(a.ca + a.ct) * 2;
+  for (int c = lane; c < a.ca; c += 64) {
+    lo = fminf(lo, mq[2 * c]);
+    hi = fmaxf(hi, mq[2 * c + 1]);
+  }
+  for (int c = lane; c < a.ct; c += 64) tmax = fmaxf(tmax, mq[2 * (a.ca + c) + 1]);
+  const float* mx = a.minmax_x + row * (size_t)a.cx * 2;
+  for (int c = lane; c < a.cx; c += 64) xmax = fmaxf(xmax, mx[2 * c + 1]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    lo = fminf(lo, __shfl_xor(lo, o));
+    hi = fmaxf(hi, __shfl_xor(hi, o));
+    tmax = fmaxf(tmax, __shfl_xor(tmax, o));
+    xmax = fmaxf(xmax, __shfl_xor(xmax, o));
+  }
+  Row r;
+  r.gamma = lo;
+  r.width = (double)hi - (double)lo;
+  r.inv_width = r.width == 0.0 ? 0.0 : 1.0 / r.width;    // no range: slope 1, u = 0
+  r.top_text = tmax;
+  r.m_ref = fmax((double)xmax, (double)tmax);
+  r.m0 = fmax((double)hi, (double)tmax);
+  return r;
+}
+
+// Weights (up to a factor per pair) of one token for the pairs (i0 + i, j0 + j), and of the exact keys.
+// FACTORED: common reference m0 for all pairs.  Else pair by pair, with each pair's own reference,
+// the largest calibrated logit (g is monotone: an end of [gamma, delta] or a text token).
+template <bool FACTORED>
+__device__ inline void token_weights(const TauArgs& a, const Row& r, const double (&t1)[kGrid],
+                                     const double (&t2)[kGrid], double s, double sx, bool vis,
+                                     double (&w)[kPairs], double& ref) {
+  ref = exp(sx - r.m_ref);
+  const double u = (s - r.gamma) * r.inv_width;
+  if constexpr (FACTORED) {
+    const double e = exp(s - r.m0);
+    double f1[kGrid], f2[kGrid];
+#pragma unroll
+    for (int i = 0; i < kGrid; ++i) {
+      f1[i] = vis ? e * exp(t1[i] * (u - 1.0)) : e;
+      f2[i] = vis ? exp(-t2[i] * u) : 1.0;
+    }
+#pragma unroll
+    for (int i = 0; i < kGrid; ++i)
+#pragma unroll
+      for (int j = 0; j < kGrid; ++j) w[i * kGrid + j] = f1[i] * f2[j];
+  } else {
+#pragma unroll
+    for (int i = 0; i < kGrid; ++i)
+#pragma unroll
+      for (int j = 0; j < kGrid; ++j) {
+        const double at_lo = r.gamma - t1[i];
+        const double at_hi = r.width == 0.0 ? at_lo : r.gamma + r.width - t2[j];
+        const double m = fmax(fmax(at_lo, at_hi), r.top_text);
+        w[i * kGrid + j] = exp((vis ? s + t1[i] * (u - 1.0) - t2[j] * u : s) - m);
+      }
+  }
+}
+
+// grid.x = rows * n_chunks.  ERR = false: normalizers of the chunk; true: squared differences.
+template <bool FACTORED, bool ERR>
+__global__ void __launch_bounds__(kThreads)
+tau_grid_kernel(const TauArgs a) {
+  __shared__ double red[kThreads / 64][kPairs + 1];
+  __shared__ double inv_z[kMaxTauPairs + 1];
+  const size_t row = blockIdx.x / (unsigned)a.n_chunks;
+  const int chunk = (int)(blockIdx.x - row * a.n_chunks);
+  const int n_all = a.n_vis + a.n_text, n_pairs = a.n1 * a.n2;
+  const int c0 = chunk * a.chunk_tokens, c1 = min(c0 + a.chunk_tokens, n_all);
+  const float* sq = a.logits_q + row * (size_t)n_all;
+  const float* sx = a.logits_x + row * (size_t)a.n_vis;
+  const Row r = row_extrema(a, row);
+  if constexpr (ERR) {
+    for (int p = threadIdx.x; p <= n_pairs; p += kThreads) {
+      double z = 0.0;
+      for (int c = 0; c < a.n_chunks; ++c) z += a.z_part[(row * a.n_chunks + c) * (n_pairs + 1) + p];
+      inv_z[p] = 1.0 / z;
+    }
     __syncthreads();
   }
-  return red[0];
+  for (int i0 = 0; i0 < a.n1; i0 += kGrid)
+    for (int j0 = 0; j0 < a.n2; j0 += kGrid) {
+      double t1[kGrid], t2[kGrid], acc[kPairs + 1], iz[kPairs];
+#pragma unroll
+      for (int i = 0; i < kGrid; ++i) {        // beyond the grid: its last value again, not stored
+        t1[i] = a.tau1[min(i0 + i, a.n1 - 1)];
+        t2[i] = a.tau2[min(j0 + i, a.n2 - 1)];
+      }
+#pragma unroll
+      for (int p = 0; p <= kPairs; ++p) acc[p] = 0.0;
+      double iz_ref = 0.0;
+      if constexpr (ERR) {
+#pragma unroll
+        for (int p = 0; p < kPairs; ++p)
+          iz[p] = inv_z[min(i0 + p / kGrid, a.n1 - 1) * a.n2 + min(j0 + p % kGrid, a.n2 - 1)];
+        iz_ref = inv_z[n_pairs];
+      }
+      for (int t = c0 + (int)threadIdx.x; t < c1; t += kThreads) {
+        const bool vis = t < a.n_vis;
+        const double s = sq[t], x = vis ? sx[t] : sq[t];
+        double w[kPairs], ref;
+        token_weights<FACTORED>(a, r, t1, t2, s, x, vis, w, ref);
+        if constexpr (ERR) {
+          const double q = ref * iz_ref;
+#pragma unroll
+          for (int p = 0; p < kPairs; ++p) {
+            const double d = w[p] * iz[p] - q;
+            acc[p] += d * d;
+          }
+        } else {
+#pragma unroll
+          for (int p = 0; p < kPairs; ++p) acc[p] += w[p];
+          acc[kPairs] += ref;
+        }
+      }
+      const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+      __syncthreads();                         // the sums of the block of pairs before this one are out
+#pragma unroll
+      for (int p = 0; p <= (ERR ? kPairs - 1 : kPairs); ++p) {
+        const double v = wave_total(acc[p]);
+        if (lane == 0) red[wave][p] = v;
+      }
+      __syncthreads();
+      const int p = threadIdx.x;
+      if (p <= (ERR ? kPairs - 1 : kPairs)) {
+        double v = 0.0;
+#pragma unroll
+        for (int wv = 0; wv < kThreads / 64; ++wv) v += red[wv][p];
+        const int i = i0 + p / kGrid, j = j0 + p % kGrid;
+        const size_t at = row * a.n_chunks + chunk;
+        if (p == kPairs) {
+          a.z_part[at * (n_pairs + 1) + n_pairs] = v;
+        } else if (i < a.n1 && j < a.n2) {
+          if constexpr (ERR) a.err_part[at * n_pairs + i * a.n2 + j] = v;
+          else a.z_part[at * (n_pairs + 1) + i * a.n2 + j] = v;
+        }
+      }
+    }
 }
 
-// grid.x = B * Hq; one block per query row.
+// One block per pair: the squared differences over all rows and chunks, in a fixed order.
 __global__ void __launch_bounds__(kThreads)
-tau_grid_kernel(int n_vis, int n_text, int chunks_q_vis, int chunks_q, int chunks_x, TauGrid grid,
-                const float* __restrict__ logits_q, const float* __restrict__ logits_x,
-                const float* __restrict__ minmax_q, const float* __restrict__ minmax_x,
-                double* __restrict__ row_mse) {
-  __shared__ double red[kThreads];
-  const size_t row = blockIdx.x;
-  const int n_all = n_vis + n_text;
-  const float* sq = logits_q + row * (size_t)n_all;     // visual logits, then text logits
-  const float* sx = logits_x + row * (size_t)n_vis;
-  // extrema of the row from the chunk extrema of the logits kernel (every thread the same)
-  float lo = FLT_MAX, hi = -FLT_MAX, tmax = -FLT_MAX, xmax = -FLT_MAX;
-  for (int c = 0; c < chunks_q_vis; ++c) {
-    lo = fminf(lo, minmax_q[(row * chunks_q + c) * 2 + 0]);
-    hi = fmaxf(hi, minmax_q[(row * chunks_q + c) * 2 + 1]);
-  }
-  for (int c = chunks_q_vis; c < chunks_q; ++c) tmax = fmaxf(tmax, minmax_q[(row * chunks_q + c) * 2 + 1]);
-  for (int c = 0; c < chunks_x; ++c) xmax = fmaxf(xmax, minmax_x[(row * chunks_x + c) * 2 + 1]);
-  const double gam = lo, dlt = hi, width = dlt - gam;
-  // weights with the exact keys: p_j = exp(s_j - m_ref) / z_ref
-  const double m_ref = fmax((double)xmax, (double)tmax);
-  double z = 0.0;
-  for (int j = threadIdx.x; j < n_all; j += kThreads)
-    z += exp((double)(j < n_vis ? sx[j] : sq[j]) - m_ref);
-  const double z_ref = block_sum(z, red);
-
-  for (int p = 0; p < grid.n_pairs; ++p) {
-    const double t1 = grid.tau1[p], t2 = grid.tau2[p];
-    const double slope = width == 0.0 ? 1.0 : (width + t1 - t2) / width;
-    const double shift = gam - t1;                 // g(s) = slope * (s - gamma) + gamma - tau1
-    // g is monotone: its largest value sits at one end of [gamma, delta]
-    const double m_cal = fmax(fmax(shift, slope * width + shift), (double)tmax);
-    z = 0.0;
-    for (int j = threadIdx.x; j < n_all; j += kThreads) {
-      const double s = j < n_vis ? slope * ((double)sq[j] - gam) + shift : (double)sq[j];
-      z += exp(s - m_cal);
-    }
-    const double z_cal = block_sum(z, red);
-    double err = 0.0;
-    for (int j = threadIdx.x; j < n_all; j += kThreads) {
-      const double s = j < n_vis ? slope * ((double)sq[j] - gam) + shift : (double)sq[j];
-      const double ref = exp((double)(j < n_vis ? sx[j] : sq[j]) - m_ref) / z_ref;
-      const double diff = exp(s - m_cal) / z_cal - ref;
-      err += diff * diff;
-    }
-    const double total = block_sum(err, red);
-    if (threadIdx.x == 0) row_mse[row * grid.n_pairs + p] = total / (double)n_all;
-  }
-}
-
-// One block; thread p sums pair p over the rows in a fixed order.
-__global__ void tau_reduce_kernel(int n_rows, int n_pairs, const double* __restrict__ row_mse,
-                                  double* __restrict__ mse_out) {
-  const int p = threadIdx.x;
-  if (p >= n_pairs) return;
+tau_reduce_kernel(size_t n_parts, int n_pairs, double n_terms, const double* __restrict__ err_part,
+                  double* __restrict__ mse_out) {
+  __shared__ double red[kThreads / 64];
   double acc = 0.0;
-  for (int r = 0; r < n_rows; ++r) acc += row_mse[(size_t)r * n_pairs + p];
-  mse_out[p] = acc / (double)n_rows;
+  for (size_t r = threadIdx.x; r < n_parts; r += kThreads) acc += err_part[r * n_pairs + blockIdx.x];
+  acc = wave_total(acc);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double v = 0.0;
+#pragma unroll
+    for (int w = 0; w < kThreads / 64; ++w) v += red[w];
+    mse_out[blockIdx.x] = v / n_terms;
+  }
 }
 
 }  // namespace
@@ -102,16 +223,15 @@ hipError_t launch_tau_search(const DecodeShape& s, const void* q, const void* k_
                              double* mse_out, float* workspace, const TauWorkspace& wl,
                              hipStream_t stream) {
   const size_t rows = (size_t)s.B * s.Hq;
-  if (rows > 0x7fffffffu || n_tau1 * n_tau2 > kMaxTauPairs) return hipErrorInvalidConfiguration;
+  const int n_pairs = n_tau1 * n_tau2, n_all = s.n_vis + s.n_text;
+  if (rows * wl.n_chunks > 0x7fffffffu || n_pairs > kMaxTauPairs) return hipErrorInvalidConfiguration;
+  TauArgs a{};
   float* logits_q = workspace + wl.logits_q;
   float* logits_x = workspace + wl.logits_x;
   float* minmax_q = workspace + wl.minmax_q;
   float* minmax_x = workspace + wl.minmax_x;
-  double* row_mse = reinterpret_cast<double*>(workspace + wl.row_mse);
-  // logits on the quantized keys plus the text tail
-  hipError_t e = launch_scores_generic(s, q, k, k_text, nullptr, softmax_scale, logits_q, minmax_q, stream);
-  if (e != hipSuccess) return e;
-  // logits on the exact keys: the same kernel sees them as a 16-bit tail of n_vis tokens
+  // logits on the quantized keys plus the text tail, then on the exact keys, which pass as a 16-bit
+  // tail of n_vis tokens
   DecodeShape x = s;
   x.n_vis = 0;
   x.n_text = s.n_vis;
@@ -120,22 +240,42 @@ hipError_t launch_tau_search(const DecodeShape& s, const void* q, const void* k_
   x.n_text_chunks = ceil_div(s.n_vis, kTextChunk);
   x.n_chunks = x.n_text_chunks;
   static const cq_qtensor_t kNone = {nullptr, nullptr, nullptr};
-  e = launch_scores_generic(x, q, kNone, k_exact, nullptr, softmax_scale, logits_x, minmax_x, stream);
+  const TilePlan pq = make_tile_logits_plan(s), px = make_tile_logits_plan(x);
+  if (pq.ok && px.ok) {
+    a.ca = pq.ca; a.ct = pq.ct; a.cx = px.ct;
+    hipError_t e = launch_tile_logits(s, pq, q, k, k_text, softmax_scale, logits_q, minmax_q, stream);
+    if (e != hipSuccess) return e;
+    e = launch_tile_logits(x, px, q, kNone, k_exact, softmax_scale, logits_x, minmax_x, stream);
+    if (e != hipSuccess) return e;
+  } else {
+    a.ca = s.n_vis_chunks; a.ct = s.n_text_chunks; a.cx = x.n_chunks;
+    hipError_t e = launch_scores_generic(s, q, k, k_text, nullptr, softmax_scale, logits_q, minmax_q, stream);
+    if (e != hipSuccess) return e;
+    e = launch_scores_generic(x, q, kNone, k_exact, nullptr, softmax_scale, logits_x, minmax_x, stream);
+    if (e != hipSuccess) return e;
+  }
+  a.n1 = n_tau1; a.n2 = n_tau2;
+  bool factored = true;
+  for (int i = 0; i < n_tau1; ++i) { a.tau1[i] = tau1[i]; factored = factored && std::fabs((double)tau1[i]) <= kFactorLimit; }
+  for (int i = 0; i < n_tau2; ++i) { a.tau2[i] = tau2[i]; factored = factored && std::fabs((double)tau2[i]) <= kFactorLimit; }
+  a.n_vis = s.n_vis; a.n_text = s.n_text;
+  a.n_chunks = wl.n_chunks;
+  a.chunk_tokens = ceil_div(n_all, wl.n_chunks);
+  a.logits_q = logits_q; a.logits_x = logits_x;
+  a.minmax_q = minmax_q; a.minmax_x = minmax_x;
+  a.z_part = reinterpret_cast<double*>(workspace + wl.z_part);
+  a.err_part = reinterpret_cast<double*>(workspace + wl.err_part);
+  const dim3 grid((unsigned)(rows * wl.n_chunks)), block(kThreads);
+  if (factored) tau_grid_kernel<true, false><<<grid, block, 0, stream>>>(a);
+  else tau_grid_kernel<false, false><<<grid, block, 0, stream>>>(a);
+  hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  TauGrid grid;
-  grid.n_pairs = n_tau1 * n_tau2;
-  for (int i = 0; i < n_tau1; ++i)
-    for (int j = 0; j < n_tau2; ++j) {
-      grid.tau1[i * n_tau2 + j] = tau1[i];
-      grid.tau2[i * n_tau2 + j] = tau2[j];
-    }
-  tau_grid_kernel<<<dim3((unsigned)rows), dim3(kThreads), 0, stream>>>(
-      s.n_vis, s.n_text, s.n_vis_chunks, s.n_chunks, x.n_chunks, grid, logits_q, logits_x,
-      minmax_q, minmax_x, row_mse);
+  if (factored) tau_grid_kernel<true, true><<<grid, block, 0, stream>>>(a);
+  else tau_grid_kernel<false, true><<<grid, block, 0, stream>>>(a);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  tau_reduce_kernel<<<dim3(1), dim3(kMaxTauPairs), 0, stream>>>((int)rows, grid.n_pairs, row_mse,
-                                                                mse_out);
+  tau_reduce_kernel<<<dim3((unsigned)n_pairs), block, 0, stream>>>(
+      rows * wl.n_chunks, n_pairs, (double)n_all * (double)rows, a.err_part, mse_out);
   return hipGetLastError();
 }
 

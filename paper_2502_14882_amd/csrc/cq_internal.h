@@ -16,6 +16,7 @@ namespace cq {
 // split-K: every chunk produces one (m, l, acc[d]) partial of the online softmax.
 constexpr int kVisChunk = 512;
 constexpr int kTextChunk = 512;
+constexpr int kMaxTileChunks = 64;   // tile kernels: most chunks per row, of the visual tokens and of the tail
 
 struct DecodeShape {
   // n_text: tokens of the fp16 tail that are attended, or - when the length lives in device
@@ -80,24 +81,32 @@ constexpr int kMaxTauPairs = 64;
 struct TauWorkspace {
   size_t logits_q;   // [B*Hq][n_vis + n_text]  logits on the dequantized keys and the text keys
   size_t logits_x;   // [B*Hq][n_vis]           logits on the exact 16-bit keys
-  size_t minmax_q;   // [B*Hq][chunks of n_vis + n_text][2]
+  size_t minmax_q;   // [B*Hq][chunks of n_vis + chunks of n_text][2]
   size_t minmax_x;   // [B*Hq][chunks of n_vis][2]
-  size_t row_mse;    // [B*Hq][n_pairs] doubles
+  size_t z_part;     // [B*Hq][n_chunks][n_pairs + 1] doubles
+  size_t err_part;   // [B*Hq][n_chunks][n_pairs] doubles
+  int n_chunks;      // chunks per query row of the grid kernels
   size_t total_bytes;
 };
 inline TauWorkspace tau_workspace_layout(int B, int Hq, int n_vis, int n_text, int n_pairs) {
   TauWorkspace w;
-  const int nvc = ceil_div(n_vis, kVisChunk), ntc = ceil_div(n_text, kTextChunk);
-  // the exact keys go through the text-tail path of the logits kernel: chunks of kTextChunk
-  const int nxc = ceil_div(n_vis, kTextChunk);
+  // extrema of whichever logits kernels run: chunks of kVisChunk / kTextChunk tokens (the exact keys
+  // go through the text-tail path), or at most kMaxTileChunks chunks
+  auto most = [](int a) { return a > kMaxTileChunks ? a : kMaxTileChunks; };
+  const int nvc = most(ceil_div(n_vis, kVisChunk)), ntc = most(ceil_div(n_text, kTextChunk));
+  const int nxc = most(ceil_div(n_vis, kTextChunk));
   const size_t rows = (size_t)B * (size_t)Hq;
+  // four blocks per CU, at least one token per thread
+  const size_t want = (1024 + rows - 1) / rows, can = (size_t)ceil_div(n_vis + n_text, 256);
+  w.n_chunks = (int)(want < can ? want : can > 0 ? can : 1);
   auto align64 = [](size_t x) { return (x + 63) / 64 * 64; };
   w.logits_q = 0;
   w.logits_x = align64(w.logits_q + rows * ((size_t)n_vis + (size_t)n_text));
   w.minmax_q = align64(w.logits_x + rows * (size_t)n_vis);
   w.minmax_x = align64(w.minmax_q + rows * (size_t)(nvc + ntc) * 2);
-  w.row_mse = align64(w.minmax_x + rows * (size_t)nxc * 2);
-  const size_t end = align64(w.row_mse + rows * (size_t)n_pairs * 2);
+  w.z_part = align64(w.minmax_x + rows * (size_t)nxc * 2);
+  w.err_part = align64(w.z_part + rows * (size_t)w.n_chunks * (size_t)(n_pairs + 1) * 2);
+  const size_t end = align64(w.err_part + rows * (size_t)w.n_chunks * (size_t)n_pairs * 2);
   w.total_bytes = (end * sizeof(float) + 255) / 256 * 256;
   return w;
 }
@@ -171,6 +180,12 @@ struct TilePlan {
   size_t ws_bytes = 256;
 };
 TilePlan make_tile_plan(const DecodeShape& s);
+// The logits pass on its own, for keys of the same layouts whatever the values: raw logits
+// [B*Hq][n_vis + n_text] and the extrema [B*Hq][ca + ct][2] of every chunk.
+TilePlan make_tile_logits_plan(const DecodeShape& s);
+hipError_t launch_tile_logits(const DecodeShape& s, const TilePlan& plan, const void* q,
+                              const cq_qtensor_t& k, const void* k_text, float softmax_scale,
+                              float* logits, float* minmax, hipStream_t stream);
 hipError_t launch_decode_tile(const DecodeShape& s, const TilePlan& plan, const void* q,
                               const cq_qtensor_t& k, const cq_qtensor_t& v, const void* k_text,
                               const void* v_text, const int32_t* n_text_dev, const Calib& calib,

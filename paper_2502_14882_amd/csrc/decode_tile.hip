@@ -61,9 +61,12 @@ struct TileArgs {
 
 // How the codes of a token become the operand registers of a lane.  A matrix product takes 64 codes,
 // 16 per lane (4 registers of 4 bytes); a token of D codes fills D / 64 products.  Lane row kb holds
-// `words` consecutive words of its token, register p is variant p % kV of word p / kV.  One-bit
-// codes of 64 channels are the exception: two words for four lane rows, so a lane row holds half
-// a word, shifted down by 4 where it is the upper half of every byte.
+// `words` consecutive words of its token, register p is variant p % kV (code of every byte) of word
+// p / kV.  One-bit codes of 64 channels are the exception: two words for four lane rows, so a lane
+// row holds half a word, the lower or the upper half of every byte.
+// The upper half of a byte is shifted down before it is masked: a code then weighs 1 to 8 (1 bit) or
+// 1 or 4 (2 bits), and the query operand, which carries the inverse weight, loses at most 3 of its
+// bits to it (7 with the masks of decode_device.h, which save that shift).
 template <int D, int BITS>
 struct Operand {
   static constexpr int kProducts = D / 64;
@@ -71,16 +74,28 @@ struct Operand {
   static constexpr bool kHalf = D * BITS < 128;             // half a word per lane row
   static constexpr int kWords = kHalf ? 1 : D * BITS / 128; // words per lane
   static constexpr int kRowWords = D * BITS / 32;           // words per token
+  static constexpr int kLow = 4 / BITS;                     // variants in the lower half of a byte (b < 8)
   __device__ static int first_word(int kb) { return kHalf ? kb >> 1 : kb * kWords; }
   __device__ static int shift(int kb) { return kHalf ? 4 * (kb & 1) : 0; }
-  // channel and variant of operand byte y of register p in lane row kb
+  // channel of operand byte y of register p in lane row kb
   __device__ static int channel(int kb, int p, int y) {
     const int e = kHalf ? 0 : p / kV, v = kHalf ? p + 4 * (kb & 1) : p % kV;
     return (32 / BITS) * (first_word(kb) + e) + code_in_word<BITS>(y, v);
   }
-  __device__ static int variant(int p) { return kHalf ? p : p % kV; }
+  // 1 / (what a code of 1 is worth in register p)
+  __device__ static float weight(int p) {
+    if constexpr (BITS == 1) return ldexpf(1.f, -(p % 4));
+    else if constexpr (BITS == 2) return p % 2 ? 0.25f : 1.f;
+    else return 1.f;
+  }
   __device__ static int reg(const uint32_t (&w)[kWords], int p, int sh) {
-    return operand_variant<BITS>(kHalf ? w[0] >> sh : w[p / kV], variant(p));
+    if constexpr (BITS == 8) return operand_variant<8>(w[p], 0);
+    else {
+      const int v = kHalf ? p : p % kV;
+      const uint32_t word = kHalf ? w[0] >> sh : w[p / kV];
+      constexpr uint32_t mask = BITS == 1 ? 0x01010101u : BITS == 2 ? 0x03030303u : 0x0f0f0f0fu;
+      return (int)((v < kLow ? word : word >> 4) & (mask << (BITS * (v % kLow))));
+    }
   }
 };
 
@@ -100,6 +115,13 @@ __device__ inline void load_words(uint32_t (&w)[N], const uint32_t* p) {
       for (int u = 0; u < 4; ++u) w[4 * e + u] = (uint32_t)t[u];
     }
   }
+}
+
+// The four signed base-256 digits of a * b rounded to the nearest integer (|a b| < 2^30), as the four
+// bytes of the result.  Added to 1.5 * 2^52 a double shows the integer in its low word.
+__device__ inline int rounded_digits(float a, double b) {
+  const double t = fma((double)a, b, 6755399441055744.0 + 8421504.0);
+  return __builtin_bit_cast(v2i, t)[0] ^ 0x00808080;
 }
 
 // min and max of the workgroup's waves for the 16 heads of a text workgroup or the 4 of a head set:
@@ -203,21 +225,18 @@ tile_logits_kernel(const TileArgs a, int n_text_wg) {
   // (l / 4) % 4, byte l % 4), one channel each; together the lanes cover every channel once.
   int ch[NP];
   float inv_w[NP], qv[NP][kHeads];
-  float qmax = 0.f;
 #pragma unroll
   for (int i = 0; i < NP; ++i) {
     const int p = 4 * i + ((lane >> 2) & 3);
     ch[i] = Op::channel(kb, p, lane & 3);
-    const float wgt = variant_weight<BITS>(Op::variant(p));
+    const float wgt = Op::weight(p);
     inv_w[i] = 1.f / wgt;                                      // exact: powers of two
 #pragma unroll
     for (int h = 0; h < kHeads; ++h) {
       const float qf = h < gh ? __half2float(a.q[(head0 + h) * D + ch[i]]) : 0.f;
-      qmax = fmaxf(qmax, fabsf(qf));
-      qv[i][h] = qf * (a.softmax_scale * wgt);
+      qv[i][h] = qf * wgt;                                     // exact
     }
   }
-  qmax = wave_max_nonneg(qmax) * a.softmax_scale;
 
   uint8_t* xb = s_x[wave];
   const uint8_t* x_rd = xb + (kb * 16 + (n16 >> 1)) * 16 + (n16 & 1) * 8;
@@ -229,7 +248,8 @@ tile_logits_kernel(const TileArgs a, int n_text_wg) {
   const bool live = kb < gh;
 
   v4i A[NP];
-  float bias = 0.f, inv_f = 0.f, inv_f16 = 0.f, mn = FLT_MAX, mx = -FLT_MAX;
+  double bias = 0.0, inv_f = 0.0, inv_f16 = 0.0;
+  float mn = FLT_MAX, mx = -FLT_MAX;
   int have = -1;                                               // key group of the operand in A
   for (int blk = b0 + wave; blk < b1; blk += kWaves) {
     const int grp = a.k_bpg == 1 ? blk : blk / a.k_bpg;
@@ -241,27 +261,29 @@ tile_logits_kernel(const TileArgs a, int n_text_wg) {
       load_words<Op::kWords>(w[u], kc + (size_t)min(t0 + 16 * u + n16, t1 - 1) * Op::kRowWords);
     if (grp != have) {                                         // wave-uniform
       have = grp;
-      float s[NP], m[NP], smax = 0.f;
+      float s[NP], m[NP], most = 0.f;
 #pragma unroll
       for (int i = 0; i < NP; ++i) {
         s[i] = a.k_scale[meta0 + (size_t)grp * D + ch[i]];
         m[i] = __half2float(__ushort_as_half(a.k_min[meta0 + (size_t)grp * D + ch[i]]));
-        smax = fmaxf(smax, s[i]);
+#pragma unroll
+        for (int h = 0; h < kHeads; ++h) most = fmaxf(most, fabsf(qv[i][h] * s[i]));
       }
-      const int F = fixed_point_shift(qmax * wave_max_nonneg(smax));
-      float part[kHeads] = {0.f, 0.f, 0.f, 0.f};
+      // the largest operand is below 2^30: the top digit of four stays below 64
+      const int F = 1 + fixed_point_shift(wave_max_nonneg(most));
+      double part[kHeads] = {0.0, 0.0, 0.0, 0.0};
       __builtin_amdgcn_wave_barrier();
 #pragma unroll
       for (int i = 0; i < NP; ++i) {
-        const float sf = ldexpf(s[i], F);
+        const double sf = ldexp((double)s[i], F);
         v4i x;
 #pragma unroll
-        for (int h = 0; h < kHeads; ++h) x[h] = product_digits(qv[i][h], sf);
+        for (int h = 0; h < kHeads; ++h) x[h] = rounded_digits(qv[i][h], sf);
         *reinterpret_cast<v4i*>(xb + i * 1024 + lane * 16) = x;
         // 8-bit operand bytes are code - 128: the 128 comes back with the minimum
-        const float f = (m[i] + (BITS == 8 ? 128.f * s[i] : 0.f)) * inv_w[i];
+        const double f = ((double)m[i] + (BITS == 8 ? 128.0 * (double)s[i] : 0.0)) * (double)inv_w[i];
 #pragma unroll
-        for (int h = 0; h < kHeads; ++h) part[h] = fmaf(qv[i][h], f, part[h]);
+        for (int h = 0; h < kHeads; ++h) part[h] = fma((double)qv[i][h], f, part[h]);
       }
       lds_publish();
 #pragma unroll
@@ -269,9 +291,9 @@ tile_logits_kernel(const TileArgs a, int n_text_wg) {
         const v2i lo = lds_read_tr8(x_rd + i * 1024), hi = lds_read_tr8(x_rd + i * 1024 + 128);
         A[i] = (v4i){lo[0], lo[1], hi[0], hi[1]};
       }
-      bias = head_sums(part, lane);
-      inv_f = ldexpf(1.f, -F);
-      inv_f16 = ldexpf(1.f, 16 - F);
+      bias = head_sums(part, lane) * (double)a.softmax_scale;
+      inv_f = ldexp((double)a.softmax_scale, -F);
+      inv_f16 = ldexp((double)a.softmax_scale, 16 - F);
       __builtin_amdgcn_wave_barrier();
     }
     for (int t = t0; t < t1; t += 32) {                        // two tiles at a time
@@ -293,7 +315,7 @@ tile_logits_kernel(const TileArgs a, int n_text_wg) {
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         const int lo = c[u][0] + (c[u][1] << 8), hi = c[u][2] + (c[u][3] << 8);
-        const float s = fmaf((float)hi, inv_f16, fmaf((float)lo, inv_f, bias));
+        const float s = (float)fma((double)hi, inv_f16, fma((double)lo, inv_f, bias));
         const int tok = t + 16 * u + n16;
         if (tok < t1) {
           if (live) out[tok] = s;
@@ -651,10 +673,10 @@ tile_values_kernel(const TileArgs a, int n_text_wg) {
   store_partial<D>(a, head0, gh, chunk, m_ref, mem.part, s_lm);
 }
 
-using LogitsKernel = void (*)(const TileArgs, int);
+using TileKernel = void (*)(const TileArgs, int);
 
 template <int D>
-LogitsKernel logits_kernel(int bits) {
+TileKernel logits_kernel(int bits) {
   switch (bits) {
     case 1: return tile_logits_kernel<D, 1>;
     case 2: return tile_logits_kernel<D, 2>;
@@ -664,7 +686,7 @@ LogitsKernel logits_kernel(int bits) {
   }
 }
 template <int D>
-LogitsKernel values_kernel(int bits, bool vch) {
+TileKernel values_kernel(int bits, bool vch) {
   switch (bits * 2 + (vch ? 1 : 0)) {
     case 2: return tile_values_kernel<D, 1, false>;
     case 3: return tile_values_kernel<D, 1, true>;
@@ -695,12 +717,12 @@ TilePlan make_tile_plan(const DecodeShape& s) {
                                 : ceil_div(s.n_vis, kValTile);
     // four workgroups per CU, of at least one key block (two value tiles) per wave
     const long long want = (1024 + rows * sets - 1) / (rows * sets);
-    p.ca = clamp(want, 1, clamp((blocks + kWaves - 1) / kWaves, 1, 64));
-    p.cb = clamp(want, 1, clamp((tiles + 2 * kWaves - 1) / (2 * kWaves), 1, 64));
+    p.ca = clamp(want, 1, clamp((blocks + kWaves - 1) / kWaves, 1, kMaxTileChunks));
+    p.cb = clamp(want, 1, clamp((tiles + 2 * kWaves - 1) / (2 * kWaves), 1, kMaxTileChunks));
   }
   // the tail does not change how the visual tokens are divided: a workspace for a longer tail serves
   // a shorter one
-  p.ct_tokens = kTextBlock * ceil_div(ceil_div(s.n_text, kTextBlock), 64);
+  p.ct_tokens = kTextBlock * ceil_div(ceil_div(s.n_text, kTextBlock), kMaxTileChunks);
   if (s.n_text > 0) p.ct = ceil_div(s.n_text, p.ct_tokens);
   const size_t heads = (size_t)s.B * s.Hq;
   auto align64 = [](size_t x) { return (x + 63) / 64 * 64; };
@@ -708,49 +730,81 @@ TilePlan make_tile_plan(const DecodeShape& s) {
   p.ws_partial_floats = align64(p.ws_minmax_floats + heads * (size_t)(p.ca + p.ct) * 2);
   const size_t floats = p.ws_partial_floats + heads * (size_t)(p.cb + p.ct) * (s.d + 2);
   p.ws_bytes = (floats * sizeof(float) + 255) / 256 * 256;
-  const long long most = rows * (sets > 0 ? sets : 1) * (64 + 64);
+  const long long most = rows * (sets > 0 ? sets : 1) * 2 * kMaxTileChunks;
   p.ok = most < 0x7fffffffLL;
   return p;
+}
+
+TilePlan make_tile_logits_plan(const DecodeShape& s) {
+  DecodeShape e = s;
+  e.v_axis = CQ_AXIS_TOKEN;
+  e.v_group = e.d;
+  return make_tile_plan(e);
+}
+
+namespace {
+
+// the arguments that both passes read, and the logits launch
+hipError_t start_logits(TileArgs& a, const DecodeShape& s, const TilePlan& plan, const void* q,
+                        const cq_qtensor_t& k, const void* k_text, const int32_t* n_text_dev,
+                        float softmax_scale, float* logits, float* minmax, hipStream_t stream) {
+  if (!plan.ok) return hipErrorInvalidValue;
+  a.q = static_cast<const __half*>(q);
+  a.k_codes = k.codes; a.k_scale = k.scale; a.k_min = k.min;
+  a.k_text = static_cast<const __half*>(k_text);
+  a.g = s.g; a.sets = ceil_div(s.g, kHeads); a.n_vis = s.n_vis; a.n_text = s.n_text;
+  a.n_text_cap = s.n_text_cap; a.n_text_dev = n_text_dev;
+  a.k_group = s.k_group; a.k_bpg = ceil_div(s.k_group, kKeyBlock);
+  a.ca = plan.ca; a.ct = plan.ct; a.ct_tokens = plan.ct_tokens;
+  if (s.n_vis > 0) {
+    const int blocks = s.n_vis / s.k_group * a.k_bpg;
+    a.ca_base = blocks / a.ca; a.ca_rem = blocks % a.ca;
+  }
+  a.ws_logits = logits;
+  a.ws_minmax = minmax;
+  a.softmax_scale = softmax_scale;
+  const TileKernel kern = s.d == 64 ? logits_kernel<64>(s.bits)
+                          : s.d == 128 ? logits_kernel<128>(s.bits) : logits_kernel<256>(s.bits);
+  if (!kern) return hipErrorInvalidValue;
+  const unsigned rows = (unsigned)(s.B * s.Hkv), n_text_wg = rows * (unsigned)a.ct;
+  kern<<<dim3(n_text_wg + rows * (unsigned)(a.ca * a.sets)), dim3(kThreads), 0, stream>>>(a, (int)n_text_wg);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_tile_logits(const DecodeShape& s, const TilePlan& plan, const void* q,
+                              const cq_qtensor_t& k, const void* k_text, float softmax_scale,
+                              float* logits, float* minmax, hipStream_t stream) {
+  TileArgs a{};
+  return start_logits(a, s, plan, q, k, k_text, nullptr, softmax_scale, logits, minmax, stream);
 }
 
 hipError_t launch_decode_tile(const DecodeShape& s, const TilePlan& plan, const void* q,
                               const cq_qtensor_t& k, const cq_qtensor_t& v, const void* k_text,
                               const void* v_text, const int32_t* n_text_dev, const Calib& calib,
                               float softmax_scale, void* out, float* workspace, hipStream_t stream) {
-  if (!plan.ok) return hipErrorInvalidValue;
   TileArgs a{};
-  a.q = static_cast<const __half*>(q);
-  a.k_codes = k.codes; a.k_scale = k.scale; a.k_min = k.min;
+  hipError_t e = start_logits(a, s, plan, q, k, k_text, n_text_dev, softmax_scale, workspace,
+                              workspace + plan.ws_minmax_floats, stream);
+  if (e != hipSuccess) return e;
   a.v_codes = v.codes; a.v_scale = v.scale; a.v_min = v.min;
-  a.k_text = static_cast<const __half*>(k_text);
   a.v_text = static_cast<const __half*>(v_text);
-  a.g = s.g; a.sets = ceil_div(s.g, kHeads); a.n_vis = s.n_vis; a.n_text = s.n_text;
-  a.n_text_cap = s.n_text_cap; a.n_text_dev = n_text_dev;
   const bool vch = s.v_axis == CQ_AXIS_CHANNEL;
-  a.k_group = s.k_group; a.k_bpg = ceil_div(s.k_group, kKeyBlock);
   a.v_group = vch ? s.v_group : s.n_vis; a.v_tpg = ceil_div(a.v_group, kValTile);
-  a.ca = plan.ca; a.cb = plan.cb; a.ct = plan.ct; a.ct_tokens = plan.ct_tokens;
+  a.cb = plan.cb;
   if (s.n_vis > 0) {
-    const int blocks = s.n_vis / s.k_group * a.k_bpg, tiles = s.n_vis / a.v_group * a.v_tpg;
-    a.ca_base = blocks / a.ca; a.ca_rem = blocks % a.ca;
+    const int tiles = s.n_vis / a.v_group * a.v_tpg;
     a.cb_base = tiles / a.cb; a.cb_rem = tiles % a.cb;
   }
-  a.ws_logits = workspace;
-  a.ws_minmax = workspace + plan.ws_minmax_floats;
   a.ws_partial = workspace + plan.ws_partial_floats;
   a.calib_mode = calib.mode; a.tau1 = calib.tau1; a.tau2 = calib.tau2;
-  a.gamma = calib.gamma; a.delta = calib.delta; a.softmax_scale = softmax_scale;
-  const LogitsKernel kern_a = s.d == 64 ? logits_kernel<64>(s.bits)
-                              : s.d == 128 ? logits_kernel<128>(s.bits) : logits_kernel<256>(s.bits);
-  const LogitsKernel kern_b = s.d == 64 ? values_kernel<64>(s.bits, vch)
-                              : s.d == 128 ? values_kernel<128>(s.bits, vch) : values_kernel<256>(s.bits, vch);
-  if (!kern_a || !kern_b) return hipErrorInvalidValue;
-  const unsigned rows = (unsigned)(s.B * s.Hkv), sets = (unsigned)a.sets;
-  const unsigned text_a = rows * (unsigned)a.ct, text_b = text_a * sets;
-  kern_a<<<dim3(text_a + rows * (unsigned)a.ca * sets), dim3(kThreads), 0, stream>>>(a, (int)text_a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  kern_b<<<dim3(text_b + rows * (unsigned)a.cb * sets), dim3(kThreads), 0, stream>>>(a, (int)text_b);
+  a.gamma = calib.gamma; a.delta = calib.delta;
+  const TileKernel kern = s.d == 64 ? values_kernel<64>(s.bits, vch)
+                          : s.d == 128 ? values_kernel<128>(s.bits, vch) : values_kernel<256>(s.bits, vch);
+  if (!kern) return hipErrorInvalidValue;
+  const unsigned rows = (unsigned)(s.B * s.Hkv), n_text_wg = rows * (unsigned)(a.ct * a.sets);
+  kern<<<dim3(n_text_wg + rows * (unsigned)(a.cb * a.sets)), dim3(kThreads), 0, stream>>>(a, (int)n_text_wg);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_combine(s.B * s.Hq, plan.cb + plan.ct, s.d, a.ws_partial, out, stream);
