@@ -353,21 +353,23 @@ int cq_quantize_kv(const cq_layout_t* L, const void* k_f16, const void* v_f16,
     return fail(CQ_ERR_UNSUPPORTED, "no tuned quantizer for this layout");
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int rows = L->batch * L->n_kv_heads;
-  if (do_k) {
-    hipError_t e = (path != CQ_PATH_GENERIC && k_tuned)
-        ? cq::launch_quantize_tuned(k_f16, *k_out, rows, L->n_vis, L->head_dim, L->bits, L->k_axis,
-                                    L->k_group, s)
-        : cq::launch_quantize_generic(k_f16, *k_out, rows, L->n_vis, L->head_dim, L->bits,
-                                      L->k_axis, L->k_group, s);
-    if (e != hipSuccess) return hip_fail(e, "quantize keys");
+  cq::QuantizeJob jobs[2];         // tensors that the tile kernels take, together
+  int n_jobs = 0;
+  for (int i = 0; i < 2; ++i) {
+    if (i == 0 ? !do_k : !do_v) continue;
+    const cq::QuantizeJob job = i == 0 ? cq::QuantizeJob{k_f16, *k_out, L->k_axis, L->k_group}
+                                       : cq::QuantizeJob{v_f16, *v_out, L->v_axis, L->v_group};
+    if (path != CQ_PATH_GENERIC && (i == 0 ? k_tuned : v_tuned)) {
+      jobs[n_jobs++] = job;
+      continue;
+    }
+    const hipError_t e = cq::launch_quantize_generic(job.x_f16, job.out, rows, L->n_vis, L->head_dim, L->bits,
+                                                     job.axis, job.group, s);
+    if (e != hipSuccess) return hip_fail(e, i == 0 ? "quantize keys" : "quantize values");
   }
-  if (do_v) {
-    hipError_t e = (path != CQ_PATH_GENERIC && v_tuned)
-        ? cq::launch_quantize_tuned(v_f16, *v_out, rows, L->n_vis, L->head_dim, L->bits, L->v_axis,
-                                    L->v_group, s)
-        : cq::launch_quantize_generic(v_f16, *v_out, rows, L->n_vis, L->head_dim, L->bits,
-                                      L->v_axis, L->v_group, s);
-    if (e != hipSuccess) return hip_fail(e, "quantize values");
+  if (n_jobs > 0) {
+    const hipError_t e = cq::launch_quantize_tuned(jobs, n_jobs, rows, L->n_vis, L->head_dim, L->bits, s);
+    if (e != hipSuccess) return hip_fail(e, "quantize");
   }
   return CQ_OK;
 }

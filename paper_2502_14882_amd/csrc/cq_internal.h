@@ -119,11 +119,17 @@ hipError_t launch_tau_search(const DecodeShape& s, const void* q, const void* k_
 // Register-resident tile quantizer (quantize_tile.h): head_dim 64, 128 or 256, b in {1,2,4,8}, any
 // channel-wise group of tokens, channel groups of 32 to 256, any n_vis.
 bool quantize_tuned_supported(int n_vis, int d, int bits, int axis, int group);
-hipError_t launch_quantize_tuned(const void* x_f16, const cq_qtensor_t& out, int rows, int n_vis,
-                                 int d, int bits, int axis, int group, hipStream_t stream);
+// One or two tensors of the same shape, in as few launches as their statistics allow.
+struct QuantizeJob {
+  const void* x_f16;
+  cq_qtensor_t out;
+  int axis, group;
+};
+hipError_t launch_quantize_tuned(const QuantizeJob* jobs, int n_jobs, int rows, int n_vis, int d, int bits,
+                                 hipStream_t stream);
 // its head dimensions other than 128
-hipError_t launch_quantize_heads(const void* x_f16, const cq_qtensor_t& out, size_t n_tokens, int d,
-                                 int bits, int axis, int group, hipStream_t stream);
+hipError_t launch_quantize_64(const QuantizeJob* jobs, int n_jobs, size_t n_tokens, int bits, hipStream_t stream);
+hipError_t launch_quantize_256(const QuantizeJob* jobs, int n_jobs, size_t n_tokens, int bits, hipStream_t stream);
 
 // Merge the per-chunk partials [n_rows][n_chunks][d + 2] of the online softmax into out.
 hipError_t launch_combine(int n_rows, int n_chunks, int d, const float* partial, void* out,

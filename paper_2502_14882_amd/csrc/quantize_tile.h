@@ -1,6 +1,6 @@
 // Tile quantizer for head_dim 64, 128 and 256, b in {1, 2, 4, 8}, any group of tokens (channel axis)
-// or of channels (token axis), any number of tokens (gfx950).  Included by quantize_tuned.hip and
-// quantize_heads.hip, which instantiate it for their head dimensions.
+// or of channels (token axis), any number of tokens (gfx950).  Included by quantize_tuned.hip,
+// quantize_64.hip and quantize_256.hip, which instantiate it for their head dimensions.
 //
 // One 256-thread block quantizes a tile of 128 tokens x D channels (32 KB of fp16 at D = 128), read
 // once with 16-byte loads and kept in registers:
@@ -33,9 +33,9 @@
 // Results are bit-identical to evaluating the quantize equation element by element in fp64.
 //
 // Bound: HBM, and the launches of a small call.  Keys and values of 64 rows x 3003 tokens, D = 128, 2
-// bits, whole-sequence statistics (111 MB): 62 us, where the shape-agnostic kernel, one thread per
-// channel walking the sequence, took 4480 us.  128 x 8 rows x 16384 tokens, 1 bit, groups of 128
-// (9.33 GB): 1755 us = 5.3 TB/s.
+// bits, whole-sequence statistics (111 MB): 4480 us on the shape-agnostic kernel, one thread per
+// channel walking the sequence, 62 us here, 52 us with both tensors in one launch per pass.  128 x 8
+// rows x 16384 tokens, 1 bit, groups of 128 (9.33 GB): 1755 us = 5.3 TB/s.
 #ifndef CQ_QUANTIZE_TILE_H_
 #define CQ_QUANTIZE_TILE_H_
 
@@ -186,15 +186,18 @@ __device__ inline _Float16* seq_partials(const QArgs& a, size_t seq) {
   return reinterpret_cast<_Float16*>(a.codes + last_tok * (D * BITS / 32));
 }
 
-// First pass of a long group: block (sequence, sp) scans its share of the tokens.
+// First pass of a long group: block (sequence, sp) scans its share of the tokens.  The first n_first
+// blocks work on one tensor, the rest on the other (as in the tile kernels below).
 template <int D, int BITS>
 __global__ void __launch_bounds__(kThreads)
-row_extrema_kernel(const QArgs a) {
+row_extrema_kernel(const QArgs first, const QArgs second, unsigned n_first) {
   constexpr int kOct = D / 8, kSlots = 64 / kOct, kLoads = 32 / kSlots;
   __shared__ __align__(16) _Float16 s_part[2][4][D];
+  const QArgs a = blockIdx.x < n_first ? first : second;
+  const unsigned block = blockIdx.x < n_first ? blockIdx.x : blockIdx.x - n_first;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c8 = lane & (kOct - 1), ts = lane / kOct;
-  const unsigned seq = blockIdx.x / (unsigned)a.splits, sp = blockIdx.x - seq * (unsigned)a.splits;
+  const unsigned seq = block / (unsigned)a.splits, sp = block - seq * (unsigned)a.splits;
   const int t0 = (int)((long long)a.seq_tokens * sp / a.splits);
   const int t1 = (int)((long long)a.seq_tokens * (sp + 1) / a.splits);     // > t0: a share has tokens
   const v8h* src = reinterpret_cast<const v8h*>(a.x) + (size_t)seq * a.seq_tokens * kOct + c8;
@@ -244,27 +247,39 @@ row_extrema_kernel(const QArgs a) {
   }
 }
 
+// What a tile needs in LDS.
+template <int D, int AXIS, int BITS, int GROUP>
+struct TileMem {
+  static constexpr int L = (1 << BITS) - 1;
+  static constexpr int kG = GROUP == 0 ? kTile : GROUP;   // a tile of a long group is one group
+  static constexpr int NG = AXIS == CQ_AXIS_CHANNEL ? kTile / kG : D / kG;          // groups per tile / token
+  static constexpr bool kWide = BITS > 2;                 // per-element arithmetic instead of thresholds
+  static constexpr int kStats = AXIS == CQ_AXIS_CHANNEL ? NG * D : kTile * NG;      // groups of the tile
+  __align__(16) _Float16 s_part[2][4][AXIS == CQ_AXIS_CHANNEL ? D : 8];   // per-wave min, max
+  __align__(16) _Float16 s_stat[AXIS == CQ_AXIS_TOKEN ? kStats : 1][2];   // min, max
+  __align__(16) _Float16 s_thr[kWide ? 8 : (AXIS == CQ_AXIS_CHANNEL ? NG * L * D : kStats * 4)];
+  __align__(16) double s_rinv[kWide ? kStats : 1];
+  __align__(16) _Float16 s_alpha[kWide ? kStats : 8];
+  __align__(16) uint32_t s_codes[kTile * (D * BITS / 32)];
+};
+
 // AXIS: CQ_AXIS_CHANNEL (GROUP tokens per group; GROUP = 0: long groups, extrema from
 // row_extrema_kernel) or CQ_AXIS_TOKEN (GROUP channels per group)
 template <int D, int AXIS, int BITS, int GROUP>
-__global__ void __launch_bounds__(kThreads)
-quantize_tile_kernel(const QArgs a) {
+__device__ __forceinline__ void quantize_tile(const QArgs& a, const unsigned block, TileMem<D, AXIS, BITS, GROUP>& sm) {
+  using Mem = TileMem<D, AXIS, BITS, GROUP>;
   constexpr int kOct = D / 8;                             // lanes per token
   constexpr int kSlots = 64 / kOct, kLoads = 32 / kSlots; // tokens per wave-wide load, loads per wave
-  constexpr int L = (1 << BITS) - 1;
+  constexpr int L = Mem::L, kG = Mem::kG, NG = Mem::NG;
   constexpr int kWords = D * BITS / 32;                   // words per token
-  constexpr bool kWhole = GROUP == 0;
+  constexpr bool kWhole = GROUP == 0, kWide = Mem::kWide;
   static_assert(!kWhole || AXIS == CQ_AXIS_CHANNEL, "long groups are channel-wise");
-  constexpr int kG = kWhole ? kTile : GROUP;              // a tile of a long group is one group
-  constexpr int NG = AXIS == CQ_AXIS_CHANNEL ? kTile / kG : D / kG;          // groups per tile / token
-  constexpr bool kWide = BITS > 2;                        // per-element arithmetic instead of thresholds
-  constexpr int kStats = AXIS == CQ_AXIS_CHANNEL ? NG * D : kTile * NG;      // groups of the tile
-  __shared__ __align__(16) _Float16 s_part[2][4][AXIS == CQ_AXIS_CHANNEL ? D : 8];   // per-wave min, max
-  __shared__ __align__(16) _Float16 s_stat[AXIS == CQ_AXIS_TOKEN ? kStats : 1][2];   // min, max
-  __shared__ __align__(16) _Float16 s_thr[kWide ? 8 : (AXIS == CQ_AXIS_CHANNEL ? NG * L * D : kStats * 4)];
-  __shared__ __align__(16) double s_rinv[kWide ? kStats : 1];
-  __shared__ __align__(16) _Float16 s_alpha[kWide ? kStats : 8];
-  __shared__ __align__(16) uint32_t s_codes[kTile * kWords];
+  auto& s_part = sm.s_part;
+  auto& s_stat = sm.s_stat;
+  auto& s_thr = sm.s_thr;
+  auto& s_rinv = sm.s_rinv;
+  auto& s_alpha = sm.s_alpha;
+  auto& s_codes = sm.s_codes;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c8 = lane & (kOct - 1), ts = lane / kOct;
@@ -273,15 +288,15 @@ quantize_tile_kernel(const QArgs a) {
   if constexpr (kWhole) {
     // block = seq * tiles_launch + tile; the quotient by the host's fl(2^32 / tiles_launch) + 1 where
     // that is exact (a division by a run-time value costs dozens of instructions ahead of the loads)
-    const unsigned wseq = a.tiles_launch == 1 ? blockIdx.x
-                        : a.launch_magic ? __umulhi(blockIdx.x, a.launch_magic)
-                                         : blockIdx.x / (unsigned)a.tiles_launch;
-    wtile = a.tile_first + (int)(blockIdx.x - wseq * (unsigned)a.tiles_launch);
+    const unsigned wseq = a.tiles_launch == 1 ? block
+                        : a.launch_magic ? __umulhi(block, a.launch_magic)
+                                         : block / (unsigned)a.tiles_launch;
+    wtile = a.tile_first + (int)(block - wseq * (unsigned)a.tiles_launch);
     seq = wseq;
     tok0 = seq * (size_t)a.seq_tokens + (wtile ? a.first_tokens + (size_t)(wtile - 1) * kTile : 0);
     nt = wtile ? kTile : a.first_tokens;
   } else {
-    tok0 = (size_t)blockIdx.x * a.tile_stride;
+    tok0 = (size_t)block * a.tile_stride;
     const size_t left = a.n_tokens - tok0;
     nt = left < (size_t)a.tile_stride ? (int)left : a.tile_stride;
   }
@@ -367,7 +382,7 @@ quantize_tile_kernel(const QArgs a) {
       const double alpha = h_to_double(mbits);
       const double range = ((double)(float)hi - alpha) + 0.0;
       if (g * GROUP < nt) {                    // a short last tile holds whole groups only
-        const size_t meta = ((size_t)blockIdx.x * NG + g) * D + c;
+        const size_t meta = ((size_t)block * NG + g) * D + c;
         a.scale[meta] = (float)(range / (double)L);
         a.minv[meta] = mbits;
       }
@@ -528,90 +543,173 @@ quantize_tile_kernel(const QArgs a) {
   }
 }
 
-// long groups: extrema pass, all tiles but the last of every group, the last tiles
+template <int D, int AXIS, int BITS, int GROUP>
+__global__ void __launch_bounds__(kThreads)
+quantize_tile_kernel(const QArgs a) {
+  __shared__ TileMem<D, AXIS, BITS, GROUP> sm;
+  quantize_tile<D, AXIS, BITS, GROUP>(a, blockIdx.x, sm);
+}
+
+// Keys and values in one launch, the first n_first blocks on the keys (channel-wise, KGROUP).
+template <int D, int BITS, int KGROUP, int VAXIS, int VGROUP>
+__global__ void __launch_bounds__(kThreads)
+quantize_pair_kernel(const QArgs keys, const QArgs values, unsigned n_first) {
+  __shared__ union {
+    TileMem<D, CQ_AXIS_CHANNEL, BITS, KGROUP> k;
+    TileMem<D, VAXIS, BITS, VGROUP> v;
+  } sm;
+  if constexpr (VAXIS == CQ_AXIS_CHANNEL && VGROUP == KGROUP) {
+    const QArgs a = blockIdx.x < n_first ? keys : values;
+    quantize_tile<D, CQ_AXIS_CHANNEL, BITS, KGROUP>(a, blockIdx.x < n_first ? blockIdx.x : blockIdx.x - n_first, sm.k);
+  } else {
+    if (blockIdx.x < n_first) quantize_tile<D, CQ_AXIS_CHANNEL, BITS, KGROUP>(keys, blockIdx.x, sm.k);
+    else quantize_tile<D, VAXIS, BITS, VGROUP>(values, blockIdx.x - n_first, sm.v);
+  }
+}
+
+// One tensor as the launches below see it.
+struct Task {
+  QArgs a{};
+  int axis = 0, kernel_group = 0;        // GROUP of the kernel: 0 = long groups
+  size_t blocks = 0, n_seq = 0;          // tile blocks; long groups
+};
+
+// n_vis is a multiple of a channel-wise group.
+template <int D>
+Task make_task(const void* x_f16, const cq_qtensor_t& out, size_t n_tokens, int bits, int axis, int group) {
+  Task t;
+  t.axis = axis;
+  t.a.x = static_cast<const __half*>(x_f16);
+  t.a.codes = out.codes; t.a.scale = out.scale; t.a.minv = out.min;
+  t.a.n_tokens = n_tokens;
+  t.a.tile_stride = kTile;
+  const bool flat = axis == CQ_AXIS_TOKEN || group == 32 || group == 64 || group == 128;
+  t.kernel_group = flat ? group : kTile;
+  if (!flat && group > kTile) {
+    t.kernel_group = 0;
+    t.n_seq = n_tokens / group;
+    t.a.seq_tokens = group;
+    t.a.tiles_seq = ceil_div(group, kTile);
+    t.a.first_tokens = group - (t.a.tiles_seq - 1) * kTile;
+    // enough blocks in the first pass to fill the chip, as far as the last tile's code words hold
+    // their partials
+    const size_t want = (2048 + t.n_seq - 1) / t.n_seq;
+    t.a.splits = want < 4 ? 4 : want < (size_t)max_splits(bits) ? (int)want : max_splits(bits);
+    t.blocks = t.n_seq * (size_t)t.a.tiles_seq;
+    return t;
+  }
+  if (!flat) t.a.tile_stride = group;          // a short group is a tile of its own
+  t.blocks = (n_tokens + t.a.tile_stride - 1) / t.a.tile_stride;
+  return t;
+}
+
+// long groups: extrema pass, all tiles but the last of every group, the last tiles; u: NULL, or a second
+// tensor with long groups
 template <int D, int BITS>
-hipError_t launch_long_groups(QArgs a, unsigned n_seq, hipStream_t stream) {
-  row_extrema_kernel<D, BITS><<<dim3(n_seq * (unsigned)a.splits), dim3(kThreads), 0, stream>>>(a);
+hipError_t launch_long_groups(const Task& t, const Task* u, hipStream_t stream) {
+  QArgs a = t.a, b = u ? u->a : t.a;
+  const size_t na = t.n_seq, nb = u ? u->n_seq : 0;
+  row_extrema_kernel<D, BITS><<<dim3((unsigned)(na * a.splits + nb * b.splits)), dim3(kThreads), 0, stream>>>(
+      a, b, (unsigned)(na * a.splits));
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  a.tile_first = 0;
-  a.tiles_launch = a.tiles_seq - 1;
-  {
-    const unsigned long long blocks = (unsigned long long)n_seq * (unsigned)a.tiles_launch;
-    a.launch_magic = a.tiles_launch > 1 && blocks * (unsigned)a.tiles_launch < (1ull << 32)
-                         ? (unsigned)((1ull << 32) / (unsigned)a.tiles_launch + 1) : 0u;
+  auto share = [](QArgs& q, size_t n_seq, int first, int count) -> unsigned {
+    q.tile_first = first;
+    q.tiles_launch = count;
+    const unsigned long long blocks = (unsigned long long)n_seq * (unsigned)count;
+    q.launch_magic = count > 1 && blocks * (unsigned)count < (1ull << 32)
+                         ? (unsigned)((1ull << 32) / (unsigned)count + 1) : 0u;
+    return (unsigned)blocks;
+  };
+  for (int last = 0; last < 2; ++last) {
+    const unsigned ba = last ? share(a, na, a.tiles_seq - 1, 1) : share(a, na, 0, a.tiles_seq - 1);
+    if (u) {
+      const unsigned bb = last ? share(b, nb, b.tiles_seq - 1, 1) : share(b, nb, 0, b.tiles_seq - 1);
+      quantize_pair_kernel<D, BITS, 0, CQ_AXIS_CHANNEL, 0><<<dim3(ba + bb), dim3(kThreads), 0, stream>>>(a, b, ba);
+    } else {
+      quantize_tile_kernel<D, CQ_AXIS_CHANNEL, BITS, 0><<<dim3(ba), dim3(kThreads), 0, stream>>>(a);
+    }
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
   }
-  quantize_tile_kernel<D, CQ_AXIS_CHANNEL, BITS, 0>
-      <<<dim3(n_seq * (unsigned)a.tiles_launch), dim3(kThreads), 0, stream>>>(a);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  a.tile_first = a.tiles_seq - 1;
-  a.tiles_launch = 1;
-  a.launch_magic = 0;
-  quantize_tile_kernel<D, CQ_AXIS_CHANNEL, BITS, 0><<<dim3(n_seq), dim3(kThreads), 0, stream>>>(a);
+  return hipSuccess;
+}
+
+template <int D, int BITS>
+hipError_t launch_tiles(const Task& t, hipStream_t stream) {
+  if (t.kernel_group == 0) return launch_long_groups<D, BITS>(t, nullptr, stream);
+  void (*kern)(const QArgs) = nullptr;
+  const int g = t.kernel_group;
+  if (t.axis == CQ_AXIS_CHANNEL)               // 128: also one group per short tile
+    kern = g == 32 ? quantize_tile_kernel<D, CQ_AXIS_CHANNEL, BITS, 32>
+         : g == 64 ? quantize_tile_kernel<D, CQ_AXIS_CHANNEL, BITS, 64> : quantize_tile_kernel<D, CQ_AXIS_CHANNEL, BITS, 128>;
+  else if (g == 32) kern = quantize_tile_kernel<D, CQ_AXIS_TOKEN, BITS, 32>;
+  else if (g == 64) kern = quantize_tile_kernel<D, CQ_AXIS_TOKEN, BITS, 64>;
+  if constexpr (D >= 128) { if (t.axis == CQ_AXIS_TOKEN && g == 128) kern = quantize_tile_kernel<D, CQ_AXIS_TOKEN, BITS, 128>; }
+  if constexpr (D >= 256) { if (t.axis == CQ_AXIS_TOKEN && g == 256) kern = quantize_tile_kernel<D, CQ_AXIS_TOKEN, BITS, 256>; }
+  if (!kern) return hipErrorInvalidValue;
+  kern<<<dim3((unsigned)t.blocks), dim3(kThreads), 0, stream>>>(t.a);
   return hipGetLastError();
 }
 
+// The kernel that takes both tensors in one launch; NULL where there is none.  The pairs that callers
+// combine: groups of tokens for the keys with values token-wise over the head or in groups of
+// tokens of their own.
 template <int D, int BITS>
-hipError_t launch_tiles(const QArgs& a, int axis, int group, unsigned blocks, hipStream_t stream) {
-#define CQ_TILE(AXIS, G) \
-  quantize_tile_kernel<D, AXIS, BITS, G><<<dim3(blocks), dim3(kThreads), 0, stream>>>(a); \
-  return hipGetLastError()
-  if (axis == CQ_AXIS_CHANNEL) {
-    if (group == 32) { CQ_TILE(CQ_AXIS_CHANNEL, 32); }
-    if (group == 64) { CQ_TILE(CQ_AXIS_CHANNEL, 64); }
-    CQ_TILE(CQ_AXIS_CHANNEL, 128);             // 128, or one group per short tile
+auto pair_kernel(const Task& k, const Task& v) -> void (*)(const QArgs, const QArgs, unsigned) {
+  if (k.axis != CQ_AXIS_CHANNEL) return nullptr;
+  const int kg = k.kernel_group, vg = v.kernel_group;
+  if (v.axis == CQ_AXIS_TOKEN) {
+    if (vg != D) return nullptr;
+    return kg == 32 ? quantize_pair_kernel<D, BITS, 32, CQ_AXIS_TOKEN, D>
+         : kg == 64 ? quantize_pair_kernel<D, BITS, 64, CQ_AXIS_TOKEN, D>
+         : kg == 128 ? quantize_pair_kernel<D, BITS, 128, CQ_AXIS_TOKEN, D> : nullptr;
   }
-  if (group == 32) { CQ_TILE(CQ_AXIS_TOKEN, 32); }
-  if (group == 64) { CQ_TILE(CQ_AXIS_TOKEN, 64); }
-  if constexpr (D >= 128) {
-    if (group == 128) { CQ_TILE(CQ_AXIS_TOKEN, 128); }
-  }
-  if constexpr (D >= 256) {
-    if (group == 256) { CQ_TILE(CQ_AXIS_TOKEN, 256); }
-  }
-#undef CQ_TILE
-  return hipErrorInvalidValue;
+  if (vg == 64)
+    return kg == 32 ? quantize_pair_kernel<D, BITS, 32, CQ_AXIS_CHANNEL, 64>
+         : kg == 64 ? quantize_pair_kernel<D, BITS, 64, CQ_AXIS_CHANNEL, 64>
+         : kg == 128 ? quantize_pair_kernel<D, BITS, 128, CQ_AXIS_CHANNEL, 64> : nullptr;
+  if (vg == 128)
+    return kg == 32 ? quantize_pair_kernel<D, BITS, 32, CQ_AXIS_CHANNEL, 128>
+         : kg == 64 ? quantize_pair_kernel<D, BITS, 64, CQ_AXIS_CHANNEL, 128>
+         : kg == 128 ? quantize_pair_kernel<D, BITS, 128, CQ_AXIS_CHANNEL, 128> : nullptr;
+  return nullptr;
 }
 
-// One tensor of n_tokens = rows * n_vis tokens.  n_vis is a multiple of a channel-wise group.
-template <int D>
-hipError_t launch_quantize_dim(const void* x_f16, const cq_qtensor_t& out, size_t n_tokens, int bits,
-                               int axis, int group, hipStream_t stream) {
-  QArgs a{};
-  a.x = static_cast<const __half*>(x_f16);
-  a.codes = out.codes; a.scale = out.scale; a.minv = out.min;
-  a.n_tokens = n_tokens;
-  a.tile_stride = kTile;
-  const bool flat = axis == CQ_AXIS_TOKEN || group == 32 || group == 64 || group == 128;
-  if (!flat && group > kTile) {
-    const size_t n_seq = n_tokens / group;
-    a.seq_tokens = group;
-    a.tiles_seq = ceil_div(group, kTile);
-    a.first_tokens = group - (a.tiles_seq - 1) * kTile;
-    // enough blocks in the first pass to fill the chip, as far as the last tile's code words hold
-    // their partials
-    const size_t want = (2048 + n_seq - 1) / n_seq;
-    a.splits = want < 4 ? 4 : want < (size_t)max_splits(bits) ? (int)want : max_splits(bits);
-    if (n_seq * (size_t)a.tiles_seq > 0x7fffffffu || n_seq * (size_t)a.splits > 0x7fffffffu)
-      return hipErrorInvalidConfiguration;
-    switch (bits) {
-      case 1: return launch_long_groups<D, 1>(a, (unsigned)n_seq, stream);
-      case 2: return launch_long_groups<D, 2>(a, (unsigned)n_seq, stream);
-      case 4: return launch_long_groups<D, 4>(a, (unsigned)n_seq, stream);
-      case 8: return launch_long_groups<D, 8>(a, (unsigned)n_seq, stream);
+// Largest tensor (elements) whose keys and values go out together.  Two launches leave a part of the
+// chip idle at the end of the first and all of it waiting at the start of the second: together,
+// 1 to 8 bits, 3.4 M elements take 7-10 us instead of 12-14, 27 M (D = 128) 10-20 % less, 67 M 4-12 %
+// less (between 2 % more and 8 % less at D = 256).  Beyond that the streams of both tensors only
+// disturb each other: 134 M elements between 3 % less and 5 % more, 537 M up to 6 % more.
+constexpr size_t kPairElements = (size_t)80 << 20;
+
+// Up to two tensors (v: NULL for one) in as few launches as their kernels allow.
+template <int D, int BITS>
+hipError_t launch_tasks(const Task& k, const Task* v, hipStream_t stream) {
+  if (v && k.a.n_tokens * D <= kPairElements) {
+    if (k.kernel_group == 0 && v->kernel_group == 0) return launch_long_groups<D, BITS>(k, v, stream);
+    if (auto kern = pair_kernel<D, BITS>(k, *v)) {
+      kern<<<dim3((unsigned)(k.blocks + v->blocks)), dim3(kThreads), 0, stream>>>(k.a, v->a, (unsigned)k.blocks);
+      return hipGetLastError();
     }
-    return hipErrorInvalidValue;
   }
-  if (!flat) a.tile_stride = group;            // a short group is a tile of its own
-  const size_t blocks = (n_tokens + a.tile_stride - 1) / a.tile_stride;
-  if (blocks > 0x7fffffffu) return hipErrorInvalidConfiguration;
-  const unsigned nb = (unsigned)blocks;
+  const hipError_t e = launch_tiles<D, BITS>(k, stream);
+  return e != hipSuccess || !v ? e : launch_tiles<D, BITS>(*v, stream);
+}
+
+template <int D>
+hipError_t launch_quantize_dim(const QuantizeJob* jobs, int n_jobs, size_t n_tokens, int bits, hipStream_t stream) {
+  Task t[2];
+  for (int i = 0; i < n_jobs; ++i) {
+    t[i] = make_task<D>(jobs[i].x_f16, jobs[i].out, n_tokens, bits, jobs[i].axis, jobs[i].group);
+    if (t[i].blocks > 0x7fffffffu || t[i].n_seq * t[i].a.splits > 0x7fffffffu) return hipErrorInvalidConfiguration;
+  }
+  const Task* v = n_jobs > 1 ? &t[1] : nullptr;
   switch (bits) {
-    case 1: return launch_tiles<D, 1>(a, axis, group, nb, stream);
-    case 2: return launch_tiles<D, 2>(a, axis, group, nb, stream);
-    case 4: return launch_tiles<D, 4>(a, axis, group, nb, stream);
-    case 8: return launch_tiles<D, 8>(a, axis, group, nb, stream);
+    case 1: return launch_tasks<D, 1>(t[0], v, stream);
+    case 2: return launch_tasks<D, 2>(t[0], v, stream);
+    case 4: return launch_tasks<D, 4>(t[0], v, stream);
+    case 8: return launch_tasks<D, 8>(t[0], v, stream);
   }
   return hipErrorInvalidValue;
 }

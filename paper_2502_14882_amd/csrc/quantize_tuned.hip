@@ -12,11 +12,13 @@ bool quantize_tuned_supported(int n_vis, int d, int bits, int axis, int group) {
   return group <= d && (group == 32 || group == 64 || group == 128 || group == 256);
 }
 
-hipError_t launch_quantize_tuned(const void* x_f16, const cq_qtensor_t& out, int rows, int n_vis,
-                                 int d, int bits, int axis, int group, hipStream_t stream) {
+hipError_t launch_quantize_tuned(const QuantizeJob* jobs, int n_jobs, int rows, int n_vis, int d, int bits,
+                                 hipStream_t stream) {
   const size_t n_tokens = (size_t)rows * (size_t)n_vis;
-  if (d == 128) return launch_quantize_dim<128>(x_f16, out, n_tokens, bits, axis, group, stream);
-  return launch_quantize_heads(x_f16, out, n_tokens, d, bits, axis, group, stream);
+  if (d == 128) return launch_quantize_dim<128>(jobs, n_jobs, n_tokens, bits, stream);
+  if (d == 64) return launch_quantize_64(jobs, n_jobs, n_tokens, bits, stream);
+  if (d == 256) return launch_quantize_256(jobs, n_jobs, n_tokens, bits, stream);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace cq

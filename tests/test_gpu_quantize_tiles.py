@@ -37,3 +37,25 @@ def test_short_tiles_and_any_group(d, bits):
             H.assert_qtensor_equal(got, O.quantize_tensor(k.numpy(), bits, axis, group), what)
     finally:
         cq.cq_bench_set_kernel_path(prev)
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("bits", [1, 8])
+def test_keys_and_values_in_one_call(d, bits):
+    """Every pair of key and value statistics that one launch takes, and two that it does not, on
+    keys and values that differ; a row of 384 tokens is three tiles of each."""
+    prev = cq.cq_bench_set_kernel_path(cq.CQ_PATH_TUNED)
+    try:
+        w = synth.WORKLOADS[3].replace(batch=2, n_kv_heads=1, n_q_heads=1, head_dim=d, n_vis=384, seed=d)
+        x_cpu = synth.make_inputs(w, "cpu", parts=("k", "v"))
+        x = H.to_device(x_cpu)
+        for kg in (32, 64, 128, 384, 192):
+            for vax, vg in ((1, d), (0, 32), (0, 64), (0, 128), (0, 384), (0, 96)):
+                lay = cq.make_layout(2, 1, 1, d, 384, bits, 0, vax, kg, vg)
+                k, v = cq.cq_quantize_kv(lay, x["k"], x["v"])
+                torch.cuda.synchronize()
+                what = "d %d bits %d keys %d values %d/%d" % (d, bits, kg, vax, vg)
+                H.assert_qtensor_equal(k, O.quantize_tensor(x_cpu["k"].numpy(), bits, 0, kg), what)
+                H.assert_qtensor_equal(v, O.quantize_tensor(x_cpu["v"].numpy(), bits, vax, vg), what)
+    finally:
+        cq.cq_bench_set_kernel_path(prev)
