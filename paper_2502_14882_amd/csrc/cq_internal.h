@@ -176,13 +176,13 @@ hipError_t launch_decode_stream(const DecodeShape& s, const StreamPlan& plan, co
 
 // Tile decode (decode_tile.hip) for the layouts the two above do not take: head_dim 64, 128 or 256,
 // channel-wise keys and values in groups of any size or values token-wise over the whole head, any
-// number of query heads per KV head.  Logits pass, values pass, combine.
+// number of query heads per KV head.  Logits pass, values pass.
 struct TilePlan {
   bool ok = false;
   int ca = 0, cb = 0;              // chunks per row of the visual tokens: logits pass, values pass
   int ct = 0, ct_tokens = 0;       // chunks per row of the fp16 tail, tokens per chunk
-  size_t ws_minmax_floats = 0;     // workspace: [logits | extrema | partials], offsets in floats
-  size_t ws_partial_floats = 0;
+  size_t ws_minmax_floats = 0;     // workspace: [logits | extrema | partials | counts], offsets in floats
+  size_t ws_partial_floats = 0, ws_count_floats = 0;
   size_t ws_bytes = 256;
 };
 TilePlan make_tile_plan(const DecodeShape& s);

@@ -8,7 +8,7 @@
 //                 workgroup of 4 waves: raw logits in fp32 and the extrema of the chunk to the workspace
 //   values pass   the same division of the tokens into chunks of their own: g of Sec. 3.2 from the row's
 //                 extrema, weights, one partial (m, l, acc[D]) of the joint softmax per (head, chunk)
-//   combine       the shared kernel of decode_generic.hip
+//                 the workgroup that stores the last partial of its heads merges them all
 //
 // Both contractions over packed codes run on the int8 matrix cores as in decode_fused.hip (codes
 // picked out of a word by AND masks, the other operand as four signed base-256 digits of a 29-bit
@@ -17,11 +17,13 @@
 // run of 64-token tiles (values); groups and the row's end cut blocks and tiles short, a short one
 // reads its last token again and the surplus is neither stored nor weighted.
 //
-// Nothing is pipelined by hand: with 4-wave workgroups of at most 128 registers 16 waves share a CU
-// and hide each other's latency.  Bound: issue of vector instructions and, on small calls, the three
-// launches.  Against the shape-agnostic kernels, which dequantize element by element: 64 rows x 3003
-// tokens, 2 bits, whole-sequence keys and values 618 -> 21.6 us; 64 rows x 3328 tokens of 64
-// channels, 1 bit, 422 -> 18.9 us.  Over key and value groups from 1 to 48 tokens, head_dim 64 to 256
+// Bound: on small calls latency - two launches, and in each wave a chain of few round trips to memory: all
+// that a wave needs first is asked for at once (its first codes and parameters, then the query;
+// its first value tile, then the extrema), a key block's codes together, a share of the tail
+// together.  On large ones the issue of vector instructions; 16 waves share a CU and hide each other's
+// latency.  Against the shape-agnostic kernels, which dequantize element by element: 64 rows x
+// 3003 tokens, 2 bits, whole-sequence keys and values 618 -> 15.8 us; 64 rows x 3328 tokens of 64
+// channels, 1 bit, 422 -> 14.3 us.  Over key and value groups from 1 to 48 tokens, head_dim 64 to 256
 // and 1 and 8 bits they are 1.8 (value groups of one token) to 26 times as fast, so they take every
 // layout they can.
 #include <hip/hip_fp16.h>
@@ -38,7 +40,8 @@ constexpr int kWaves = 4;
 constexpr int kThreads = kWaves * 64;
 constexpr int kKeyBlock = 128;       // most tokens per key block (8 tiles of 16)
 constexpr int kValTile = 64;         // tokens per value tile
-constexpr int kTextBlock = 256;      // tokens of the fp16 tail per workgroup and round: 64 per wave
+constexpr int kTextShare = 32;       // tokens of the fp16 tail per wave and round
+constexpr int kTextBlock = kWaves * kTextShare;
 constexpr int kMaxRun = 1024;        // value tiles between two folds of the int32 digit sums (2^20 each)
 
 struct TileArgs {
@@ -56,6 +59,8 @@ struct TileArgs {
   float* ws_logits;            // [B*Hq][n_vis + n_text]
   float* ws_minmax;            // [B*Hq][ca + ct][2]
   float* ws_partial;           // [B*Hq][cb + ct][D + 2]
+  int* ws_count;               // [rows][sets] partials stored so far; NULL: no values pass follows
+  __half* out;
   int calib_mode; float tau1, tau2, gamma, delta, softmax_scale;
 };
 
@@ -164,21 +169,31 @@ __device__ inline void text_logits(const TileArgs& a, size_t row, int chunk, flo
     float mn[4], mx[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) { mn[r] = FLT_MAX; mx[r] = -FLT_MAX; }
-    for (int t = t0 + 16 * wave; t < t1; t += 16 * kWaves) {
-      const int tok = t + n16;
-      const __half* kp = keys + (size_t)min(tok, t1 - 1) * D + 8 * kb;
-      v4f c = {0.f, 0.f, 0.f, 0.f};
+    // a round's tiles of a wave in flight together: a tail's workgroup is short, and waits once
+    constexpr int kFly = kTextShare / 16;
+    for (int tb = t0 + 16 * wave; tb < t1; tb += 16 * kWaves * kFly) {
+      v8h kv[kFly][D / 32];
 #pragma unroll
-      for (int s = 0; s < D / 32; ++s)
-        c = __builtin_amdgcn_mfma_f32_16x16x32_f16(A[s], *reinterpret_cast<const v8h*>(kp + 32 * s), c, 0, 0, 0);
-      if (tok < t1) {
+      for (int u = 0; u < kFly; ++u) {
+        const __half* kp = keys + (size_t)min(tb + 16 * kWaves * u + n16, t1 - 1) * D + 8 * kb;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {          // result rows 4 kb + r are heads
-          if (4 * kb + r < nh) {
-            const float s = c[r] * a.softmax_scale;
-            a.ws_logits[(head0 + 4 * kb + r) * n_all + a.n_vis + tok] = s;
-            mn[r] = fminf(mn[r], s);
-            mx[r] = fmaxf(mx[r], s);
+        for (int s = 0; s < D / 32; ++s) kv[u][s] = *reinterpret_cast<const v8h*>(kp + 32 * s);
+      }
+#pragma unroll
+      for (int u = 0; u < kFly; ++u) {
+        const int tok = tb + 16 * kWaves * u + n16;
+        v4f c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < D / 32; ++s) c = __builtin_amdgcn_mfma_f32_16x16x32_f16(A[s], kv[u][s], c, 0, 0, 0);
+        if (tok < t1) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {        // result rows 4 kb + r are heads
+            if (4 * kb + r < nh) {
+              const float s = c[r] * a.softmax_scale;
+              a.ws_logits[(head0 + 4 * kb + r) * n_all + a.n_vis + tok] = s;
+              mn[r] = fminf(mn[r], s);
+              mx[r] = fmaxf(mx[r], s);
+            }
           }
         }
       }
@@ -197,25 +212,27 @@ __device__ inline void text_logits(const TileArgs& a, size_t row, int chunk, flo
   }
 }
 
-// grid: rows * ct text workgroups, then rows * ca * sets visual ones
+// grid: x = row, y = chunk of the tail, then chunk of the visual tokens, z = head set (the tail's
+// workgroups take all heads and leave the others of their column at once)
 template <int D, int BITS>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(D == 256 ? 2 : 4)))
-tile_logits_kernel(const TileArgs a, int n_text_wg) {
+tile_logits_kernel(const TileArgs a) {
   using Op = Operand<D, BITS>;
   constexpr int NP = Op::kProducts;
+  // tiles of 16 tokens whose codes are asked for together: a block's, as far as registers go
+  constexpr int kFly = Op::kWords <= 4 ? 8 : Op::kWords == 8 ? 4 : 2;
   __shared__ __align__(16) uint8_t s_x[kWaves][NP * 1024];     // query operand of a wave's key group
   __shared__ float red[kWaves][16][2];
-  if ((int)blockIdx.x < n_text_wg) {
-    const unsigned row = blockIdx.x / (unsigned)a.ct;
-    text_logits<D>(a, row, (int)(blockIdx.x - row * (unsigned)a.ct), red);
+  const size_t row = blockIdx.x;
+  if (blockIdx.y == 0 && blockIdx.z == 0 && a.ws_count)          // for the values pass behind this one
+    for (int i = threadIdx.x; i < a.sets; i += kThreads) a.ws_count[row * a.sets + i] = 0;
+  if ((int)blockIdx.y < a.ct) {
+    if (blockIdx.z == 0) text_logits<D>(a, row, (int)blockIdx.y, red);
     return;
   }
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n16 = lane & 15, kb = lane >> 4;
-  const unsigned piece = (blockIdx.x - n_text_wg) / (unsigned)a.sets;
-  const int set = (int)(blockIdx.x - n_text_wg - piece * (unsigned)a.sets);
-  const size_t row = piece / (unsigned)a.ca;
-  const int chunk = (int)(piece - row * a.ca);
+  const int set = (int)blockIdx.z, chunk = (int)blockIdx.y - a.ct;
   const int b0 = chunk_first(a.ca_base, a.ca_rem, chunk), b1 = chunk_first(a.ca_base, a.ca_rem, chunk + 1);
   const int gh = min(kHeads, a.g - set * kHeads);              // live heads of the set
   const size_t head0 = row * a.g + (size_t)set * kHeads;
@@ -224,20 +241,8 @@ tile_logits_kernel(const TileArgs a, int n_text_wg) {
   // Writer of the query operand: lane l writes row l of every product (lane row l / 16, register
   // (l / 4) % 4, byte l % 4), one channel each; together the lanes cover every channel once.
   int ch[NP];
-  float inv_w[NP], qv[NP][kHeads];
 #pragma unroll
-  for (int i = 0; i < NP; ++i) {
-    const int p = 4 * i + ((lane >> 2) & 3);
-    ch[i] = Op::channel(kb, p, lane & 3);
-    const float wgt = Op::weight(p);
-    inv_w[i] = 1.f / wgt;                                      // exact: powers of two
-#pragma unroll
-    for (int h = 0; h < kHeads; ++h) {
-      const float qf = h < gh ? __half2float(a.q[(head0 + h) * D + ch[i]]) : 0.f;
-      qv[i][h] = qf * wgt;                                     // exact
-    }
-  }
-
+  for (int i = 0; i < NP; ++i) ch[i] = Op::channel(kb, 4 * i + ((lane >> 2) & 3), lane & 3);
   uint8_t* xb = s_x[wave];
   const uint8_t* x_rd = xb + (kb * 16 + (n16 >> 1)) * 16 + (n16 & 1) * 8;
   const uint32_t* kc = a.k_codes + row * (size_t)a.n_vis * Op::kRowWords + Op::first_word(kb);
@@ -251,21 +256,46 @@ tile_logits_kernel(const TileArgs a, int n_text_wg) {
   double bias = 0.0, inv_f = 0.0, inv_f16 = 0.0;
   float mn = FLT_MAX, mx = -FLT_MAX;
   int have = -1;                                               // key group of the operand in A
-  for (int blk = b0 + wave; blk < b1; blk += kWaves) {
-    const int grp = a.k_bpg == 1 ? blk : blk / a.k_bpg;
-    const int t0 = grp * a.k_group + (blk - grp * a.k_bpg) * kKeyBlock;
-    const int t1 = min(t0 + kKeyBlock, (grp + 1) * a.k_group);
-    uint32_t w[2][Op::kWords];
+  int grp, t0, t1;                                             // of the block whose loads are in flight
+  uint32_t w[kFly][Op::kWords];
+  float s[NP];
+  uint16_t m[NP];
+  auto load_tiles = [&](int t) {                               // the kFly tiles from token t of the block
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
-      load_words<Op::kWords>(w[u], kc + (size_t)min(t0 + 16 * u + n16, t1 - 1) * Op::kRowWords);
-    if (grp != have) {                                         // wave-uniform
-      have = grp;
-      float s[NP], m[NP], most = 0.f;
+    for (int u = 0; u < kFly; ++u)
+      load_words<Op::kWords>(w[u], kc + (size_t)min(t + 16 * u + n16, t1 - 1) * Op::kRowWords);
+  };
+  auto load_block = [&](int blk, int group_loaded) {           // codes, and parameters if they change
+    grp = a.k_bpg == 1 ? blk : blk / a.k_bpg;
+    t0 = grp * a.k_group + (blk - grp * a.k_bpg) * kKeyBlock;
+    t1 = min(t0 + kKeyBlock, (grp + 1) * a.k_group);
+    load_tiles(t0);
+    if (grp != group_loaded) {
 #pragma unroll
       for (int i = 0; i < NP; ++i) {
         s[i] = a.k_scale[meta0 + (size_t)grp * D + ch[i]];
-        m[i] = __half2float(__ushort_as_half(a.k_min[meta0 + (size_t)grp * D + ch[i]]));
+        m[i] = a.k_min[meta0 + (size_t)grp * D + ch[i]];
+      }
+    }
+  };
+  // the first block is asked for before the query, so that a wave waits for memory once
+  if (b0 + wave < b1) load_block(b0 + wave, -1);
+  float inv_w[NP], qv[NP][kHeads];
+#pragma unroll
+  for (int i = 0; i < NP; ++i) {
+    const float wgt = Op::weight(4 * i + ((lane >> 2) & 3));
+    inv_w[i] = 1.f / wgt;                                      // exact: powers of two
+#pragma unroll
+    for (int h = 0; h < kHeads; ++h)
+      qv[i][h] = h < gh ? __half2float(a.q[(head0 + h) * D + ch[i]]) * wgt : 0.f;      // exact
+  }
+  for (int blk = b0 + wave; blk < b1; blk += kWaves) {
+    if (blk != b0 + wave) load_block(blk, have);
+    if (grp != have) {                                         // wave-uniform
+      have = grp;
+      float most = 0.f;
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
 #pragma unroll
         for (int h = 0; h < kHeads; ++h) most = fmaxf(most, fabsf(qv[i][h] * s[i]));
       }
@@ -281,7 +311,7 @@ tile_logits_kernel(const TileArgs a, int n_text_wg) {
         for (int h = 0; h < kHeads; ++h) x[h] = rounded_digits(qv[i][h], sf);
         *reinterpret_cast<v4i*>(xb + i * 1024 + lane * 16) = x;
         // 8-bit operand bytes are code - 128: the 128 comes back with the minimum
-        const double f = ((double)m[i] + (BITS == 8 ? 128.0 * (double)s[i] : 0.0)) * (double)inv_w[i];
+        const double f = ((double)__half2float(__ushort_as_half(m[i])) + (BITS == 8 ? 128.0 * (double)s[i] : 0.0)) * (double)inv_w[i];
 #pragma unroll
         for (int h = 0; h < kHeads; ++h) part[h] = fma((double)qv[i][h], f, part[h]);
       }
@@ -296,37 +326,34 @@ tile_logits_kernel(const TileArgs a, int n_text_wg) {
       inv_f16 = ldexp((double)a.softmax_scale, 16 - F);
       __builtin_amdgcn_wave_barrier();
     }
-    for (int t = t0; t < t1; t += 32) {                        // two tiles at a time
-      uint32_t wn[2][Op::kWords];
+    for (int t = t0; t < t1; t += 16 * kFly) {
+      if (t != t0) load_tiles(t);
 #pragma unroll
-      for (int u = 0; u < 2; ++u)
-        load_words<Op::kWords>(wn[u], kc + (size_t)min(t + 32 + 16 * u + n16, t1 - 1) * Op::kRowWords);
-      v4i c[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
+      for (int u0 = 0; u0 < kFly; u0 += 2) {                   // two tiles at a time
+        if (t + 16 * u0 >= t1) break;                          // wave-uniform
+        v4i c[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
 #pragma unroll
-      for (int i = 0; i < NP; ++i) {
-        v4i B[2];
+        for (int i = 0; i < NP; ++i) {
+          v4i B[2];
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
+          for (int u = 0; u < 2; ++u)
 #pragma unroll
-          for (int v = 0; v < 4; ++v) B[u][v] = Op::reg(w[u], 4 * i + v, sh);
+            for (int v = 0; v < 4; ++v) B[u][v] = Op::reg(w[u0 + u], 4 * i + v, sh);
 #pragma unroll
-        for (int u = 0; u < 2; ++u) c[u] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A[i], B[u], c[u], 0, 0, 0);
-      }
+          for (int u = 0; u < 2; ++u) c[u] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A[i], B[u], c[u], 0, 0, 0);
+        }
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int lo = c[u][0] + (c[u][1] << 8), hi = c[u][2] + (c[u][3] << 8);
-        const float s = (float)fma((double)hi, inv_f16, fma((double)lo, inv_f, bias));
-        const int tok = t + 16 * u + n16;
-        if (tok < t1) {
-          if (live) out[tok] = s;
-          mn = fminf(mn, s);
-          mx = fmaxf(mx, s);
+        for (int u = 0; u < 2; ++u) {
+          const int lo = c[u][0] + (c[u][1] << 8), hi = c[u][2] + (c[u][3] << 8);
+          const float s = (float)fma((double)hi, inv_f16, fma((double)lo, inv_f, bias));
+          const int tok = t + 16 * (u0 + u) + n16;
+          if (tok < t1) {
+            if (live) out[tok] = s;
+            mn = fminf(mn, s);
+            mx = fmaxf(mx, s);
+          }
         }
       }
-#pragma unroll
-      for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int e = 0; e < Op::kWords; ++e) w[u][e] = wn[u][e];
     }
   }
   mn = row_min(mn);
@@ -340,22 +367,87 @@ tile_logits_kernel(const TileArgs a, int n_text_wg) {
 }
 
 // ===================================================================================== values pass
-// the workgroup's partial of the joint softmax for the heads of a set, from per-wave sums in LDS
+// Partials cross from one XCD's L2 to another's inside a launch: stored and loaded at device scope (past
+// L2), eight bytes at a time.
+__device__ inline void store_device(float* p, float a, float b) {
+  __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), __builtin_bit_cast(unsigned long long, (v2f){a, b}),
+                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline v2f load_device(const float* p) {
+  return __builtin_bit_cast(v2f, __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT));
+}
+
+// The end of a workgroup of the values pass: its waves' sums become one partial (m, l, acc[D]) of the
+// joint softmax per head of the set.  The workgroup that finds all other partials of its (row, head
+// set) stored merges them into the output: nobody waits for anybody, and the result does not
+// depend on who comes last.  Each wave's stores have reached memory (vmcnt 0) before the barrier
+// that precedes the workgroup's count.  With a launch of the shared combine kernel in its place
+// the two calls measured at the top of this file took 16.6 and 16.0 us.
 template <int D>
-__device__ inline void store_partial(const TileArgs& a, size_t head0, int gh, int slot, const float* m_ref,
-                                     const float (*s_part)[kHeads][D], const float (*s_lm)[kHeads][2]) {
+__device__ inline void finish_chunk(const TileArgs& a, size_t row, int set, size_t head0, int gh, int slot,
+                                    const float* m_ref, const float (*s_part)[kHeads][D],
+                                    const float (*s_lm)[kHeads][2]) {
+  __shared__ int s_last;
+  constexpr int kPairs = D / 2;                // two channels per thread
+  const int n_slots = a.cb + a.ct;
   __syncthreads();
-  for (int e = threadIdx.x; e < gh * D; e += kThreads) {
-    const int h = e / D, c = e % D;
-    float num = 0.f, den = 0.f;
+  for (int e = threadIdx.x; e < gh * kPairs; e += kThreads) {
+    const int h = e / kPairs, c = 2 * (e % kPairs);
+    v2f num = {0.f, 0.f};
+    float den = 0.f;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
-      num += s_part[w][h][c] + s_lm[w][h][1];
+      num += *reinterpret_cast<const v2f*>(&s_part[w][h][c]) + s_lm[w][h][1];
       den += s_lm[w][h][0];
     }
-    float* out = a.ws_partial + ((head0 + h) * (size_t)(a.cb + a.ct) + slot) * (D + 2);
-    if (c == 0) { out[0] = m_ref[h]; out[1] = den; }
-    out[2 + c] = num;
+    if (n_slots == 1) {
+      *reinterpret_cast<__half2*>(a.out + (head0 + h) * D + c) = __floats2half2_rn(num[0] / den, num[1] / den);
+      continue;
+    }
+    float* out = a.ws_partial + ((head0 + h) * (size_t)n_slots + slot) * (D + 2);
+    if (c == 0) store_device(out, m_ref[h], den);
+    store_device(out + 2 + c, num[0], num[1]);
+  }
+  if (n_slots == 1) return;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0)
+    s_last = __hip_atomic_fetch_add(a.ws_count + row * a.sets + set, 1, __ATOMIC_RELAXED,
+                                    __HIP_MEMORY_SCOPE_AGENT) == n_slots - 1;
+  __syncthreads();
+  if (!s_last) return;
+  for (int e = threadIdx.x; e < gh * kPairs; e += kThreads) {
+    const int h = e / kPairs, c = 2 * (e % kPairs);
+    const float* base = a.ws_partial + (head0 + h) * (size_t)n_slots * (D + 2);
+    // sixteen partials at a time, their loads independent of each other; each batch brings its own
+    // reference point (online softmax over batches).  A chunk without tokens has weight 0.
+    float M = -FLT_MAX, den = 0.f;
+    v2f num = {0.f, 0.f};
+    for (int i0 = 0; i0 < n_slots; i0 += 16) {
+      v2f ml[16], acc[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        const float* p = base + (size_t)min(i0 + u, n_slots - 1) * (D + 2);
+        ml[u] = load_device(p);
+        acc[u] = load_device(p + 2 + c);
+      }
+      float Mb = M;
+#pragma unroll
+      for (int u = 0; u < 16; ++u) Mb = fmaxf(Mb, ml[u][0]);     // a repeated partial changes nothing
+      const float keep = __builtin_amdgcn_exp2f((M - Mb) * kLog2e);
+      num *= keep;
+      den *= keep;
+      M = Mb;
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        const float w = i0 + u < n_slots ? __builtin_amdgcn_exp2f((ml[u][0] - M) * kLog2e) : 0.f;
+        num[0] = fmaf(w, acc[u][0], num[0]);
+        num[1] = fmaf(w, acc[u][1], num[1]);
+        den = fmaf(w, ml[u][1], den);
+      }
+    }
+    *reinterpret_cast<__half2*>(a.out + (head0 + h) * D + c) = __floats2half2_rn(num[0] / den, num[1] / den);
   }
 }
 
@@ -381,8 +473,13 @@ __device__ inline void text_values(const TileArgs& a, size_t row, int set, int c
     for (int j = 0; j < 8; ++j) acc[h][j] = 0.f;
   }
   const int c8 = lane & (kOct - 1), ts = lane / kOct;
-  for (int t = t0 + 64 * wave; t < t1; t += 64 * kWaves) {
-    const int nt = min(64, t1 - t);
+  constexpr int kLoads = kTextShare / kSlots;                  // a share's loads are in flight together
+  for (int t = t0 + kTextShare * wave; t < t1; t += kTextBlock) {
+    const int nt = min(kTextShare, t1 - t);
+    v8h v[kLoads];
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i)           // past the end: the last token, which gets weight 0
+      v[i] = *reinterpret_cast<const v8h*>(vals + (size_t)(t + min(i * kSlots + ts, nt - 1)) * D + 8 * c8);
     v4f p = {0.f, 0.f, 0.f, 0.f};
     if (lane < nt) {
 #pragma unroll
@@ -393,39 +490,57 @@ __device__ inline void text_values(const TileArgs& a, size_t row, int set, int c
 #pragma unroll
     for (int h = 0; h < kHeads; ++h) l[h] += p[h];
     __builtin_amdgcn_wave_barrier();
-    *reinterpret_cast<v4f*>(s_p[64 * wave + lane]) = p;
+    if (lane < kTextShare) *reinterpret_cast<v4f*>(s_p[kTextShare * wave + lane]) = p;
     lds_publish();
-#pragma unroll 4
-    for (int i = 0; i < 64 / kSlots; ++i) {
-      if (i * kSlots >= nt) break;             // wave-uniform
-      const int j = i * kSlots + ts;           // past the end: the last token with weight 0
-      const v8h v = *reinterpret_cast<const v8h*>(vals + (size_t)(t + min(j, nt - 1)) * D + 8 * c8);
-      const v4f w = *reinterpret_cast<const v4f*>(s_p[64 * wave + j]);
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      const v4f w = *reinterpret_cast<const v4f*>(s_p[kTextShare * wave + i * kSlots + ts]);
 #pragma unroll
       for (int h = 0; h < kHeads; ++h)
 #pragma unroll
-        for (int u = 0; u < 8; ++u) acc[h][u] = fmaf(w[h], (float)v[u], acc[h][u]);
+        for (int u = 0; u < 8; ++u) acc[h][u] = fmaf(w[h], (float)v[i][u], acc[h][u]);
     }
     __builtin_amdgcn_wave_barrier();
   }
-#pragma unroll
-  for (int h = 0; h < kHeads; ++h) {
+  // sum over the token slots; the paired folds leave one head per half or row of the wave
+  if constexpr (D == 256) {                    // two slots: lanes 0-31 and 32-63
+    float r[2][8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-#pragma unroll
-      for (int o = kOct; o <= 32; o <<= 1) acc[h][u] += __shfl_xor(acc[h][u], o);
-      if (ts == 0) s_part[wave][h][8 * c8 + u] = acc[h][u];
+      r[0][u] = fold_halves(acc[0][u], acc[1][u]);
+      r[1][u] = fold_halves(acc[2][u], acc[3][u]);
     }
-    const float lw = wave_sum(l[h]);
-    if (lane == 0) { s_lm[wave][h][0] = lw; s_lm[wave][h][1] = 0.f; }
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+      for (int u = 0; u < 8; u += 4)
+        *reinterpret_cast<v4f*>(&s_part[wave][2 * e + (lane >> 5)][8 * c8 + u]) =
+            (v4f){r[e][u], r[e][u + 1], r[e][u + 2], r[e][u + 3]};
+  } else {                                     // four slots (rows of 16 lanes), or eight (half rows)
+    float r[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      if constexpr (D == 64) {
+#pragma unroll
+        for (int h = 0; h < kHeads; ++h) acc[h][u] += dpp_f32<0x128>(acc[h][u]);     // row_ror 8
+      }
+      r[u] = fold_rows(fold_halves(acc[0][u], acc[2][u]), fold_halves(acc[1][u], acc[3][u]));
+    }
+    if (D == 128 || (lane & 8) == 0) {
+#pragma unroll
+      for (int u = 0; u < 8; u += 4)
+        *reinterpret_cast<v4f*>(&s_part[wave][lane >> 4][8 * c8 + u]) = (v4f){r[u], r[u + 1], r[u + 2], r[u + 3]};
+    }
   }
-  store_partial<D>(a, head0, gh, a.cb + chunk, m_ref, s_part, s_lm);
+  const float lw = head_sums(l, lane);
+  if ((lane & 15) == 0) { s_lm[wave][lane >> 4][0] = lw; s_lm[wave][lane >> 4][1] = 0.f; }
+  finish_chunk<D>(a, row, set, head0, gh, a.cb + chunk, m_ref, s_part, s_lm);
 }
 
-// grid: rows * ct * sets text workgroups, then rows * cb * sets visual ones
+// grid: x = row, y = chunk of the tail, then chunk of the visual tokens, z = head set
 template <int D, int BITS, bool VCH>
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(D == 256 || BITS == 8 ? 2 : 4)))
-tile_values_kernel(const TileArgs a, int n_text_wg) {
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(D == 256 || BITS == 8 ? 2 : D == 128 && BITS >= 2 && VCH ? 3 : 4)))
+tile_values_kernel(const TileArgs a) {
   constexpr int CB = D * BITS / 8;                             // code bytes per token
   constexpr int kV = 8 / BITS;
   constexpr int kBlocks = CB >= 16 ? CB / 16 : 1;              // 16-byte column blocks (8 bytes: half of one)
@@ -443,53 +558,17 @@ tile_values_kernel(const TileArgs a, int n_text_wg) {
   __shared__ __align__(16) Mem mem;
   __shared__ __align__(16) float s_lm[kWaves][kHeads][2];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const bool is_text = (int)blockIdx.x < n_text_wg;
-  const unsigned bid = is_text ? blockIdx.x : blockIdx.x - n_text_wg;
-  const unsigned piece = bid / (unsigned)a.sets, per_row = (unsigned)(is_text ? a.ct : a.cb);
-  const int set = (int)(bid - piece * (unsigned)a.sets);
-  const size_t row = piece / per_row;
-  const int chunk = (int)(piece - row * per_row);
-  if (is_text) {
-    __shared__ __align__(16) float s_tp[kWaves * 64][kHeads];
-    text_values<D>(a, row, set, chunk, s_tp, mem.part, s_lm);
+  const size_t row = blockIdx.x;
+  const int set = (int)blockIdx.z, chunk = (int)blockIdx.y - a.ct;
+  if (chunk < 0) {
+    __shared__ __align__(16) float s_tp[kTextBlock][kHeads];
+    text_values<D>(a, row, set, (int)blockIdx.y, s_tp, mem.part, s_lm);
     return;
   }
   const int n16 = lane & 15, kb = lane >> 4;
   const int gh = min(kHeads, a.g - set * kHeads);
   const size_t head0 = row * a.g + (size_t)set * kHeads;
   const size_t n_all = (size_t)a.n_vis + a.n_text;
-
-  // ---- calibration line and reference point per head (Sec. 3.2): lane 16 h + c folds chunks c,
-  // c + 16, ... of head h
-  float a2[kHeads], c2[kHeads], m_ref[kHeads];
-  {
-    const float* mm = a.ws_minmax + (head0 + min(kb, gh - 1)) * (size_t)(a.ca + a.ct) * 2;
-    float lo_l = FLT_MAX, hi_l = -FLT_MAX;
-    for (int c = n16; c < a.ca; c += 16) {
-      lo_l = fminf(lo_l, mm[2 * c]);
-      hi_l = fmaxf(hi_l, mm[2 * c + 1]);
-    }
-    lo_l = row_min(lo_l);
-    hi_l = row_max(hi_l);
-#pragma unroll
-    for (int h = 0; h < kHeads; ++h) {
-      const float lo = lane_value(lo_l, 16 * h), hi = lane_value(hi_l, 16 * h);
-      float slope = 1.f, gam = 0.f, shift = 0.f;               // s' = slope * (s - gam) + shift
-      if (a.calib_mode != CQ_CALIB_NONE) {
-        const float glo = a.calib_mode == CQ_CALIB_DYNAMIC ? lo : a.gamma;
-        const float ghi = a.calib_mode == CQ_CALIB_DYNAMIC ? hi : a.delta;
-        const float width = ghi - glo;
-        slope = width == 0.f ? 1.f : (width + a.tau1 - a.tau2) / width;
-        gam = glo;
-        shift = glo - a.tau1;
-      }
-      // the map is monotone: an end of the row's range is its maximum, every weight is <= 1
-      const float M = fmaxf(slope * (lo - gam) + shift, slope * (hi - gam) + shift);
-      m_ref[h] = M;
-      a2[h] = h < gh ? slope * kLog2e : 0.f;
-      c2[h] = h < gh ? (shift - slope * gam - M) * kLog2e : -200.f;     // no head: weight 0
-    }
-  }
 
   // the wave's run of tiles
   const int u0 = chunk_first(a.cb_base, a.cb_rem, chunk), u1 = chunk_first(a.cb_base, a.cb_rem, chunk + 1);
@@ -527,6 +606,9 @@ tile_values_kernel(const TileArgs a, int n_text_wg) {
   v4i piece_r[kPieces];
   float lgv[kHeads], sc = 0.f;
   uint16_t mi = 0;
+  float gs[VCH ? NACC : 1];                                    // channel-wise: parameters of group `params_of`
+  uint16_t gm[VCH ? NACC : 1];
+  int params_of = -1;
   auto tile_at = [&](int k, int& grp, int& tok0, int& nt) {
     grp = a.v_tpg == 1 ? k : k / a.v_tpg;
     const int sub = k - grp * a.v_tpg;
@@ -558,8 +640,52 @@ tile_values_kernel(const TileArgs a, int n_text_wg) {
       mi = vm[j];
     }
     load_pieces(tok0, nt, 0);
+    if constexpr (VCH) {
+      if (grp != params_of) {                                  // wave-uniform; the group before is folded
+        params_of = grp;
+#pragma unroll
+        for (int p = 0; p < NACC; ++p) {
+          const size_t at = meta0 + (size_t)grp * D + channel(p);
+          gs[p] = a.v_scale[at];
+          gm[p] = a.v_min[at];
+        }
+      }
+    }
   };
+  // the first tile is asked for before the extrema are folded, so that a wave waits for memory once
   if (k0 < k1) load_tile(k0);
+  // ---- calibration line and reference point per head (Sec. 3.2): lane 16 h + c folds chunks c,
+  // c + 16, ... of head h
+  float a2[kHeads], c2[kHeads], m_ref[kHeads];
+  {
+    const float* mm = a.ws_minmax + (head0 + min(kb, gh - 1)) * (size_t)(a.ca + a.ct) * 2;
+    float lo_l = FLT_MAX, hi_l = -FLT_MAX;
+    for (int c = n16; c < a.ca; c += 16) {
+      lo_l = fminf(lo_l, mm[2 * c]);
+      hi_l = fmaxf(hi_l, mm[2 * c + 1]);
+    }
+    lo_l = row_min(lo_l);
+    hi_l = row_max(hi_l);
+#pragma unroll
+    for (int h = 0; h < kHeads; ++h) {
+      const float lo = lane_value(lo_l, 16 * h), hi = lane_value(hi_l, 16 * h);
+      float slope = 1.f, gam = 0.f, shift = 0.f;               // s' = slope * (s - gam) + shift
+      if (a.calib_mode != CQ_CALIB_NONE) {
+        const float glo = a.calib_mode == CQ_CALIB_DYNAMIC ? lo : a.gamma;
+        const float ghi = a.calib_mode == CQ_CALIB_DYNAMIC ? hi : a.delta;
+        const float width = ghi - glo;
+        slope = width == 0.f ? 1.f : (width + a.tau1 - a.tau2) / width;
+        gam = glo;
+        shift = glo - a.tau1;
+      }
+      // the map is monotone: an end of the row's range is its maximum, every weight is <= 1
+      const float M = fmaxf(slope * (lo - gam) + shift, slope * (hi - gam) + shift);
+      m_ref[h] = M;
+      a2[h] = h < gh ? slope * kLog2e : 0.f;
+      c2[h] = h < gh ? (shift - slope * gam - M) * kLog2e : -200.f;     // no head: weight 0
+    }
+  }
+
   for (int k = k0; k < k1; ++k) {
     int grp, tok0, nt;
     tile_at(k, grp, tok0, nt);
@@ -592,17 +718,6 @@ tile_values_kernel(const TileArgs a, int n_text_wg) {
       xs[h] = product_digits(p, vsf);
     }
     const bool fold = VCH && (k + 1 == k1 || (k + 1 - grp * a.v_tpg) == a.v_tpg || run + 1 == kMaxRun);
-    float gs[VCH ? NACC : 1], gm[VCH ? NACC : 1];
-    if constexpr (VCH) {
-      if (fold) {                                              // wave-uniform
-#pragma unroll
-        for (int p = 0; p < NACC; ++p) {
-          const size_t at = meta0 + (size_t)grp * D + channel(p);
-          gs[p] = a.v_scale[at];
-          gm[p] = __half2float(__ushort_as_half(a.v_min[at]));
-        }
-      }
-    }
     __builtin_amdgcn_wave_barrier();
     *reinterpret_cast<v4i*>(xbuf + 16 * lane) = xs;
     v4i A;
@@ -623,7 +738,7 @@ tile_values_kernel(const TileArgs a, int n_text_wg) {
       }
       // the next loads go out under the products
       if (pass + 1 < kPasses) load_pieces(tok0, nt, pass + 1);
-      else if (k + 1 < k1) load_tile(k + 1);
+      else if (k + 1 < k1 && !fold) load_tile(k + 1);         // behind a fold: its parameters are in use
       constexpr int kPassBlocks = SW >= 16 ? SW / 16 : 1;
 #pragma unroll
       for (int cbl = 0; cbl < kPassBlocks; ++cbl) {
@@ -649,11 +764,12 @@ tile_values_kernel(const TileArgs a, int n_text_wg) {
 #pragma unroll
         for (int p = 0; p < NACC; ++p) {
           const float s = gs[p] * variant_weight<BITS>(p % kV);
-          const float add = gm[p] + (BITS == 8 ? 128.f * gs[p] : 0.f);
+          const float add = __half2float(__ushort_as_half(gm[p])) + (BITS == 8 ? 128.f * gs[p] : 0.f);
           facc[p] = fmaf(digits_to_float(acc[p]) * 0x1p-29f, s, fmaf(wsum, add, facc[p]));
           acc[p] = (v4i){0, 0, 0, 0};
         }
         run = 0;
+        if (k + 1 < k1) load_tile(k + 1);
       }
     }
   }
@@ -665,15 +781,12 @@ tile_values_kernel(const TileArgs a, int n_text_wg) {
                         : fmaf(digits_to_float(acc[p]), inv_f, facc[p]) * variant_weight<BITS>(p % kV);
     if (CB >= 16 || n16 < 8) mem.part[wave][kb][channel(p)] = v;
   }
-#pragma unroll
-  for (int h = 0; h < kHeads; ++h) {
-    const float l = wave_sum(lsum[h]), m = wave_sum(msum[h]);
-    if (lane == 0) { s_lm[wave][h][0] = l; s_lm[wave][h][1] = m; }
-  }
-  store_partial<D>(a, head0, gh, chunk, m_ref, mem.part, s_lm);
+  const float l = head_sums(lsum, lane), m = head_sums(msum, lane);      // of head kb
+  if (n16 == 0) { s_lm[wave][kb][0] = l; s_lm[wave][kb][1] = m; }
+  finish_chunk<D>(a, row, set, head0, gh, chunk, m_ref, mem.part, s_lm);
 }
 
-using TileKernel = void (*)(const TileArgs, int);
+using TileKernel = void (*)(const TileArgs);
 
 template <int D>
 TileKernel logits_kernel(int bits) {
@@ -728,10 +841,11 @@ TilePlan make_tile_plan(const DecodeShape& s) {
   auto align64 = [](size_t x) { return (x + 63) / 64 * 64; };
   p.ws_minmax_floats = align64(heads * ((size_t)s.n_vis + s.n_text));
   p.ws_partial_floats = align64(p.ws_minmax_floats + heads * (size_t)(p.ca + p.ct) * 2);
-  const size_t floats = p.ws_partial_floats + heads * (size_t)(p.cb + p.ct) * (s.d + 2);
+  p.ws_count_floats = align64(p.ws_partial_floats + heads * (size_t)(p.cb + p.ct) * (s.d + 2));
+  const size_t floats = p.ws_count_floats + (size_t)(rows * sets);
   p.ws_bytes = (floats * sizeof(float) + 255) / 256 * 256;
-  const long long most = rows * (sets > 0 ? sets : 1) * 2 * kMaxTileChunks;
-  p.ok = most < 0x7fffffffLL;
+  // grid: rows x chunks x head sets
+  p.ok = rows * sets * 2 * kMaxTileChunks < 0x7fffffffLL && sets <= 65535;
   return p;
 }
 
@@ -766,8 +880,7 @@ hipError_t start_logits(TileArgs& a, const DecodeShape& s, const TilePlan& plan,
   const TileKernel kern = s.d == 64 ? logits_kernel<64>(s.bits)
                           : s.d == 128 ? logits_kernel<128>(s.bits) : logits_kernel<256>(s.bits);
   if (!kern) return hipErrorInvalidValue;
-  const unsigned rows = (unsigned)(s.B * s.Hkv), n_text_wg = rows * (unsigned)a.ct;
-  kern<<<dim3(n_text_wg + rows * (unsigned)(a.ca * a.sets)), dim3(kThreads), 0, stream>>>(a, (int)n_text_wg);
+  kern<<<dim3((unsigned)(s.B * s.Hkv), (unsigned)(a.ct + a.ca), (unsigned)a.sets), dim3(kThreads), 0, stream>>>(a);
   return hipGetLastError();
 }
 
@@ -785,6 +898,8 @@ hipError_t launch_decode_tile(const DecodeShape& s, const TilePlan& plan, const 
                               const void* v_text, const int32_t* n_text_dev, const Calib& calib,
                               float softmax_scale, void* out, float* workspace, hipStream_t stream) {
   TileArgs a{};
+  a.ws_count = reinterpret_cast<int*>(workspace + plan.ws_count_floats);
+  a.out = static_cast<__half*>(out);
   hipError_t e = start_logits(a, s, plan, q, k, k_text, n_text_dev, softmax_scale, workspace,
                               workspace + plan.ws_minmax_floats, stream);
   if (e != hipSuccess) return e;
@@ -803,11 +918,8 @@ hipError_t launch_decode_tile(const DecodeShape& s, const TilePlan& plan, const 
   const TileKernel kern = s.d == 64 ? values_kernel<64>(s.bits, vch)
                           : s.d == 128 ? values_kernel<128>(s.bits, vch) : values_kernel<256>(s.bits, vch);
   if (!kern) return hipErrorInvalidValue;
-  const unsigned rows = (unsigned)(s.B * s.Hkv), n_text_wg = rows * (unsigned)(a.ct * a.sets);
-  kern<<<dim3(n_text_wg + rows * (unsigned)(a.cb * a.sets)), dim3(kThreads), 0, stream>>>(a, (int)n_text_wg);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_combine(s.B * s.Hq, plan.cb + plan.ct, s.d, a.ws_partial, out, stream);
+  kern<<<dim3((unsigned)(s.B * s.Hkv), (unsigned)(a.ct + a.cb), (unsigned)a.sets), dim3(kThreads), 0, stream>>>(a);
+  return hipGetLastError();
 }
 
 }  // namespace cq
