@@ -131,6 +131,7 @@ struct DecodeCall {
   bool tuned;               // the tuned kernels run (else the shape-agnostic ones)
   bool streamed;            // tuned, split rows: the streaming kernels with logits kept in scratch
   bool tiled;               // not tuned: the tile kernels run (else the shape-agnostic ones)
+  bool tile_by_choice;      // a layout of the tuned kernels that the tile kernels finish sooner
   cq::FusedPlan plan;       // valid when tuned
   cq::StreamPlan stream;    // valid when streamed
   cq::TilePlan tile;        // valid when tiled
@@ -159,6 +160,39 @@ int check_calib(const cq_calib_t* calib, cq::Calib* c) {
   return CQ_OK;
 }
 
+// Whether the tile kernels finish a call sooner than the tuned kernels that could take it.  The fused
+// kernel gives a row (a chunk of a row) to one CU, which moves about 27 GB/s, and the streaming
+// kernels take three launches; with few rows the tile kernels, two launches over many small
+// workgroups, win.  Microseconds per call inside a recorded graph, fitted to measurements of both sides
+// over 8 to 256 rows (batch x KV heads) of 1024 to 32768 tokens, 1 to 8 bits, key groups of 32 tokens to
+// the whole row, 1 to 6 query heads per KV head; for example (tuned / tile)
+//   1 bit, 4 heads:  8 rows x 3328 tokens 12.5 / 11.8, x 8192 21.8 / 14.4; 32 rows x 8192 22.1 / 19.6;
+//                    8 rows x 1024 9.1 / 11.6 and 64 rows x 8192 22.2 / 27.1 stay fused
+//   1 bit, 6 heads:  8 rows x 3328 20.7 / 12.5, 64 rows 22.6 / 19.5; 128 rows 26.0 / 27.3 stay streamed
+//   4 bits:          32 rows x 3328 17.7 / 14.8;  8 bits: 8 rows x 3328 37.5 / 14.9, 128 rows 43.0 / 36.2
+// The tail's length plays no part: a workspace that serves a long tail serves a short one.
+bool tile_is_faster(cq::DecodeShape s, const cq::FusedPlan& with_tail) {
+  const double rows = (double)s.B * s.Hkv, kn = s.n_vis * 1e-3, mtok = rows * s.n_vis * 1e-6;
+  if (mtok > 2.0 || (s.g <= 4 && s.bits <= 2 && s.n_vis <= 1024)) return false;
+  s.n_text = 0;
+  const cq::FusedPlan plan = with_tail.n_chunks == 1 ? with_tail : cq::make_fused_plan(s, 0);
+  const bool streamed = (plan.n_chunks > 1 || plan.nhb > 1) && cq::make_stream_plan(s, 0).ok;
+  // bits:                           1     2     4     8
+  static const double kTilePerM[] = {26.0, 28.0, 36.0, 58.0};    // per million tokens
+  static const double kRowPerK[] = {1.65, 2.1, 3.0, 9.0};        // fused: per thousand tokens of a row
+  const int i = s.bits == 1 ? 0 : s.bits == 2 ? 1 : s.bits == 4 ? 2 : 3;
+  const bool two_sets = s.g > 4;
+  const double tile = 10.6 + (two_sets ? 0.35 : 0.25) * kn + (two_sets ? 1.6 : 1.0) * kTilePerM[i] * mtok;
+  const double group = s.k_axis == CQ_AXIS_CHANNEL && s.k_group == 32 ? 1.65 : s.k_group == 64 ? 1.25 : 1.0;
+  const double per_k = kRowPerK[i] * group;
+  const double workgroups = rows * plan.nhb * plan.n_chunks;
+  const double rounds = std::ceil(workgroups / 256.0), chunk_kn = kn / plan.n_chunks;
+  const double tuned = plan.n_chunks == 1 && plan.nhb == 1 ? (s.bits == 8 ? 9.5 : 7.0) + per_k * kn * rounds
+                       : streamed ? (two_sets ? 18.0 + 16.0 * mtok : 15.5 + 14.5 * mtok)
+                                  : 12.0 + 1.5 * per_k * chunk_kn * rounds;
+  return tile < 0.98 * tuned;
+}
+
 // Kernel selection and scratch size for a valid layout: one plan per call, used by the size query,
 // by the argument check and by the launch.
 // scratch_limit: the most scratch the caller can offer.  Rows that have to be split run on the
@@ -177,10 +211,20 @@ int select_kernels(const cq_layout_t* L, int n_text, int n_text_cap, size_t scra
     call->stream = cq::make_stream_plan(call->shape, g_decode_chunks);
     call->streamed = call->stream.ok && call->stream.ws_bytes <= scratch_limit;
   }
-  call->tiled = false;
-  if (!call->tuned && g_kernel_path == CQ_PATH_AUTO) {
-    call->tile = cq::make_tile_plan(call->shape);
-    call->tiled = call->tile.ok && call->tile.ws_bytes <= scratch_limit;
+  call->tiled = call->tile_by_choice = false;
+  if (g_kernel_path == CQ_PATH_AUTO) {
+    if (!call->tuned) {
+      call->tile = cq::make_tile_plan(call->shape);
+      call->tiled = call->tile.ok && call->tile.ws_bytes <= scratch_limit;
+    } else if (L->n_vis > 0 && g_decode_chunks == 0 && tile_is_faster(call->shape, call->plan)) {
+      call->tile = cq::make_tile_plan(call->shape);
+      call->tile_by_choice = call->tile.ok;
+      // not beyond the scratch of the allocation-free entry point: both entry points run the same kernels
+      if (call->tile.ok && call->tile.ws_bytes <= (size_t)CQ_NOALLOC_SCRATCH_BYTES) {
+        call->tiled = true;
+        call->tuned = call->streamed = false;
+      }
+    }
   }
   call->generic_ws = cq::workspace_layout(L->batch, L->n_q_heads, L->head_dim, L->n_vis, n_text);
   call->ws_bytes = call->streamed ? call->stream.ws_bytes
@@ -325,6 +369,9 @@ size_t cq_decode_workspace_bytes(const cq_layout_t* L, int32_t n_text, const cq_
   if (check_layout(L, true) != CQ_OK || n_text < 0 || check_calib(calib, &c) != CQ_OK) return 0;
   DecodeCall call;
   if (select_kernels(L, n_text, n_text, SIZE_MAX, &call) != CQ_OK) return 0;
+  // with a shorter tail the same workspace may have to serve the tile kernels
+  if (call.tile_by_choice && !call.tiled && call.ws_bytes < (size_t)CQ_NOALLOC_SCRATCH_BYTES)
+    return (size_t)CQ_NOALLOC_SCRATCH_BYTES;
   return call.ws_bytes;
 }
 

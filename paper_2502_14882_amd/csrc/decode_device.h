@@ -130,67 +130,11 @@ __device__ inline float lane_value(float v, int lane) {     // wave-uniform copy
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
 }
 
-// The same lane moves for doubles, half by half.
-template <int CTRL>
-__device__ inline double dpp_f64(double v) {
-  const v2i x = __builtin_bit_cast(v2i, v);
-  const v2i r = {__builtin_amdgcn_update_dpp(x[0], x[0], CTRL, 0xF, 0xF, true),
-                 __builtin_amdgcn_update_dpp(x[1], x[1], CTRL, 0xF, 0xF, true)};
-  return __builtin_bit_cast(double, r);
-}
-template <int CTRL> __device__ inline float dpp_move(float v) { return dpp_f32<CTRL>(v); }
-template <int CTRL> __device__ inline double dpp_move(double v) { return dpp_f64<CTRL>(v); }
-// a + (a of the other half of the wave) in lanes 0-31, the same of b in lanes 32-63: a paired swap of
-// two values and one add halve both
-__device__ inline float fold_halves(float a, float b) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b), false, false);
-  return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
-}
-__device__ inline double fold_halves(double a, double b) {
-  const v2u x = __builtin_bit_cast(v2u, a), y = __builtin_bit_cast(v2u, b);
-  const auto lo = __builtin_amdgcn_permlane32_swap(x[0], y[0], false, false);
-  const auto hi = __builtin_amdgcn_permlane32_swap(x[1], y[1], false, false);
-  return __builtin_bit_cast(double, (v2u){lo[0], hi[0]}) + __builtin_bit_cast(double, (v2u){lo[1], hi[1]});
-}
-// the same over neighbouring rows of 16 lanes
-__device__ inline float fold_rows(float a, float b) {
-  const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b), false, false);
-  return __builtin_bit_cast(float, (unsigned)r[0]) + __builtin_bit_cast(float, (unsigned)r[1]);
-}
-__device__ inline double fold_rows(double a, double b) {
-  const v2u x = __builtin_bit_cast(v2u, a), y = __builtin_bit_cast(v2u, b);
-  const auto lo = __builtin_amdgcn_permlane16_swap(x[0], y[0], false, false);
-  const auto hi = __builtin_amdgcn_permlane16_swap(x[1], y[1], false, false);
-  return __builtin_bit_cast(double, (v2u){lo[0], hi[0]}) + __builtin_bit_cast(double, (v2u){lo[1], hi[1]});
-}
-
-// Sum over the wave of the four heads' parts, head kb = lane / 16 in every lane of row kb.  A
-// transposing butterfly leaves lane (.., b1, b0) with head 2*b0 + b1 after two steps, the remaining
-// steps add lanes that hold the same head.  Every lane of a row then holds the row's sum for head
-// bitrev2(lane & 3); what is wanted is the sum over the four rows, head kb in row kb: the four heads
-// side by side (quad broadcasts), then a transposing fold over the rows with paired lane swaps - all
-// on the vector unit, where this used to take three LDS round trips per group.
-template <typename T>
-__device__ inline T head_sums(const T (&part)[kHeads], int lane) {
-  const bool b0 = lane & 1, b1 = lane & 2;
-  T u0 = b0 ? part[2] : part[0], u1 = b0 ? part[3] : part[1];
-  const T g0 = b0 ? part[0] : part[2], g1 = b0 ? part[1] : part[3];
-  u0 += dpp_move<0xB1>(g0);                // quad_perm 1,0,3,2: lane ^ 1
-  u1 += dpp_move<0xB1>(g1);
-  T r = b1 ? u1 : u0;
-  const T g2 = b1 ? u0 : u1;
-  r += dpp_move<0x4E>(g2);                 // quad_perm 2,3,0,1: lane ^ 2
-  r += dpp_move<0x124>(r);                 // row_ror 4
-  r += dpp_move<0x128>(r);                 // row_ror 8
-  const T h0 = dpp_move<0x00>(r), h1 = dpp_move<0xAA>(r);     // quad lanes 0 and 2
-  const T h2 = dpp_move<0x55>(r), h3 = dpp_move<0xFF>(r);     // quad lanes 1 and 3
-  // heads 0 | 2 and 1 | 3 in the halves, then rows 0..3: heads 0, 1, 2, 3
-  return fold_rows(fold_halves(h0, h2), fold_halves(h1, h3));
-}
-
 // Additive post-scaling term of one key group, sum_c q'[h][c] * min[c] for the four heads.  Every
 // lane brings two channels (q' already carries the softmax scale and the lane's operand weight
-// w, which inv_w = 1/w takes out again, per channel).
+// w, which inv_w = 1/w takes out again, per channel).  A transposing butterfly leaves lane (.., b1, b0) with head
+// 2*b0 + b1 after two steps, the remaining steps add lanes that hold the same head; the result
+// lane of head kb = lane / 16 then fetches its head.
 // off0/off1: what the operand bytes leave out per channel (128 * scale for 8-bit codes, else 0).
 __device__ inline float group_bias(const float (&qv0)[kHeads], const float (&qv1)[kHeads],
                                    uint16_t m0, uint16_t m1, float off0, float off1, float inv_w0,
@@ -200,7 +144,30 @@ __device__ inline float group_bias(const float (&qv0)[kHeads], const float (&qv1
   float part[kHeads];
 #pragma unroll
   for (int h = 0; h < kHeads; ++h) part[h] = fmaf(qv0[h], f0, qv1[h] * f1);
-  return head_sums(part, lane);
+  const bool b0 = lane & 1, b1 = lane & 2;
+  float u0 = b0 ? part[2] : part[0], u1 = b0 ? part[3] : part[1];
+  const float g0 = b0 ? part[0] : part[2], g1 = b0 ? part[1] : part[3];
+  u0 += dpp_f32<0xB1>(g0);                 // quad_perm 1,0,3,2: lane ^ 1
+  u1 += dpp_f32<0xB1>(g1);
+  float r = b1 ? u1 : u0;
+  const float g2 = b1 ? u0 : u1;
+  r += dpp_f32<0x4E>(g2);                  // quad_perm 2,3,0,1: lane ^ 2
+  r += dpp_f32<0x124>(r);                  // row_ror 4
+  r += dpp_f32<0x128>(r);                  // row_ror 8
+  // Every lane of a row now holds the row's sum for head bitrev2(lane & 3).  What is wanted is the
+  // sum over the four rows, head kb in row kb: the four heads side by side (quad broadcasts), then
+  // a transposing fold over the rows with paired lane swaps (a swap of two values and one add
+  // halve both) - all on the vector unit, where this used to take three LDS round trips per group.
+  const float h0 = dpp_f32<0x00>(r), h1 = dpp_f32<0xAA>(r);     // quad lanes 0 and 2
+  const float h2 = dpp_f32<0x55>(r), h3 = dpp_f32<0xFF>(r);     // quad lanes 1 and 3
+  auto bits_of = [](float v) { return __builtin_bit_cast(unsigned, v); };
+  auto float_of = [](unsigned v) { return __builtin_bit_cast(float, v); };
+  const auto e = __builtin_amdgcn_permlane32_swap(bits_of(h0), bits_of(h2), false, false);
+  const auto o = __builtin_amdgcn_permlane32_swap(bits_of(h1), bits_of(h3), false, false);
+  const float s02 = float_of(e[0]) + float_of(e[1]);            // head 0 in lanes 0-31, head 2 in 32-63
+  const float s13 = float_of(o[0]) + float_of(o[1]);            // head 1 | head 3
+  const auto t = __builtin_amdgcn_permlane16_swap(bits_of(s02), bits_of(s13), false, false);
+  return float_of(t[0]) + float_of(t[1]);                       // rows 0..3: heads 0, 1, 2, 3
 }
 
 // Fixed-point operands are |x| < 2^29, four signed base-256 digits.  The wide range is needed

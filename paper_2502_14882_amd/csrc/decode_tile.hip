@@ -32,6 +32,7 @@
 
 #include "cq_internal.h"
 #include "decode_device.h"
+#include "decode_fold.h"
 
 namespace cq {
 namespace {
@@ -51,8 +52,8 @@ struct TileArgs {
   const __half* k_text; const __half* v_text;
   int g, sets, n_vis, n_text, n_text_cap;    // sets = ceil(g / 4)
   const int32_t* n_text_dev;   // NULL, or the tail length in device memory (n_text is then its bound)
-  int k_group, k_bpg;          // tokens per key group, blocks per group
-  int v_group, v_tpg;          // tokens per value group (token-wise: n_vis), tiles per group
+  int k_group, k_bpg, k_groups;   // tokens per key group, blocks per group, groups per row
+  int v_group, v_tpg, v_groups;   // tokens per value group (token-wise: n_vis), tiles per group, groups per row
   int ca, ca_base, ca_rem;     // logits pass: chunks per row, in key blocks
   int cb, cb_base, cb_rem;     // values pass: chunks per row, in value tiles
   int ct, ct_tokens;           // chunks of the fp16 tail per row, tokens per chunk
@@ -121,6 +122,10 @@ __device__ inline void load_words(uint32_t (&w)[N], const uint32_t* p) {
     }
   }
 }
+
+// k / per without a division where there is nothing to divide: one part, or parts of one (a division
+// by a value that is only known at run time takes about 40 instructions)
+__device__ inline int part_of(int k, int per) { return per == 1 ? k : k < per ? 0 : k / per; }
 
 // The four signed base-256 digits of a * b rounded to the nearest integer (|a b| < 2^30), as the four
 // bytes of the result.  Added to 1.5 * 2^52 a double shows the integer in its low word.
@@ -247,8 +252,7 @@ tile_logits_kernel(const TileArgs a) {
   const uint8_t* x_rd = xb + (kb * 16 + (n16 >> 1)) * 16 + (n16 & 1) * 8;
   const uint32_t* kc = a.k_codes + row * (size_t)a.n_vis * Op::kRowWords + Op::first_word(kb);
   const int sh = Op::shift(kb);
-  const int n_groups = a.n_vis / a.k_group;
-  const size_t meta0 = row * (size_t)n_groups * D;
+  const size_t meta0 = row * (size_t)a.k_groups * D;
   float* out = a.ws_logits + (head0 + min(kb, gh - 1)) * n_all;     // result lane: head kb, token n16
   const bool live = kb < gh;
 
@@ -266,7 +270,7 @@ tile_logits_kernel(const TileArgs a) {
       load_words<Op::kWords>(w[u], kc + (size_t)min(t + 16 * u + n16, t1 - 1) * Op::kRowWords);
   };
   auto load_block = [&](int blk, int group_loaded) {           // codes, and parameters if they change
-    grp = a.k_bpg == 1 ? blk : blk / a.k_bpg;
+    grp = part_of(blk, a.k_bpg);
     t0 = grp * a.k_group + (blk - grp * a.k_bpg) * kKeyBlock;
     t1 = min(t0 + kKeyBlock, (grp + 1) * a.k_group);
     load_tiles(t0);
@@ -578,7 +582,7 @@ tile_values_kernel(const TileArgs a) {
   const uint8_t* vc = reinterpret_cast<const uint8_t*>(a.v_codes) + row * (size_t)a.n_vis * CB;
   const float* vs = a.v_scale + row * (size_t)a.n_vis;         // token-wise
   const uint16_t* vm = a.v_min + row * (size_t)a.n_vis;
-  const size_t meta0 = VCH ? row * (size_t)(a.n_vis / a.v_group) * D : 0;
+  const size_t meta0 = VCH ? row * (size_t)a.v_groups * D : 0;
   const float* lg[kHeads];
 #pragma unroll
   for (int h = 0; h < kHeads; ++h) lg[h] = a.ws_logits + (head0 + min(h, gh - 1)) * n_all;
@@ -610,7 +614,7 @@ tile_values_kernel(const TileArgs a) {
   uint16_t gm[VCH ? NACC : 1];
   int params_of = -1;
   auto tile_at = [&](int k, int& grp, int& tok0, int& nt) {
-    grp = a.v_tpg == 1 ? k : k / a.v_tpg;
+    grp = part_of(k, a.v_tpg);
     const int sub = k - grp * a.v_tpg;
     tok0 = grp * a.v_group + sub * kValTile;
     nt = min(kValTile, a.v_group - sub * kValTile);
@@ -871,7 +875,8 @@ hipError_t start_logits(TileArgs& a, const DecodeShape& s, const TilePlan& plan,
   a.k_group = s.k_group; a.k_bpg = ceil_div(s.k_group, kKeyBlock);
   a.ca = plan.ca; a.ct = plan.ct; a.ct_tokens = plan.ct_tokens;
   if (s.n_vis > 0) {
-    const int blocks = s.n_vis / s.k_group * a.k_bpg;
+    a.k_groups = s.n_vis / s.k_group;
+    const int blocks = a.k_groups * a.k_bpg;
     a.ca_base = blocks / a.ca; a.ca_rem = blocks % a.ca;
   }
   a.ws_logits = logits;
@@ -909,7 +914,8 @@ hipError_t launch_decode_tile(const DecodeShape& s, const TilePlan& plan, const 
   a.v_group = vch ? s.v_group : s.n_vis; a.v_tpg = ceil_div(a.v_group, kValTile);
   a.cb = plan.cb;
   if (s.n_vis > 0) {
-    const int tiles = s.n_vis / a.v_group * a.v_tpg;
+    a.v_groups = s.n_vis / a.v_group;
+    const int tiles = a.v_groups * a.v_tpg;
     a.cb_base = tiles / a.cb; a.cb_rem = tiles % a.cb;
   }
   a.ws_partial = workspace + plan.ws_partial_floats;
