@@ -112,7 +112,8 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
 
 def _stream(t: torch.Tensor) -> Optional[int]:
     if t.is_cuda:
-        return torch.cuda.current_stream(t.device).cuda_stream or None
+        # the current stream's handle without building a Stream object around it
+        return torch._C._cuda_getCurrentRawStream(t.get_device()) or None
     return None
 
 
@@ -132,11 +133,13 @@ def make_layout(batch, n_q_heads, n_kv_heads, head_dim, n_vis, bits=1,
                     k_group, v_group)
 
 
+def _meta_shape_of(B: int, H: int, n: int, d: int, axis: int, group: int):
+    group = group if group > 1 else 1
+    return (B, H, n // group, d) if axis == CQ_AXIS_CHANNEL else (B, H, n, d // group)
+
+
 def _meta_shape(layout: CqLayout, axis: int, group: int):
-    B, H, n, d = layout.batch, layout.n_kv_heads, layout.n_vis, layout.head_dim
-    if axis == CQ_AXIS_CHANNEL:
-        return (B, H, n // max(group, 1), d)
-    return (B, H, n, d // max(group, 1))
+    return _meta_shape_of(layout.batch, layout.n_kv_heads, layout.n_vis, layout.head_dim, axis, group)
 
 
 def alloc_qtensor(layout: CqLayout, axis: int, group: int, device) -> QTensor:
@@ -172,31 +175,40 @@ def cq_decode_workspace_bytes(layout: CqLayout, n_text: int, calib: Optional[CqC
                                                ctypes.byref(calib) if calib is not None else None))
 
 
+# The checks run on every call, in the time the GPU could already be working: layout fields are read
+# once each, shapes are compared as they are (a torch.Size is a tuple), texts are only made on failure.
+
 def _check_decode_tensors(layout: CqLayout, q, k_text, v_text, out) -> int:
     """Shapes against the layout (a mismatch would be an out-of-bounds read on the device);
     returns the tail's capacity."""
-    assert q.dtype == torch.float16 and q.is_contiguous()
-    assert tuple(q.shape) == (layout.batch, layout.n_q_heads, layout.head_dim), \
-        "q is %s, the layout says %s" % (tuple(q.shape), (layout.batch, layout.n_q_heads, layout.head_dim))
-    assert out.dtype == torch.float16 and out.is_contiguous() and out.shape == q.shape
+    f16 = torch.float16
+    batch, d = layout.batch, layout.head_dim
+    shape = q.shape
+    assert q.dtype is f16 and q.is_contiguous()
+    assert shape == (batch, layout.n_q_heads, d), \
+        "q is %s, the layout says %s" % (tuple(shape), (batch, layout.n_q_heads, d))
+    assert out.dtype is f16 and out.is_contiguous() and out.shape == shape
     if k_text is None:
         assert v_text is None
         return 0
-    assert k_text.dtype == torch.float16 and k_text.is_contiguous()
-    assert v_text is not None and v_text.dtype == torch.float16 and v_text.is_contiguous()
-    assert v_text.shape == k_text.shape and k_text.dim() == 4
-    assert tuple(k_text.shape[:2]) == (layout.batch, layout.n_kv_heads) and \
-        k_text.shape[3] == layout.head_dim, "text tail is %s" % (tuple(k_text.shape),)
-    return int(k_text.shape[2])
+    assert k_text.dtype is f16 and k_text.is_contiguous()
+    assert v_text is not None and v_text.dtype is f16 and v_text.is_contiguous()
+    tail = k_text.shape
+    assert v_text.shape == tail and len(tail) == 4
+    assert tail[0] == batch and tail[1] == layout.n_kv_heads and tail[3] == d, \
+        "text tail is %s" % (tuple(tail),)
+    return tail[2]
 
 
 def _check_qtensor(layout: CqLayout, t: "QTensor", axis: int, group: int, what: str) -> None:
-    want = (layout.batch, layout.n_kv_heads, layout.n_vis, layout.head_dim * layout.bits // 32)
-    assert tuple(t.codes.shape) == want and t.codes.is_contiguous(), "%s codes are %s" % (what, tuple(t.codes.shape))
-    meta = _meta_shape(layout, axis, group)
-    assert tuple(t.scale.shape) == meta and tuple(t.min.shape) == meta, "%s parameters are %s" % (what, tuple(t.scale.shape))
-    assert t.scale.dtype == torch.float32 and t.min.dtype == torch.float16
-    assert t.scale.is_contiguous() and t.min.is_contiguous()
+    codes, scale, low = t
+    batch, heads, n, d = layout.batch, layout.n_kv_heads, layout.n_vis, layout.head_dim
+    assert codes.shape == (batch, heads, n, d * layout.bits // 32) and codes.is_contiguous(), \
+        "%s codes are %s" % (what, tuple(codes.shape))
+    meta = _meta_shape_of(batch, heads, n, d, axis, group)
+    assert scale.shape == meta and low.shape == meta, "%s parameters are %s" % (what, tuple(scale.shape))
+    assert scale.dtype is torch.float32 and low.dtype is torch.float16
+    assert scale.is_contiguous() and low.is_contiguous()
 
 
 def make_calib(mode=CQ_CALIB_NONE, tau1=0.0, tau2=0.0, gamma=0.0, delta=0.0) -> CqCalib:
