@@ -10,16 +10,19 @@
 // kernels' logits pass where it takes the layout, else the shape-agnostic one; the exact keys pass
 // as a 16-bit tail), the weights in fp64.
 //
-// The grid costs n1 + n2 + 2 exponentials per token and pass instead of one per pair: with
-// u = (s - gamma) / (delta - gamma),  g(s) = s + tau1 (u - 1) - tau2 u,  so a weight is
-// e^s e^(tau1 (u - 1)) e^(-tau2 u).  Blocks of 4 x 4 pairs stay in registers; a row is cut into chunks
-// so that every CU works, and two passes (normalizers, then squared differences) meet in memory.
-// Bound: fp64 arithmetic.  128 query rows x 3456 tokens, 4 x 4 grid: 416 -> 57 us (logits 2 x 124 -> 2 x
-// 6, grid 136 -> 17 + 24, sum over rows 31 -> 4), against 64 bits 2e-7 -> 3e-8.
+// The grid costs n1 + n2 + 2 exponentials per token and pass (4 where the taus are evenly spaced
+// from 0) instead of one per pair: with u = (s - gamma) / (delta - gamma),  g(s) = s + tau1 (u - 1) -
+// tau2 u,  so a weight is e^s e^(tau1 (u - 1)) e^(-tau2 u).  Blocks of 4 x 4 pairs stay in registers;
+// a row is cut into chunks so that every CU works, and two passes (normalizers, then squared
+// differences) meet in memory.
+// Bound: fp64 arithmetic.  128 query rows x 3456 tokens, 4 x 4 grid: 416 us at first (one exponential
+// per pair, a block per row), 55.6 us with factors and chunks, 42.8 with the sums folded by lane swaps,
+// 32.9 with even spacing and the normalizers loaded eight at a time; against 64 bits 2e-7 -> 3e-8.
 #include <cfloat>
 #include <cmath>
 
 #include "cq_internal.h"
+#include "decode_fold.h"
 
 namespace cq {
 namespace {
@@ -31,8 +34,13 @@ constexpr int kPairs = kGrid * kGrid;
 // three factors then stay within e^+-150 of 1.  Beyond it every pair gets its own exponential.
 constexpr double kFactorLimit = 50.0;
 
+// How the weights of a block of pairs are formed.  kEven: both lists are evenly spaced (as {0, 1, 2, 3}
+// is), so the factors of a list are a geometric series of two exponentials.
+enum { kPairwise = 0, kFactors = 1, kEven = 2 };
+
 struct TauArgs {
   float tau1[kMaxTauPairs], tau2[kMaxTauPairs];
+  double step1, step2;                   // kEven: distance of neighbouring taus
   int n1, n2, n_vis, n_text, n_chunks, chunk_tokens;
   int ca, ct, cx;                        // chunk extrema: quantized visual, text, exact keys
   const float* logits_q;                 // [rows][n_vis + n_text]: quantized visual, then text
@@ -43,10 +51,17 @@ struct TauArgs {
   double* err_part;                      // [rows][n_chunks][n1 n2] squared differences
 };
 
+// sum over each row of 16 lanes, every lane of the row gets it
+__device__ inline double row_total(double v) {
+  v += dpp_f64<0xB1>(v);      // quad_perm 1,0,3,2
+  v += dpp_f64<0x4E>(v);      // quad_perm 2,3,0,1
+  v += dpp_f64<0x141>(v);     // row_half_mirror
+  return v + dpp_f64<0x140>(v);
+}
 __device__ inline double wave_total(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
+  v = row_total(v);
+  v += __shfl_xor(v, 16);
+  return v + __shfl_xor(v, 32);
 }
 
 // What every thread of a block knows about its query row.
@@ -65,8 +80,12 @@ __device__ inline Row row_extrema(const TauArgs& a, size_t row) {
   for (int c = lane; c < a.ct; c += 64) tmax = fmaxf(tmax, mq[2 * (a.ca + c) + 1]);
   const float* mx = a.minmax_x + row * (size_t)a.cx * 2;
   for (int c = lane; c < a.cx; c += 64) xmax = fmaxf(xmax, mx[2 * c + 1]);
+  lo = row_min(lo);
+  hi = row_max(hi);
+  tmax = row_max(tmax);
+  xmax = row_max(xmax);
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
+  for (int o = 16; o <= 32; o <<= 1) {
     lo = fminf(lo, __shfl_xor(lo, o));
     hi = fmaxf(hi, __shfl_xor(hi, o));
     tmax = fmaxf(tmax, __shfl_xor(tmax, o));
@@ -83,21 +102,33 @@ __device__ inline Row row_extrema(const TauArgs& a, size_t row) {
 }
 
 // Weights (up to a factor per pair) of one token for the pairs (i0 + i, j0 + j), and of the exact keys.
-// FACTORED: common reference m0 for all pairs.  Else pair by pair, with each pair's own reference,
+// With factors: common reference m0 for all pairs.  Else pair by pair, with each pair's own reference,
 // the largest calibrated logit (g is monotone: an end of [gamma, delta] or a text token).
-template <bool FACTORED>
+template <int MODE>
 __device__ inline void token_weights(const TauArgs& a, const Row& r, const double (&t1)[kGrid],
                                      const double (&t2)[kGrid], double s, double sx, bool vis,
                                      double (&w)[kPairs], double& ref) {
   ref = exp(sx - r.m_ref);
   const double u = (s - r.gamma) * r.inv_width;
-  if constexpr (FACTORED) {
+  if constexpr (MODE != kPairwise) {
     const double e = exp(s - r.m0);
     double f1[kGrid], f2[kGrid];
+    if constexpr (MODE == kEven) {
+      const double x1 = vis ? u - 1.0 : 0.0, x2 = vis ? -u : 0.0;
+      const double by1 = exp(a.step1 * x1), by2 = exp(a.step2 * x2);
+      f1[0] = t1[0] == 0.0 ? e : e * exp(t1[0] * x1);          // wave-uniform
+      f2[0] = t2[0] == 0.0 ? 1.0 : exp(t2[0] * x2);
 #pragma unroll
-    for (int i = 0; i < kGrid; ++i) {
-      f1[i] = vis ? e * exp(t1[i] * (u - 1.0)) : e;
-      f2[i] = vis ? exp(-t2[i] * u) : 1.0;
+      for (int i = 1; i < kGrid; ++i) {
+        f1[i] = f1[i - 1] * by1;
+        f2[i] = f2[i - 1] * by2;
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < kGrid; ++i) {
+        f1[i] = vis ? e * exp(t1[i] * (u - 1.0)) : e;
+        f2[i] = vis ? exp(-t2[i] * u) : 1.0;
+      }
     }
 #pragma unroll
     for (int i = 0; i < kGrid; ++i)
@@ -117,7 +148,7 @@ __device__ inline void token_weights(const TauArgs& a, const Row& r, const doubl
 }
 
 // grid.x = rows * n_chunks.  ERR = false: normalizers of the chunk; true: squared differences.
-template <bool FACTORED, bool ERR>
+template <int MODE, bool ERR>
 __global__ void __launch_bounds__(kThreads)
 tau_grid_kernel(const TauArgs a) {
   __shared__ double red[kThreads / 64][kPairs + 1];
@@ -132,7 +163,14 @@ tau_grid_kernel(const TauArgs a) {
   if constexpr (ERR) {
     for (int p = threadIdx.x; p <= n_pairs; p += kThreads) {
       double z = 0.0;
-      for (int c = 0; c < a.n_chunks; ++c) z += a.z_part[(row * a.n_chunks + c) * (n_pairs + 1) + p];
+      const double* zp = a.z_part + row * a.n_chunks * (size_t)(n_pairs + 1) + p;
+      for (int c0 = 0; c0 < a.n_chunks; c0 += 8) {           // eight loads in flight
+        double v[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) v[c] = zp[(size_t)min(c0 + c, a.n_chunks - 1) * (n_pairs + 1)];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) z += c0 + c < a.n_chunks ? v[c] : 0.0;
+      }
       inv_z[p] = 1.0 / z;
     }
     __syncthreads();
@@ -158,7 +196,7 @@ tau_grid_kernel(const TauArgs a) {
         const bool vis = t < a.n_vis;
         const double s = sq[t], x = vis ? sx[t] : sq[t];
         double w[kPairs], ref;
-        token_weights<FACTORED>(a, r, t1, t2, s, x, vis, w, ref);
+        token_weights<MODE>(a, r, t1, t2, s, x, vis, w, ref);
         if constexpr (ERR) {
           const double q = ref * iz_ref;
 #pragma unroll
@@ -174,10 +212,16 @@ tau_grid_kernel(const TauArgs a) {
       }
       const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
       __syncthreads();                         // the sums of the block of pairs before this one are out
+      // four sums at a time: paired lane swaps leave one per row of 16 lanes (17 sums through LDS
+      // exchanges took a third of the kernel)
 #pragma unroll
-      for (int p = 0; p <= (ERR ? kPairs - 1 : kPairs); ++p) {
-        const double v = wave_total(acc[p]);
-        if (lane == 0) red[wave][p] = v;
+      for (int p = 0; p < kPairs; p += 4) {
+        const double v = row_total(fold_rows(fold_halves(acc[p], acc[p + 2]), fold_halves(acc[p + 1], acc[p + 3])));
+        if ((lane & 15) == 0) red[wave][p + (lane >> 4)] = v;
+      }
+      if constexpr (!ERR) {
+        const double v = wave_total(acc[kPairs]);
+        if (lane == 0) red[wave][kPairs] = v;
       }
       __syncthreads();
       const int p = threadIdx.x;
@@ -260,18 +304,28 @@ hipError_t launch_tau_search(const DecodeShape& s, const void* q, const void* k_
   for (int i = 0; i < n_tau2; ++i) { a.tau2[i] = tau2[i]; factored = factored && std::fabs((double)tau2[i]) <= kFactorLimit; }
   a.n_vis = s.n_vis; a.n_text = s.n_text;
   a.n_chunks = wl.n_chunks;
-  a.chunk_tokens = ceil_div(n_all, wl.n_chunks);
+  a.chunk_tokens = ceil_div(ceil_div(n_all, kThreads), wl.n_chunks) * kThreads;
   a.logits_q = logits_q; a.logits_x = logits_x;
   a.minmax_q = minmax_q; a.minmax_x = minmax_x;
   a.z_part = reinterpret_cast<double*>(workspace + wl.z_part);
   a.err_part = reinterpret_cast<double*>(workspace + wl.err_part);
   const dim3 grid((unsigned)(rows * wl.n_chunks)), block(kThreads);
-  if (factored) tau_grid_kernel<true, false><<<grid, block, 0, stream>>>(a);
-  else tau_grid_kernel<false, false><<<grid, block, 0, stream>>>(a);
+  auto spacing = [](const float* t, int n, double* step) {     // whether t is evenly spaced, exactly
+    *step = n > 1 ? (double)t[1] - (double)t[0] : 0.0;
+    for (int i = 2; i < n; ++i)
+      if ((double)t[i] - (double)t[i - 1] != *step) return false;
+    return true;
+  };
+  const bool even = spacing(tau1, n_tau1, &a.step1) && spacing(tau2, n_tau2, &a.step2);
+  const int mode = !factored ? kPairwise : even ? kEven : kFactors;
+  if (mode == kEven) tau_grid_kernel<kEven, false><<<grid, block, 0, stream>>>(a);
+  else if (mode == kFactors) tau_grid_kernel<kFactors, false><<<grid, block, 0, stream>>>(a);
+  else tau_grid_kernel<kPairwise, false><<<grid, block, 0, stream>>>(a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (factored) tau_grid_kernel<true, true><<<grid, block, 0, stream>>>(a);
-  else tau_grid_kernel<false, true><<<grid, block, 0, stream>>>(a);
+  if (mode == kEven) tau_grid_kernel<kEven, true><<<grid, block, 0, stream>>>(a);
+  else if (mode == kFactors) tau_grid_kernel<kFactors, true><<<grid, block, 0, stream>>>(a);
+  else tau_grid_kernel<kPairwise, true><<<grid, block, 0, stream>>>(a);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   tau_reduce_kernel<<<dim3((unsigned)n_pairs), block, 0, stream>>>(

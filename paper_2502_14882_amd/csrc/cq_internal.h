@@ -96,9 +96,9 @@ inline TauWorkspace tau_workspace_layout(int B, int Hq, int n_vis, int n_text, i
   const int nvc = most(ceil_div(n_vis, kVisChunk)), ntc = most(ceil_div(n_text, kTextChunk));
   const int nxc = most(ceil_div(n_vis, kTextChunk));
   const size_t rows = (size_t)B * (size_t)Hq;
-  // four blocks per CU, at least one token per thread
-  const size_t want = (1024 + rows - 1) / rows, can = (size_t)ceil_div(n_vis + n_text, 256);
-  w.n_chunks = (int)(want < can ? want : can > 0 ? can : 1);
+  // about four blocks per CU, each of them whole rounds of one token per thread
+  const int want = (int)((1024 + rows - 1) / rows), rounds = ceil_div(n_vis + n_text, 256);
+  w.n_chunks = rounds > 0 ? ceil_div(rounds, ceil_div(rounds, want)) : 1;
   auto align64 = [](size_t x) { return (x + 63) / 64 * 64; };
   w.logits_q = 0;
   w.logits_x = align64(w.logits_q + rows * ((size_t)n_vis + (size_t)n_text));
