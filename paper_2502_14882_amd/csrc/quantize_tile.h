@@ -321,9 +321,19 @@ __device__ __forceinline__ void quantize_tile(const QArgs& a, const unsigned blo
       const int c = tid;
       const _Float16* part = seq_partials<D, BITS>(a, seq);
       _Float16 lo = part[c], hi = part[D + c];
-      for (int sp = 1; sp < a.splits; ++sp) {
-        lo = (_Float16)fminf((float)lo, (float)part[(sp * 2 + 0) * D + c]);
-        hi = (_Float16)fmaxf((float)hi, (float)part[(sp * 2 + 1) * D + c]);
+      for (int sp0 = 1; sp0 < a.splits; sp0 += 8) {          // eight partials in flight (repeated past the end)
+        _Float16 l[8], h[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const int sp = min(sp0 + i, a.splits - 1);
+          l[i] = part[(sp * 2 + 0) * D + c];
+          h[i] = part[(sp * 2 + 1) * D + c];
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          lo = (_Float16)fminf((float)lo, (float)l[i]);
+          hi = (_Float16)fmaxf((float)hi, (float)h[i]);
+        }
       }
       const uint16_t mbits = canonical_zero(__builtin_bit_cast(uint16_t, lo));
       const double alpha = h_to_double(mbits);
