@@ -59,3 +59,49 @@ def test_tile_decode(d, bits):
                                        cq.make_calib(*args))
         torch.cuda.synchronize()
         _check(out, ref, what + " length on the device")
+
+
+@pytest.mark.parametrize("d,n_vis,batch", [(64, 640, 2), (128, 4224, 1)])
+def test_recorded_step_on_the_tile_kernels(d, n_vis, batch):
+    """A growing step (append, attend) recorded once and replayed with eager work and synchronizations
+    in between: the count by which the last workgroup of a row is found starts over in every replay.
+    (128, 4224 tokens, 2 rows: a layout of the fused kernel that the tile kernels finish sooner.)"""
+    w = synth.WORKLOADS[1].replace(batch=batch, n_kv_heads=2, n_q_heads=8, head_dim=d, n_vis=n_vis, n_text=126,
+                                   seed=d)
+    lay = cq.make_layout(batch, 8, 2, d, n_vis, 1, 0, 1, 64, d)
+    x_cpu = synth.make_inputs(w, "cpu")
+    x = H.to_device(x_cpu)
+    kq, vq = H.oracle_quantize(x_cpu, lay)
+    kd, vd = cq.cq_quantize_kv(lay, x["k"], x["v"])
+    first, cap = 123, 126
+    tails = [x[t].clone() for t in ("k_text", "v_text")]
+    length = torch.tensor([first], dtype=torch.int32, device="cuda")
+    new = [torch.zeros(batch, 2, 1, d, dtype=torch.float16, device="cuda") for _ in range(2)]
+    calib = cq.make_calib(cq.CQ_CALIB_DYNAMIC, 1, 2)
+    ws = torch.empty(cq.cq_decode_workspace_bytes(lay, cap, calib), dtype=torch.uint8, device="cuda")
+    assert ws.numel() > 256                             # logits in scratch: not the one-launch kernel
+    out = torch.zeros_like(x["q"])
+
+    def step():
+        cq.cq_append_text_kv_devlen(lay, *tails, length, *new)
+        cq.cq_decode_attn_devlen(lay, x["q"], kd, vd, *tails, length, cap, calib, out=out, workspace=ws)
+
+    step()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step()
+    length.fill_(first)
+    for i in range(3):
+        at = first + i
+        for t, n in zip(("k_text", "v_text"), new):
+            n.copy_(x[t][:, :, at:at + 1])
+        out.zero_()
+        ws.fill_(255)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert int(length) == at + 1
+        ref = O.decode_attn(x_cpu["q"].numpy(), kq, vq, x_cpu["k_text"].numpy(), x_cpu["v_text"].numpy(), at + 1,
+                            O.CALIB_DYNAMIC, 1.0, 2.0)
+        _check(out, ref, "d %d replay %d" % (d, i))
