@@ -400,8 +400,11 @@ def main() -> int:
         fused = False
     cq.cq_bench_set_kernel_path(prev_path)
     split = fused and ws.numel() > 256          # rows split over workgroups: the scratch says so
+    # (the tile kernels keep their logits in fp32, the streaming ones in 16 bits)
+    tiled = args.path == "auto" and ws.numel() >= w.batch * w.n_q_heads * (w.n_vis + w.n_text) * 4
     streamed = split and ws.numel() > w.batch * w.n_q_heads * w.n_vis * 2
-    kernel_name = ("stream_logits_kernel + stream_values_kernel + combine_kernel (all launches of one call)"
+    kernel_name = ("tile_logits_kernel + tile_values_kernel (both launches of one call)" if tiled else
+                   "stream_logits_kernel + stream_values_kernel + combine_kernel (all launches of one call)"
                    if streamed else
                    "fused_row_kernel, extrema pass + partial pass, + combine_kernel (all launches of one call)"
                    if split else

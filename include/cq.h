@@ -120,11 +120,12 @@ typedef struct {
 } cq_calib_t;
 
 /* Bytes of scratch cq_decode_attn needs for this shape and calibration (a multiple of 256,
- * > 0): what the kernels that the call will select use.  A row that one workgroup can own
- * (the tuned one-launch kernel) needs the minimum of 256 bytes; a row split over several
+ * > 0): what the kernels that the call will select use.  A batch whose rows are each owned by one
+ * workgroup (the tuned one-launch kernel) needs the minimum of 256 bytes; a row split over several
  * workgroups needs one (m, l, acc[d]) partial of the online softmax per (batch, query head,
- * chunk), plus the chunks' logit extrema with CQ_CALIB_DYNAMIC; the shape-agnostic kernels
- * also keep one float per (batch, query head, token).  n_text is the largest tail length the
+ * chunk), plus the chunks' logit extrema with CQ_CALIB_DYNAMIC; the tile kernels (few rows, and
+ * layouts the tuned ones do not take) and the shape-agnostic kernels also keep one float per
+ * (batch, query head, token).  n_text is the largest tail length the
  * workspace has to serve; `calib` may be NULL (= CQ_CALIB_NONE).  Returns 0 if the layout,
  * n_text or the calibration mode is invalid. */
 size_t cq_decode_workspace_bytes(const cq_layout_t *layout, int32_t n_text,
