@@ -187,11 +187,14 @@ struct TilePlan {
 };
 TilePlan make_tile_plan(const DecodeShape& s);
 // The logits pass on its own, for keys of the same layouts whatever the values: raw logits
-// [B*Hq][n_vis + n_text] and the extrema [B*Hq][ca + ct][2] of every chunk.
+// [B*Hq][n_vis + n_text] and the extrema [B*Hq][ca + ct][2] of every chunk; in the same launch those of
+// x_tokens 16-bit keys x_keys [B*Hkv][x_tokens][d], whose plan has them as a tail: [B*Hq][x_tokens] and
+// [B*Hq][x_plan.ct][2].
 TilePlan make_tile_logits_plan(const DecodeShape& s);
 hipError_t launch_tile_logits(const DecodeShape& s, const TilePlan& plan, const void* q,
                               const cq_qtensor_t& k, const void* k_text, float softmax_scale,
-                              float* logits, float* minmax, hipStream_t stream);
+                              float* logits, float* minmax, const TilePlan& x_plan, const void* x_keys,
+                              int x_tokens, float* x_logits, float* x_minmax, hipStream_t stream);
 hipError_t launch_decode_tile(const DecodeShape& s, const TilePlan& plan, const void* q,
                               const cq_qtensor_t& k, const cq_qtensor_t& v, const void* k_text,
                               const void* v_text, const int32_t* n_text_dev, const Calib& calib,

@@ -57,6 +57,8 @@ struct TileArgs {
   int ca, ca_base, ca_rem;     // logits pass: chunks per row, in key blocks
   int cb, cb_base, cb_rem;     // values pass: chunks per row, in value tiles
   int ct, ct_tokens;           // chunks of the fp16 tail per row, tokens per chunk
+  // logits pass on its own: logits of a second set of 16-bit keys [rows][x_tokens][D] in the same launch
+  const __half* x_keys; int x_tokens, x_ct, x_ct_tokens; float* x_logits; float* x_minmax;
   float* ws_logits;            // [B*Hq][n_vis + n_text]
   float* ws_minmax;            // [B*Hq][ca + ct][2]
   float* ws_partial;           // [B*Hq][cb + ct][D + 2]
@@ -154,14 +156,19 @@ __device__ inline void store_extrema(float (*red)[16][2], int n_heads, float* mm
 // ===================================================================================== logits pass
 // A workgroup's share of the fp16 tail: all query heads of the KV head, 16 at a time, on the fp16
 // matrix cores (products of fp16 numbers are exact in fp32).  keys: the row's first text key.
+struct TextSpan {
+  const __half* keys;          // the row's first key
+  int n, chunk_tokens;
+  float* logits;               // of the row's first head and first token
+  size_t pitch;                // between two heads
+  float* minmax;               // of the row's first head and the chunk
+  size_t mm_pitch;
+};
 template <int D>
-__device__ inline void text_logits(const TileArgs& a, size_t row, int chunk, float (*red)[16][2]) {
+__device__ inline void text_logits(const TileArgs& a, const TextSpan& x, size_t row, int chunk, float (*red)[16][2]) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n16 = lane & 15, kb = lane >> 4;
-  const int n_text = a.n_text_dev ? min(max(*a.n_text_dev, 0), a.n_text) : a.n_text;
-  const int t0 = chunk * a.ct_tokens, t1 = min(t0 + a.ct_tokens, n_text);
-  const size_t n_all = (size_t)a.n_vis + a.n_text;
-  const __half* keys = a.k_text + row * (size_t)a.n_text_cap * D;
+  const int t0 = chunk * x.chunk_tokens, t1 = min(t0 + x.chunk_tokens, x.n);
   for (int h0 = 0; h0 < a.g; h0 += 16) {
     const int nh = min(16, a.g - h0);
     const size_t head0 = row * a.g + h0;
@@ -180,7 +187,7 @@ __device__ inline void text_logits(const TileArgs& a, size_t row, int chunk, flo
       v8h kv[kFly][D / 32];
 #pragma unroll
       for (int u = 0; u < kFly; ++u) {
-        const __half* kp = keys + (size_t)min(tb + 16 * kWaves * u + n16, t1 - 1) * D + 8 * kb;
+        const __half* kp = x.keys + (size_t)min(tb + 16 * kWaves * u + n16, t1 - 1) * D + 8 * kb;
 #pragma unroll
         for (int s = 0; s < D / 32; ++s) kv[u][s] = *reinterpret_cast<const v8h*>(kp + 32 * s);
       }
@@ -195,7 +202,7 @@ __device__ inline void text_logits(const TileArgs& a, size_t row, int chunk, flo
           for (int r = 0; r < 4; ++r) {        // result rows 4 kb + r are heads
             if (4 * kb + r < nh) {
               const float s = c[r] * a.softmax_scale;
-              a.ws_logits[(head0 + 4 * kb + r) * n_all + a.n_vis + tok] = s;
+              x.logits[(h0 + 4 * kb + r) * x.pitch + tok] = s;
               mn[r] = fminf(mn[r], s);
               mx[r] = fmaxf(mx[r], s);
             }
@@ -211,14 +218,13 @@ __device__ inline void text_logits(const TileArgs& a, size_t row, int chunk, flo
         red[wave][4 * kb + r][1] = hi;
       }
     }
-    const size_t pitch = (size_t)(a.ca + a.ct) * 2;
-    store_extrema(red, nh, a.ws_minmax + head0 * pitch + (size_t)(a.ca + chunk) * 2, pitch);
+    store_extrema(red, nh, x.minmax + h0 * x.mm_pitch, x.mm_pitch);
     __syncthreads();
   }
 }
 
-// grid: x = row, y = chunk of the tail, then chunk of the visual tokens, z = head set (the tail's
-// workgroups take all heads and leave the others of their column at once)
+// grid: x = row, y = chunk of the tail, of the visual tokens, of the second set of keys, z = head set
+// (the workgroups of 16-bit keys take all heads and leave the others of their column at once)
 template <int D, int BITS>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(D == 256 ? 2 : 4)))
 tile_logits_kernel(const TileArgs a) {
@@ -231,8 +237,24 @@ tile_logits_kernel(const TileArgs a) {
   const size_t row = blockIdx.x;
   if (blockIdx.y == 0 && blockIdx.z == 0 && a.ws_count)          // for the values pass behind this one
     for (int i = threadIdx.x; i < a.sets; i += kThreads) a.ws_count[row * a.sets + i] = 0;
-  if ((int)blockIdx.y < a.ct) {
-    if (blockIdx.z == 0) text_logits<D>(a, row, (int)blockIdx.y, red);
+  const bool tail = (int)blockIdx.y < a.ct;
+  if (tail || (int)blockIdx.y >= a.ct + a.ca) {
+    if (blockIdx.z != 0) return;
+    const int chunk = (int)blockIdx.y - (tail ? 0 : a.ct + a.ca);
+    const size_t head0 = row * a.g, pitch = (size_t)a.n_vis + a.n_text;
+    TextSpan x;
+    if (tail) {
+      const size_t mm_pitch = (size_t)(a.ca + a.ct) * 2;
+      x = {a.k_text + row * (size_t)a.n_text_cap * D, a.n_text_dev ? min(max(*a.n_text_dev, 0), a.n_text) : a.n_text,
+           a.ct_tokens, a.ws_logits + head0 * pitch + a.n_vis, pitch,
+           a.ws_minmax + head0 * mm_pitch + (size_t)(a.ca + chunk) * 2, mm_pitch};
+    } else {
+      const size_t mm_pitch = (size_t)a.x_ct * 2;
+      x = {a.x_keys + row * (size_t)a.x_tokens * D, a.x_tokens, a.x_ct_tokens,
+           a.x_logits + head0 * a.x_tokens, (size_t)a.x_tokens, a.x_minmax + head0 * mm_pitch + (size_t)chunk * 2,
+           mm_pitch};
+    }
+    text_logits<D>(a, x, row, chunk, red);
     return;
   }
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -885,7 +907,7 @@ hipError_t start_logits(TileArgs& a, const DecodeShape& s, const TilePlan& plan,
   const TileKernel kern = s.d == 64 ? logits_kernel<64>(s.bits)
                           : s.d == 128 ? logits_kernel<128>(s.bits) : logits_kernel<256>(s.bits);
   if (!kern) return hipErrorInvalidValue;
-  kern<<<dim3((unsigned)(s.B * s.Hkv), (unsigned)(a.ct + a.ca), (unsigned)a.sets), dim3(kThreads), 0, stream>>>(a);
+  kern<<<dim3((unsigned)(s.B * s.Hkv), (unsigned)(a.ct + a.ca + a.x_ct), (unsigned)a.sets), dim3(kThreads), 0, stream>>>(a);
   return hipGetLastError();
 }
 
@@ -893,8 +915,12 @@ hipError_t start_logits(TileArgs& a, const DecodeShape& s, const TilePlan& plan,
 
 hipError_t launch_tile_logits(const DecodeShape& s, const TilePlan& plan, const void* q,
                               const cq_qtensor_t& k, const void* k_text, float softmax_scale,
-                              float* logits, float* minmax, hipStream_t stream) {
+                              float* logits, float* minmax, const TilePlan& x_plan, const void* x_keys,
+                              int x_tokens, float* x_logits, float* x_minmax, hipStream_t stream) {
   TileArgs a{};
+  a.x_keys = static_cast<const __half*>(x_keys);
+  a.x_tokens = x_tokens; a.x_ct = x_plan.ct; a.x_ct_tokens = x_plan.ct_tokens;
+  a.x_logits = x_logits; a.x_minmax = x_minmax;
   return start_logits(a, s, plan, q, k, k_text, nullptr, softmax_scale, logits, minmax, stream);
 }
 
