@@ -159,6 +159,7 @@ struct DecodeCall {
   cq::TilePlan tile;        // valid when tiled
   cq::Workspace generic_ws; // valid when neither tuned nor tiled
   size_t ws_bytes;          // scratch the selected kernels touch
+  size_t ws_query_bytes;    // scratch that serves this tail length and every shorter one
 };
 
 int check_calib(const cq_calib_t* calib, cq::Calib* c) {
@@ -192,7 +193,7 @@ int check_calib(const cq_calib_t* calib, cq::Calib* c) {
 //                    8 rows x 1024 9.1 / 11.6 and 64 rows x 8192 22.2 / 27.1 stay fused
 //   1 bit, 6 heads:  8 rows x 3328 20.7 / 12.5, 64 rows 22.6 / 19.5; 128 rows 26.0 / 27.3 stay streamed
 //   4 bits:          32 rows x 3328 17.7 / 14.8;  8 bits: 8 rows x 3328 37.5 / 14.9, 128 rows 43.0 / 36.2
-// The tail's length plays no part: a workspace that serves a long tail serves a short one.
+// The tail's length plays no part in the rule.
 bool tile_is_faster(cq::DecodeShape s, const cq::FusedPlan& with_tail) {
   const double rows = (double)s.B * s.Hkv, kn = s.n_vis * 1e-3, mtok = rows * s.n_vis * 1e-6;
   if (mtok > 2.0 || (s.g <= 4 && s.bits <= 2 && s.n_vis <= 1024)) return false;
@@ -241,8 +242,9 @@ int select_kernels(const cq_layout_t* L, int n_text, int n_text_cap, size_t scra
     } else if (L->n_vis > 0 && g_decode_chunks == 0 && tile_is_faster(call->shape, call->plan)) {
       call->tile = cq::make_tile_plan(call->shape);
       call->tile_by_choice = call->tile.ok;
-      // not beyond the scratch of the allocation-free entry point: both entry points run the same kernels
-      if (call->tile.ok && call->tile.ws_bytes <= (size_t)CQ_NOALLOC_SCRATCH_BYTES) {
+      // not beyond the scratch of the allocation-free entry point: both entry points run the same kernels.
+      // By the size that never falls as the tail grows: where a tail stays here, so does every shorter one.
+      if (call->tile.ok && call->tile.ws_reserve_bytes <= (size_t)CQ_NOALLOC_SCRATCH_BYTES) {
         call->tiled = true;
         call->tuned = call->streamed = false;
       }
@@ -253,6 +255,7 @@ int select_kernels(const cq_layout_t* L, int n_text, int n_text_cap, size_t scra
                    : call->tuned  ? call->plan.ws_bytes
                    : call->tiled  ? call->tile.ws_bytes
                                   : call->generic_ws.total_bytes;
+  call->ws_query_bytes = call->tiled ? call->tile.ws_reserve_bytes : call->ws_bytes;
   return CQ_OK;
 }
 
@@ -392,9 +395,9 @@ size_t cq_decode_workspace_bytes(const cq_layout_t* L, int32_t n_text, const cq_
   DecodeCall call;
   if (select_kernels(L, n_text, n_text, SIZE_MAX, &call) != CQ_OK) return 0;
   // with a shorter tail the same workspace may have to serve the tile kernels
-  if (call.tile_by_choice && !call.tiled && call.ws_bytes < (size_t)CQ_NOALLOC_SCRATCH_BYTES)
+  if (call.tile_by_choice && !call.tiled && call.ws_query_bytes < (size_t)CQ_NOALLOC_SCRATCH_BYTES)
     return (size_t)CQ_NOALLOC_SCRATCH_BYTES;
-  return call.ws_bytes;
+  return call.ws_query_bytes;
 }
 
 int cq_quantize_kv(const cq_layout_t* L, const void* k_f16, const void* v_f16,

@@ -183,7 +183,8 @@ struct TilePlan {
   int ct = 0, ct_tokens = 0;       // chunks per row of the fp16 tail, tokens per chunk
   size_t ws_minmax_floats = 0;     // workspace: [logits | extrema | partials | counts], offsets in floats
   size_t ws_partial_floats = 0, ws_count_floats = 0;
-  size_t ws_bytes = 256;
+  size_t ws_bytes = 256;           // workspace the launches touch
+  size_t ws_reserve_bytes = 256;   // the most that a tail of up to n_text tokens needs (never falls with n_text)
 };
 TilePlan make_tile_plan(const DecodeShape& s);
 // The logits pass on its own, for keys of the same layouts whatever the values: raw logits

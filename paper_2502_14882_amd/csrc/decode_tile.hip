@@ -859,17 +859,23 @@ TilePlan make_tile_plan(const DecodeShape& s) {
     p.ca = clamp(want, 1, clamp((blocks + kWaves - 1) / kWaves, 1, kMaxTileChunks));
     p.cb = clamp(want, 1, clamp((tiles + 2 * kWaves - 1) / (2 * kWaves), 1, kMaxTileChunks));
   }
-  // the tail does not change how the visual tokens are divided: a workspace for a longer tail serves
-  // a shorter one
+  // the tail does not change how the visual tokens are divided
   p.ct_tokens = kTextBlock * ceil_div(ceil_div(s.n_text, kTextBlock), kMaxTileChunks);
   if (s.n_text > 0) p.ct = ceil_div(s.n_text, p.ct_tokens);
   const size_t heads = (size_t)s.B * s.Hq;
   auto align64 = [](size_t x) { return (x + 63) / 64 * 64; };
-  p.ws_minmax_floats = align64(heads * ((size_t)s.n_vis + s.n_text));
-  p.ws_partial_floats = align64(p.ws_minmax_floats + heads * (size_t)(p.ca + p.ct) * 2);
-  p.ws_count_floats = align64(p.ws_partial_floats + heads * (size_t)(p.cb + p.ct) * (s.d + 2));
-  const size_t floats = p.ws_count_floats + (size_t)(rows * sets);
-  p.ws_bytes = (floats * sizeof(float) + 255) / 256 * 256;
+  auto lay_out = [&](int ct) {
+    p.ws_minmax_floats = align64(heads * ((size_t)s.n_vis + s.n_text));
+    p.ws_partial_floats = align64(p.ws_minmax_floats + heads * (size_t)(p.ca + ct) * 2);
+    p.ws_count_floats = align64(p.ws_partial_floats + heads * (size_t)(p.cb + ct) * (s.d + 2));
+    return ((p.ws_count_floats + (size_t)(rows * sets)) * sizeof(float) + 255) / 256 * 256;
+  };
+  // Where the chunks of the tail grow their number falls, from 64 to 33 past 8192 tokens.  What a caller
+  // is asked for does not: it counts the most chunks that a tail of up to n_text tokens is cut into, so
+  // that a workspace for a longer tail serves a shorter one.
+  const int text_blocks = ceil_div(s.n_text, kTextBlock);
+  p.ws_reserve_bytes = lay_out(text_blocks < kMaxTileChunks ? text_blocks : kMaxTileChunks);
+  p.ws_bytes = lay_out(p.ct);
   // grid: rows x chunks x head sets
   p.ok = rows * sets * 2 * kMaxTileChunks < 0x7fffffffLL && sets <= 65535;
   return p;

@@ -1,0 +1,62 @@
+"""Sizes of the scratch, on the host: a workspace of the size asked for the largest tail serves every
+shorter one.  Nothing is launched: the decode calls below bring a workspace too small for any kernel
+and are refused, with the size they need in the message."""
+import ctypes
+import random
+import re
+
+import pytest
+
+from paper_2502_14882_amd import binding as cq
+
+FAKE = 0x10000     # aligned, non-NULL, never touched
+DYN = (cq.CQ_CALIB_DYNAMIC, 1.0, 2.0)
+
+
+def needed(lay, n_text):
+    """Bytes that cq_decode_attn itself asks for."""
+    t = cq.CqQTensor(FAKE, FAKE, FAKE)
+    calib = cq.make_calib(*DYN)
+    rc = cq.lib().cq_decode_attn(ctypes.byref(lay), FAKE, ctypes.byref(t), ctypes.byref(t), FAKE, FAKE, n_text,
+                                 n_text, ctypes.byref(calib), 0.0, FAKE, FAKE, 0, None)
+    assert rc == cq.CQ_ERR_WORKSPACE
+    return int(re.search(rb"(\d+) needed", cq.lib().cq_last_error()).group(1))
+
+
+# where the tail's chunks grow: 64 chunks of 128 tokens are 8192
+TAILS = [0, 1, 127, 128, 129, 1000, 4096, 6785, 7493, 8191, 8192, 8193, 8320, 9000, 10000, 16384, 16385, 24576,
+         24577, 40000]
+
+
+@pytest.mark.parametrize("args", [
+    (1, 16, 4, 64, 3328, 1, 0, 1, 128, 64),       # a layout only the tile kernels take
+    (1, 4, 4, 64, 1024, 1, 0, 1, 64, 64),
+    (2, 8, 2, 256, 1003, 4, 0, 0, 1003, 1003),
+    (1, 32, 8, 128, 3328, 1, 0, 1, 128, 128),     # layouts that they finish sooner than the fused kernel
+    (1, 32, 8, 128, 3328, 1, 0, 1, 64, 128),
+    (3, 6, 2, 128, 0, 1, 0, 1, 32, 128),          # a tail and nothing else
+])
+def test_the_largest_tail_serves_the_shorter_ones(args):
+    lay, calib = cq.make_layout(*args), cq.make_calib(*DYN)
+    tails = [t for t in TAILS if args[4] + t > 0]
+    sizes = [cq.cq_decode_workspace_bytes(lay, t, calib) for t in tails]
+    assert sizes == sorted(sizes), list(zip(tails, sizes))
+    for t, size in zip(tails, sizes):
+        assert needed(lay, t) <= size, (t, size)
+
+
+def test_drawn_layouts():
+    rng = random.Random(20)
+    for _ in range(400):
+        d, bits = rng.choice((64, 128, 256)), rng.choice((1, 2, 4, 8))
+        n_q, n_kv = rng.choice(((1, 1), (8, 2), (14, 2), (32, 8), (16, 16), (40, 4)))
+        n = int(2 ** rng.uniform(0, 14))
+        v_axis, v_group = rng.choice(((0, n), (1, d)))
+        lay = cq.make_layout(int(2 ** rng.uniform(0, 6)), n_q, n_kv, d, n, bits, 0, v_axis, n, v_group)
+        calib = cq.make_calib(*DYN)
+        longest = int(2 ** rng.uniform(0, 16))
+        top = cq.cq_decode_workspace_bytes(lay, longest, calib)
+        for t in [longest] + [rng.randrange(longest) for _ in range(20)]:
+            what = ({f: getattr(lay, f) for f, _ in lay._fields_}, longest, t)
+            assert cq.cq_decode_workspace_bytes(lay, t, calib) <= top, what
+            assert needed(lay, t) <= top, what
