@@ -500,7 +500,7 @@ size_t cq_tau_search_workspace_bytes(const cq_layout_t* L, int32_t n_text, int32
       (long long)n_tau1 * n_tau2 > cq::kMaxTauPairs)
     return 0;
   return cq::tau_workspace_layout(L->batch, L->n_q_heads, L->n_vis, n_text, n_tau1 * n_tau2)
-      .total_bytes;
+      .reserve_bytes;
 }
 
 int cq_tau_search(const cq_layout_t* L, const void* q_f16, const void* k_exact_f16,

@@ -87,6 +87,7 @@ struct TauWorkspace {
   size_t err_part;   // [B*Hq][n_chunks][n_pairs] doubles
   int n_chunks;      // chunks per query row of the grid kernels
   size_t total_bytes;
+  size_t reserve_bytes;   // the most that a tail of up to n_text tokens needs (never falls with n_text)
 };
 inline TauWorkspace tau_workspace_layout(int B, int Hq, int n_vis, int n_text, int n_pairs) {
   TauWorkspace w;
@@ -105,9 +106,14 @@ inline TauWorkspace tau_workspace_layout(int B, int Hq, int n_vis, int n_text, i
   w.minmax_q = align64(w.logits_x + rows * (size_t)n_vis);
   w.minmax_x = align64(w.minmax_q + rows * (size_t)(nvc + ntc) * 2);
   w.z_part = align64(w.minmax_x + rows * (size_t)nxc * 2);
-  w.err_part = align64(w.z_part + rows * (size_t)w.n_chunks * (size_t)(n_pairs + 1) * 2);
-  const size_t end = align64(w.err_part + rows * (size_t)w.n_chunks * (size_t)n_pairs * 2);
-  w.total_bytes = (end * sizeof(float) + 255) / 256 * 256;
+  auto lay_out = [&](int n_chunks) {
+    w.err_part = align64(w.z_part + rows * (size_t)n_chunks * (size_t)(n_pairs + 1) * 2);
+    const size_t end = align64(w.err_part + rows * (size_t)n_chunks * (size_t)n_pairs * 2);
+    return (end * sizeof(float) + 255) / 256 * 256;
+  };
+  // whole rounds per chunk: one round more can mean fewer chunks, but never more than these
+  w.reserve_bytes = lay_out(rounds > want ? want : rounds > 0 ? rounds : 1);
+  w.total_bytes = lay_out(w.n_chunks);
   return w;
 }
 hipError_t launch_tau_search(const DecodeShape& s, const void* q, const void* k_exact,

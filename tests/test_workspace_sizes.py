@@ -60,3 +60,23 @@ def test_drawn_layouts():
             what = ({f: getattr(lay, f) for f, _ in lay._fields_}, longest, t)
             assert cq.cq_decode_workspace_bytes(lay, t, calib) <= top, what
             assert needed(lay, t) <= top, what
+
+
+def test_tau_search_the_largest_tail_serves_the_shorter_ones():
+    """The chunks of the grid kernels are whole rounds of tokens, so their number can fall as the tail grows."""
+    rng = random.Random(21)
+    t_q = cq.CqQTensor(FAKE, FAKE, FAKE)
+    grid = (ctypes.c_float * 4)(0.0, 1.0, 2.0, 3.0)
+    for _ in range(400):
+        d, n_text = rng.choice((64, 96, 128)), int(2 ** rng.uniform(0, 14))
+        n_q, n_kv = rng.choice(((1, 1), (8, 2), (32, 8), (16, 16)))
+        n = int(2 ** rng.uniform(0, 14))
+        lay = cq.make_layout(int(2 ** rng.uniform(0, 5)), n_q, n_kv, d, n, 1, 0, 0, n, n)
+        top = cq.cq_tau_search_workspace_bytes(lay, n_text, 4, 4)
+        for t in [n_text] + [rng.randrange(n_text) for _ in range(20)]:
+            what = ({f: getattr(lay, f) for f, _ in lay._fields_}, n_text, t)
+            assert cq.cq_tau_search_workspace_bytes(lay, t, 4, 4) <= top, what
+            rc = cq.lib().cq_tau_search(ctypes.byref(lay), FAKE, FAKE, ctypes.byref(t_q), FAKE, t, t, grid, 4, grid, 4,
+                                        0.0, FAKE, FAKE, 0, None)
+            assert rc == cq.CQ_ERR_WORKSPACE
+            assert int(re.search(rb"(\d+) needed", cq.lib().cq_last_error()).group(1)) <= top, what
