@@ -234,11 +234,20 @@ int select_kernels(const cq_layout_t* L, int n_text, int n_text_cap, size_t scra
     call->stream = cq::make_stream_plan(call->shape, g_decode_chunks);
     call->streamed = call->stream.ok && call->stream.ws_bytes <= scratch_limit;
   }
+  call->generic_ws = cq::workspace_layout(L->batch, L->n_q_heads, L->head_dim, L->n_vis, n_text);
   call->tiled = call->tile_by_choice = false;
+  // Every entry point runs the same kernels on a layout that the tuned ones do not take.  Where the
+  // shape-agnostic kernels fit the scratch of the allocation-free entry point, the tile kernels stay
+  // within it too, with fewer chunks if need be; where they would not, that entry point refuses
+  // what does not fit.
+  const bool within_noalloc = call->generic_ws.total_bytes <= (size_t)CQ_NOALLOC_SCRATCH_BYTES;
+  bool reserve_all = false;
   if (g_kernel_path == CQ_PATH_AUTO) {
     if (!call->tuned) {
-      call->tile = cq::make_tile_plan(call->shape);
+      call->tile = cq::make_tile_plan(call->shape, within_noalloc ? (size_t)CQ_NOALLOC_SCRATCH_BYTES : SIZE_MAX);
       call->tiled = call->tile.ok && call->tile.ws_bytes <= scratch_limit;
+      // a shorter tail may use all of it
+      reserve_all = within_noalloc && call->tile.ws_reserve_bytes > (size_t)CQ_NOALLOC_SCRATCH_BYTES;
     } else if (L->n_vis > 0 && g_decode_chunks == 0 && tile_is_faster(call->shape, call->plan)) {
       call->tile = cq::make_tile_plan(call->shape);
       call->tile_by_choice = call->tile.ok;
@@ -250,12 +259,13 @@ int select_kernels(const cq_layout_t* L, int n_text, int n_text_cap, size_t scra
       }
     }
   }
-  call->generic_ws = cq::workspace_layout(L->batch, L->n_q_heads, L->head_dim, L->n_vis, n_text);
   call->ws_bytes = call->streamed ? call->stream.ws_bytes
                    : call->tuned  ? call->plan.ws_bytes
                    : call->tiled  ? call->tile.ws_bytes
                                   : call->generic_ws.total_bytes;
-  call->ws_query_bytes = call->tiled ? call->tile.ws_reserve_bytes : call->ws_bytes;
+  call->ws_query_bytes = reserve_all   ? (size_t)CQ_NOALLOC_SCRATCH_BYTES
+                         : call->tiled ? call->tile.ws_reserve_bytes
+                                       : call->ws_bytes;
   return CQ_OK;
 }
 

@@ -190,9 +190,12 @@ struct TilePlan {
   size_t ws_minmax_floats = 0;     // workspace: [logits | extrema | partials | counts], offsets in floats
   size_t ws_partial_floats = 0, ws_count_floats = 0;
   size_t ws_bytes = 256;           // workspace the launches touch
-  size_t ws_reserve_bytes = 256;   // the most that a tail of up to n_text tokens needs (never falls with n_text)
+  // the most that a tail of up to n_text tokens needs without a limit (never falls with n_text)
+  size_t ws_reserve_bytes = 256;
 };
-TilePlan make_tile_plan(const DecodeShape& s);
+// limit: the most scratch the plan may use; it takes fewer chunks to stay within it, and is not ok if
+// one of each kind is still too much
+TilePlan make_tile_plan(const DecodeShape& s, size_t limit = SIZE_MAX);
 // The logits pass on its own, for keys of the same layouts whatever the values: raw logits
 // [B*Hq][n_vis + n_text] and the extrema [B*Hq][ca + ct][2] of every chunk; in the same launch those of
 // x_tokens 16-bit keys x_keys [B*Hkv][x_tokens][d], whose plan has them as a tail: [B*Hq][x_tokens] and

@@ -841,7 +841,7 @@ TileKernel values_kernel(int bits, bool vch) {
 
 }  // namespace
 
-TilePlan make_tile_plan(const DecodeShape& s) {
+TilePlan make_tile_plan(const DecodeShape& s, size_t limit) {
   TilePlan p;
   if (s.d != 64 && s.d != 128 && s.d != 256) return p;
   if (s.bits != 1 && s.bits != 2 && s.bits != 4 && s.bits != 8) return p;
@@ -876,8 +876,21 @@ TilePlan make_tile_plan(const DecodeShape& s) {
   const int text_blocks = ceil_div(s.n_text, kTextBlock);
   p.ws_reserve_bytes = lay_out(text_blocks < kMaxTileChunks ? text_blocks : kMaxTileChunks);
   p.ws_bytes = lay_out(p.ct);
+  // within the limit: fewer chunks, of whichever kind has more of them
+  bool fits = true;
+  while (p.ws_bytes > limit && fits) {
+    if (p.ct > 1 && (p.ct >= p.cb || p.cb <= 1)) {
+      p.ct_tokens = kTextBlock * ceil_div(text_blocks, p.ct - 1);
+      p.ct = ceil_div(s.n_text, p.ct_tokens);
+    } else if (p.cb > 1) {
+      --p.cb;
+    } else {
+      fits = false;
+    }
+    p.ws_bytes = lay_out(p.ct);
+  }
   // grid: rows x chunks x head sets
-  p.ok = rows * sets * 2 * kMaxTileChunks < 0x7fffffffLL && sets <= 65535;
+  p.ok = fits && rows * sets * 2 * kMaxTileChunks < 0x7fffffffLL && sets <= 65535;
   return p;
 }
 

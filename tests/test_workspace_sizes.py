@@ -35,6 +35,8 @@ TAILS = [0, 1, 127, 128, 129, 1000, 4096, 6785, 7493, 8191, 8192, 8193, 8320, 90
     (1, 32, 8, 128, 3328, 1, 0, 1, 128, 128),     # layouts that they finish sooner than the fused kernel
     (1, 32, 8, 128, 3328, 1, 0, 1, 64, 128),
     (3, 6, 2, 128, 0, 1, 0, 1, 32, 128),          # a tail and nothing else
+    (48, 16, 4, 64, 1024, 1, 0, 1, 64, 64),       # passes 8 MiB inside the range
+    (8, 32, 8, 128, 3003, 1, 0, 0, 3003, 3003),
 ])
 def test_the_largest_tail_serves_the_shorter_ones(args):
     lay, calib = cq.make_layout(*args), cq.make_calib(*DYN)

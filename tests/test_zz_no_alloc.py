@@ -79,3 +79,43 @@ def test_a_shape_beyond_the_scratch_is_refused():
     with pytest.raises(cq.CqError) as e:
         cq.cq_decode_attn_noalloc(lay, x["q"], k_dev, v_dev, x["k_text"], x["v_text"], w.n_text, calib)
     assert e.value.status == cq.CQ_ERR_WORKSPACE
+
+
+# (batch, q heads, KV heads, head_dim, n_vis, key group, value axis, value group, tails): layouts of the
+# tile kernels whose scratch passes the size of the array inside the range of tails, while the
+# shape-agnostic kernels would still fit it.  The last one does not fit it with either.
+@pytest.mark.parametrize("shape,tails", [
+    ((16, 32, 8, 64, 3328, 64, 1, 64), (158, 159, 160, 200, 239)),
+    ((8, 32, 8, 128, 3003, 3003, 0, 3003), (2100, 2160, 2800, 3487)),
+    ((48, 16, 4, 64, 1024, 64, 1, 64), (800, 1024)),
+    ((64, 16, 16, 64, 1024, 1024, 0, 1024), (900, 1014))])
+def test_the_same_kernels_on_both_sides_of_the_scratch_limit(shape, tails):
+    B, nq, nkv, d, n, kg, vax, vg = shape
+    w = synth.WORKLOADS[1].replace(batch=B, n_q_heads=nq, n_kv_heads=nkv, head_dim=d, n_vis=n,
+                                   n_text=max(tails), seed=n)
+    x = synth.make_inputs(w, "cuda")
+    lay = cq.make_layout(B, nq, nkv, d, n, 1, 0, vax, kg, vg)
+    k, v = cq.cq_quantize_kv(lay, x["k"], x["v"])
+    calib = cq.make_calib(cq.CQ_CALIB_DYNAMIC, 1.0, 2.0)
+
+    def agnostic(n_text, size_only=False):
+        prev = cq.cq_bench_set_kernel_path(cq.CQ_PATH_GENERIC)
+        try:
+            if size_only:
+                return cq.cq_decode_workspace_bytes(lay, n_text, calib)
+            return cq.cq_decode_attn(lay, x["q"], k, v, x["k_text"], x["v_text"], n_text, calib)
+        finally:
+            cq.cq_bench_set_kernel_path(prev)
+
+    for n_text in tails:
+        want = cq.cq_decode_attn(lay, x["q"], k, v, x["k_text"], x["v_text"], n_text, calib)
+        try:
+            got = cq.cq_decode_attn_noalloc(lay, x["q"], k, v, x["k_text"], x["v_text"], n_text, calib)
+        except cq.CqError as e:
+            assert e.status == cq.CQ_ERR_WORKSPACE
+            assert agnostic(n_text, size_only=True) > cq.CQ_NOALLOC_SCRATCH_BYTES, (shape, n_text)
+            continue
+        torch.cuda.synchronize()
+        assert torch.equal(got, want), (shape, n_text)
+        err = O.rel_l2(got.cpu().numpy().astype(np.float64), agnostic(n_text).cpu().numpy().astype(np.float64))
+        assert err <= 2 * H.REGRESSION_TOL, (shape, n_text, err)      # two fp16 results
