@@ -127,7 +127,9 @@ typedef struct {
  * layouts the tuned ones do not take) and the shape-agnostic kernels also keep one float per
  * (batch, query head, token).  n_text is the largest tail length the
  * workspace has to serve; `calib` may be NULL (= CQ_CALIB_NONE).  Returns 0 if the layout,
- * n_text or the calibration mode is invalid. */
+ * n_text or the calibration mode is invalid.
+ * A decode call also accepts less where it would run the tile kernels and the workspace holds what
+ * the tuned (else the shape-agnostic) kernels need: those run then, slower. */
 size_t cq_decode_workspace_bytes(const cq_layout_t *layout, int32_t n_text,
                                  const cq_calib_t *calib);
 

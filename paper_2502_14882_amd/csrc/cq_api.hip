@@ -150,14 +150,14 @@ struct DecodeCall {
   cq::DecodeShape shape;
   cq::Calib calib;
   float softmax_scale;
-  bool tuned;               // the tuned kernels run (else the shape-agnostic ones)
+  bool tuned;               // a layout of the tuned kernels (else of the shape-agnostic ones)
   bool streamed;            // tuned, split rows: the streaming kernels with logits kept in scratch
-  bool tiled;               // not tuned: the tile kernels run (else the shape-agnostic ones)
+  bool tiled;               // the tile kernels run, in place of either
   bool tile_by_choice;      // a layout of the tuned kernels that the tile kernels finish sooner
   cq::FusedPlan plan;       // valid when tuned
   cq::StreamPlan stream;    // valid when streamed
   cq::TilePlan tile;        // valid when tiled
-  cq::Workspace generic_ws; // valid when neither tuned nor tiled
+  cq::Workspace generic_ws;
   size_t ws_bytes;          // scratch the selected kernels touch
   size_t ws_query_bytes;    // scratch that serves this tail length and every shorter one
 };
@@ -216,6 +216,11 @@ bool tile_is_faster(cq::DecodeShape s, const cq::FusedPlan& with_tail) {
   return tile < 0.98 * tuned;
 }
 
+// Scratch of the kernels that run where the tile kernels do not.
+size_t ws_without_tiles(const DecodeCall& c) {
+  return c.streamed ? c.stream.ws_bytes : c.tuned ? c.plan.ws_bytes : c.generic_ws.total_bytes;
+}
+
 // Kernel selection and scratch size for a valid layout: one plan per call, used by the size query,
 // by the argument check and by the launch.
 // scratch_limit: the most scratch the caller can offer.  Rows that have to be split run on the
@@ -253,16 +258,10 @@ int select_kernels(const cq_layout_t* L, int n_text, int n_text_cap, size_t scra
       call->tile_by_choice = call->tile.ok;
       // not beyond the scratch of the allocation-free entry point: both entry points run the same kernels.
       // By the size that never falls as the tail grows: where a tail stays here, so does every shorter one.
-      if (call->tile.ok && call->tile.ws_reserve_bytes <= (size_t)CQ_NOALLOC_SCRATCH_BYTES) {
-        call->tiled = true;
-        call->tuned = call->streamed = false;
-      }
+      call->tiled = call->tile.ok && call->tile.ws_reserve_bytes <= (size_t)CQ_NOALLOC_SCRATCH_BYTES;
     }
   }
-  call->ws_bytes = call->streamed ? call->stream.ws_bytes
-                   : call->tuned  ? call->plan.ws_bytes
-                   : call->tiled  ? call->tile.ws_bytes
-                                  : call->generic_ws.total_bytes;
+  call->ws_bytes = call->tiled ? call->tile.ws_bytes : ws_without_tiles(*call);
   call->ws_query_bytes = reserve_all   ? (size_t)CQ_NOALLOC_SCRATCH_BYTES
                          : call->tiled ? call->tile.ws_reserve_bytes
                                        : call->ws_bytes;
@@ -309,7 +308,11 @@ int launch_decode(const DecodeCall& call, const void* q_f16, const cq_qtensor_t*
   const cq_qtensor_t& kq = k ? *k : kNone;
   const cq_qtensor_t& vq = v ? *v : kNone;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const hipError_t e = call.streamed
+  const hipError_t e = call.tiled
+      ? cq::launch_decode_tile(call.shape, call.tile, q_f16, kq, vq, k_text_f16, v_text_f16,
+                               n_text_dev, call.calib, call.softmax_scale, out_f16,
+                               static_cast<float*>(workspace), st)
+      : call.streamed
       ? cq::launch_decode_stream(call.shape, call.stream, q_f16, kq, vq, k_text_f16, v_text_f16,
                                  n_text_dev, call.calib, call.softmax_scale, out_f16,
                                  static_cast<float*>(workspace), st)
@@ -317,10 +320,6 @@ int launch_decode(const DecodeCall& call, const void* q_f16, const cq_qtensor_t*
       ? cq::launch_decode_fused(call.shape, call.plan, q_f16, kq, vq, k_text_f16, v_text_f16,
                                 n_text_dev, call.calib, call.softmax_scale, out_f16,
                                 static_cast<float*>(workspace), st)
-      : call.tiled
-      ? cq::launch_decode_tile(call.shape, call.tile, q_f16, kq, vq, k_text_f16, v_text_f16,
-                               n_text_dev, call.calib, call.softmax_scale, out_f16,
-                               static_cast<float*>(workspace), st)
       : cq::launch_decode_generic(call.shape, q_f16, kq, vq, k_text_f16, v_text_f16, n_text_dev,
                                   call.calib, call.softmax_scale, out_f16,
                                   static_cast<float*>(workspace), call.generic_ws, st);
@@ -354,12 +353,18 @@ int noalloc_scratch(void** out) {
   return CQ_OK;
 }
 
-int check_workspace(const void* workspace, size_t workspace_bytes, size_t need) {
+// The kernels that the tile kernels stand in for need less scratch (256 bytes where one workgroup owns
+// a row): a workspace that holds what they need, but not more, is accepted, and they run.
+int check_workspace(DecodeCall* call, const void* workspace, size_t workspace_bytes) {
   if (!workspace) return fail(CQ_ERR_WORKSPACE, "workspace is NULL");
   if ((reinterpret_cast<uintptr_t>(workspace) & 255u) != 0)
     return fail(CQ_ERR_WORKSPACE, "workspace must be 256-byte aligned");
-  if (workspace_bytes < need)
-    return fail(CQ_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, need);
+  if (call->tiled && workspace_bytes < call->ws_bytes && workspace_bytes >= ws_without_tiles(*call)) {
+    call->tiled = false;
+    call->ws_bytes = ws_without_tiles(*call);
+  }
+  if (workspace_bytes < call->ws_bytes)
+    return fail(CQ_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, call->ws_bytes);
   return CQ_OK;
 }
 
@@ -465,7 +470,7 @@ int cq_decode_attn(const cq_layout_t* L, const void* q_f16, const cq_qtensor_t* 
   int rc = check_decode(L, q_f16, k, v, k_text_f16, v_text_f16, n_text, n_text_cap, false, calib,
                         softmax_scale, out_f16, SIZE_MAX, &call);
   if (rc != CQ_OK) return rc;
-  if ((rc = check_workspace(workspace, workspace_bytes, call.ws_bytes)) != CQ_OK) return rc;
+  if ((rc = check_workspace(&call, workspace, workspace_bytes)) != CQ_OK) return rc;
   return launch_decode(call, q_f16, k, v, k_text_f16, v_text_f16, nullptr, out_f16, workspace, stream);
 }
 
@@ -499,7 +504,7 @@ int cq_decode_attn_devlen(const cq_layout_t* L, const void* q_f16, const cq_qten
   int rc = check_decode(L, q_f16, k, v, k_text_f16, v_text_f16, n_text_max, n_text_cap, true, calib,
                         softmax_scale, out_f16, SIZE_MAX, &call);
   if (rc != CQ_OK) return rc;
-  if ((rc = check_workspace(workspace, workspace_bytes, call.ws_bytes)) != CQ_OK) return rc;
+  if ((rc = check_workspace(&call, workspace, workspace_bytes)) != CQ_OK) return rc;
   return launch_decode(call, q_f16, k, v, k_text_f16, v_text_f16, n_text_dev, out_f16, workspace,
                        stream);
 }

@@ -119,3 +119,35 @@ def test_the_same_kernels_on_both_sides_of_the_scratch_limit(shape, tails):
         assert torch.equal(got, want), (shape, n_text)
         err = O.rel_l2(got.cpu().numpy().astype(np.float64), agnostic(n_text).cpu().numpy().astype(np.float64))
         assert err <= 2 * H.REGRESSION_TOL, (shape, n_text, err)      # two fp16 results
+
+
+@pytest.mark.parametrize("shape,n_text,path", [
+    ((1, 32, 8, 128, 3328, 128, 1, 128), 100, cq.CQ_PATH_TUNED),       # one workgroup per row: 256 bytes
+    ((1, 12, 2, 128, 2560, 128, 1, 128), 100, cq.CQ_PATH_TUNED),       # split rows: partials
+    ((2, 8, 2, 64, 1000, 1000, 0, 1000), 300, cq.CQ_PATH_GENERIC)])    # the shape-agnostic kernels
+def test_a_workspace_of_the_size_the_other_kernels_need_is_enough(shape, n_text, path):
+    """A program that keeps the size its layout needs without the tile kernels is served by the kernels
+    that need no more; a byte block less is refused."""
+    B, nq, nkv, d, n, kg, vax, vg = shape
+    w = synth.WORKLOADS[1].replace(batch=B, n_q_heads=nq, n_kv_heads=nkv, head_dim=d, n_vis=n, n_text=n_text, seed=n)
+    x = synth.make_inputs(w, "cuda")
+    lay = cq.make_layout(B, nq, nkv, d, n, 1, 0, vax, kg, vg)
+    k, v = cq.cq_quantize_kv(lay, x["k"], x["v"])
+    calib = cq.make_calib(cq.CQ_CALIB_DYNAMIC, 1.0, 2.0)
+    args = (lay, x["q"], k, v, x["k_text"], x["v_text"], n_text, calib)
+    prev = cq.cq_bench_set_kernel_path(path)
+    try:
+        size = cq.cq_decode_workspace_bytes(lay, n_text, calib)
+        want = cq.cq_decode_attn(*args)
+    finally:
+        cq.cq_bench_set_kernel_path(prev)
+    assert 0 < size < cq.cq_decode_workspace_bytes(lay, n_text, calib)     # the tile kernels run, with more
+    got = cq.cq_decode_attn(*args, workspace=torch.empty(size, dtype=torch.uint8, device="cuda"))
+    n_dev = torch.tensor([n_text], dtype=torch.int32, device="cuda")
+    dev = cq.cq_decode_attn_devlen(lay, x["q"], k, v, x["k_text"], x["v_text"], n_dev, n_text, calib,
+                                   workspace=torch.empty(size, dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    assert torch.equal(got, want) and torch.equal(dev, want)
+    with pytest.raises(cq.CqError) as e:
+        cq.cq_decode_attn(*args, workspace=torch.empty(size, dtype=torch.uint8, device="cuda")[:size - 256])
+    assert e.value.status == cq.CQ_ERR_WORKSPACE
