@@ -153,7 +153,6 @@ struct DecodeCall {
   bool tuned;               // a layout of the tuned kernels (else of the shape-agnostic ones)
   bool streamed;            // tuned, split rows: the streaming kernels with logits kept in scratch
   bool tiled;               // the tile kernels run, in place of either
-  bool tile_by_choice;      // a layout of the tuned kernels that the tile kernels finish sooner
   cq::FusedPlan plan;       // valid when tuned
   cq::StreamPlan stream;    // valid when streamed
   cq::TilePlan tile;        // valid when tiled
@@ -240,25 +239,29 @@ int select_kernels(const cq_layout_t* L, int n_text, int n_text_cap, size_t scra
     call->streamed = call->stream.ok && call->stream.ws_bytes <= scratch_limit;
   }
   call->generic_ws = cq::workspace_layout(L->batch, L->n_q_heads, L->head_dim, L->n_vis, n_text);
-  call->tiled = call->tile_by_choice = false;
+  call->tiled = false;
   // Every entry point runs the same kernels on a layout that the tuned ones do not take.  Where the
   // shape-agnostic kernels fit the scratch of the allocation-free entry point, the tile kernels stay
   // within it too, with fewer chunks if need be; where they would not, that entry point refuses
   // what does not fit.
   const bool within_noalloc = call->generic_ws.total_bytes <= (size_t)CQ_NOALLOC_SCRATCH_BYTES;
-  bool reserve_all = false;
+  bool reserve_all = false;          // a shorter tail may use all of that scratch
   if (g_kernel_path == CQ_PATH_AUTO) {
     if (!call->tuned) {
       call->tile = cq::make_tile_plan(call->shape, within_noalloc ? (size_t)CQ_NOALLOC_SCRATCH_BYTES : SIZE_MAX);
       call->tiled = call->tile.ok && call->tile.ws_bytes <= scratch_limit;
-      // a shorter tail may use all of it
       reserve_all = within_noalloc && call->tile.ws_reserve_bytes > (size_t)CQ_NOALLOC_SCRATCH_BYTES;
     } else if (L->n_vis > 0 && g_decode_chunks == 0 && tile_is_faster(call->shape, call->plan)) {
       call->tile = cq::make_tile_plan(call->shape);
-      call->tile_by_choice = call->tile.ok;
       // not beyond the scratch of the allocation-free entry point: both entry points run the same kernels.
       // By the size that never falls as the tail grows: where a tail stays here, so does every shorter one.
-      call->tiled = call->tile.ok && call->tile.ws_reserve_bytes <= (size_t)CQ_NOALLOC_SCRATCH_BYTES;
+      const size_t most = (size_t)CQ_NOALLOC_SCRATCH_BYTES;
+      call->tiled = call->tile.ok && call->tile.ws_reserve_bytes <= most;
+      if (call->tile.ok && !call->tiled) {       // a shorter tail may still run them
+        cq::DecodeShape no_tail = call->shape;
+        no_tail.n_text = 0;
+        reserve_all = ws_without_tiles(*call) <= most && cq::make_tile_plan(no_tail).ws_reserve_bytes <= most;
+      }
     }
   }
   call->ws_bytes = call->tiled ? call->tile.ws_bytes : ws_without_tiles(*call);
@@ -409,9 +412,6 @@ size_t cq_decode_workspace_bytes(const cq_layout_t* L, int32_t n_text, const cq_
   if (check_layout(L, true) != CQ_OK || n_text < 0 || check_calib(calib, &c) != CQ_OK) return 0;
   DecodeCall call;
   if (select_kernels(L, n_text, n_text, SIZE_MAX, &call) != CQ_OK) return 0;
-  // with a shorter tail the same workspace may have to serve the tile kernels
-  if (call.tile_by_choice && !call.tiled && call.ws_query_bytes < (size_t)CQ_NOALLOC_SCRATCH_BYTES)
-    return (size_t)CQ_NOALLOC_SCRATCH_BYTES;
   return call.ws_query_bytes;
 }
 

@@ -82,3 +82,15 @@ def test_tau_search_the_largest_tail_serves_the_shorter_ones():
                                         0.0, FAKE, FAKE, 0, None)
             assert rc == cq.CQ_ERR_WORKSPACE
             assert int(re.search(rb"(\d+) needed", cq.lib().cq_last_error()).group(1)) <= top, what
+
+
+def test_no_scratch_for_kernels_that_never_run():
+    """Where the tile kernels would finish sooner but no tail is short enough for them to stay within the
+    scratch of the allocation-free entry point, the query asks for what the call uses."""
+    lay, calib = cq.make_layout(16, 32, 8, 128, 6400, 8, 0, 1, 128, 128), cq.make_calib(*DYN)
+    assert 16 * 32 * 6400 * 4 > cq.CQ_NOALLOC_SCRATCH_BYTES            # the logits alone
+    for t in (0, 100, 1000):
+        assert cq.cq_decode_workspace_bytes(lay, t, calib) == needed(lay, t) < 4 << 20
+    # one that fits with a short tail keeps asking for it
+    lay = cq.make_layout(16, 32, 8, 128, 2560, 8, 0, 1, 128, 128)
+    assert needed(lay, 100) > 4 << 20 and cq.cq_decode_workspace_bytes(lay, 4096, calib) >= needed(lay, 100)
