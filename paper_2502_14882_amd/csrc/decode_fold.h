@@ -42,6 +42,18 @@ __device__ inline double fold_rows(double a, double b) {
   return __builtin_bit_cast(double, (v2u){lo[0], hi[0]}) + __builtin_bit_cast(double, (v2u){lo[1], hi[1]});
 }
 
+// the larger of the two halves' values, and of neighbouring rows', in every lane
+__device__ inline float max_halves(float v) {
+  const unsigned u = __builtin_bit_cast(unsigned, v);
+  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return fmaxf(__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1]));
+}
+__device__ inline float max_rows(float v) {
+  const unsigned u = __builtin_bit_cast(unsigned, v);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return fmaxf(__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1]));
+}
+
 // Sum over the wave of the four heads' parts, head kb = lane / 16 in every lane of row kb.  A
 // transposing butterfly leaves lane (.., b1, b0) with head 2*b0 + b1 after two steps, the remaining
 // steps add lanes that hold the same head.  Every lane of a row then holds the row's sum for head

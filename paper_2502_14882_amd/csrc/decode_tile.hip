@@ -17,6 +17,12 @@
 // run of 64-token tiles (values); groups and the row's end cut blocks and tiles short, a short one
 // reads its last token again and the surplus is neither stored nor weighted.
 //
+// Precision.  Keys: one fixed-point scale per key group and head set, 30 bits, results put together in fp64.
+// Values: a scale per head that follows the products weight * scale (see Scales), sums in fp32.  A
+// host model of the sums, 3328 tokens, relative to fp64: 1e-7 to 2e-7 whether or not a token's scale stands out
+// a thousandfold (fp32 multiply-adds over dequantized values: 2e-7 to 4e-7; one scale for all heads set by the
+// largest token scale: 6e-7 to 1e-5).  The maxima cost 0.1 to 0.3 us a call.
+//
 // Bound: on small calls latency - two launches, and in each wave a chain of few round trips to memory: all
 // that a wave needs first is asked for at once (its first codes and parameters, then the query;
 // its first value tile, then the extrema), a key block's codes together, a share of the tail
@@ -563,6 +569,36 @@ __device__ inline void text_values(const TileArgs& a, size_t row, int set, int c
   finish_chunk<D>(a, row, set, head0, gh, a.cb + chunk, m_ref, s_part, s_lm);
 }
 
+// a * b + the bias of the four signed base-256 digits: as an integer ^ 0x00808080 its bytes are the digits.
+// Above 2^23 the fma rounds to nearest integers, and fp32 has no more below 2^24.
+__device__ inline float digits_bias(float a, float b) { return fmaf(a, b, 8421504.f); }
+
+// Fixed-point scales of the four heads, powers of two from 2^-90 to 2^90, as the bits of floats.
+struct Scales {
+  static constexpr int kOne = 127 << 23, kStart = (90 + 127) << 23;
+  int up[kHeads] = {kStart, kStart, kStart, kStart};           // wave-uniform
+  __device__ float of(int h) const { return __builtin_bit_cast(float, up[h]); }
+  __device__ float inverse(int kb) const {                     // of head kb
+    const int a = kb & 1 ? up[1] : up[0], b = kb & 1 ? up[3] : up[2];
+    return __builtin_bit_cast(float, 2 * kOne - (kb & 2 ? b : a));
+  }
+  // Lowered until w * scale < 2^26 for the heads' w >= 0 of all lanes.  The maxima by a transposing
+  // butterfly, as in head_sums: lane l of a row ends up with head bitrev2(l & 3).
+  __device__ void lower(const float (&w)[kHeads], int lane) {
+    const bool b0 = lane & 1, b1 = lane & 2;
+    const float u0 = fmaxf(b0 ? w[2] : w[0], dpp_f32<0xB1>(b0 ? w[0] : w[2]));
+    const float u1 = fmaxf(b0 ? w[3] : w[1], dpp_f32<0xB1>(b0 ? w[1] : w[3]));
+    float r = fmaxf(b1 ? u1 : u0, dpp_f32<0x4E>(b1 ? u0 : u1));
+    r = fmaxf(r, dpp_f32<0x124>(r));
+    r = max_rows(max_halves(fmaxf(r, dpp_f32<0x128>(r))));
+    // r < 2^(e - 126) for its exponent field e: the scale 2^(26 - (e - 126)), its field 279 - e
+    const int fits = min(max(279 - (__builtin_bit_cast(int, r) >> 23), 127 - 90), 127 + 90) << 23;
+    constexpr int kLane[kHeads] = {0, 2, 1, 3};
+#pragma unroll
+    for (int h = 0; h < kHeads; ++h) up[h] = min(up[h], __builtin_amdgcn_readlane(fits, kLane[h]));
+  }
+};
+
 // grid: x = row, y = chunk of the tail, then chunk of the visual tokens, z = head set
 template <int D, int BITS, bool VCH>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(D == 256 || BITS == 8 ? 2 : D == 128 && BITS >= 2 && VCH ? 3 : 4)))
@@ -625,8 +661,12 @@ tile_values_kernel(const TileArgs a) {
   for (int p = 0; p < NACC; ++p) { acc[p] = (v4i){0, 0, 0, 0}; facc[p] = 0.f; }
 #pragma unroll
   for (int h = 0; h < kHeads; ++h) lsum[h] = msum[h] = 0.f;
-  int F = 90;                                                  // token-wise: running fixed-point shift
-  float fit_below = ldexpf(1.f, 29 - 90);
+  // What goes into the matrix product is w = p (channel-wise values) or p * scale (token-wise), as the
+  // integer nearest to w times a power of two.  That scale is a head's own and follows the products, not
+  // the tokens' scales: the largest w so far of the head is in [2^25, 2^29), so no bits are spent on a
+  // token that stands out but that the head does not look at, nor on what another head looks at.  It
+  // only drops, within a channel-wise group (whose parameters are its own).
+  Scales scales;
   int run = 0;
 
   v4i piece_r[kPieces];
@@ -666,20 +706,23 @@ tile_values_kernel(const TileArgs a) {
       mi = vm[j];
     }
     load_pieces(tok0, nt, 0);
+  };
+  auto load_params = [&](int grp) {
+    params_of = grp;
     if constexpr (VCH) {
-      if (grp != params_of) {                                  // wave-uniform; the group before is folded
-        params_of = grp;
 #pragma unroll
-        for (int p = 0; p < NACC; ++p) {
-          const size_t at = meta0 + (size_t)grp * D + channel(p);
-          gs[p] = a.v_scale[at];
-          gm[p] = a.v_min[at];
-        }
+      for (int p = 0; p < NACC; ++p) {
+        const size_t at = meta0 + (size_t)grp * D + channel(p);
+        gs[p] = a.v_scale[at];
+        gm[p] = a.v_min[at];
       }
     }
   };
   // the first tile is asked for before the extrema are folded, so that a wave waits for memory once
-  if (k0 < k1) load_tile(k0);
+  if (k0 < k1) {
+    load_tile(k0);
+    load_params(part_of(k0, a.v_tpg));
+  }
   // ---- calibration line and reference point per head (Sec. 3.2): lane 16 h + c folds chunks c,
   // c + 16, ... of head h
   float a2[kHeads], c2[kHeads], m_ref[kHeads];
@@ -712,38 +755,57 @@ tile_values_kernel(const TileArgs a) {
     }
   }
 
+  // the digit sums into fp32, weighted (channel-wise: by the parameters of the group they belong to)
+  auto bank = [&]() {
+    const float unit = scales.inverse(kb);
+    const float wsum = VCH ? digits_to_float(acc_w) * unit : 0.f;
+    acc_w = (v4i){0, 0, 0, 0};
+#pragma unroll
+    for (int p = 0; p < NACC; ++p) {
+      const float sum = digits_to_float(acc[p]) * unit;
+      acc[p] = (v4i){0, 0, 0, 0};
+      if constexpr (VCH) {
+        const float add = __half2float(__ushort_as_half(gm[p])) + (BITS == 8 ? 128.f * gs[p] : 0.f);
+        facc[p] = fmaf(sum, gs[p] * variant_weight<BITS>(p % kV), fmaf(wsum, add, facc[p]));
+      } else {
+        facc[p] += sum;
+      }
+    }
+    run = 0;
+  };
+
   for (int k = k0; k < k1; ++k) {
     int grp, tok0, nt;
     tile_at(k, grp, tok0, nt);
-    const bool have = lane < nt;
-    float vsf = 536870912.f, vmf = 0.f;                        // channel-wise: weights p * 2^29
-    if constexpr (!VCH) {
-      // the largest scale so far sets the shift; when it drops, bank the digit sums in fp32 first
-      // (the four digit sums of a value cannot be shifted one by one)
-      if (__builtin_amdgcn_ballot_w64(sc >= fit_below) != 0 || run == kMaxRun) {
-        const float w_old = ldexpf(1.f, -F);
-#pragma unroll
-        for (int p = 0; p < NACC; ++p) {
-          facc[p] = fmaf(digits_to_float(acc[p]), w_old, facc[p]);
-          acc[p] = (v4i){0, 0, 0, 0};
-        }
-        run = 0;
-        F = min(F, fixed_point_shift(wave_max_nonneg(sc)));
-        fit_below = ldexpf(1.f, 29 - F);
-      }
-      vsf = ldexpf(sc, F);
-      vmf = __half2float(__ushort_as_half(mi)) + (BITS == 8 ? 128.f * sc : 0.f);
-    }
-    v4i xs;
+    const bool have = lane < nt, next_group = VCH && grp != params_of;         // (the latter wave-uniform)
+    float w[kHeads], x[kHeads];
 #pragma unroll
     for (int h = 0; h < kHeads; ++h) {
       const float e = __builtin_amdgcn_exp2f(fmaf(lgv[h], a2[h], c2[h]));
       const float p = have ? e : 0.f;
       lsum[h] += p;
-      if constexpr (!VCH) msum[h] = fmaf(p, vmf, msum[h]);
-      xs[h] = product_digits(p, vsf);
+      if constexpr (VCH) {
+        w[h] = p;
+      } else {
+        w[h] = p * sc;
+        msum[h] = fmaf(p, __half2float(__ushort_as_half(mi)) + (BITS == 8 ? 128.f * sc : 0.f), msum[h]);
+      }
+      x[h] = digits_bias(w[h], scales.of(h));
     }
-    const bool fold = VCH && (k + 1 == k1 || (k + 1 - grp * a.v_tpg) == a.v_tpg || run + 1 == kMaxRun);
+    const bool over = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])) >= 0x1p29f;
+    if (__builtin_amdgcn_ballot_w64(over) != 0 || run == kMaxRun || next_group) {
+      if (run) bank();           // the four digit sums of a value cannot be scaled one by one
+      if (next_group) {
+        load_params(grp);
+        scales = Scales();
+      }
+      scales.lower(w, lane);
+#pragma unroll
+      for (int h = 0; h < kHeads; ++h) x[h] = digits_bias(w[h], scales.of(h));
+    }
+    v4i xs;
+#pragma unroll
+    for (int h = 0; h < kHeads; ++h) xs[h] = (int)x[h] ^ 0x00808080;
     __builtin_amdgcn_wave_barrier();
     *reinterpret_cast<v4i*>(xbuf + 16 * lane) = xs;
     v4i A;
@@ -764,7 +826,7 @@ tile_values_kernel(const TileArgs a) {
       }
       // the next loads go out under the products
       if (pass + 1 < kPasses) load_pieces(tok0, nt, pass + 1);
-      else if (k + 1 < k1 && !fold) load_tile(k + 1);         // behind a fold: its parameters are in use
+      else if (k + 1 < k1) load_tile(k + 1);
       constexpr int kPassBlocks = SW >= 16 ? SW / 16 : 1;
 #pragma unroll
       for (int cbl = 0; cbl < kPassBlocks; ++cbl) {
@@ -784,27 +846,13 @@ tile_values_kernel(const TileArgs a) {
     if constexpr (VCH) {
       const v4i ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
       acc_w = __builtin_amdgcn_mfma_i32_16x16x64_i8(A, ones, acc_w, 0, 0, 0);
-      if (fold) {
-        const float wsum = digits_to_float(acc_w) * 0x1p-29f;
-        acc_w = (v4i){0, 0, 0, 0};
-#pragma unroll
-        for (int p = 0; p < NACC; ++p) {
-          const float s = gs[p] * variant_weight<BITS>(p % kV);
-          const float add = __half2float(__ushort_as_half(gm[p])) + (BITS == 8 ? 128.f * gs[p] : 0.f);
-          facc[p] = fmaf(digits_to_float(acc[p]) * 0x1p-29f, s, fmaf(wsum, add, facc[p]));
-          acc[p] = (v4i){0, 0, 0, 0};
-        }
-        run = 0;
-        if (k + 1 < k1) load_tile(k + 1);
-      }
     }
   }
+  if (run) bank();
   __syncthreads();                                             // the stages become the partial sums
-  const float inv_f = ldexpf(1.f, -F);
 #pragma unroll
   for (int p = 0; p < NACC; ++p) {
-    const float v = VCH ? facc[p]
-                        : fmaf(digits_to_float(acc[p]), inv_f, facc[p]) * variant_weight<BITS>(p % kV);
+    const float v = VCH ? facc[p] : facc[p] * variant_weight<BITS>(p % kV);
     if (CB >= 16 || n16 < 8) mem.part[wave][kb][channel(p)] = v;
   }
   const float l = head_sums(lsum, lane), m = head_sums(msum, lane);      // of head kb

@@ -105,3 +105,38 @@ def test_recorded_step_on_the_tile_kernels(d, n_vis, batch):
         ref = O.decode_attn(x_cpu["q"].numpy(), kq, vq, x_cpu["k_text"].numpy(), x_cpu["v_text"].numpy(), at + 1,
                             O.CALIB_DYNAMIC, 1.0, 2.0)
         _check(out, ref, "d %d replay %d" % (d, i))
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("bits", [1, 2, 4, 8])
+def test_values_that_stand_out(d, bits):
+    """One group of tokens holds values 3e6 times the others' and, for the first query head, weights of 2e-8
+    of theirs: both parts count alike in that head's result, and each has to keep fp32's bits.  The
+    heads differ in scale, down to one whose weights are all equal (where the outliers are everything), so
+    no fixed-point format that the heads share can hold them.  The bar is what rounding the exact
+    result to fp16 gives for that head, plus 1e-4: weights are within 17.5 x 2^-22 = 4e-6 (fp32 logits), sums
+    of 1000 terms in fp32 within 1e-5."""
+    n, group, n_text = 1000, 40, 3
+    gen = torch.Generator().manual_seed(d + bits)
+    q0 = torch.randn(d, generator=gen)
+    q = torch.stack([q0, 0.5 * q0, 0.1 * q0, 0.0 * q0]).half().view(1, 4, d)
+    k = 0.05 * torch.randn(1, 1, n, d, generator=gen)
+    v = 0.01 * torch.randn(1, 1, n, d, generator=gen)
+    out = slice(5 * group, 6 * group)
+    k[:, :, out] = -17.5 * d ** 0.5 * q0 / q0.square().sum()
+    v[:, :, out] = 30000.0 * torch.randn(1, 1, group, d, generator=gen).clamp(-2, 2)
+    kt, vt = 0.05 * torch.randn(1, 1, n_text, d, generator=gen), 0.01 * torch.randn(1, 1, n_text, d, generator=gen)
+    x_cpu = {"q": q, "k": k.half(), "v": v.half(), "k_text": kt.half(), "v_text": vt.half()}
+    x = H.to_device(x_cpu)
+    for vax, vg in ((1, d), (0, group), (0, n)):
+        what = "d %d bits %d values %d/%d" % (d, bits, vax, vg)
+        print(what, flush=True)
+        lay = cq.make_layout(1, 4, 1, d, n, bits, 0, vax, group, vg)
+        kq, vq = H.oracle_quantize(x_cpu, lay)
+        kd, vd = cq.cq_quantize_kv(lay, x["k"], x["v"])
+        ref = O.decode_attn(x_cpu["q"].numpy(), kq, vq, x_cpu["k_text"].numpy(), x_cpu["v_text"].numpy(), n_text,
+                            O.CALIB_NONE)
+        got = cq.cq_decode_attn(lay, x["q"], kd, vd, x["k_text"], x["v_text"], n_text).cpu().numpy()
+        for h in range(4):
+            err, least = H.row_rel_l2(got[:, h], ref[:, h]), H.row_rel_l2(ref[:, h].astype(np.float16), ref[:, h])
+            assert err <= least + 1e-4, "%s head %d: rel L2 %.3e, fp16 rounding %.3e" % (what, h, err, least)
