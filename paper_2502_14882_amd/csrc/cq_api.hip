@@ -433,13 +433,12 @@ int cq_quantize_kv(const cq_layout_t* L, const void* k_f16, const void* v_f16,
     if (!aligned16(v_f16)) return fail(CQ_ERR_ALIGN, "v_f16 must be 16-byte aligned");
   }
   if (L->n_vis == 0) return CQ_OK;
-  const int path = g_kernel_path;
-  const bool k_tuned = cq::quantize_tuned_supported(L->n_vis, L->head_dim, L->bits, L->k_axis, L->k_group);
-  const bool v_tuned = cq::quantize_tuned_supported(L->n_vis, L->head_dim, L->bits, L->v_axis, L->v_group);
+  const int path = g_kernel_path, rows = L->batch * L->n_kv_heads;
+  const bool k_tuned = cq::quantize_tuned_supported(rows, L->n_vis, L->head_dim, L->bits, L->k_axis, L->k_group);
+  const bool v_tuned = cq::quantize_tuned_supported(rows, L->n_vis, L->head_dim, L->bits, L->v_axis, L->v_group);
   if (path == CQ_PATH_TUNED && ((do_k && !k_tuned) || (do_v && !v_tuned)))
     return fail(CQ_ERR_UNSUPPORTED, "no tuned quantizer for this layout");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int rows = L->batch * L->n_kv_heads;
   cq::QuantizeJob jobs[2];         // tensors that the tile kernels take, together
   int n_jobs = 0;
   for (int i = 0; i < 2; ++i) {

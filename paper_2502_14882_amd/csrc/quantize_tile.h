@@ -590,8 +590,7 @@ struct Task {
 };
 
 // n_vis is a multiple of a channel-wise group.
-template <int D>
-Task make_task(const void* x_f16, const cq_qtensor_t& out, size_t n_tokens, int bits, int axis, int group) {
+inline Task make_task(const void* x_f16, const cq_qtensor_t& out, size_t n_tokens, int bits, int axis, int group) {
   Task t;
   t.axis = axis;
   t.a.x = static_cast<const __half*>(x_f16);
@@ -616,6 +615,12 @@ Task make_task(const void* x_f16, const cq_qtensor_t& out, size_t n_tokens, int 
   if (!flat) t.a.tile_stride = group;          // a short group is a tile of its own
   t.blocks = (n_tokens + t.a.tile_stride - 1) / t.a.tile_stride;
   return t;
+}
+
+// Whether the launches of a tensor stay within 2^32 - 1 threads, which HIP takes.
+inline bool launchable(const Task& t) {
+  const size_t most = 0xffffffffu / kThreads;
+  return t.blocks <= most && t.n_seq * (size_t)t.a.splits <= most;
 }
 
 // long groups: extrema pass, all tiles but the last of every group, the last tiles; u: NULL, or a second
@@ -724,8 +729,8 @@ template <int D>
 hipError_t launch_quantize_dim(const QuantizeJob* jobs, int n_jobs, size_t n_tokens, int bits, hipStream_t stream) {
   Task t[2];
   for (int i = 0; i < n_jobs; ++i) {
-    t[i] = make_task<D>(jobs[i].x_f16, jobs[i].out, n_tokens, bits, jobs[i].axis, jobs[i].group);
-    if (t[i].blocks > 0x7fffffffu || t[i].n_seq * t[i].a.splits > 0x7fffffffu) return hipErrorInvalidConfiguration;
+    t[i] = make_task(jobs[i].x_f16, jobs[i].out, n_tokens, bits, jobs[i].axis, jobs[i].group);
+    if (!launchable(t[i])) return hipErrorInvalidConfiguration;
   }
   const Task* v = n_jobs > 1 ? &t[1] : nullptr;
   switch (bits) {

@@ -4,12 +4,13 @@
 
 namespace cq {
 
-bool quantize_tuned_supported(int n_vis, int d, int bits, int axis, int group) {
+bool quantize_tuned_supported(int rows, int n_vis, int d, int bits, int axis, int group) {
   if ((d != 64 && d != 128 && d != 256) || n_vis <= 0 || group < 1) return false;
   if (bits != 1 && bits != 2 && bits != 4 && bits != 8) return false;
-  if (axis == CQ_AXIS_CHANNEL) return n_vis % group == 0;
-  if (axis != CQ_AXIS_TOKEN) return false;
-  return group <= d && (group == 32 || group == 64 || group == 128 || group == 256);
+  if (axis == CQ_AXIS_CHANNEL ? n_vis % group != 0
+                              : axis != CQ_AXIS_TOKEN || group > d || (group != 32 && group != 64 && group != 128 && group != 256))
+    return false;
+  return launchable(make_task(nullptr, cq_qtensor_t{}, (size_t)rows * (size_t)n_vis, bits, axis, group));
 }
 
 hipError_t launch_quantize_tuned(const QuantizeJob* jobs, int n_jobs, int rows, int n_vis, int d, int bits,

@@ -305,3 +305,16 @@ def test_bench_refuses_more_than_one_gpu():
                        capture_output=True, text=True, timeout=120)
     assert r.returncode != 0
     assert "one GPU" in (r.stdout + r.stderr)
+
+
+def test_quantizer_kernels_stop_where_a_launch_does():
+    """The tile kernels of the quantizer refuse layouts of more blocks than a launch takes (2^32 - 1 threads),
+    on the host, and leave them to the shape-agnostic kernels."""
+    cq.cq_bench_set_kernel_path(cq.CQ_PATH_TUNED)
+    try:
+        # (160: a long group, whose extrema pass has four blocks)
+        for d, n, group in ((64, 1 << 24, 1), (64, 20 << 24, 20), (128, 40 << 24, 40), (64, 160 << 22, 160)):
+            lay = cq.make_layout(1, 1, 1, d, n, 1, 0, 0, group, group)
+            assert _quant(lay) == cq.CQ_ERR_UNSUPPORTED, (d, n, group)
+    finally:
+        cq.cq_bench_set_kernel_path(cq.CQ_PATH_AUTO)

@@ -59,3 +59,15 @@ def test_keys_and_values_in_one_call(d, bits):
                 H.assert_qtensor_equal(v, O.quantize_tensor(x_cpu["v"].numpy(), bits, vax, vg), what)
     finally:
         cq.cq_bench_set_kernel_path(prev)
+
+
+def test_more_groups_than_blocks_in_a_launch():
+    """2^24 + 5 groups of one token: more blocks of 256 threads than a launch takes (2^32 - 1 threads), so
+    the tile kernels leave them to the others.  A group of one token is its own minimum."""
+    n, d = (1 << 24) + 5, 64
+    lay = cq.make_layout(1, 1, 1, d, n, 1, 0, 0, 1, 1)
+    x = torch.randn(n, d, device="cuda", dtype=torch.float16, generator=torch.Generator("cuda").manual_seed(1))
+    out, _ = cq.cq_quantize_kv(lay, x.view(1, 1, n, d), None)
+    torch.cuda.synchronize()
+    assert torch.equal(out.min.view(n, d), x + 0.0)
+    assert int(out.codes.count_nonzero()) == 0 and int(out.scale.count_nonzero()) == 0
