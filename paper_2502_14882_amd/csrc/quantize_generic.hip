@@ -27,13 +27,13 @@ __device__ inline uint32_t exact_code(float x, double alpha, double D, double L)
   return (uint32_t)rint(((double)x - alpha) * L / D);
 }
 
-// One block per (row, token group); one thread per channel.
+// One block per (row, token group), the first one being first_block; one thread per channel.
 __global__ void quantize_channel_axis(const __half* __restrict__ x, uint32_t* __restrict__ codes,
                                       float* __restrict__ scale, uint16_t* __restrict__ minv,
-                                      int n_vis, int d, int bits, int group) {
+                                      int n_vis, int d, int bits, int group, size_t first_block) {
   __shared__ uint8_t tile[kTileTokens][kMaxDim];
   const int n_groups = n_vis / group;
-  const size_t blk = blockIdx.x;
+  const size_t blk = first_block + blockIdx.x;
   const size_t row = blk / n_groups;
   const int t = (int)(blk % n_groups);
   const int c = threadIdx.x;
@@ -110,13 +110,17 @@ hipError_t launch_quantize_generic(const void* x_f16, const cq_qtensor_t& out, i
   if (axis == CQ_AXIS_CHANNEL) {
     const size_t blocks = (size_t)rows * (size_t)(n_vis / group);
     if (blocks > 0x7fffffffu) return hipErrorInvalidConfiguration;
-    quantize_channel_axis<<<dim3((unsigned)blocks), dim3(d), 0, stream>>>(
-        x, out.codes, out.scale, out.min, n_vis, d, bits, group);
+    const size_t most = 0xffffffffu / (unsigned)d;     // a launch takes 2^32 - 1 threads
+    for (size_t first = 0; first < blocks; first += most) {
+      const size_t n = blocks - first < most ? blocks - first : most;
+      quantize_channel_axis<<<dim3((unsigned)n), dim3(d), 0, stream>>>(
+          x, out.codes, out.scale, out.min, n_vis, d, bits, group, first);
+    }
   } else {
     const size_t n_tokens = (size_t)rows * (size_t)n_vis;
     const size_t items = n_tokens * (size_t)(d / group);
     const size_t blocks = (items + 255) / 256;
-    if (blocks > 0x7fffffffu) return hipErrorInvalidConfiguration;
+    if (blocks > 0xffffffffu / 256) return hipErrorInvalidConfiguration;     // beyond what a launch takes
     quantize_token_axis<<<dim3((unsigned)blocks), dim3(256), 0, stream>>>(
         x, out.codes, out.scale, out.min, n_tokens, d, bits, group);
   }

@@ -61,13 +61,19 @@ def test_keys_and_values_in_one_call(d, bits):
         cq.cq_bench_set_kernel_path(prev)
 
 
-def test_more_groups_than_blocks_in_a_launch():
+@pytest.mark.parametrize("d", [64, 256])
+def test_more_groups_than_blocks_in_a_launch(d):
     """2^24 + 5 groups of one token: more blocks of 256 threads than a launch takes (2^32 - 1 threads), so
-    the tile kernels leave them to the others.  A group of one token is its own minimum."""
-    n, d = (1 << 24) + 5, 64
+    the tile kernels leave them to the others, which take one thread per channel: one launch, or two.  A
+    group of one token is its own minimum."""
+    n = (1 << 24) + 5
     lay = cq.make_layout(1, 1, 1, d, n, 1, 0, 0, 1, 1)
     x = torch.randn(n, d, device="cuda", dtype=torch.float16, generator=torch.Generator("cuda").manual_seed(1))
     out, _ = cq.cq_quantize_kv(lay, x.view(1, 1, n, d), None)
     torch.cuda.synchronize()
-    assert torch.equal(out.min.view(n, d), x + 0.0)
-    assert int(out.codes.count_nonzero()) == 0 and int(out.scale.count_nonzero()) == 0
+    x.add_(0.0)                                        # a zero minimum is stored as +0
+    assert torch.equal(out.min.view(n, d), x)
+    for t in (out.codes, out.scale):
+        assert int(t.max()) == 0 and int(t.min()) == 0
+    del x, out
+    torch.cuda.empty_cache()
