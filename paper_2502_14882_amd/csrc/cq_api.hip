@@ -445,7 +445,8 @@ int cq_quantize_kv(const cq_layout_t* L, const void* k_f16, const void* v_f16,
     if (i == 0 ? !do_k : !do_v) continue;
     const cq::QuantizeJob job = i == 0 ? cq::QuantizeJob{k_f16, *k_out, L->k_axis, L->k_group}
                                        : cq::QuantizeJob{v_f16, *v_out, L->v_axis, L->v_group};
-    if (path != CQ_PATH_GENERIC && (i == 0 ? k_tuned : v_tuned)) {
+    if (path != CQ_PATH_GENERIC && (i == 0 ? k_tuned : v_tuned) &&
+        (path == CQ_PATH_TUNED || cq::quantize_tile_is_faster(L->head_dim, L->bits, job.axis, job.group))) {
       jobs[n_jobs++] = job;
       continue;
     }

@@ -125,6 +125,7 @@ hipError_t launch_tau_search(const DecodeShape& s, const void* q, const void* k_
 // Register-resident tile quantizer (quantize_tile.h): head_dim 64, 128 or 256, b in {1,2,4,8}, any
 // channel-wise group of tokens, channel groups of 32 to 256, any n_vis, as far as a launch reaches.
 bool quantize_tuned_supported(int rows, int n_vis, int d, int bits, int axis, int group);
+bool quantize_tile_is_faster(int d, int bits, int axis, int group);
 // One or two tensors of the same shape, in as few launches as their statistics allow.
 struct QuantizeJob {
   const void* x_f16;

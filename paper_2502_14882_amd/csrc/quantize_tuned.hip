@@ -13,6 +13,21 @@ bool quantize_tuned_supported(int rows, int n_vis, int d, int bits, int axis, in
   return launchable(make_task(nullptr, cq_qtensor_t{}, (size_t)rows * (size_t)n_vis, bits, axis, group));
 }
 
+// Whether the tile kernels also finish sooner than the shape-agnostic ones.  They do, but for short groups of
+// tokens: a group under 128 tokens other than 32 and 64 is a block of 256 threads of its own, which
+// derives the parameters and thresholds of every channel for a few tokens, while the other kernel spends
+// one thread per channel on it.  Microseconds, one tensor of 128 rows x 4096 tokens, shape-agnostic / tile:
+//   128 channels, 1 bit:   4 tokens 161 / 348, 12: 118 / 121, 16: 114 / 96, 31: 114 / 52
+//                 2 bits:  4 tokens 144 / 600, 16: 109 / 154, 24: 112 / 105, 31: 114 / 84
+//                 8 bits:  1 token 299 / 2691, 16: 115 / 194, 24: 118 / 135, 31: 122 / 109
+//   256 channels, 2 bits:  16 tokens 287 / 286; 8 rows: 14.0 / 22.6, 24: 16.4 / 18.2, 31: 17.8 / 15.9
+// The line is where the slower of 8, 64 and 256 rows breaks even.
+bool quantize_tile_is_faster(int d, int bits, int axis, int group) {
+  if (axis == CQ_AXIS_TOKEN) return true;
+  const int line = bits == 1 ? 16 : bits == 2 ? 24 : 28;
+  return group >= line * (d == 256 ? 9 : 8) / 8;
+}
+
 hipError_t launch_quantize_tuned(const QuantizeJob* jobs, int n_jobs, int rows, int n_vis, int d, int bits,
                                  hipStream_t stream) {
   const size_t n_tokens = (size_t)rows * (size_t)n_vis;

@@ -61,6 +61,30 @@ def test_keys_and_values_in_one_call(d, bits):
         cq.cq_bench_set_kernel_path(prev)
 
 
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("bits", [1, 2, 4, 8])
+def test_both_sides_of_the_shortest_group(d, bits):
+    """Channel-wise groups around the length from which the tile kernels are used, keys on one side of it
+    and values on the other: bit for bit the same as the oracle, and as the tile kernels wherever
+    they can run."""
+    n = 16 * 27 * 7
+    w = synth.WORKLOADS[4].replace(batch=1, n_kv_heads=2, n_q_heads=2, head_dim=d, n_vis=n, seed=d + bits)
+    x_cpu = synth.make_inputs(w, "cpu", parts=("k", "v"))
+    x = H.to_device(x_cpu)
+    for kg, vg in ((1, 28), (12, 18), (16, 27), (14, 24), (21, 9), (28, 36)):
+        lay = cq.make_layout(1, 2, 2, d, n, bits, 0, 0, kg, vg)
+        want = [O.quantize_tensor(x_cpu[t].numpy(), bits, 0, g) for t, g in (("k", kg), ("v", vg))]
+        for path in (cq.CQ_PATH_AUTO, cq.CQ_PATH_TUNED):
+            prev = cq.cq_bench_set_kernel_path(path)
+            try:
+                got = cq.cq_quantize_kv(lay, x["k"], x["v"])
+                torch.cuda.synchronize()
+            finally:
+                cq.cq_bench_set_kernel_path(prev)
+            for g, r, name in zip(got, want, "kv"):
+                H.assert_qtensor_equal(g, r, "d %d bits %d groups %d/%d %s path %d" % (d, bits, kg, vg, name, path))
+
+
 @pytest.mark.parametrize("d", [64, 256])
 def test_more_groups_than_blocks_in_a_launch(d):
     """2^24 + 5 groups of one token: more blocks of 256 threads than a launch takes (2^32 - 1 threads), so
