@@ -18,10 +18,12 @@ extern "C" {
 #endif
 
 /* Kernel selection for cq_quantize_kv / cq_decode_attn* on this thread.  AUTO picks the tuned
- * kernels when the shape allows and the shape-agnostic ones otherwise; GENERIC forces the
- * shape-agnostic kernels; TUNED returns CQ_ERR_UNSUPPORTED instead of falling back.
+ * or the tile kernels when the shape allows and the shape-agnostic ones otherwise; GENERIC forces the
+ * shape-agnostic kernels; TUNED returns CQ_ERR_UNSUPPORTED instead of falling back, and never takes
+ * the tile decode kernels; TILE forces those, and returns CQ_ERR_UNSUPPORTED where they do not take
+ * the layout (for cq_quantize_kv it is TUNED).
  * Returns the previous value, or CQ_ERR_UNSUPPORTED (-3) for an unknown one. */
-enum { CQ_PATH_AUTO = 0, CQ_PATH_GENERIC = 1, CQ_PATH_TUNED = 2 };
+enum { CQ_PATH_AUTO = 0, CQ_PATH_GENERIC = 1, CQ_PATH_TUNED = 2, CQ_PATH_TILE = 3 };
 int cq_bench_set_kernel_path(int path);
 
 /* Chunks per (batch, KV head) row of the tuned decode on this thread: 0 = the library's own

@@ -18,7 +18,7 @@ LIB_PATH = os.path.join(_HERE, "libcq.so")
 
 CQ_AXIS_CHANNEL, CQ_AXIS_TOKEN = 0, 1
 CQ_CALIB_NONE, CQ_CALIB_DYNAMIC, CQ_CALIB_FIXED = 0, 1, 2
-CQ_PATH_AUTO, CQ_PATH_GENERIC, CQ_PATH_TUNED = 0, 1, 2
+CQ_PATH_AUTO, CQ_PATH_GENERIC, CQ_PATH_TUNED, CQ_PATH_TILE = 0, 1, 2, 3
 CQ_OK, CQ_ERR_NULL, CQ_ERR_SHAPE, CQ_ERR_UNSUPPORTED = 0, -1, -2, -3
 CQ_ERR_WORKSPACE, CQ_ERR_HIP, CQ_ERR_ALIGN = -4, -5, -6
 

@@ -246,6 +246,11 @@ int select_kernels(const cq_layout_t* L, int n_text, int n_text_cap, size_t scra
   // what does not fit.
   const bool within_noalloc = call->generic_ws.total_bytes <= (size_t)CQ_NOALLOC_SCRATCH_BYTES;
   bool reserve_all = false;          // a shorter tail may use all of that scratch
+  if (g_kernel_path == CQ_PATH_TILE) {
+    call->tile = cq::make_tile_plan(call->shape);
+    call->tiled = call->tile.ok;
+    if (!call->tiled) return fail(CQ_ERR_UNSUPPORTED, "no tile decode kernel for this layout");
+  }
   if (g_kernel_path == CQ_PATH_AUTO) {
     if (!call->tuned) {
       call->tile = cq::make_tile_plan(call->shape, within_noalloc ? (size_t)CQ_NOALLOC_SCRATCH_BYTES : SIZE_MAX);
@@ -362,7 +367,8 @@ int check_workspace(DecodeCall* call, const void* workspace, size_t workspace_by
   if (!workspace) return fail(CQ_ERR_WORKSPACE, "workspace is NULL");
   if ((reinterpret_cast<uintptr_t>(workspace) & 255u) != 0)
     return fail(CQ_ERR_WORKSPACE, "workspace must be 256-byte aligned");
-  if (call->tiled && workspace_bytes < call->ws_bytes && workspace_bytes >= ws_without_tiles(*call)) {
+  if (call->tiled && g_kernel_path == CQ_PATH_AUTO && workspace_bytes < call->ws_bytes &&
+      workspace_bytes >= ws_without_tiles(*call)) {
     call->tiled = false;
     call->ws_bytes = ws_without_tiles(*call);
   }
@@ -393,7 +399,7 @@ const char* cq_status_string(int status) {
 }
 
 int cq_bench_set_kernel_path(int path) {
-  if (path != CQ_PATH_AUTO && path != CQ_PATH_GENERIC && path != CQ_PATH_TUNED)
+  if (path < CQ_PATH_AUTO || path > CQ_PATH_TILE)
     return fail(CQ_ERR_UNSUPPORTED, "unknown kernel path %d", path);
   const int prev = g_kernel_path;
   g_kernel_path = path;
@@ -433,7 +439,7 @@ int cq_quantize_kv(const cq_layout_t* L, const void* k_f16, const void* v_f16,
     if (!aligned16(v_f16)) return fail(CQ_ERR_ALIGN, "v_f16 must be 16-byte aligned");
   }
   if (L->n_vis == 0) return CQ_OK;
-  const int path = g_kernel_path, rows = L->batch * L->n_kv_heads;
+  const int path = g_kernel_path == CQ_PATH_TILE ? CQ_PATH_TUNED : g_kernel_path, rows = L->batch * L->n_kv_heads;
   const bool k_tuned = cq::quantize_tuned_supported(rows, L->n_vis, L->head_dim, L->bits, L->k_axis, L->k_group);
   const bool v_tuned = cq::quantize_tuned_supported(rows, L->n_vis, L->head_dim, L->bits, L->v_axis, L->v_group);
   if (path == CQ_PATH_TUNED && ((do_k && !k_tuned) || (do_v && !v_tuned)))

@@ -25,6 +25,24 @@ MODES = {"none": (cq.CQ_CALIB_NONE, 0, 0, 0, 0), "dynamic": (cq.CQ_CALIB_DYNAMIC
          "fixed": (cq.CQ_CALIB_FIXED, 3, 1, -9, 9), "falling": (cq.CQ_CALIB_FIXED, 0, 3, -1, 1)}
 
 
+@pytest.fixture
+def tile_path():
+    """The tile kernels or an error: no other kernels can stand in for them unseen."""
+    prev = cq.cq_bench_set_kernel_path(cq.CQ_PATH_TILE)
+    yield
+    cq.cq_bench_set_kernel_path(prev)
+
+
+def _auto_takes_the_tiles(lay, n_text, calib):
+    """Without the switch the tile kernels run as well, unless the tuned ones take the layout."""
+    sizes = {}
+    for path in (cq.CQ_PATH_TUNED, cq.CQ_PATH_AUTO, cq.CQ_PATH_TILE):
+        prev = cq.cq_bench_set_kernel_path(path)
+        sizes[path] = cq.cq_decode_workspace_bytes(lay, n_text, calib)
+        cq.cq_bench_set_kernel_path(prev)
+    return sizes[cq.CQ_PATH_TUNED] or sizes[cq.CQ_PATH_AUTO] == sizes[cq.CQ_PATH_TILE]
+
+
 def _check(out, ref, what):
     got = out.cpu().numpy().astype(np.float64)
     assert np.isfinite(got).all(), what
@@ -35,7 +53,7 @@ def _check(out, ref, what):
 
 @pytest.mark.parametrize("d", [64, 128, 256])
 @pytest.mark.parametrize("bits", [1, 2, 4, 8])
-def test_tile_decode(d, bits):
+def test_tile_decode(d, bits, tile_path):
     for n_vis, kg, vax, vg, g, n_text, calib in CASES:
         vg = vg or d
         what = "d %d bits %d n_vis %d kg %d v %d/%d g %d n_text %d %s" % (d, bits, n_vis, kg, vax, vg, g, n_text, calib)
@@ -48,6 +66,7 @@ def test_tile_decode(d, bits):
         kq, vq = H.oracle_quantize(x_cpu, lay)
         kd, vd = cq.cq_quantize_kv(lay, x["k"], x["v"]) if n_vis else (None, None)
         args = MODES[calib]
+        assert _auto_takes_the_tiles(lay, n_text, cq.make_calib(*args)), what
         ref = O.decode_attn(x_cpu["q"].numpy(), kq, vq, x_cpu["k_text"].numpy(), x_cpu["v_text"].numpy(),
                             n_text, *args, 0.0)
         out = cq.cq_decode_attn(lay, x["q"], kd, vd, x["k_text"], x["v_text"], n_text, cq.make_calib(*args))
@@ -109,7 +128,7 @@ def test_recorded_step_on_the_tile_kernels(d, n_vis, batch):
 
 @pytest.mark.parametrize("d", [64, 128, 256])
 @pytest.mark.parametrize("bits", [1, 2, 4, 8])
-def test_values_that_stand_out(d, bits):
+def test_values_that_stand_out(d, bits, tile_path):
     """One group of tokens holds values 3e6 times the others' and, for the first query head, weights of 2e-8
     of theirs: both parts count alike in that head's result, and each has to keep fp32's bits.  The
     heads differ in scale, down to one whose weights are all equal (where the outliers are everything), so
@@ -140,3 +159,52 @@ def test_values_that_stand_out(d, bits):
         for h in range(4):
             err, least = H.row_rel_l2(got[:, h], ref[:, h]), H.row_rel_l2(ref[:, h].astype(np.float16), ref[:, h])
             assert err <= least + 1e-4, "%s head %d: rel L2 %.3e, fp16 rounding %.3e" % (what, h, err, least)
+
+
+@pytest.mark.parametrize("d,bits,vax", [(64, 1, 1), (128, 2, 0), (256, 1, 1)])
+def test_many_partials(d, bits, vax, tile_path):
+    """One row of 32768 tokens is 64 chunks, a tail of 8193 another 33 of 256 tokens (64 of 128 are 8192): the
+    last workgroup merges 97 partials in seven batches, and a tail workgroup takes two rounds."""
+    n, n_text = 32768, 8193
+    w = synth.WORKLOADS[2].replace(batch=1, n_kv_heads=1, n_q_heads=3, head_dim=d, n_vis=n, n_text=n_text, seed=d)
+    x_cpu = synth.make_inputs(w, "cpu")
+    lay = cq.make_layout(1, 3, 1, d, n, bits, 0, vax, 512, d if vax else 512)
+    x = H.to_device(x_cpu)
+    kq, vq = H.oracle_quantize(x_cpu, lay)
+    kd, vd = cq.cq_quantize_kv(lay, x["k"], x["v"])
+    for t in (n_text, 8192, 130):
+        ref = O.decode_attn(x_cpu["q"].numpy(), kq, vq, x_cpu["k_text"].numpy(), x_cpu["v_text"].numpy(), t,
+                            O.CALIB_DYNAMIC, 1.0, 2.0)
+        out = cq.cq_decode_attn(lay, x["q"], kd, vd, x["k_text"], x["v_text"], t, cq.make_calib(cq.CQ_CALIB_DYNAMIC, 1, 2))
+        torch.cuda.synchronize()
+        _check(out, ref, "d %d bits %d tail %d" % (d, bits, t))
+
+
+@pytest.mark.parametrize("d,bits,vax", [(64, 1, 0), (128, 8, 1)])
+def test_long_runs(d, bits, vax, tile_path):
+    """A row of 16.8 million tokens: 1025 value tiles per wave, one more than the int32 digit sums hold, and
+    code words beyond 2^31 bytes (128 channels, 8 bits).  With a query of zeros all weights are equal, so the
+    result is the mean of the dequantized values, 0.5 on average: formed here in fp64.  fp32 sums of equal
+    terms, banked every 1024 tiles, stay far below fp16's rounding."""
+    n = 64 * 4 * 64 * 1025
+    gen = torch.Generator("cuda").manual_seed(d)
+    x = torch.empty(1, 1, n, d, dtype=torch.float16, device="cuda").uniform_(0, 1, generator=gen)
+    lay = cq.make_layout(1, 1, 1, d, n, bits, 0, vax, 512, d if vax else n)
+    k, v = cq.cq_quantize_kv(lay, x, x)
+    q = torch.zeros(1, 1, d, dtype=torch.float16, device="cuda")
+    out = cq.cq_decode_attn(lay, q, k, v, None, None, 0)
+    torch.cuda.synchronize()
+    del x
+    total, step = torch.zeros(d, dtype=torch.float64, device="cuda"), n // 64
+    shifts = torch.arange(32 - bits, -1, -bits, device="cuda", dtype=torch.int32)
+    for t in range(0, n, step):
+        words = v.codes[0, 0, t:t + step]
+        codes = ((words[:, :, None] >> shifts) & ((1 << bits) - 1)).view(step, d).double()
+        if vax:
+            total += (codes * v.scale[0, 0, t:t + step].double() + v.min[0, 0, t:t + step].double()).sum(0)
+        else:
+            total += (codes * v.scale[0, 0].double() + v.min[0, 0].double()).sum(0)
+    ref = (total / n).cpu().numpy().reshape(1, 1, d)
+    _check(out, ref, "d %d bits %d" % (d, bits))
+    del k, v
+    torch.cuda.empty_cache()
