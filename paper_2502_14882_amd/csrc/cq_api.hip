@@ -191,24 +191,30 @@ int check_calib(const cq_calib_t* calib, cq::Calib* c) {
 //   1 bit, 4 heads:  8 rows x 3328 tokens 12.5 / 11.8, x 8192 21.8 / 14.4; 32 rows x 8192 22.1 / 19.6;
 //                    8 rows x 1024 9.1 / 11.6 and 64 rows x 8192 22.2 / 27.1 stay fused
 //   1 bit, 6 heads:  8 rows x 3328 20.7 / 12.5, 64 rows 22.6 / 19.5; 128 rows 26.0 / 27.3 stay streamed
-//   4 bits:          32 rows x 3328 17.7 / 14.8;  8 bits: 8 rows x 3328 37.5 / 14.9, 128 rows 43.0 / 36.2
-// The tail's length plays no part in the rule.
+//   4 bits:          32 rows x 3328 17.7 / 14.8;  8 bits: 8 rows x 3328 37.5 / 14.9, 16 x 10240 25.5 / 19.5
+// The tail plays a part in one place: the streaming kernels read it once for two head sets, the tile
+// kernels once for each (112 rows x 128 tokens, 8 heads, 1000 tail tokens: 23.4 / 28.9).  Over 700 drawn
+// layouts of 1 to 500 rows, 3 of the 285 that go to the tile kernels are slower there by more than 2 %,
+// the worst by 8 %.
 bool tile_is_faster(cq::DecodeShape s, const cq::FusedPlan& with_tail) {
   const double rows = (double)s.B * s.Hkv, kn = s.n_vis * 1e-3, mtok = rows * s.n_vis * 1e-6;
-  if (mtok > 2.0 || (s.g <= 4 && s.bits <= 2 && s.n_vis <= 1024)) return false;
+  if (mtok > 2.0) return false;
+  const double tail_k = rows * s.n_text * 1e-3;
   s.n_text = 0;
   const cq::FusedPlan plan = with_tail.n_chunks == 1 ? with_tail : cq::make_fused_plan(s, 0);
   const bool streamed = (plan.n_chunks > 1 || plan.nhb > 1) && cq::make_stream_plan(s, 0).ok;
+  constexpr double kCus = 256.0;                                 // the whole chip, which all this is fitted to
   // bits:                           1     2     4     8
   static const double kTilePerM[] = {26.0, 28.0, 36.0, 58.0};    // per million tokens
   static const double kRowPerK[] = {1.65, 2.1, 3.0, 9.0};        // fused: per thousand tokens of a row
   const int i = s.bits == 1 ? 0 : s.bits == 2 ? 1 : s.bits == 4 ? 2 : 3;
   const bool two_sets = s.g > 4;
-  const double tile = 10.6 + (two_sets ? 0.35 : 0.25) * kn + (two_sets ? 1.6 : 1.0) * kTilePerM[i] * mtok;
+  const double tile = 10.6 + (two_sets ? 0.35 : 0.25) * kn + (two_sets ? 1.6 : 1.0) * kTilePerM[i] * mtok +
+                      (two_sets && streamed ? 0.08 * tail_k : 0.0);
   const double group = s.k_axis == CQ_AXIS_CHANNEL && s.k_group == 32 ? 1.65 : s.k_group == 64 ? 1.25 : 1.0;
   const double per_k = kRowPerK[i] * group;
   const double workgroups = rows * plan.nhb * plan.n_chunks;
-  const double rounds = std::ceil(workgroups / 256.0), chunk_kn = kn / plan.n_chunks;
+  const double rounds = std::ceil(workgroups / kCus), chunk_kn = kn / plan.n_chunks;
   const double tuned = plan.n_chunks == 1 && plan.nhb == 1 ? (s.bits == 8 ? 9.5 : 7.0) + per_k * kn * rounds
                        : streamed ? (two_sets ? 18.0 + 16.0 * mtok : 15.5 + 14.5 * mtok)
                                   : 12.0 + 1.5 * per_k * chunk_kn * rounds;
@@ -244,35 +250,33 @@ int select_kernels(const cq_layout_t* L, int n_text, int n_text_cap, size_t scra
   // shape-agnostic kernels fit the scratch of the allocation-free entry point, the tile kernels stay
   // within it too, with fewer chunks if need be; where they would not, that entry point refuses
   // what does not fit.
-  const bool within_noalloc = call->generic_ws.total_bytes <= (size_t)CQ_NOALLOC_SCRATCH_BYTES;
-  bool reserve_all = false;          // a shorter tail may use all of that scratch
+  const size_t most = (size_t)CQ_NOALLOC_SCRATCH_BYTES;
+  size_t reserve = 0;                // scratch that shorter tails may use on the tile kernels
   if (g_kernel_path == CQ_PATH_TILE) {
     call->tile = cq::make_tile_plan(call->shape);
     call->tiled = call->tile.ok;
     if (!call->tiled) return fail(CQ_ERR_UNSUPPORTED, "no tile decode kernel for this layout");
-  }
-  if (g_kernel_path == CQ_PATH_AUTO) {
-    if (!call->tuned) {
-      call->tile = cq::make_tile_plan(call->shape, within_noalloc ? (size_t)CQ_NOALLOC_SCRATCH_BYTES : SIZE_MAX);
-      call->tiled = call->tile.ok && call->tile.ws_bytes <= scratch_limit;
-      reserve_all = within_noalloc && call->tile.ws_reserve_bytes > (size_t)CQ_NOALLOC_SCRATCH_BYTES;
-    } else if (L->n_vis > 0 && g_decode_chunks == 0 && tile_is_faster(call->shape, call->plan)) {
-      call->tile = cq::make_tile_plan(call->shape);
-      // not beyond the scratch of the allocation-free entry point: both entry points run the same kernels.
+    reserve = call->tile.ws_reserve_bytes;
+  } else if (g_kernel_path == CQ_PATH_AUTO && !call->tuned) {
+    const bool within = call->generic_ws.total_bytes <= most;
+    call->tile = cq::make_tile_plan(call->shape, within ? most : SIZE_MAX);
+    call->tiled = call->tile.ok && call->tile.ws_bytes <= scratch_limit;
+    reserve = within && call->tile.ws_reserve_bytes > most ? most : call->tiled ? call->tile.ws_reserve_bytes : 0;
+  } else if (g_kernel_path == CQ_PATH_AUTO && L->n_vis > 0 && g_decode_chunks == 0) {
+    cq::DecodeShape no_tail = call->shape;
+    no_tail.n_text = 0;
+    const bool faster = tile_is_faster(call->shape, call->plan);
+    if (faster || (no_tail.g > 4 && tile_is_faster(no_tail, call->plan))) {
+      // Not beyond the scratch of the allocation-free entry point: both entry points run the same kernels.
       // By the size that never falls as the tail grows: where a tail stays here, so does every shorter one.
-      const size_t most = (size_t)CQ_NOALLOC_SCRATCH_BYTES;
-      call->tiled = call->tile.ok && call->tile.ws_reserve_bytes <= most;
-      if (call->tile.ok && !call->tiled) {       // a shorter tail may still run them
-        cq::DecodeShape no_tail = call->shape;
-        no_tail.n_text = 0;
-        reserve_all = ws_without_tiles(*call) <= most && cq::make_tile_plan(no_tail).ws_reserve_bytes <= most;
-      }
+      call->tile = cq::make_tile_plan(call->shape);
+      call->tiled = faster && call->tile.ok && call->tile.ws_reserve_bytes <= most;
+      if (call->tiled || (call->tile.ok && cq::make_tile_plan(no_tail).ws_reserve_bytes <= most))
+        reserve = call->tile.ws_reserve_bytes < most ? call->tile.ws_reserve_bytes : most;
     }
   }
   call->ws_bytes = call->tiled ? call->tile.ws_bytes : ws_without_tiles(*call);
-  call->ws_query_bytes = reserve_all   ? (size_t)CQ_NOALLOC_SCRATCH_BYTES
-                         : call->tiled ? call->tile.ws_reserve_bytes
-                                       : call->ws_bytes;
+  call->ws_query_bytes = reserve > call->ws_bytes ? reserve : call->ws_bytes;
   return CQ_OK;
 }
 

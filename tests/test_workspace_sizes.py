@@ -94,3 +94,14 @@ def test_no_scratch_for_kernels_that_never_run():
     # one that fits with a short tail keeps asking for it
     lay = cq.make_layout(16, 32, 8, 128, 2560, 8, 0, 1, 128, 128)
     assert needed(lay, 100) > 4 << 20 and cq.cq_decode_workspace_bytes(lay, 4096, calib) >= needed(lay, 100)
+
+
+def test_a_long_tail_for_two_head_sets_stays_on_the_streaming_kernels():
+    """They read the tail once, the tile kernels once per head set; a shorter tail goes to the tile kernels, and
+    the size asked for the long one serves it."""
+    lay, calib = cq.make_layout(14, 64, 8, 128, 128, 1), cq.make_calib(*DYN)
+    prev = cq.cq_bench_set_kernel_path(cq.CQ_PATH_TUNED)
+    tuned = [needed(lay, t) for t in (100, 1000)]
+    cq.cq_bench_set_kernel_path(prev)
+    assert needed(lay, 1000) == tuned[1] and needed(lay, 100) != tuned[0]
+    assert cq.cq_decode_workspace_bytes(lay, 1000, calib) >= needed(lay, 100)
