@@ -376,6 +376,17 @@ int check_workspace(DecodeCall* call, const void* workspace, size_t workspace_by
     call->tiled = false;
     call->ws_bytes = ws_without_tiles(*call);
   }
+  // Split rows of the fused kernel: with a shorter tail a row may be cut into more chunks, to fill the last
+  // round of workgroups, than a workspace for a longer one holds partials of.  The fewest that fit on
+  // chip never grow as the tail shrinks.
+  if (call->tuned && !call->streamed && !call->tiled && call->plan.n_chunks > 2 && workspace_bytes < call->ws_bytes &&
+      g_decode_chunks == 0) {
+    const cq::FusedPlan fewest = cq::make_fused_plan(call->shape, 2);
+    if (fewest.ok && fewest.ws_bytes <= workspace_bytes) {
+      call->plan = fewest;
+      call->ws_bytes = fewest.ws_bytes;
+    }
+  }
   if (workspace_bytes < call->ws_bytes)
     return fail(CQ_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, call->ws_bytes);
   return CQ_OK;

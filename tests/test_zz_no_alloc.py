@@ -151,3 +151,26 @@ def test_a_workspace_of_the_size_the_other_kernels_need_is_enough(shape, n_text,
     with pytest.raises(cq.CqError) as e:
         cq.cq_decode_attn(*args, workspace=torch.empty(size, dtype=torch.uint8, device="cuda")[:size - 256])
     assert e.value.status == cq.CQ_ERR_WORKSPACE
+
+
+def test_split_rows_with_a_workspace_for_a_longer_tail():
+    """Rows of 45824 tokens are cut into more chunks with a tail of 9386 tokens than with one of 10914, to fill the
+    last round of workgroups: the workspace of the latter serves the former, with fewer chunks."""
+    n, longest, n_text = 45824, 10914, 9386
+    w = synth.WORKLOADS[1].replace(batch=10, n_kv_heads=1, n_q_heads=2, n_vis=n, n_text=longest, seed=3)
+    x = synth.make_inputs(w, "cuda")
+    lay = cq.make_layout(10, 2, 1, 128, n, 4, 0, 1, 128, 128)
+    calib = cq.make_calib(cq.CQ_CALIB_DYNAMIC, 1.0, 2.0)
+    k, v = cq.cq_quantize_kv(lay, x["k"], x["v"])
+    args = (lay, x["q"], k, v, x["k_text"], x["v_text"], n_text, calib)
+    prev = cq.cq_bench_set_kernel_path(cq.CQ_PATH_TUNED)
+    try:
+        size = cq.cq_decode_workspace_bytes(lay, longest, calib)
+        assert size < cq.cq_decode_workspace_bytes(lay, n_text, calib)
+        want = cq.cq_decode_attn(*args)
+        got = cq.cq_decode_attn(*args, workspace=torch.empty(size, dtype=torch.uint8, device="cuda"))
+        torch.cuda.synchronize()
+    finally:
+        cq.cq_bench_set_kernel_path(prev)
+    err = O.rel_l2(got.cpu().numpy().astype(np.float64), want.cpu().numpy().astype(np.float64))
+    assert err <= 2 * H.REGRESSION_TOL, err      # two fp16 results
