@@ -43,15 +43,15 @@ __device__ inline double fold_rows(double a, double b) {
 }
 
 // the larger of the two halves' values, and of neighbouring rows', in every lane
-__device__ inline float max_halves(float v) {
-  const unsigned u = __builtin_bit_cast(unsigned, v);
-  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  return fmaxf(__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1]));
+template <int CTRL>
+__device__ inline int dpp_i32(int v) { return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xF, 0xF, true); }
+__device__ inline int max_halves(int v) {
+  const auto r = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
+  return max((int)r[0], (int)r[1]);
 }
-__device__ inline float max_rows(float v) {
-  const unsigned u = __builtin_bit_cast(unsigned, v);
-  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  return fmaxf(__builtin_bit_cast(float, (unsigned)r[0]), __builtin_bit_cast(float, (unsigned)r[1]));
+__device__ inline int max_rows(int v) {
+  const auto r = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
+  return max((int)r[0], (int)r[1]);
 }
 
 // Sum over the wave of the four heads' parts, head kb = lane / 16 in every lane of row kb.  A

@@ -19,9 +19,11 @@
 //
 // Precision.  Keys: one fixed-point scale per key group and head set, 30 bits, results put together in fp64.
 // Values: a scale per head that follows the products weight * scale (see Scales), sums in fp32.  A
-// host model of the sums, 3328 tokens, relative to fp64: 1e-7 to 2e-7 whether or not a token's scale stands out
-// a thousandfold (fp32 multiply-adds over dequantized values: 2e-7 to 4e-7; one scale for all heads set by the
-// largest token scale: 6e-7 to 1e-5).  The maxima cost 0.1 to 0.3 us a call.
+// host model of the sums, 3328 tokens, relative to fp64: 0.6e-7 to 2e-7 whether or not a token's scale stands
+// out a thousandfold (fp32 multiply-adds over dequantized values: 2e-7 to 4e-7; one scale for all heads set by
+// the largest token scale: 6e-7 to 1e-5); 1e-6 where a wave takes 4096 tokens of very uneven weights
+// (logits with a deviation of 6; fp32 2e-7), a two hundredth of the output's rounding.  Following the
+// products costs a small call 0.1 to 0.2 us.
 //
 // Bound: on small calls latency - two launches, and in each wave a chain of few round trips to memory: all
 // that a wave needs first is asked for at once (its first codes and parameters, then the query;
@@ -575,24 +577,32 @@ __device__ inline float digits_bias(float a, float b) { return fmaf(a, b, 842150
 
 // Fixed-point scales of the four heads, powers of two from 2^-90 to 2^90, as the bits of floats.
 struct Scales {
-  static constexpr int kOne = 127 << 23, kStart = (90 + 127) << 23;
-  int up[kHeads] = {kStart, kStart, kStart, kStart};           // wave-uniform
+  static constexpr int kOne = 127 << 23;
+  int up[kHeads];                                              // wave-uniform
+  __device__ explicit Scales(int exponent) {
+#pragma unroll
+    for (int h = 0; h < kHeads; ++h) up[h] = (exponent + 127) << 23;
+  }
   __device__ float of(int h) const { return __builtin_bit_cast(float, up[h]); }
   __device__ float inverse(int kb) const {                     // of head kb
     const int a = kb & 1 ? up[1] : up[0], b = kb & 1 ? up[3] : up[2];
     return __builtin_bit_cast(float, 2 * kOne - (kb & 2 ? b : a));
   }
   // Lowered until w * scale < 2^26 for the heads' w >= 0 of all lanes.  The maxima by a transposing
-  // butterfly, as in head_sums: lane l of a row ends up with head bitrev2(l & 3).
+  // butterfly, as in head_sums: lane l of a row ends up with head bitrev2(l & 3).  Floats that are not
+  // negative order like their bits, and integer maxima need no second instruction for NaNs.
   __device__ void lower(const float (&w)[kHeads], int lane) {
     const bool b0 = lane & 1, b1 = lane & 2;
-    const float u0 = fmaxf(b0 ? w[2] : w[0], dpp_f32<0xB1>(b0 ? w[0] : w[2]));
-    const float u1 = fmaxf(b0 ? w[3] : w[1], dpp_f32<0xB1>(b0 ? w[1] : w[3]));
-    float r = fmaxf(b1 ? u1 : u0, dpp_f32<0x4E>(b1 ? u0 : u1));
-    r = fmaxf(r, dpp_f32<0x124>(r));
-    r = max_rows(max_halves(fmaxf(r, dpp_f32<0x128>(r))));
+    int i[kHeads];
+#pragma unroll
+    for (int h = 0; h < kHeads; ++h) i[h] = __builtin_bit_cast(int, w[h]);
+    const int u0 = max(b0 ? i[2] : i[0], dpp_i32<0xB1>(b0 ? i[0] : i[2]));
+    const int u1 = max(b0 ? i[3] : i[1], dpp_i32<0xB1>(b0 ? i[1] : i[3]));
+    int r = max(b1 ? u1 : u0, dpp_i32<0x4E>(b1 ? u0 : u1));
+    r = max(r, dpp_i32<0x124>(r));
+    r = max_rows(max_halves(max(r, dpp_i32<0x128>(r))));
     // r < 2^(e - 126) for its exponent field e: the scale 2^(26 - (e - 126)), its field 279 - e
-    const int fits = min(max(279 - (__builtin_bit_cast(int, r) >> 23), 127 - 90), 127 + 90) << 23;
+    const int fits = min(max(279 - (r >> 23), 127 - 90), 127 + 90) << 23;
     constexpr int kLane[kHeads] = {0, 2, 1, 3};
 #pragma unroll
     for (int h = 0; h < kHeads; ++h) up[h] = min(up[h], __builtin_amdgcn_readlane(fits, kLane[h]));
@@ -665,8 +675,10 @@ tile_values_kernel(const TileArgs a) {
   // integer nearest to w times a power of two.  That scale is a head's own and follows the products, not
   // the tokens' scales: the largest w so far of the head is in [2^25, 2^29), so no bits are spent on a
   // token that stands out but that the head does not look at, nor on what another head looks at.  It
-  // only drops, within a channel-wise group (whose parameters are its own).
-  Scales scales;
+  // only drops, within a channel-wise group (whose parameters are its own).  Where the group is the whole
+  // row all weights meet the same parameters and the largest is 1: 2^28 throughout, as weights far below
+  // count for nothing.
+  Scales scales(VCH && a.v_groups == 1 ? 28 : 90);
   int run = 0;
 
   v4i piece_r[kPieces];
@@ -792,12 +804,13 @@ tile_values_kernel(const TileArgs a) {
       }
       x[h] = digits_bias(w[h], scales.of(h));
     }
-    const bool over = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])) >= 0x1p29f;
+    auto bits_of = [](float v) { return __builtin_bit_cast(int, v); };
+    const bool over = max(max(bits_of(x[0]), bits_of(x[1])), max(bits_of(x[2]), bits_of(x[3]))) >= bits_of(0x1p29f);
     if (__builtin_amdgcn_ballot_w64(over) != 0 || run == kMaxRun || next_group) {
       if (run) bank();           // the four digit sums of a value cannot be scaled one by one
       if (next_group) {
         load_params(grp);
-        scales = Scales();
+        scales = Scales(90);
       }
       scales.lower(w, lane);
 #pragma unroll
