@@ -175,12 +175,13 @@ int cq_append_text_kv(const cq_layout_t *layout, void *k_text_f16, void *v_text_
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, results
  * (bit for bit) and errors as cq_decode_attn, without the workspace: whatever scratch the
  * selected kernels need (chunk extrema and online-softmax partials of split rows, logits of the
- * shape-agnostic kernels) lives in an array of CQ_NOALLOC_SCRATCH_BYTES inside the library's
- * device image, one copy per GPU, held until the process ends.  The call allocates and frees
- * nothing; the first call on a device looks the array's address up once (not under capture).
- * A shape that needs more scratch than the array holds (compare
- * cq_decode_workspace_bytes(layout, n_text, calib) with CQ_NOALLOC_SCRATCH_BYTES) returns
- * CQ_ERR_WORKSPACE and launches nothing: use cq_decode_attn with a workspace for it.
+ * tile and of the shape-agnostic kernels) lives in an array of CQ_NOALLOC_SCRATCH_BYTES inside the
+ * library's device image, one copy per GPU, held until the process ends.  The call allocates and
+ * frees nothing; the first call on a device looks the array's address up once (not under capture).
+ * A call whose kernels need more scratch than the array holds returns CQ_ERR_WORKSPACE and launches
+ * nothing: use cq_decode_attn with a workspace for it.  One exception: split rows whose kept
+ * 16-bit logits exceed the array (the long-context layouts with 1- and 2-bit codes) are not refused but
+ * run on the kernels that form the logits twice, to the same accuracy but not to the same bits.
  * Every call on a GPU shares that GPU's array and nothing in it needs clearing between calls
  * (each call writes what it reads), but two calls that overlap in time on one GPU - different
  * streams, or different threads - race on it: serialise them, or give them workspaces.
@@ -233,8 +234,8 @@ int cq_decode_attn_devlen(const cq_layout_t *layout, const void *q_f16, const cq
  *                     returns; 1 <= n_tau1 * n_tau2 <= 64
  *   softmax_scale   : 0 means 1/sqrt(d)
  *   mse_out      out: double [n_tau1][n_tau2] (device, 8-byte aligned)
- *   workspace       : device scratch of at least cq_tau_search_workspace_bytes(), 256-byte
- *                     aligned (the logits of both key sets: 4 * B * Hq * (2 n_vis + n_text) bytes
+ *   workspace       : device scratch of at least cq_tau_search_workspace_bytes() for this or a larger
+ *                     n_text, 256-byte aligned (the logits of both key sets: 4 * B * Hq * (2 n_vis + n_text) bytes
  *                     and a little more)
  * Works for every layout of the keys; the values play no part.  A calibration-time utility: its
  * kernels are plain (fp64 weights).  Errors: CQ_ERR_NULL, CQ_ERR_ALIGN, CQ_ERR_SHAPE (n_vis == 0,

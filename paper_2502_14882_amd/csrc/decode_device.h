@@ -1,5 +1,5 @@
-// Device helpers shared by the tuned decode kernels (decode_fused.hip, decode_stream.hip): vector
-// types, streaming loads, wave reductions on the DPP network, the fixed-point operand format of
+// Device helpers shared by the decode kernels on the matrix cores (decode_fused.hip, decode_stream.hip,
+// decode_tile.hip; through decode_fold.h also calib_search.hip): vector types, streaming loads, wave reductions on the DPP network, the fixed-point operand format of
 // the int8 matrix-core contractions and the masks that turn packed codes into operands.
 // Internal to libcq (not part of the ABI); everything is inline device code.
 #ifndef CQ_DECODE_DEVICE_H_
@@ -217,8 +217,6 @@ template <int BITS>
 __device__ inline int code_in_word(int y, int v) {
   return (32 / BITS - 1) - ((8 / BITS) * y + v);
 }
-
-// TILES = 16-token tiles per key group (k_group / 16); BITS = code width (1, 2, 4 or 8); VCH = values
 
 }  // namespace
 }  // namespace cq

@@ -1,5 +1,5 @@
 // Folds over the wave for floats and doubles alike, on the vector unit (DPP moves and lane swaps).
-// Internal to libcq; used by the tile decode kernels.
+// Internal to libcq; used by decode_tile.hip and calib_search.hip.
 #ifndef CQ_DECODE_FOLD_H_
 #define CQ_DECODE_FOLD_H_
 
@@ -58,8 +58,8 @@ __device__ inline int max_rows(int v) {
 // transposing butterfly leaves lane (.., b1, b0) with head 2*b0 + b1 after two steps, the remaining
 // steps add lanes that hold the same head.  Every lane of a row then holds the row's sum for head
 // bitrev2(lane & 3); what is wanted is the sum over the four rows, head kb in row kb: the four heads
-// side by side (quad broadcasts), then a transposing fold over the rows with paired lane swaps - all
-// on the vector unit, where this used to take three LDS round trips per group.
+// side by side (quad broadcasts), then a transposing fold over the rows with paired lane swaps.  (The
+// fold inside group_bias of decode_device.h, for either type.)
 template <typename T>
 __device__ inline T head_sums(const T (&part)[kHeads], int lane) {
   const bool b0 = lane & 1, b1 = lane & 2;

@@ -30,10 +30,10 @@
 // its first value tile, then the extrema), a key block's codes together, a share of the tail
 // together.  On large ones the issue of vector instructions; 16 waves share a CU and hide each other's
 // latency.  Against the shape-agnostic kernels, which dequantize element by element: 64 rows x
-// 3003 tokens, 2 bits, whole-sequence keys and values 618 -> 15.8 us; 64 rows x 3328 tokens of 64
-// channels, 1 bit, 422 -> 14.3 us.  Over key and value groups from 1 to 48 tokens, head_dim 64 to 256
-// and 1 and 8 bits they are 1.8 (value groups of one token) to 26 times as fast, so they take every
-// layout they can.
+// 3003 tokens, 2 bits, whole-sequence keys and values 618 -> 15.6 us; 64 rows x 3328 tokens of 64
+// channels, 1 bit, 422 -> 14.1 us.  Over key and value groups from 1 to 48 tokens, head_dim 64 to 256
+// and 1 and 8 bits they are 1.8 (value groups of one token) to 26 times as fast, and over 230 drawn
+// layouts and tails never slower, so they take every layout they can.
 #include <hip/hip_fp16.h>
 
 #include <cfloat>

@@ -34,7 +34,8 @@
 //
 // Bound: HBM, and the launches of a small call.  Keys and values of 64 rows x 3003 tokens, D = 128, 2
 // bits, whole-sequence statistics (111 MB): 4480 us on the shape-agnostic kernel, one thread per
-// channel walking the sequence, 62 us here, 52 us with both tensors in one launch per pass.  128 x 8
+// channel walking the sequence, 44.8 us here.  Groups of a few tokens spend a block on little
+// (quantize_tile_is_faster has the line from which these kernels are used).  128 x 8
 // rows x 16384 tokens, 1 bit, groups of 128 (9.33 GB): 1755 us = 5.3 TB/s.
 #ifndef CQ_QUANTIZE_TILE_H_
 #define CQ_QUANTIZE_TILE_H_
