@@ -26,7 +26,7 @@
  *     the host before any HIP call, so nothing is launched when one is returned.
  *     cq_last_error() gives a message for the last failure on the calling thread.
  *   - The library keeps no state between calls beyond that thread-local message (and caches
- *     of device properties); it reads no environment variable.
+ *     of device properties, and a counter of calls); it reads no environment variable.
  *   - Inputs must be finite; NaN/Inf behaviour is undefined (the paper is silent).
  *   - Query head hq attends to KV head hq / (n_q_heads / n_kv_heads).
  */
@@ -121,9 +121,9 @@ typedef struct {
 
 /* Bytes of scratch cq_decode_attn needs for this shape and calibration (a multiple of 256,
  * > 0): what the kernels that the call will select use.  A batch whose rows are each owned by one
- * workgroup (the tuned one-launch kernel) needs the minimum of 256 bytes; a row split over several
+ * workgroup (the tuned kernel) needs the minimum of 256 bytes; a row split over several
  * workgroups needs one (m, l, acc[d]) partial of the online softmax per (batch, query head,
- * chunk), plus the chunks' logit extrema with CQ_CALIB_DYNAMIC; the tile kernels (few rows, and
+ * chunk), plus the chunks' logit extrema; the tile kernels (few rows, and
  * layouts the tuned ones do not take) and the shape-agnostic kernels also keep one float per
  * (batch, query head, token).  n_text is the largest tail length the
  * workspace has to serve; `calib` may be NULL (= CQ_CALIB_NONE).  Returns 0 if the layout,
@@ -181,7 +181,7 @@ int cq_append_text_kv(const cq_layout_t *layout, void *k_text_f16, void *v_text_
  * A call whose kernels need more scratch than the array holds returns CQ_ERR_WORKSPACE and launches
  * nothing: use cq_decode_attn with a workspace for it.  One exception: split rows whose kept
  * 16-bit logits exceed the array (the long-context layouts with 1- and 2-bit codes) are not refused but
- * run on the kernels that form the logits twice, to the same accuracy but not to the same bits.
+ * run on the kernels that keep them on chip, to the same accuracy but not to the same bits.
  * Every call on a GPU shares that GPU's array and nothing in it needs clearing between calls
  * (each call writes what it reads), but two calls that overlap in time on one GPU - different
  * streams, or different threads - race on it: serialise them, or give them workspaces.

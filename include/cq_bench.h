@@ -28,8 +28,12 @@ int cq_bench_set_kernel_path(int path);
 
 /* Chunks per (batch, KV head) row of the tuned decode on this thread: 0 = the library's own
  * choice (the fewest that fit on chip), n >= 1 = at least n (clamped to what the row allows).
- * cq_decode_workspace_bytes follows the switch.  Returns the previous value, or
+ * cq_decode_workspace_bytes follows the switch.  Two flags may be added.  CQ_CHUNKS_ONE_LAUNCH: split
+ * rows stay on the kernels that keep their logits on chip.  CQ_CHUNKS_ALONE: the workgroups that share
+ * a row there do not wait for each other's extrema at all; each forms those of the whole row itself,
+ * as it otherwise does only after waiting in vain.  Returns the previous value, or
  * CQ_ERR_SHAPE (-2) for a negative one. */
+enum { CQ_CHUNKS_ALONE = 1 << 16, CQ_CHUNKS_ONE_LAUNCH = 1 << 17 };
 int cq_bench_set_decode_chunks(int n_chunks);
 
 /* Enqueue a plain streaming read of `bytes` bytes at `buf` (device, 16-byte aligned).  `sink`

@@ -1,12 +1,30 @@
 // Host side of libcq: argument validation, kernel-path selection, status strings.
 // Every check here runs before the first HIP call, so a rejected call launches nothing.
 #include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
 
 #include "cq_internal.h"
+#include "decode_meet.h"
+
+namespace cq {
+
+u64 meeting_tag() {
+  // a counter, mixed (the finalizer of splitmix64), from a start that differs between processes
+  static std::atomic<u64> calls{(u64)std::chrono::steady_clock::now().time_since_epoch().count()};
+  for (;;) {
+    u64 z = calls.fetch_add(0x9e3779b97f4a7c15ull, std::memory_order_relaxed);
+    z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;
+    z = (z ^ (z >> 27)) * 0x94d049bb133111ebull;
+    z = (z ^ (z >> 31)) & ~(u64)0xff;
+    if ((unsigned)z != 0 && (unsigned)(z >> 32) != 0) return z;
+  }
+}
+
+}  // namespace cq
 
 namespace {
 
@@ -14,6 +32,7 @@ thread_local char g_last_error[256] = "";
 // test / benchmark switches (cq_bench.h): per thread, never touched by the product calls
 thread_local int g_kernel_path = CQ_PATH_AUTO;
 thread_local int g_decode_chunks = 0;
+thread_local bool g_alone = false, g_one_launch = false;
 
 int fail(int status, const char* fmt, ...) {
   va_list ap;
@@ -230,17 +249,18 @@ size_t ws_without_tiles(const DecodeCall& c) {
 // by the argument check and by the launch.
 // scratch_limit: the most scratch the caller can offer.  Rows that have to be split run on the
 // streaming kernels, which keep the raw logits in scratch (2 bytes per query head and visual
-// token); when that does not fit the limit they run as chunks of the fused kernel, which form the
-// logits twice and keep only extrema and partials.
+// token); when that does not fit the limit they run as chunks of the fused kernel, whose logits stay on
+// chip and which keeps only extrema and partials in scratch.
 int select_kernels(const cq_layout_t* L, int n_text, int n_text_cap, size_t scratch_limit,
                    DecodeCall* call) {
   call->shape = make_shape(L, n_text, n_text_cap);
   call->plan = cq::make_fused_plan(call->shape, g_decode_chunks);
+  if (g_alone) call->plan.patience = 0;
   if (g_kernel_path == CQ_PATH_TUNED && !call->plan.ok)
     return fail(CQ_ERR_UNSUPPORTED, "no tuned decode kernel for this layout");
   call->tuned = g_kernel_path != CQ_PATH_GENERIC && call->plan.ok;
   call->streamed = false;
-  if (call->tuned && (call->plan.n_chunks > 1 || call->plan.nhb > 1)) {
+  if (call->tuned && (call->plan.n_chunks > 1 || call->plan.nhb > 1) && !g_one_launch) {
     call->stream = cq::make_stream_plan(call->shape, g_decode_chunks);
     call->streamed = call->stream.ok && call->stream.ws_bytes <= scratch_limit;
   }
@@ -423,8 +443,10 @@ int cq_bench_set_kernel_path(int path) {
 
 int cq_bench_set_decode_chunks(int n_chunks) {
   if (n_chunks < 0) return fail(CQ_ERR_SHAPE, "n_chunks=%d must be >= 0", n_chunks);
-  const int prev = g_decode_chunks;
-  g_decode_chunks = n_chunks;
+  const int prev = g_decode_chunks + (g_alone ? CQ_CHUNKS_ALONE : 0) + (g_one_launch ? CQ_CHUNKS_ONE_LAUNCH : 0);
+  g_alone = n_chunks & CQ_CHUNKS_ALONE;
+  g_one_launch = n_chunks & CQ_CHUNKS_ONE_LAUNCH;
+  g_decode_chunks = n_chunks & (CQ_CHUNKS_ALONE - 1);
   return prev;
 }
 

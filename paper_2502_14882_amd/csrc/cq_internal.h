@@ -142,16 +142,20 @@ hipError_t launch_quantize_256(const QuantizeJob* jobs, int n_jobs, size_t n_tok
 hipError_t launch_combine(int n_rows, int n_chunks, int d, const float* partial, void* out,
                           hipStream_t stream);
 
-// Tuned decode for head_dim 128 (see decode_fused.hip for the layouts it takes): one fused launch
-// when a workgroup can own a whole row, else extrema pass + partial pass + combine over chunks
-// of the row.  The plan is made once per call on the host and says what will run.
+// Rows that several workgroups of a launch share (decode_meet.h): how often a workgroup looks for the extrema of
+// the others before it forms them itself.  A look takes about a microsecond.
+constexpr int kPatience = 100;
+
+// Tuned decode for head_dim 128 (see decode_fused.hip for the layouts it takes): one launch, a workgroup
+// per row or per chunk of a row.  The plan is made once per call on the host and says what will run.
 struct FusedPlan {
   bool ok = false;            // a tuned kernel exists for the shape
   int nhb = 1;                // blocks of 4 query heads per KV head
   int n_chunks = 1;           // chunks per row
   int stride = 0;             // floats between the logit rows of two heads in LDS
   size_t lds = 0;             // dynamic LDS bytes per workgroup
-  size_t ws_minmax_floats = 0;  // split rows: [B*Hq][n_chunks][2] (offset of the partials)
+  int patience = kPatience;
+  size_t ws_count_floats = 0, ws_partial_floats = 0;   // split rows: [words | counts | partials], offsets in floats
   size_t ws_bytes = 256;      // workspace the launches touch (a multiple of 256, >= 256)
 };
 // min_chunks: 0 = the fewest chunks that fit on chip, n >= 1 = at least n (test override)

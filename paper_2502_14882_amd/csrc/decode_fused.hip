@@ -19,6 +19,15 @@
 //     eight 16-byte rows.  A token's 128 one-bit codes are exactly one such row.
 // The additive term of post-scaling (q . min_t, resp. sum_j p_j min_j) stays in fp32.
 //
+// Rows that do not fit the LDS of one workgroup are cut into chunks of tokens, a workgroup each, in the same
+// launch (SPLIT): the workgroups of a row exchange the extrema of their logits between the phases and
+// the last one merges the partials (decode_meet.h).  The logits of a row are formed once and stay on chip.
+// Before, the extrema took a launch of their own that formed all logits, a second launch formed them
+// again, and a third merged.  Recorded in a graph, 8 KV heads, before / now: 8 sequences x 65536 + 1024 tokens,
+// 4 bits, 6 query heads per KV head 207 / 154 us; 8 x 16384 + 128, 1 bit, channel-wise values 28.0 / 20.5;
+// 8 x 65536 + 128, 1 bit, key groups of 32 108 / 72; 64 x 4096 + 256, 8 bits, 6 heads 286 / 195; a launch of
+// one chunk with two head blocks, 32 x 3328 + 128, 4 bits, 6 heads 55.5 / 34.4.
+//
 // Work split inside the workgroup (12 waves): waves 0..7 stream the packed visual cache, waves
 // 8..11 stream the fp16 text tail at the same time (its two contractions on the fp16 matrix cores:
 // 16 x 16 x 32 for the logits, 4 x 4 x 4 blocks for the values), so the bandwidth-heavy text reads
@@ -36,6 +45,7 @@
 
 #include "cq_internal.h"
 #include "decode_device.h"
+#include "decode_meet.h"
 
 namespace cq {
 namespace {
@@ -55,12 +65,6 @@ constexpr int kRedPerHead = 6;
 // parameter); the other rings make no difference.
 constexpr int kRingK = 2, kRingV = 2, kRingT = 2, kRingTV = 4;
 static_assert(kRingV % 2 == 0, "value tiles alternate between two LDS buffers");
-// kModeFull: the workgroup owns the whole row and writes `out`.  A row that does not fit LDS, has
-// more than 4 query heads per KV head, or belongs to a batch too small to fill the chip is split
-// into chunks: kModeExtrema publishes the extrema of each chunk's visual logits (needed first
-// for the dynamic calibration range), kModePartial recomputes the chunk's logits in LDS and
-// writes one online-softmax partial per (head, chunk) for the combine kernel.
-enum { kModeFull = 0, kModeExtrema = 1, kModePartial = 2 };
 
 struct FusedArgs {
   const __half* q;
@@ -79,34 +83,48 @@ struct FusedArgs {
   int k_prow, k_pstride, v_prow, v_pstride;
   int unit;          // chunk boundaries are multiples of unit key groups
   int stride;        // floats between the logit rows of two heads in LDS
-  int mode, n_chunks, nhb;   // kMode*, chunks per row, blocks of 4 query heads per KV head
+  int n_chunks, nhb;         // chunks per row, blocks of 4 query heads per KV head
   int n_pieces;              // rows * n_chunks
   unsigned chunks_magic;     // fl(2^32 / n_chunks) + 1, or 0 when n_chunks == 1
   int units_base, units_rem;       // units of visual tokens per chunk: quotient and remainder
   int tblocks_base, tblocks_rem;   // 64-token text blocks per chunk, likewise
-  float* ws_minmax;  // split rows: [B*Hq][n_chunks][2] extrema of the visual logits
-  float* ws_partial; // split rows: [B*Hq][n_chunks][d + 2] partials (m, l, acc) for the combine
+  // split rows (decode_meet.h): [B*Hq][n_chunks][2] words of the exchange, [rows][nhb] counts,
+  // [B*Hq][n_chunks][d + 2] partials (m, l, acc)
+  u64* ws_words; u64* ws_count; float* ws_partial;
+  u64 tag; int patience;     // of the call; looks at the words before a workgroup goes on alone
   int calib_mode; float tau1, tau2, gamma, delta, softmax_scale;
 };
 
 
 extern __shared__ __align__(16) uint8_t smem[];
 
+// SPLIT = several workgroups per row.  TILES = 16-token tiles per key group.  VCH = values are
 // quantized channel-wise over groups of tokens (Sec. 3.1, the paper's own choice) instead of
 // token-wise.
 // KW = key statistics over the whole sequence: one parameter group per row, so the query operand,
 // its shift and the additive term are formed once per wave instead of once per 128 tokens.
-template <int TILES, int BITS, bool VCH, bool KW = false, bool NT = true, int RK = kRingK>
+template <bool SPLIT, int TILES, int BITS, bool VCH, bool KW = false, bool NT = true, int RK = kRingK>
 __global__ void __launch_bounds__(kThreads)
-fused_row_kernel(const FusedArgs a) {
+fused_row_kernel(const FusedArgs args) {
   // code words, see stream_load: a key instruction covers whole lines up to b = 4, a value
   // instruction up to b = 2 (wider value codes are read token by token in 16-byte pieces)
   constexpr bool kNtKeys = NT && BITS <= 4, kNtCodes = NT && BITS <= 2;
   static_assert(!KW || TILES == 8, "whole-sequence keys are processed 128 tokens at a time");
+  // Split rows: one pass over the workgroup's own chunk, unless the other workgroups' extrema do not turn up;
+  // then one pass over each of the other chunks for their extrema, and one more over its own.
+  u64 count_seen = 0;
+  float row_lo = FLT_MAX, row_hi = -FLT_MAX;     // lane 16h + w: extrema of head h over those chunks
+  for (int pass = 0;; ++pass) {
+  // A pass begins from nothing: arguments and lane number out of the compiler's sight, so that it keeps no
+  // address alive from pass to pass (90 scalar and 40 vector registers of them were spilled).
+  int tid = threadIdx.x;
+  auto kernarg = __builtin_amdgcn_kernarg_segment_ptr();
+  if constexpr (SPLIT) asm volatile("" : "+v"(tid), "+s"(kernarg));
+  const FusedArgs& a = SPLIT ? *(const FusedArgs*)kernarg : args;
   // the wave index as a scalar: what depends on the wave's role then branches and counts on the
   // scalar unit (1.5 % of the whole kernel)
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // workgroup = (row = b * Hkv + kvh, block of 4 query heads, chunk of the row's tokens)
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // workgroup = (row = b * Hkv + kvh, block of 4 query heads, chunk of the row's tokens: own)
   // Workgroups are handed to the 8 XCDs round-robin.  With two head blocks per KV head, the two
   // workgroups that read the same (row, chunk) get block indices 8 apart: same XCD, started
   // together, so the second one's key/value reads are served by that XCD's L2.
@@ -123,9 +141,14 @@ fused_row_kernel(const FusedArgs a) {
   // row = piece / n_chunks by multiplication with the host's fl(2^32 / n_chunks) + 1 (exact while
   // piece * n_chunks < 2^32, which the host checks)
   const int row = a.chunks_magic ? (int)__umulhi((unsigned)piece, a.chunks_magic) : piece;
-  const int chunk = piece - row * a.n_chunks;
+  const int own = piece - row * a.n_chunks;
   const int gh = min(kHeads, a.g - hb * kHeads);            // live query heads of this block
   const size_t head0 = (size_t)row * a.g + (size_t)hb * kHeads;   // Hq = Hkv * g
+  if constexpr (SPLIT) {
+    if (pass == 0 && tid == kThreads - 1) count_seen = count_open(a.ws_count + (size_t)row * a.nhb + hb, a.tag);
+  }
+  int chunk = SPLIT ? own + pass : 0;
+  if (SPLIT && chunk >= a.n_chunks) chunk -= a.n_chunks;
   // the chunk's share of the visual tokens (whole key groups and whole 64-token tiles) and of
   // the 64-token text blocks: the first `rem` chunks take one unit more than the others
   const int unit = a.unit;
@@ -137,7 +160,7 @@ fused_row_kernel(const FusedArgs a) {
   const int txt0 = ba * 64;
   // the tail length: the host's value, or the device's clamped to it (a growing tail in a replayed graph)
   const int n_text = a.n_text_dev ? min(max(*a.n_text_dev, 0), a.n_text) : a.n_text;
-  const int ntx = a.mode == kModeExtrema ? 0 : max(0, min(n_text, bb * 64) - txt0);
+  const int ntx = SPLIT && chunk != own ? 0 : max(0, min(n_text, bb * 64) - txt0);
   const bool vis_wave = wave < kVisWaves;
   const int tw = wave - kVisWaves;            // index among the text waves
   const int n16 = lane & 15, kb = lane >> 4;
@@ -179,14 +202,6 @@ fused_row_kernel(const FusedArgs a) {
   for (int h = 0; h < kHeads; ++h) qmax[h] = fmaxf(red[2 * h], red[2 * h + 1]) * a.softmax_scale;
   const float qmax_all = fmaxf(fmaxf(qmax[0], qmax[1]), fmaxf(qmax[2], qmax[3]));
   __syncthreads();   // red is reused below
-  // Split row: the chunk extrema of the first pass, which phase 2 needs for the calibration line,
-  // are asked for here and arrive during phase 1 (lane 16h + w: head h, chunk w; a lane beyond the
-  // live heads or chunks reads a neighbour's pair, which folds in harmlessly or is never used).
-  v2f chunk_mm = {FLT_MAX, -FLT_MAX};
-  if (a.mode == kModePartial && a.calib_mode == CQ_CALIB_DYNAMIC)
-    chunk_mm = *reinterpret_cast<const v2f*>(
-        a.ws_minmax + ((head0 + min(lane >> 4, gh - 1)) * a.n_chunks + min(lane & 15, a.n_chunks - 1)) * 2);
-
   // ring of the first value tiles of the narrow token-wise path (b <= 2): asked for during
   // phase 1, right after the first key groups, so that phase 2 does not start on a cold load
   constexpr bool kPrimeValues = !VCH && BITS <= 2;
@@ -410,11 +425,9 @@ fused_row_kernel(const FusedArgs a) {
         qv1[h] = qf[h * kD + wc1] * (a.softmax_scale * variant_weight<BITS>(wvar1));
       }
       if constexpr (kPrimeValues) {
-        if (a.mode != kModeExtrema) {
 #pragma unroll
-          for (int d = 0; d < kRingV; ++d) p2_load_tile(d, wave * 64 + d * (kVisWaves * 64));
-          pin_order();
-        }
+        for (int d = 0; d < kRingV; ++d) p2_load_tile(d, wave * 64 + d * (kVisWaves * 64));
+        pin_order();
       }
       if constexpr (KW) {
         build_operand(0, stage, A0w, A1w, bias_w, inv_f_w, inv_f16_w);
@@ -520,27 +533,11 @@ fused_row_kernel(const FusedArgs a) {
       for (int r = 0; r < 4; ++r) red[(wave * kHeads + r) * kRedPerHead + 2] = tmax[r];
   }
   __syncthreads();
-  if (a.mode == kModeExtrema) {
-    // first pass of a split row: only the extrema of this chunk's visual logits are wanted
-    if (tid < gh) {
-      float lo = FLT_MAX, hi = -FLT_MAX;
-      for (int w = 0; w < kVisWaves; ++w) {
-        lo = fminf(lo, red[(w * kHeads + tid) * kRedPerHead + 0]);
-        hi = fmaxf(hi, red[(w * kHeads + tid) * kRedPerHead + 1]);
-      }
-      float* mm = a.ws_minmax + ((head0 + tid) * a.n_chunks + chunk) * 2;
-      mm[0] = lo;
-      mm[1] = hi;
-    }
-    return;
-  }
-
   // ---- phase 2 set-up: calibration line and the softmax reference point, per head.
   // Every wave folds the per-wave extrema itself, spread over its lanes: lane 16h + w reads what
-  // wave w left for head h, a row reduction makes them the head's extrema.  With a split row the
-  // same lanes also fold the chunk extrema of the first pass (chunk w, w + 16, ...).
+  // wave w left for head h, a row reduction makes them the head's extrema.
   static_assert(kWaves <= 16 && kHeads == 4, "one row of 16 lanes per head");
-  float lo_l = FLT_MAX, hi_l = -FLT_MAX, tm_l = -FLT_MAX, glo_l = FLT_MAX, ghi_l = -FLT_MAX;
+  float lo_l = FLT_MAX, hi_l = -FLT_MAX, tm_l = -FLT_MAX;
   {
     const int h = lane >> 4, w = lane & 15;
     if (w < kVisWaves) {
@@ -549,21 +546,46 @@ fused_row_kernel(const FusedArgs a) {
     } else if (w < kWaves) {
       tm_l = red[(w * kHeads + h) * kRedPerHead + 2];
     }
-    if (a.mode == kModePartial && a.calib_mode == CQ_CALIB_DYNAMIC && h < gh) {
-      glo_l = chunk_mm[0];                  // chunk min(w, n_chunks - 1), asked for before phase 1
-      ghi_l = chunk_mm[1];
-      const float* mm = a.ws_minmax + (head0 + h) * a.n_chunks * 2;
-      for (int cidx = w + 16; cidx < a.n_chunks; cidx += 16) {
-        glo_l = fminf(glo_l, mm[2 * cidx]);
-        ghi_l = fmaxf(ghi_l, mm[2 * cidx + 1]);
-      }
-    }
     lo_l = row_min(lo_l);
     hi_l = row_max(hi_l);
     tm_l = row_max(tm_l);
-    if (a.mode == kModePartial) {
-      glo_l = row_min(glo_l);
-      ghi_l = row_max(ghi_l);
+  }
+  // ---- split row: gamma, delta are the extrema of all its chunks (Sec. 3.2)
+  if constexpr (SPLIT) {
+    if (a.calib_mode == CQ_CALIB_DYNAMIC && a.n_chunks > 1 && pass < a.n_chunks) {
+      row_lo = fminf(row_lo, lo_l);
+      row_hi = fmaxf(row_hi, hi_l);
+      if (pass > 0) { __syncthreads(); continue; }             // (red is written again)
+      float* found = red + kVisWaves * kHeads * kRedPerHead;   // slots of the first text wave
+      if (wave == 0) {
+        u64* words = a.ws_words + (head0 + min(kb, gh - 1)) * (size_t)a.n_chunks * 2;
+        if (n16 == 0 && kb < gh) post_extrema(words + 2 * own, lo_l, hi_l, a.tag);
+        bool all = false;
+        float lo = FLT_MAX, hi = -FLT_MAX;
+        for (int look = 0; !all && look < a.patience; ++look) {
+          lo = FLT_MAX;
+          hi = -FLT_MAX;
+          all = true;
+          for (int c = n16; c < a.n_chunks; c += 16) {
+            float x = lo_l, y = hi_l;
+            if (c != own) all = read_extrema(words + 2 * c, &x, &y, a.tag) && all;
+            lo = fminf(lo, x);
+            hi = fmaxf(hi, y);
+          }
+          all = __builtin_amdgcn_ballot_w64(!all) == 0;
+        }
+        lo = row_min(lo);
+        hi = row_max(hi);
+        if (n16 == 0) {
+          found[kb * kRedPerHead + 0] = lo;
+          found[kb * kRedPerHead + 1] = hi;
+        }
+        if (lane == 0) found[3] = all ? 1.f : 0.f;
+      }
+      __syncthreads();
+      if (found[3] == 0.f) { __syncthreads(); continue; }
+      row_lo = found[kb * kRedPerHead + 0];
+      row_hi = found[kb * kRedPerHead + 1];
     }
   }
   float a2[kHeads], c2v[kHeads], c2t[kHeads], mref[kHeads];
@@ -577,9 +599,9 @@ fused_row_kernel(const FusedArgs a) {
       if (a.calib_mode == CQ_CALIB_DYNAMIC) {
         glo = lo;
         ghi = hi;
-        if (a.mode == kModePartial && h < gh) {   // extrema of the whole row, from the first pass
-          glo = fminf(glo, lane_value(glo_l, 16 * h));
-          ghi = fmaxf(ghi, lane_value(ghi_l, 16 * h));
+        if (SPLIT && a.n_chunks > 1) {            // of the whole row
+          glo = lane_value(row_lo, 16 * h);
+          ghi = lane_value(row_hi, 16 * h);
         }
       }
       const float width = ghi - glo;
@@ -1159,14 +1181,29 @@ fused_row_kernel(const FusedArgs a) {
 #pragma unroll
       for (int w = 0; w < kWaves; ++w)
         num += reinterpret_cast<float*>(smem)[((size_t)w * kHeads + h) * kD + c];
-      if (a.mode == kModeFull) {
+      if (!SPLIT || a.n_chunks == 1) {
         a.out[(head0 + h) * kD + c] = __float2half_rn((num + m) / l);
       } else {          // one (m, l, acc[d]) partial of the joint softmax per (head, chunk)
-        float* part = a.ws_partial + ((head0 + h) * a.n_chunks + chunk) * (size_t)(kD + 2);
-        if (c == 0) { part[0] = red[h * kRedPerHead + 5]; part[1] = l; }
-        part[2 + c] = num + m;
+        float* part = a.ws_partial + ((head0 + h) * a.n_chunks + own) * (size_t)(kD + 2);
+        if (c == 0) store_device(part, red[h * kRedPerHead + 5], l);
+        store_device(part + 2 + c, num + m);
       }
     }
+  }
+  if constexpr (SPLIT) {
+    if (a.n_chunks == 1) return;
+    u64* count = a.ws_count + (size_t)row * a.nhb + hb;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // this wave's partials have reached memory
+    __syncthreads();
+    float* last = red + kVisWaves * kHeads * kRedPerHead;
+    if (tid == kThreads - 1) last[0] = count_in(count, a.tag, count_seen) == a.n_chunks - 1 ? 1.f : 0.f;
+    __syncthreads();
+    if (last[0] == 0.f) return;
+    merge_partials<kD, kThreads>(a.ws_partial + head0 * a.n_chunks * (kD + 2), a.n_chunks, gh, a.out + head0 * kD);
+    for (int i = tid; i < gh * a.n_chunks * 2; i += kThreads) a.ws_words[head0 * a.n_chunks * 2 + i] = 0;
+    if (tid == 0) *count = 0;
+  }
+  return;
   }
 }
 
@@ -1266,9 +1303,9 @@ FusedPlan make_fused_plan(const DecodeShape& shape, int min_chunks) {
   const int unit = chunk_unit(s);
   const int n_units = s.n_vis / (s.k_group * unit);
   const int max_chunks = n_units < 64 ? (n_units > 0 ? n_units : 1) : 64;
-  // Fewest chunks that fit LDS.  Splitting a row that fits only to fill idle CUs does not pay:
-  // every chunk repeats the fixed per-workgroup work and the logits are computed twice
-  // (measured on the 128-row configuration: 24 us whole rows, 35 us in 2 chunks, 57 us in 4).
+  // Fewest chunks that fit LDS.  Splitting a row that fits only to fill idle CUs does not pay: what the
+  // exchange and the merge take (3 us) is what two chunks save (128 rows of 3328 tokens, whole / in 2 chunks:
+  // 12.6 / 14.5 us with 1 bit, 19.4 / 20.0 with 4).
   int want = min_chunks >= 1 ? min_chunks : 1;                 // > 1: a test's or a tuner's override
   if (want > max_chunks) want = max_chunks;
   const bool forced = want > 1;
@@ -1309,16 +1346,74 @@ FusedPlan make_fused_plan(const DecodeShape& shape, int min_chunks) {
   }
   if (p.n_chunks > 1 || p.nhb > 1) {
     if (s.n_vis == 0) return p;
+    // two words per (head, chunk), a count per (row, head block), one (m, l, acc[d]) partial per (head, chunk)
     const size_t heads = (size_t)s.B * s.Hq;
-    // chunk extrema of the visual logits (read only with dynamic calibration; 12 KB on the
-    // long-context configuration), then one (m, l, acc[d]) partial per (head, chunk)
-    p.ws_minmax_floats = (heads * p.n_chunks * 2 + 63) / 64 * 64;
-    const size_t floats = p.ws_minmax_floats + heads * p.n_chunks * (size_t)(kD + 2);
+    p.ws_count_floats = (heads * p.n_chunks * 4 + 63) / 64 * 64;
+    p.ws_partial_floats = (p.ws_count_floats + (size_t)rows * 2 + 63) / 64 * 64;
+    const size_t floats = p.ws_partial_floats + heads * p.n_chunks * (size_t)(kD + 2);
     p.ws_bytes = (floats * sizeof(float) + 255) / 256 * 256;
   }
   p.ok = true;
   return p;
 }
+
+namespace {
+
+using FusedKernel = void (*)(const FusedArgs);
+struct FusedChoice { FusedKernel kern; int slot; };
+
+// SPLIT: rows that several workgroups share.  slot: the kernel's place in the table of LDS limits.
+template <bool SPLIT>
+FusedChoice pick_kernel(const DecodeShape& s, const FusedPlan& plan, bool k_whole) {
+  const bool vch = s.v_axis == CQ_AXIS_CHANNEL;
+  if (k_whole) {
+    switch (s.bits * 2 + (vch ? 1 : 0)) {
+      case 1 * 2: return {fused_row_kernel<SPLIT, 8, 1, false, true>, 18};
+      case 2 * 2: return {fused_row_kernel<SPLIT, 8, 2, false, true>, 19};
+      case 4 * 2: return {fused_row_kernel<SPLIT, 8, 4, false, true>, 20};
+      case 8 * 2: return {fused_row_kernel<SPLIT, 8, 8, false, true>, 21};
+      case 1 * 2 + 1: return {fused_row_kernel<SPLIT, 8, 1, true, true>, 22};
+      case 2 * 2 + 1: return {fused_row_kernel<SPLIT, 8, 2, true, true>, 23};
+      default: return {nullptr, 0};
+    }
+  }
+  // two head blocks per KV head: the twin workgroups share their lines through L2 (ordinary loads)
+  if (plan.nhb > 1 && !vch && s.k_group == 128 && s.bits == 1) return {fused_row_kernel<SPLIT, 8, 1, false, false, false>, 24};
+  if (plan.nhb > 1 && !vch && s.k_group == 128 && s.bits == 2) return {fused_row_kernel<SPLIT, 8, 2, false, false, false>, 25};
+  // long whole rows: three key groups in flight per wave
+  if constexpr (!SPLIT) {
+    if (plan.nhb == 1 && !vch && s.n_vis >= 48 * 128) switch (s.k_group * 4 + s.bits) {
+      case 128 * 4 + 1: return {fused_row_kernel<SPLIT, 8, 1, false, false, true, 3>, 26};
+      case 128 * 4 + 2: return {fused_row_kernel<SPLIT, 8, 2, false, false, true, 3>, 27};
+      case 32 * 4 + 1: return {fused_row_kernel<SPLIT, 2, 1, false, false, true, 3>, 28};
+      case 32 * 4 + 2: return {fused_row_kernel<SPLIT, 2, 2, false, false, true, 3>, 29};
+      default: break;
+    }
+  }
+  switch ((s.k_group * 4 + s.bits) * 2 + (vch ? 1 : 0)) {
+    case (32 * 4 + 1) * 2: return {fused_row_kernel<SPLIT, 2, 1, false>, 0};
+    case (64 * 4 + 1) * 2: return {fused_row_kernel<SPLIT, 4, 1, false>, 1};
+    case (128 * 4 + 1) * 2: return {fused_row_kernel<SPLIT, 8, 1, false>, 2};
+    case (32 * 4 + 2) * 2: return {fused_row_kernel<SPLIT, 2, 2, false>, 3};
+    case (64 * 4 + 2) * 2: return {fused_row_kernel<SPLIT, 4, 2, false>, 4};
+    case (128 * 4 + 2) * 2: return {fused_row_kernel<SPLIT, 8, 2, false>, 5};
+    case (32 * 4 + 1) * 2 + 1: return {fused_row_kernel<SPLIT, 2, 1, true>, 6};
+    case (64 * 4 + 1) * 2 + 1: return {fused_row_kernel<SPLIT, 4, 1, true>, 7};
+    case (128 * 4 + 1) * 2 + 1: return {fused_row_kernel<SPLIT, 8, 1, true>, 8};
+    case (32 * 4 + 2) * 2 + 1: return {fused_row_kernel<SPLIT, 2, 2, true>, 9};
+    case (64 * 4 + 2) * 2 + 1: return {fused_row_kernel<SPLIT, 4, 2, true>, 10};
+    case (128 * 4 + 2) * 2 + 1: return {fused_row_kernel<SPLIT, 8, 2, true>, 11};
+    case (32 * 4 + 4) * 2: return {fused_row_kernel<SPLIT, 2, 4, false>, 12};
+    case (64 * 4 + 4) * 2: return {fused_row_kernel<SPLIT, 4, 4, false>, 13};
+    case (128 * 4 + 4) * 2: return {fused_row_kernel<SPLIT, 8, 4, false>, 14};
+    case (32 * 4 + 8) * 2: return {fused_row_kernel<SPLIT, 2, 8, false>, 15};
+    case (64 * 4 + 8) * 2: return {fused_row_kernel<SPLIT, 4, 8, false>, 16};
+    case (128 * 4 + 8) * 2: return {fused_row_kernel<SPLIT, 8, 8, false>, 17};
+    default: return {nullptr, 0};
+  }
+}
+
+}  // namespace
 
 hipError_t launch_decode_fused(const DecodeShape& shape, const FusedPlan& plan, const void* q,
                                const cq_qtensor_t& k, const cq_qtensor_t& v, const void* k_text,
@@ -1350,61 +1445,18 @@ hipError_t launch_decode_fused(const DecodeShape& shape, const FusedPlan& plan, 
   a.stride = plan.stride;
   a.n_chunks = plan.n_chunks;
   a.nhb = plan.nhb;
-  a.ws_minmax = workspace;
-  a.ws_partial = workspace ? workspace + plan.ws_minmax_floats : nullptr;
-  void (*kern)(const FusedArgs) = nullptr;
-  int slot = 0;
-  const bool vch = s.v_axis == CQ_AXIS_CHANNEL;
-  if (k_whole) {
-    switch (s.bits * 2 + (vch ? 1 : 0)) {
-      case 1 * 2: kern = fused_row_kernel<8, 1, false, true>; slot = 18; break;
-      case 2 * 2: kern = fused_row_kernel<8, 2, false, true>; slot = 19; break;
-      case 4 * 2: kern = fused_row_kernel<8, 4, false, true>; slot = 20; break;
-      case 8 * 2: kern = fused_row_kernel<8, 8, false, true>; slot = 21; break;
-      case 1 * 2 + 1: kern = fused_row_kernel<8, 1, true, true>; slot = 22; break;
-      case 2 * 2 + 1: kern = fused_row_kernel<8, 2, true, true>; slot = 23; break;
-      default: return hipErrorInvalidValue;
-    }
-  } else switch ((s.k_group * 4 + s.bits) * 2 + (vch ? 1 : 0)) {
-    case (32 * 4 + 1) * 2: kern = fused_row_kernel<2, 1, false>; slot = 0; break;
-    case (64 * 4 + 1) * 2: kern = fused_row_kernel<4, 1, false>; slot = 1; break;
-    case (128 * 4 + 1) * 2: kern = fused_row_kernel<8, 1, false>; slot = 2; break;
-    case (32 * 4 + 2) * 2: kern = fused_row_kernel<2, 2, false>; slot = 3; break;
-    case (64 * 4 + 2) * 2: kern = fused_row_kernel<4, 2, false>; slot = 4; break;
-    case (128 * 4 + 2) * 2: kern = fused_row_kernel<8, 2, false>; slot = 5; break;
-    case (32 * 4 + 1) * 2 + 1: kern = fused_row_kernel<2, 1, true>; slot = 6; break;
-    case (64 * 4 + 1) * 2 + 1: kern = fused_row_kernel<4, 1, true>; slot = 7; break;
-    case (128 * 4 + 1) * 2 + 1: kern = fused_row_kernel<8, 1, true>; slot = 8; break;
-    case (32 * 4 + 2) * 2 + 1: kern = fused_row_kernel<2, 2, true>; slot = 9; break;
-    case (64 * 4 + 2) * 2 + 1: kern = fused_row_kernel<4, 2, true>; slot = 10; break;
-    case (128 * 4 + 2) * 2 + 1: kern = fused_row_kernel<8, 2, true>; slot = 11; break;
-    case (32 * 4 + 4) * 2: kern = fused_row_kernel<2, 4, false>; slot = 12; break;
-    case (64 * 4 + 4) * 2: kern = fused_row_kernel<4, 4, false>; slot = 13; break;
-    case (128 * 4 + 4) * 2: kern = fused_row_kernel<8, 4, false>; slot = 14; break;
-    case (32 * 4 + 8) * 2: kern = fused_row_kernel<2, 8, false>; slot = 15; break;
-    case (64 * 4 + 8) * 2: kern = fused_row_kernel<4, 8, false>; slot = 16; break;
-    case (128 * 4 + 8) * 2: kern = fused_row_kernel<8, 8, false>; slot = 17; break;
-    default: return hipErrorInvalidValue;
-  }
-  // long whole rows: three key groups in flight per wave
-  if (plan.n_chunks == 1 && plan.nhb == 1 && !k_whole && !vch && s.k_group == 128 && s.bits <= 2 &&
-      s.n_vis >= 48 * 128) {
-    if (s.bits == 1) { kern = fused_row_kernel<8, 1, false, false, true, 3>; slot = 26; }
-    else { kern = fused_row_kernel<8, 2, false, false, true, 3>; slot = 27; }
-  }
-  if (plan.n_chunks == 1 && plan.nhb == 1 && !k_whole && !vch && s.k_group == 32 && s.bits <= 2 &&
-      s.n_vis >= 48 * 128) {
-    if (s.bits == 1) { kern = fused_row_kernel<2, 1, false, false, true, 3>; slot = 28; }
-    else { kern = fused_row_kernel<2, 2, false, false, true, 3>; slot = 29; }
-  }
-  // two head blocks per KV head: the twin workgroups share their lines through L2 (ordinary loads)
-  if (plan.nhb > 1 && !k_whole && !vch && s.k_group == 128 && s.bits <= 2) {
-    if (s.bits == 1) { kern = fused_row_kernel<8, 1, false, false, false>; slot = 24; }
-    else { kern = fused_row_kernel<8, 2, false, false, false>; slot = 25; }
-  }
+  a.ws_words = reinterpret_cast<u64*>(workspace);
+  a.ws_count = reinterpret_cast<u64*>(workspace ? workspace + plan.ws_count_floats : nullptr);
+  a.ws_partial = workspace ? workspace + plan.ws_partial_floats : nullptr;
+  a.tag = 0;
+  a.patience = plan.patience;
+  const FusedChoice choice = plan.n_chunks == 1 ? pick_kernel<false>(s, plan, k_whole) : pick_kernel<true>(s, plan, k_whole);
+  const FusedKernel kern = choice.kern;
+  if (!kern) return hipErrorInvalidValue;
+  const int slot = choice.slot + (plan.n_chunks == 1 ? 0 : 30);
   // the kernel's dynamic LDS limit is raised once per (device, kernel) and only ever grows;
   // concurrent callers may both raise it, which is harmless
-  static std::atomic<size_t> configured[kMaxDevices][30];
+  static std::atomic<size_t> configured[kMaxDevices][60];
   int dev = 0;
   hipError_t de = hipGetDevice(&dev);
   if (de != hipSuccess) return de;
@@ -1432,22 +1484,9 @@ hipError_t launch_decode_fused(const DecodeShape& shape, const FusedPlan& plan, 
     a.tblocks_rem = n_tblocks % plan.n_chunks;
   }
   const dim3 grid((unsigned)blocks), block(kThreads);
-  if (plan.n_chunks == 1 && plan.nhb == 1) {
-    a.mode = kModeFull;
-    kern<<<grid, block, plan.lds, stream>>>(a);
-    return hipGetLastError();
-  }
-  if (calib.mode == CQ_CALIB_DYNAMIC) {
-    a.mode = kModeExtrema;
-    kern<<<grid, block, plan.lds, stream>>>(a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  a.mode = kModePartial;
+  if (plan.n_chunks > 1) a.tag = meeting_tag();
   kern<<<grid, block, plan.lds, stream>>>(a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_combine(s.B * s.Hq, plan.n_chunks, kD, a.ws_partial, out, stream);
+  return hipGetLastError();
 }
 
 }  // namespace cq

@@ -1,0 +1,105 @@
+"""Rows that several workgroups of one launch share: the exchange of the logits' extrema, the merge by the
+last workgroup, and what a workgroup does when the others' extrema do not turn up."""
+import numpy as np
+import pytest
+import torch
+
+import helpers as H
+from oracle import cq_oracle as O
+from paper_2502_14882_amd import binding as cq
+from paper_2502_14882_amd import synth
+
+pytestmark = pytest.mark.gpu
+ONE_LAUNCH, ALONE = 1 << 17, 1 << 16
+
+
+def build(B, n_q, n_kv, n, n_text, bits, k_group, v_axis, v_group, seed=5):
+    w = synth.WORKLOADS[1].replace(batch=B, n_q_heads=n_q, n_kv_heads=n_kv, n_vis=n, n_text=max(n_text, 1), seed=seed)
+    x = synth.make_inputs(w, "cpu")
+    lay = cq.make_layout(B, n_q, n_kv, 128, n, bits, 0, v_axis, k_group, v_group)
+    dev = {k: t.cuda() for k, t in x.items()}
+    k, v = cq.cq_quantize_kv(lay, dev["k"], dev["v"])
+    kq = O.quantize_tensor(x["k"].numpy(), bits, 0, k_group)
+    vq = O.quantize_tensor(x["v"].numpy(), bits, v_axis, v_group)
+    return lay, x, dev, k, v, kq, vq
+
+
+def run(lay, dev, k, v, n_text, calib, chunks, ws=None, out=None):
+    path, prev = cq.cq_bench_set_kernel_path(cq.CQ_PATH_TUNED), cq.cq_bench_set_decode_chunks(chunks)
+    try:
+        if ws is None:
+            ws = torch.empty(cq.cq_decode_workspace_bytes(lay, n_text, calib), dtype=torch.uint8, device="cuda")
+            ws.fill_(255)
+        return cq.cq_decode_attn(lay, dev["q"], k, v, dev["k_text"], dev["v_text"], n_text, calib, 0.0, out, ws)
+    finally:
+        cq.cq_bench_set_decode_chunks(prev)
+        cq.cq_bench_set_kernel_path(path)
+
+
+# (B, Hq, Hkv, n_vis, n_text, bits, key group, value axis, value group, chunks): the fewest and the most chunks,
+# chunks without a share of the tail, one and two head sets, sets that are not full, every width
+SPLIT = [(1, 4, 1, 128, 1, 1, 64, 1, 128, 2), (2, 8, 2, 1920, 200, 1, 128, 1, 128, 5), (1, 1, 1, 4096, 0, 1, 64, 1, 128, 64),
+         (1, 3, 1, 8192, 65, 2, 128, 1, 128, 17), (2, 12, 2, 2560, 130, 4, 128, 1, 128, 3), (1, 8, 1, 1024, 1000, 8, 32, 1, 128, 16),
+         (1, 7, 1, 2048, 77, 1, 2048, 0, 2048, 7), (1, 4, 2, 1152, 33, 2, 128, 0, 64, 9), (3, 5, 1, 640, 64, 2, 64, 0, 128, 5)]
+
+
+@pytest.mark.parametrize("shape", SPLIT)
+@pytest.mark.parametrize("calib", [(cq.CQ_CALIB_DYNAMIC, 1.0, 2.0), (cq.CQ_CALIB_NONE, 0.0, 0.0)])
+def test_one_launch_split_rows_match_the_oracle(shape, calib):
+    *args, chunks = shape
+    lay, x, dev, k, v, kq, vq = build(*args)
+    n_text, c = args[4], cq.make_calib(*calib)
+    got = run(lay, dev, k, v, n_text, c, ONE_LAUNCH + chunks)
+    alone = run(lay, dev, k, v, n_text, c, ONE_LAUNCH + ALONE + chunks)
+    torch.cuda.synchronize()
+    ref = O.decode_attn(x["q"].numpy(), kq, vq, x["k_text"].numpy(), x["v_text"].numpy(), n_text, *calib)
+    err = O.rel_l2(got.cpu().numpy().astype(np.float64), ref)
+    assert err <= H.REGRESSION_TOL, err
+    # extrema formed by the workgroup itself are those the others would have sent
+    assert torch.equal(got, alone)
+
+
+def test_any_workspace_contents_and_replays():
+    """The words of the exchange are recognised whatever the workspace holds, and a recorded launch, whose tag
+    stays the same, finds nothing of its last replay."""
+    lay, x, dev, k, v, _, _ = build(2, 12, 2, 2560, 130, 4, 128, 1, 128)
+    c = cq.make_calib(cq.CQ_CALIB_DYNAMIC, 1.0, 2.0)
+    want = run(lay, dev, k, v, 130, c, ONE_LAUNCH + 10)
+    prev = cq.cq_bench_set_decode_chunks(ONE_LAUNCH + 10)
+    size = cq.cq_decode_workspace_bytes(lay, 130, c)
+    cq.cq_bench_set_decode_chunks(prev)
+    ws = torch.randint(0, 256, (size,), dtype=torch.uint8, device="cuda")
+    out = torch.empty_like(want)
+    for fill in (None, 0, 255, 0x3c):
+        if fill is not None:
+            ws.fill_(fill)
+        assert torch.equal(run(lay, dev, k, v, 130, c, ONE_LAUNCH + 10, ws), want)
+    q0 = dev["q"].clone()
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        run(lay, dev, k, v, 130, c, ONE_LAUNCH + 10, ws, out)
+    for i in range(6):
+        dev["q"].copy_(q0 * (1 + i))                    # other extrema in every replay
+        if i % 3 == 2:
+            ws.random_(0, 256)
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, run(lay, dev, k, v, 130, c, ONE_LAUNCH + 10)), i
+
+
+def test_overlapping_calls_with_workspaces_of_their_own():
+    """Two streams whose workgroups compete for the compute units."""
+    c = cq.make_calib(cq.CQ_CALIB_DYNAMIC, 1.0, 2.0)
+    lay, x, dev, k, v, _, _ = build(8, 32, 8, 1024, 64, 4, 64, 1, 128)
+    want = run(lay, dev, k, v, 64, c, ONE_LAUNCH + 8)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    outs = [[] for _ in streams]
+    for _ in range(5):
+        for s, o in zip(streams, outs):
+            with torch.cuda.stream(s):
+                o.append(run(lay, dev, k, v, 64, c, ONE_LAUNCH + 8))
+    torch.cuda.synchronize()
+    assert all(torch.equal(t, want) for o in outs for t in o)
