@@ -121,6 +121,9 @@ fused_row_kernel(const FusedArgs args) {
   auto kernarg = __builtin_amdgcn_kernarg_segment_ptr();
   if constexpr (SPLIT) asm volatile("" : "+v"(tid), "+s"(kernarg));
   const FusedArgs& a = SPLIT ? *(const FusedArgs*)kernarg : args;
+  // The arguments fill five cache lines: one word of each now, together, instead of a wait for each of
+  // them where it is first used.
+  asm volatile("" :: "s"(a.q), "s"(a.out), "s"(a.k_group), "s"(a.n_chunks), "s"(a.calib_mode));
   // the wave index as a scalar: what depends on the wave's role then branches and counts on the
   // scalar unit (1.5 % of the whole kernel)
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -158,10 +161,13 @@ fused_row_kernel(const FusedArgs args) {
   const int ba = chunk_first(a.tblocks_base, a.tblocks_rem, chunk);
   const int bb = chunk_first(a.tblocks_base, a.tblocks_rem, chunk + 1);
   const int txt0 = ba * 64;
-  // the tail length: the host's value, or the device's clamped to it (a growing tail in a replayed graph)
-  const int n_text = a.n_text_dev ? min(max(*a.n_text_dev, 0), a.n_text) : a.n_text;
-  const int ntx = SPLIT && chunk != own ? 0 : max(0, min(n_text, bb * 64) - txt0);
   const bool vis_wave = wave < kVisWaves;
+  // text waves: the tail length is the host's value, or the device's clamped to it (a growing tail in a replayed graph)
+  int ntx = 0;
+  if (!vis_wave && !(SPLIT && chunk != own)) {
+    const int n_text = a.n_text_dev ? min(max(*a.n_text_dev, 0), a.n_text) : a.n_text;
+    ntx = max(0, min(n_text, bb * 64) - txt0);
+  }
   const int tw = wave - kVisWaves;            // index among the text waves
   const int n16 = lane & 15, kb = lane >> 4;
 
@@ -170,38 +176,21 @@ fused_row_kernel(const FusedArgs args) {
   uint8_t* lbytes = smem;
   size_t off = (size_t)kHeads * a.stride * sizeof(float);
   if (off < (size_t)kWaves * kHeads * kD * sizeof(float)) off = (size_t)kWaves * kHeads * kD * sizeof(float);
-  float* qf = reinterpret_cast<float*>(smem + off);   off += kHeads * kD * sizeof(float);
   off = (off + 15) & ~(size_t)15;
   uint8_t* stage = smem + off + (size_t)(vis_wave ? wave : 0) * kStageBytes;
   off += (size_t)kVisWaves * kStageBytes;
   float* red = reinterpret_cast<float*>(smem + off);   // [kWaves][kHeads][kRedPerHead]
 
-  // rows of unused heads (g < 4) are computed along but never output; keep them finite.  Their
-  // visual slots are written in phase 1 like everyone's (their query is zero, so are their
-  // logits); only the text slots and the padding behind them are never written by anyone.
-  for (int h = gh; h < kHeads; ++h)
-    for (int i = nv + tid; i < a.stride; i += kThreads) logits[h * a.stride + i] = 0.f;
-
-  // ---- phase 0: query to LDS and max |q| per head.  The fixed-point shifts and the additive
-  // post-scaling term q . min_t are formed on the fly in phases 1 and 2 from the scales and minima
-  // that the streaming loads bring in anyway, so every parameter is read exactly once.
+  // Nothing is staged ahead of phase 1: every wave asks for its own piece of the query (2 KB that all share)
+  // together with its first keys.  The fixed-point shifts and the additive post-scaling term q . min_t are
+  // formed on the fly from the scales and minima that the streaming loads bring in anyway, so every
+  // parameter is read exactly once.  What this and the text waves' early loads save is latency: 1 row x 1024 tokens
+  // 7.9 -> 6.4 us, 128 rows x 3328 12.9 -> 11.9 (1 bit) and 19.6 -> 18.1 (4 bits).  (The rows of unused heads (g < 4) are computed along on a zero query and
+  // never output; their text slots are never read.)
   const float* ks_row = a.k_scale + (size_t)row * a.k_prow + (size_t)ga * a.k_pstride;
   const uint16_t* km_row = a.k_min + (size_t)row * a.k_prow + (size_t)ga * a.k_pstride;
   const float* vs_row = a.v_scale + (size_t)row * a.n_vis + vis0;
   const uint16_t* vm_row = a.v_min + (size_t)row * a.n_vis + vis0;
-  if (tid < kHeads * kD) {
-    const int h = tid / kD, c = tid % kD;
-    const float qv = h < gh ? __half2float(a.q[(head0 + h) * kD + c]) : 0.f;
-    qf[tid] = qv;
-    const float m = wave_max_nonneg(fabsf(qv));     // waves 2h, 2h+1 hold head h
-    if (lane == 0) red[wave] = m;
-  }
-  __syncthreads();
-  float qmax[kHeads];
-#pragma unroll
-  for (int h = 0; h < kHeads; ++h) qmax[h] = fmaxf(red[2 * h], red[2 * h + 1]) * a.softmax_scale;
-  const float qmax_all = fmaxf(fmaxf(qmax[0], qmax[1]), fmaxf(qmax[2], qmax[3]));
-  __syncthreads();   // red is reused below
   // ring of the first value tiles of the narrow token-wise path (b <= 2): asked for during
   // phase 1, right after the first key groups, so that phase 2 does not start on a cold load
   constexpr bool kPrimeValues = !VCH && BITS <= 2;
@@ -218,6 +207,16 @@ fused_row_kernel(const FusedArgs args) {
     p2_vsr[slot] = stream_load<NT>(vs_row + j);
     p2_vmr[slot] = stream_load<NT>(vm_row + j);
   };
+
+  // ring of the first text values, asked for behind the first text keys: a tail's waves have little to do, and
+  // what they do is a chain of waits.  The tail goes out in shares of 64 tokens, a short one in shares of 16
+  // that still occupy all text waves (rounds over the waves; a share of 16 costs ~1.1 quarters of one of 64).
+  v8h tv_ring[kRingTV];
+  const bool small_shares = 11 * (((ntx + 15) / 16 + kTextWaves - 1) / kTextWaves) <
+                            40 * (((ntx + 63) / 64 + kTextWaves - 1) / kTextWaves);
+  const __amdgpu_buffer_rsrc_t vt_buf =
+      stream_buffer(a.v_text + ((size_t)row * a.n_text_cap + txt0) * kD, (unsigned)ntx * kD * 2);
+  const int vt_lane = (kb * kD + 8 * n16) * 2;
 
   // =================================================================== phase 1: logits
   if (vis_wave) {
@@ -249,7 +248,7 @@ fused_row_kernel(const FusedArgs args) {
       };
       int wvar0, wvar1;
       const int wr0 = row_of(wc0, wvar0), wr1 = row_of(wc1, wvar1);
-      float qv0[kHeads], qv1[kHeads];               // set below, behind the first loads
+      float qv0[kHeads], qv1[kHeads], qmax_all;     // set below, behind the first loads
       const float inv_w0 = 1.f / variant_weight<BITS>(wvar0);   // exact: powers of two
       const float inv_w1 = 1.f / variant_weight<BITS>(wvar1);
       const uint32_t* kc_lane =
@@ -410,6 +409,11 @@ fused_row_kernel(const FusedArgs args) {
           finish_tile(tile + 1, cb);
         }
       };
+      // the lane's slice of the query, then the first keys
+      uint32_t q01[kHeads];
+#pragma unroll
+      for (int h = 0; h < kHeads; ++h)
+        q01[h] = *reinterpret_cast<const uint32_t*>(a.q + (head0 + min(h, gh - 1)) * kD + wc0);
       if constexpr (KW) {                           // the row's parameters first, then the codes
         s01[0] = *reinterpret_cast<const v2f*>(ks_row + wc0);
         m01[0] = *reinterpret_cast<const uint32_t*>(km_row + wc0);
@@ -418,16 +422,23 @@ fused_row_kernel(const FusedArgs args) {
 #pragma unroll
       for (int d = 0; d < kRK; ++d) load_group(d, wave + d * kVisWaves);
       pin_order();
-      // the lane's slice of the staged query, read while the first key groups are on their way
-#pragma unroll
-      for (int h = 0; h < kHeads; ++h) {
-        qv0[h] = qf[h * kD + wc0] * (a.softmax_scale * variant_weight<BITS>(wvar0));
-        qv1[h] = qf[h * kD + wc1] * (a.softmax_scale * variant_weight<BITS>(wvar1));
-      }
       if constexpr (kPrimeValues) {
 #pragma unroll
         for (int d = 0; d < kRingV; ++d) p2_load_tile(d, wave * 64 + d * (kVisWaves * 64));
         pin_order();
+      }
+      {
+        float most = 0.f;                           // the lanes of a wave hold every element of the query
+#pragma unroll
+        for (int h = 0; h < kHeads; ++h) {
+          asm volatile("" : "+v"(q01[h]));          // (not looked at before the loads above are out)
+          const float x0 = h < gh ? __half2float(__ushort_as_half((uint16_t)(q01[h] & 0xffffu))) : 0.f;
+          const float x1 = h < gh ? __half2float(__ushort_as_half((uint16_t)(q01[h] >> 16))) : 0.f;
+          most = fmaxf(most, fmaxf(fabsf(x0), fabsf(x1)));
+          qv0[h] = x0 * (a.softmax_scale * variant_weight<BITS>(wvar0));
+          qv1[h] = x1 * (a.softmax_scale * variant_weight<BITS>(wvar1));
+        }
+        qmax_all = wave_max_nonneg(most) * a.softmax_scale;
       }
       if constexpr (KW) {
         build_operand(0, stage, A0w, A1w, bias_w, inv_f_w, inv_f16_w);
@@ -462,9 +473,8 @@ fused_row_kernel(const FusedArgs args) {
       v8h At[4];
 #pragma unroll
       for (int s = 0; s < 4; ++s)
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-          At[s][i] = n16 < gh ? (_Float16)qf[n16 * kD + 32 * s + 8 * kb + i] : (_Float16)0;
+        // (matrix rows from gh on repeat the last head and are dropped)
+        At[s] = *reinterpret_cast<const v8h*>(a.q + (head0 + min(n16, gh - 1)) * kD + 32 * s + 8 * kb);
       // Loads that touch whole cache lines: a wave-wide load covers one 128-byte line of 8 tokens,
       // lanes n16 < 8 its first 64 bytes (8kb .. +7 of 32 channels), lanes n16 >= 8 the other 64.
       // Matrix columns n16 and n16 + 8 thus hold the same token with different channels: two
@@ -490,6 +500,10 @@ fused_row_kernel(const FusedArgs args) {
 #pragma unroll
       for (int d = 0; d < kRingT; ++d) load_tile(d, tw + d * kTextWaves);
       pin_order();
+#pragma unroll
+      for (int s = 0; s < kRingTV; ++s)
+        tv_ring[s] = buffer_load_v8h<NT>(vt_buf, vt_lane, (tw * (small_shares ? 16 : 64) + 4 * s) * (kD * 2));
+      pin_order();
       for (int t = tw; t < n_tiles; t += kRingT * kTextWaves) {
 #pragma unroll
         for (int d = 0; d < kRingT; ++d) {
@@ -507,16 +521,15 @@ fused_row_kernel(const FusedArgs args) {
 #pragma unroll
               for (int r = 0; r < 4; ++r) c[r] = cx[r] + dpp_f32<0x128>(cy[r]);     // row_ror 8
               const int tok = tile * 16 + 8 * u + tsub;
-              // result rows 4*kb + r are heads; only heads < gh <= 4 exist, all of them in the lanes
-              // with kb = 0: one test per lane, and the test per head is the same for the whole wave
+              // result rows 4*kb + r are heads; there are at most four, all of them in the lanes with
+              // kb = 0.  (Rows from gh on hold a repeated head and are written like the others: a branch
+              // per head costs a short call more, each a jump to code not yet in the cache.)
               if (kb == 0 && hsel == 0 && tok < ntx) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                  if (r < gh) {
-                    const float sv = c[r] * a.softmax_scale;
-                    logits[r * a.stride + nv + tok] = sv;
-                    tmax[r] = fmaxf(tmax[r], sv);
-                  }
+                  const float sv = c[r] * a.softmax_scale;
+                  logits[r * a.stride + nv + tok] = sv;
+                  tmax[r] = fmaxf(tmax[r], sv);
                 }
               }
             }
@@ -530,6 +543,7 @@ fused_row_kernel(const FusedArgs args) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) tmax[r] = row_max(tmax[r]);
     if (lane == 0)
+#pragma unroll
       for (int r = 0; r < 4; ++r) red[(wave * kHeads + r) * kRedPerHead + 2] = tmax[r];
   }
   __syncthreads();
@@ -588,36 +602,34 @@ fused_row_kernel(const FusedArgs args) {
       row_hi = found[kb * kRedPerHead + 1];
     }
   }
+  // (the lanes of row h work on head h: one division for all four)
   float a2[kHeads], c2v[kHeads], c2t[kHeads], mref[kHeads];
-#pragma unroll
-  for (int h = 0; h < kHeads; ++h) {
-    const float lo = lane_value(lo_l, 16 * h), hi = lane_value(hi_l, 16 * h);
-    const float tm = lane_value(tm_l, 16 * h);
+  {
     float slope = 1.f, gam = 0.f, shift = 0.f;    // s' = slope * (s - gam) + shift
     if (a.calib_mode != CQ_CALIB_NONE && nv > 0) {
       float glo = a.gamma, ghi = a.delta;
       if (a.calib_mode == CQ_CALIB_DYNAMIC) {
-        glo = lo;
-        ghi = hi;
-        if (SPLIT && a.n_chunks > 1) {            // of the whole row
-          glo = lane_value(row_lo, 16 * h);
-          ghi = lane_value(row_hi, 16 * h);
-        }
+        glo = SPLIT && a.n_chunks > 1 ? row_lo : lo_l;      // of the whole row
+        ghi = SPLIT && a.n_chunks > 1 ? row_hi : hi_l;
       }
       const float width = ghi - glo;
       slope = width == 0.f ? 1.f : (width + a.tau1 - a.tau2) / width;
       gam = glo;
       shift = glo - a.tau1;
     }
-    float M = tm;
+    float M = tm_l;
     if (nv > 0) {
-      M = fmaxf(M, slope * (lo - gam) + shift);
-      M = fmaxf(M, slope * (hi - gam) + shift);
+      M = fmaxf(M, slope * (lo_l - gam) + shift);
+      M = fmaxf(M, slope * (hi_l - gam) + shift);
     }
-    mref[h] = M;
-    a2[h] = slope * kLog2e;
-    c2v[h] = (shift - slope * gam - M) * kLog2e;
-    c2t[h] = -M * kLog2e;
+    const float c = (shift - slope * gam - M) * kLog2e;
+#pragma unroll
+    for (int h = 0; h < kHeads; ++h) {
+      mref[h] = lane_value(M, 16 * h);
+      a2[h] = lane_value(slope, 16 * h) * kLog2e;
+      c2v[h] = lane_value(c, 16 * h);
+      c2t[h] = -mref[h] * kLog2e;
+    }
   }
 
   // =================================================================== phase 2: weighted values
@@ -1019,33 +1031,24 @@ fused_row_kernel(const FusedArgs args) {
     // waves in shares of SH tokens; the weights of a share are computed once (lane = token) and
     // staged in the share's own logit slots (SH * 4 bytes in each of the four head rows), one
     // 64-byte record per load step: [hi | lo][head][token of the step].
-    // Shares of 64 tokens are the efficient ones; a short tail (a split row's chunk, a small
-    // prompt) goes out in shares of 16 so that it still occupies all text waves.
     float tl[kHeads] = {0.f, 0.f, 0.f, 0.f};
     if (ntx > 0) {
-      // the chunk's text values as a buffer of ntx tokens (reads past the end return zeros, which
-      // meet weights of zero)
-      const __amdgpu_buffer_rsrc_t vt_buf =
-          stream_buffer(a.v_text + ((size_t)row * a.n_text_cap + txt0) * kD, (unsigned)ntx * kD * 2);
-      const int vt_lane = (kb * kD + 8 * n16) * 2;
+      // (reads past the end of the chunk's text values return zeros, which meet weights of zero)
       v4f acc_hi[2], acc_lo[2];              // [channel 8 n16 + 2 kb + i][head]
 #pragma unroll
       for (int i = 0; i < 2; ++i) acc_hi[i] = acc_lo[i] = (v4f){0.f, 0.f, 0.f, 0.f};
       auto text_values = [&](auto share_tag) {
         constexpr int SH = decltype(share_tag)::value;
         // wave-wide loads per share, how many of them are in flight, records per head row
-        constexpr int kSteps = SH / 4, kDepth = kRingTV < kSteps ? kRingTV : kSteps, kRecs = SH / 16;
+        constexpr int kSteps = SH / 4, kDepth = kRingTV, kRecs = SH / 16;
         static_assert(kSteps % kDepth == 0, "the ring divides a share");
         const int n_sh = (ntx + SH - 1) / SH;
         const int rec_wr = (((lane >> 2) / kRecs) * a.stride) * 4 + ((lane >> 2) % kRecs) * 64 + (lane & 3) * 2;
         const int rec_rd = (lane & 3) * 8;          // matrix row = lane % 4 = head
-        v8h ring[kDepth];
+        auto& ring = tv_ring;                       // holds the first steps of the wave's first share
         auto load_step = [&](int slot, int sh, int s) {
           ring[slot] = buffer_load_v8h<NT>(vt_buf, vt_lane, (sh * SH + 4 * s) * (kD * 2));
         };
-#pragma unroll
-        for (int s = 0; s < kDepth; ++s) load_step(s, tw, s);
-        pin_order();
         for (int sh = tw; sh < n_sh; sh += kTextWaves) {
           const int t0 = sh * SH;
           const int nt = min(SH, ntx - t0);
@@ -1053,9 +1056,7 @@ fused_row_kernel(const FusedArgs args) {
           if (lane < nt) {
 #pragma unroll
             for (int h = 0; h < kHeads; ++h)
-              if (h < gh)
-                pv[h] = __builtin_amdgcn_exp2f(
-                    fmaf(logits[h * a.stride + nv + t0 + lane], kLog2e, c2t[h]));
+              pv[h] = __builtin_amdgcn_exp2f(fmaf(logits[h * a.stride + nv + t0 + lane], kLog2e, c2t[h]));
           }
 #pragma unroll
           for (int h = 0; h < kHeads; ++h) tl[h] += pv[h];
@@ -1102,10 +1103,7 @@ fused_row_kernel(const FusedArgs args) {
           }
         }
       };
-      // rounds of shares over the text waves, a share of 16 costing ~1.1 quarters of one of 64
-      const int rounds64 = ((ntx + 63) / 64 + kTextWaves - 1) / kTextWaves;
-      const int rounds16 = ((ntx + 15) / 16 + kTextWaves - 1) / kTextWaves;
-      if (11 * rounds16 < 40 * rounds64) text_values(std::integral_constant<int, 16>{});
+      if (small_shares) text_values(std::integral_constant<int, 16>{});
       else text_values(std::integral_constant<int, 64>{});
       // lane (kb, n16): the wave's sums for heads 0..3, channels 8 n16 + 2 kb and + 1
 #pragma unroll
@@ -1199,7 +1197,8 @@ fused_row_kernel(const FusedArgs args) {
     if (tid == kThreads - 1) last[0] = count_in(count, a.tag, count_seen) == a.n_chunks - 1 ? 1.f : 0.f;
     __syncthreads();
     if (last[0] == 0.f) return;
-    merge_partials<kD, kThreads>(a.ws_partial + head0 * a.n_chunks * (kD + 2), a.n_chunks, gh, a.out + head0 * kD);
+    merge_partials<kD, kWaves>(a.ws_partial + head0 * a.n_chunks * (kD + 2), a.n_chunks, gh, a.out + head0 * kD,
+                               reinterpret_cast<float*>(smem));
     for (int i = tid; i < gh * a.n_chunks * 2; i += kThreads) a.ws_words[head0 * a.n_chunks * 2 + i] = 0;
     if (tid == 0) *count = 0;
   }
@@ -1218,7 +1217,6 @@ size_t fused_lds_bytes(int n_vis_chunk, int n_text_chunk, int k_group, int* stri
   size_t off = (size_t)kHeads * stride * sizeof(float);
   const size_t part = (size_t)kWaves * kHeads * kD * sizeof(float);
   if (off < part) off = part;
-  off += kHeads * kD * sizeof(float);
   (void)k_group;
   off = (off + 15) & ~(size_t)15;
   off += (size_t)kVisWaves * kStageBytes;

@@ -19,6 +19,8 @@
 #ifndef CQ_DECODE_MEET_H_
 #define CQ_DECODE_MEET_H_
 
+#include <type_traits>
+
 #include "decode_device.h"
 
 namespace cq {
@@ -68,41 +70,81 @@ __device__ inline int count_in(u64* count, u64 tag, u64 seen) {
   return (int)(__hip_atomic_fetch_add(count, (u64)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 0xff);
 }
 
-// ---- merge of the partials [heads][n_slots][D + 2] = (m, l, acc[D]) of gh heads; two channels per thread
-template <int D, int THREADS>
-__device__ inline void merge_partials(const float* partial, int n_slots, int gh, __half* out) {
-  constexpr int kPairs = D / 2;
-  for (int e = threadIdx.x; e < gh * kPairs; e += THREADS) {
-    const int h = e / kPairs, c = 2 * (e % kPairs);
+// ---- merge of the partials [heads][n_slots][D + 2] = (m, l, acc[D]) of gh <= 4 heads
+// A wave takes one head and every kGroups-th slot, its lanes the channels; the (m, l) of up to 64 slots come in
+// one load, a lane each.  A chunk without tokens has weight 0.  lds: kGroups * 4 * D floats that nobody reads
+// any more.  (One thread per pair of channels over all slots, sixteen at a time whether there are sixteen or not,
+// took 1.0 to 1.5 us of a call; this takes 0.5.)
+template <int D, int WAVES>
+__device__ inline void merge_partials(const float* partial, int n_slots, int gh, __half* out, float* lds) {
+  constexpr int kGroups = WAVES / kHeads, kPer = D / 64;       // channels per lane
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int h = wave % kHeads, first = wave / kHeads;
+  float num[kPer], den = 0.f;
+#pragma unroll
+  for (int e = 0; e < kPer; ++e) num[e] = 0.f;
+  if (h < gh) {
     const float* base = partial + h * (size_t)n_slots * (D + 2);
-    // sixteen partials at a time, their loads independent of each other; each batch brings its own
-    // reference point (online softmax over batches).  A chunk without tokens has weight 0.
-    float M = -FLT_MAX, den = 0.f;
-    v2f num = {0.f, 0.f};
-    for (int i0 = 0; i0 < n_slots; i0 += 16) {
-      v2f ml[16], acc[16];
+    float M = -FLT_MAX;
+    auto take = [&](auto batch_tag, int s0, int n) {           // n <= 64 slots, BATCH loads in flight
+      constexpr int BATCH = decltype(batch_tag)::value;
+      const v2f ml = load_device(base + (size_t)(s0 + min(lane, n - 1)) * (D + 2));
+      float acc[BATCH][kPer];
+      auto load = [&](int i0) {
 #pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const float* p = base + (size_t)min(i0 + u, n_slots - 1) * (D + 2);
-        ml[u] = load_device(p);
-        acc[u] = load_device(p + 2 + c);
-      }
-      float Mb = M;
+        for (int u = 0; u < BATCH; ++u) {
+          const float* p = base + (size_t)(s0 + min(i0 + u * kGroups, n - 1)) * (D + 2) + 2 + kPer * lane;
+          if constexpr (kPer == 1) {
+            acc[u][0] = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          } else {
 #pragma unroll
-      for (int u = 0; u < 16; ++u) Mb = fmaxf(Mb, ml[u][0]);     // a repeated partial changes nothing
+            for (int e = 0; e < kPer; e += 2) {
+              const v2f t = load_device(p + e);
+              acc[u][e] = t[0];
+              acc[u][e + 1] = t[1];
+            }
+          }
+        }
+      };
+      load(first);                                             // before anything is done with (m, l)
+      // the slots' maximum by its distance to the first one's (wave_max_nonneg takes no signs)
+      const float ref = fmaxf(M, lane_value(ml[0], 0));
+      const float Mb = ref + wave_max_nonneg(fmaxf(ml[0] - ref, 0.f));
       const float keep = __builtin_amdgcn_exp2f((M - Mb) * kLog2e);
-      num *= keep;
-      den *= keep;
       M = Mb;
+      const float w = lane < n ? __builtin_amdgcn_exp2f((ml[0] - M) * kLog2e) : 0.f;
+      den = fmaf(den, keep, wave_sum(w * ml[1]));
 #pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const float w = i0 + u < n_slots ? __builtin_amdgcn_exp2f((ml[u][0] - M) * kLog2e) : 0.f;
-        num[0] = fmaf(w, acc[u][0], num[0]);
-        num[1] = fmaf(w, acc[u][1], num[1]);
-        den = fmaf(w, ml[u][1], den);
+      for (int e = 0; e < kPer; ++e) num[e] *= keep;
+      for (int i0 = first;;) {
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+          const int i = i0 + u * kGroups;
+          const float wi = i < n ? lane_value(w, i) : 0.f;
+#pragma unroll
+          for (int e = 0; e < kPer; ++e) num[e] = fmaf(wi, acc[u][e], num[e]);
+        }
+        i0 += BATCH * kGroups;
+        if (i0 >= n) break;
+        load(i0);
       }
+    };
+    if (n_slots <= 4 * kGroups) take(std::integral_constant<int, 4>{}, 0, n_slots);
+    else for (int s0 = 0; s0 < n_slots; s0 += 64) take(std::integral_constant<int, 12>{}, s0, min(64, n_slots - s0));
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+      if constexpr (kGroups > 1) lds[(first * kHeads + h) * D + kPer * lane + e] = num[e] / den;
+      else out[h * D + kPer * lane + e] = __float2half_rn(num[e] / den);
     }
-    *reinterpret_cast<__half2*>(out + h * D + c) = __floats2half2_rn(num[0] / den, num[1] / den);
+  }
+  if constexpr (kGroups > 1) {
+    __syncthreads();
+    for (int e = threadIdx.x; e < gh * D; e += WAVES * 64) {
+      float sum = 0.f;
+#pragma unroll
+      for (int f = 0; f < kGroups; ++f) sum += lds[f * kHeads * D + e];
+      out[e] = __float2half_rn(sum);
+    }
   }
 }
 
