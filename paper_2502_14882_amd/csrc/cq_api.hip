@@ -201,7 +201,11 @@ int check_calib(const cq_calib_t* calib, cq::Calib* c) {
   return CQ_OK;
 }
 
-// Whether the tile kernels finish a call sooner than the tuned kernels that could take it.  The fused
+// Two sets of query heads: visual tokens from which their whole rows stay on chip (see select_kernels).
+constexpr int kTwoSetsOnChip = 256;
+
+// Whether the tile kernels finish a call sooner than the tuned kernels that could take it, asked where the fused kernel
+// does not spread its rows over the chip (8 bits, two head sets of few tokens, more rows than CUs).  The fused
 // kernel gives a row (a chunk of a row) to one CU, which moves about 27 GB/s, and the streaming
 // kernels take three launches; with few rows the tile kernels, two launches over many small
 // workgroups, win.  Microseconds per call inside a recorded graph, fitted to measurements of both sides
@@ -254,13 +258,20 @@ size_t ws_without_tiles(const DecodeCall& c) {
 int select_kernels(const cq_layout_t* L, int n_text, int n_text_cap, size_t scratch_limit,
                    DecodeCall* call) {
   call->shape = make_shape(L, n_text, n_text_cap);
-  call->plan = cq::make_fused_plan(call->shape, g_decode_chunks);
+  call->plan = cq::make_fused_plan(call->shape, g_decode_chunks,
+                                   g_kernel_path == CQ_PATH_AUTO ? cq::FusedSplit::kSpread : cq::FusedSplit::kWhole);
   if (g_alone) call->plan.patience = 0;
   if (g_kernel_path == CQ_PATH_TUNED && !call->plan.ok)
     return fail(CQ_ERR_UNSUPPORTED, "no tuned decode kernel for this layout");
   call->tuned = g_kernel_path != CQ_PATH_GENERIC && call->plan.ok;
   call->streamed = false;
-  if (call->tuned && (call->plan.n_chunks > 1 || call->plan.nhb > 1) && !g_one_launch) {
+  // Two head blocks of a whole row share its lines through one XCD's L2, and one launch takes half the time of the
+  // streaming kernels' three (64 rows of 3328 tokens, 6 heads: 11.4 / 22.2 us).  They read the tail twice, though,
+  // so where it is most of the call the streaming kernels stay.
+  const bool whole_sets = call->plan.n_chunks == 1 && call->plan.nhb > 1 && L->n_vis >= kTwoSetsOnChip &&
+                          L->bits <= 4 && g_decode_chunks == 0;
+  const bool on_chip = whole_sets || (call->plan.spread && (call->plan.nhb == 1 || L->n_vis >= kTwoSetsOnChip));
+  if (call->tuned && (call->plan.n_chunks > 1 || call->plan.nhb > 1) && !g_one_launch && !on_chip) {
     call->stream = cq::make_stream_plan(call->shape, g_decode_chunks);
     call->streamed = call->stream.ok && call->stream.ws_bytes <= scratch_limit;
   }
@@ -282,7 +293,7 @@ int select_kernels(const cq_layout_t* L, int n_text, int n_text_cap, size_t scra
     call->tile = cq::make_tile_plan(call->shape, within ? most : SIZE_MAX);
     call->tiled = call->tile.ok && call->tile.ws_bytes <= scratch_limit;
     reserve = within && call->tile.ws_reserve_bytes > most ? most : call->tiled ? call->tile.ws_reserve_bytes : 0;
-  } else if (g_kernel_path == CQ_PATH_AUTO && L->n_vis > 0 && g_decode_chunks == 0) {
+  } else if (g_kernel_path == CQ_PATH_AUTO && L->n_vis > 0 && g_decode_chunks == 0 && !on_chip) {
     cq::DecodeShape no_tail = call->shape;
     no_tail.n_text = 0;
     const bool faster = tile_is_faster(call->shape, call->plan);
@@ -396,12 +407,12 @@ int check_workspace(DecodeCall* call, const void* workspace, size_t workspace_by
     call->tiled = false;
     call->ws_bytes = ws_without_tiles(*call);
   }
-  // Split rows of the fused kernel: with a shorter tail a row may be cut into more chunks, to fill the last
-  // round of workgroups, than a workspace for a longer one holds partials of.  The fewest that fit on
-  // chip never grow as the tail shrinks.
-  if (call->tuned && !call->streamed && !call->tiled && call->plan.n_chunks > 2 && workspace_bytes < call->ws_bytes &&
+  // Rows of the fused kernel in more chunks than they must be (to fill the chip, or with a shorter tail the last round
+  // of workgroups) than the workspace holds partials of: the fewest that fit on chip, which never grow as
+  // the tail shrinks.
+  if (call->tuned && !call->streamed && !call->tiled && call->plan.n_chunks > 1 && workspace_bytes < call->ws_bytes &&
       g_decode_chunks == 0) {
-    const cq::FusedPlan fewest = cq::make_fused_plan(call->shape, 2);
+    const cq::FusedPlan fewest = cq::make_fused_plan(call->shape, 0, cq::FusedSplit::kFewest);
     if (fewest.ok && fewest.ws_bytes <= workspace_bytes) {
       call->plan = fewest;
       call->ws_bytes = fewest.ws_bytes;

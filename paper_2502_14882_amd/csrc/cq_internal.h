@@ -143,8 +143,10 @@ hipError_t launch_combine(int n_rows, int n_chunks, int d, const float* partial,
                           hipStream_t stream);
 
 // Rows that several workgroups of a launch share (decode_meet.h): how often a workgroup looks for the extrema of
-// the others before it forms them itself.  A look takes about a microsecond.
-constexpr int kPatience = 100;
+// the others before it forms them itself.  A look takes about a third of a microsecond; workgroups whose
+// neighbours start with the next round of a large grid wait for up to a round (50 us), and going on alone
+// multiplies their work.
+constexpr int kPatience = 20000;
 
 // Tuned decode for head_dim 128 (see decode_fused.hip for the layouts it takes): one launch, a workgroup
 // per row or per chunk of a row.  The plan is made once per call on the host and says what will run.
@@ -152,14 +154,20 @@ struct FusedPlan {
   bool ok = false;            // a tuned kernel exists for the shape
   int nhb = 1;                // blocks of 4 query heads per KV head
   int n_chunks = 1;           // chunks per row
+  bool spread = false;        // every workgroup has a CU of its own, and as many chunks as pay
   int stride = 0;             // floats between the logit rows of two heads in LDS
   size_t lds = 0;             // dynamic LDS bytes per workgroup
   int patience = kPatience;
   size_t ws_count_floats = 0, ws_partial_floats = 0;   // split rows: [words | counts | partials], offsets in floats
   size_t ws_bytes = 256;      // workspace the launches touch (a multiple of 256, >= 256)
 };
-// min_chunks: 0 = the fewest chunks that fit on chip, n >= 1 = at least n (test override)
-FusedPlan make_fused_plan(const DecodeShape& s, int min_chunks);
+// min_chunks: 0 = as split says, n >= 1 = at least n (test override)
+enum class FusedSplit {
+  kWhole,    // whole rows where they fit on chip, else about the fewest chunks that do
+  kFewest,   // exactly the fewest
+  kSpread,   // more, where the chip has room for them
+};
+FusedPlan make_fused_plan(const DecodeShape& s, int min_chunks, FusedSplit split = FusedSplit::kWhole);
 hipError_t launch_decode_fused(const DecodeShape& s, const FusedPlan& plan, const void* q,
                                const cq_qtensor_t& k, const cq_qtensor_t& v, const void* k_text,
                                const void* v_text, const int32_t* n_text_dev, const Calib& calib,

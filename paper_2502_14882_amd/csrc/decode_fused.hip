@@ -41,6 +41,7 @@
 
 #include <atomic>
 #include <cfloat>
+#include <cmath>
 #include <type_traits>
 
 #include "cq_internal.h"
@@ -587,6 +588,7 @@ fused_row_kernel(const FusedArgs args) {
             hi = fmaxf(hi, y);
           }
           all = __builtin_amdgcn_ballot_w64(!all) == 0;
+          if (!all) __builtin_amdgcn_s_sleep(1);
         }
         lo = row_min(lo);
         hi = row_max(hi);
@@ -1263,29 +1265,38 @@ int chunk_unit(const DecodeShape& s) {
   return align / s.k_group > 1 ? align / s.k_group : 1;
 }
 
-// largest chunk of a row split into n_chunks (same arithmetic as the kernel)
+// largest chunk of a row split into n_chunks (same arithmetic as the kernel): the first one
 void chunk_extent(const DecodeShape& s, int n_chunks, int* nv_max, int* nt_max) {
-  const int unit = chunk_unit(s);
-  const int n_units = s.n_vis / (s.k_group * unit);
-  const int n_tblocks = (s.n_text + 63) / 64;
-  *nv_max = 0;
-  *nt_max = 0;
-  for (int c = 0; c < n_chunks; ++c) {
-    const int ga = chunk_first(n_units / n_chunks, n_units % n_chunks, c) * unit;
-    const int gb = chunk_first(n_units / n_chunks, n_units % n_chunks, c + 1) * unit;
-    const int ba = chunk_first(n_tblocks / n_chunks, n_tblocks % n_chunks, c);
-    const int bb = chunk_first(n_tblocks / n_chunks, n_tblocks % n_chunks, c + 1);
-    const int nv = (gb - ga) * s.k_group;
-    int nt = (bb * 64 < s.n_text ? bb * 64 : s.n_text) - ba * 64;
-    if (nt < 0) nt = 0;
-    if (nv > *nv_max) *nv_max = nv;
-    if (nt > *nt_max) *nt_max = nt;
-  }
+  const int unit = chunk_unit(s), n_units = s.n_vis / (s.k_group * unit), n_tblocks = (s.n_text + 63) / 64;
+  *nv_max = ceil_div(n_units, n_chunks) * unit * s.k_group;
+  const int nt = ceil_div(n_tblocks, n_chunks) * 64;
+  *nt_max = nt < s.n_text ? nt : s.n_text;
+}
+
+// Chunks per row where every workgroup gets a CU of its own: what a chunk's tokens take against what the
+// exchange, the merge and each further partial cost.  Microseconds, fitted to 4000 measurements of 570 layouts
+// with 1 to 256 workgroups, head_dim 128 (6 % rms): a call takes 4.1, 3.7 more for a shared row, per thousand tokens
+// of a chunk 1.6 / 2.1 / 3.1 (1 / 2 / 4 bits; key groups of 32 another 1.0), 0.9 per 64 tokens of the tail, 0.1 per
+// chunk, and 1.3 to 2.2 where the chip is full.  That last figure is set so that two chunks on a full chip are taken
+// where they pay (96 to 128 rows, whole / in 2: 1 bit x 3584 tokens 11.4 / 12.3, x 6016 16.6 / 15.3; 2 bits x 4480
+// 15.5 / 14.9; 4 bits x 3840 18.5 / 19.4, x 4224 18.7 / 16.9).
+int spread_chunks(const DecodeShape& s, long long rows, long long cus, int n_units) {
+  const double per_k = (s.bits == 1 ? 1.6 : s.bits == 2 ? 2.1 : 3.1) +
+                       (s.k_group == 32 ? 1.0 : 0.0) + (s.v_axis == CQ_AXIS_CHANNEL ? 0.4 : 0.0);
+  const double row = per_k * 1e-3 * s.n_vis + 0.9 * ((s.n_text + 63) / 64), 
+               each = 0.1 + (s.bits == 1 ? 1.3 : s.bits == 2 ? 2.1 : 4.6) * (double)rows / (double)cus;
+  long long most = cus / rows < n_units ? cus / rows : n_units;
+  if (most > 64) most = 64;
+  long long c = (long long)(std::sqrt(row / each) + 0.5);
+  if (c > most) c = most;
+  // (half a microsecond more than the fit says: short rows scatter, and a shared one needs a larger workspace)
+  if (c < 2 || row * (double)(c - 1) / (double)c < 4.2 + each * (double)(c - 1)) return 1;
+  return ceil_div(n_units, ceil_div(n_units, (int)c));         // no more than make the largest chunk smaller
 }
 
 }  // namespace
 
-FusedPlan make_fused_plan(const DecodeShape& shape, int min_chunks) {
+FusedPlan make_fused_plan(const DecodeShape& shape, int min_chunks, FusedSplit split) {
   FusedPlan p;
   bool k_whole, v_whole;
   const DecodeShape s = processing_shape(shape, &k_whole, &v_whole);
@@ -1301,9 +1312,7 @@ FusedPlan make_fused_plan(const DecodeShape& shape, int min_chunks) {
   const int unit = chunk_unit(s);
   const int n_units = s.n_vis / (s.k_group * unit);
   const int max_chunks = n_units < 64 ? (n_units > 0 ? n_units : 1) : 64;
-  // Fewest chunks that fit LDS.  Splitting a row that fits only to fill idle CUs does not pay: what the
-  // exchange and the merge take (3 us) is what two chunks save (128 rows of 3328 tokens, whole / in 2 chunks:
-  // 12.6 / 14.5 us with 1 bit, 19.4 / 20.0 with 4).
+  // fewest chunks that fit LDS
   int want = min_chunks >= 1 ? min_chunks : 1;                 // > 1: a test's or a tuner's override
   if (want > max_chunks) want = max_chunks;
   const bool forced = want > 1;
@@ -1319,7 +1328,18 @@ FusedPlan make_fused_plan(const DecodeShape& shape, int min_chunks) {
     }
   }
   if (p.lds == 0) return p;
-  if (p.n_chunks > 1 && !forced) {
+  // Every workgroup on a CU of its own: as many chunks as pay.  (8-bit rows are bound by what the CUs read
+  // together, and the tile kernels have them.)
+  if (split == FusedSplit::kSpread && !forced && s.n_vis > 0 && s.bits <= 4 && rows * p.n_chunks <= device_cu_count()) {
+    const int c = spread_chunks(s, rows, device_cu_count(), n_units);
+    if (c > p.n_chunks) {
+      int nv, nt;
+      chunk_extent(s, c, &nv, &nt);
+      p.n_chunks = c;
+      p.lds = fused_lds_bytes(nv, nt, s.k_group, &p.stride);
+    }
+    p.spread = true;
+  } else if (p.n_chunks > 1 && !forced && split != FusedSplit::kFewest) {
     // A row that has to be split anyway: a few more chunks can fill the last round of
     // workgroups.  Cost of c chunks ~ rounds over the CUs x (tokens per chunk + a fixed cost per
     // workgroup worth ~1500 tokens).

@@ -103,3 +103,30 @@ def test_overlapping_calls_with_workspaces_of_their_own():
                 o.append(run(lay, dev, k, v, 64, c, ONE_LAUNCH + 8))
     torch.cuda.synchronize()
     assert all(torch.equal(t, want) for o in outs for t in o)
+
+
+# (B, Hq, Hkv, n_vis, n_text, bits, key group, value axis, value group) and whether rows are shared: a full chip, one
+# workgroup too many, rows too short to share, two head sets on chip from 256 tokens, 8 bits never
+SPREAD = [((16, 4, 4, 8192, 70, 1, 128, 1, 128), True), ((43, 3, 3, 4096, 70, 2, 64, 1, 128), False),
+          ((1, 2, 2, 512, 3, 1, 128, 1, 128), False), ((2, 12, 2, 2560, 130, 1, 128, 1, 128), True),
+          ((2, 16, 2, 256, 20, 2, 128, 1, 128), False), ((1, 4, 1, 16384, 1000, 4, 32, 1, 128), True),
+          ((1, 4, 4, 2048, 600, 8, 128, 1, 128), False)]
+
+
+@pytest.mark.parametrize("args,shared", SPREAD)
+def test_rows_spread_over_idle_compute_units(args, shared):
+    """What the library chooses by itself; given only the workspace that the fewest chunks need, it runs those."""
+    lay, x, dev, k, v, kq, vq = build(*args)
+    n_text, calib = args[4], cq.make_calib(cq.CQ_CALIB_DYNAMIC, 1.0, 2.0)
+    size = cq.cq_decode_workspace_bytes(lay, n_text, calib)
+    prev = cq.cq_bench_set_kernel_path(cq.CQ_PATH_TUNED)
+    whole = cq.cq_decode_workspace_bytes(lay, n_text, calib)
+    cq.cq_bench_set_kernel_path(prev)
+    if args[5] <= 4:
+        assert (size > whole) == shared, (size, whole)
+    ref = O.decode_attn(x["q"].numpy(), kq, vq, x["k_text"].numpy(), x["v_text"].numpy(), n_text, O.CALIB_DYNAMIC, 1.0, 2.0)
+    for n_bytes in {size, whole}:
+        ws = torch.empty(n_bytes, dtype=torch.uint8, device="cuda").fill_(255)
+        got = cq.cq_decode_attn(lay, dev["q"], k, v, dev["k_text"], dev["v_text"], n_text, calib, 0.0, None, ws)
+        err = O.rel_l2(got.cpu().numpy().astype(np.float64), ref)
+        assert err <= H.REGRESSION_TOL, (n_bytes, err)
