@@ -306,6 +306,7 @@ int select_kernels(const cq_layout_t* L, int n_text, int n_text_cap, size_t scra
         reserve = call->tile.ws_reserve_bytes < most ? call->tile.ws_reserve_bytes : most;
     }
   }
+  if (g_alone) call->tile.patience = 0;
   call->ws_bytes = call->tiled ? call->tile.ws_bytes : ws_without_tiles(*call);
   call->ws_query_bytes = reserve > call->ws_bytes ? reserve : call->ws_bytes;
   return CQ_OK;

@@ -202,6 +202,11 @@ struct TilePlan {
   int ct = 0, ct_tokens = 0;       // chunks per row of the fp16 tail, tokens per chunk
   size_t ws_minmax_floats = 0;     // workspace: [logits | extrema | partials | counts], offsets in floats
   size_t ws_partial_floats = 0, ws_count_floats = 0;
+  // one launch instead of two, in a part of the same workspace: [words | counts | partials]
+  bool one_launch = false;
+  int row_cb = 0, row_ct = 0;      // chunks per row of the visual tokens, of the tail
+  size_t row_tags_floats = 0, row_partial_floats = 0;
+  int patience = kPatience;
   size_t ws_bytes = 256;           // workspace the launches touch
   // the most that a tail of up to n_text tokens needs without a limit (never falls with n_text)
   size_t ws_reserve_bytes = 256;

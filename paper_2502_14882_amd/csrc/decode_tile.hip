@@ -25,10 +25,11 @@
 // (logits with a deviation of 6; fp32 2e-7), a two hundredth of the output's rounding.  Following the
 // products costs a small call 0.1 to 0.2 us.
 //
-// Bound: on small calls latency - two launches, and in each wave a chain of few round trips to memory: all
-// that a wave needs first is asked for at once (its first codes and parameters, then the query;
-// its first value tile, then the extrema), a key block's codes together, a share of the tail
-// together.  On large ones the issue of vector instructions; 16 waves share a CU and hide each other's
+// Both passes run as one launch (tile_row_kernel) where that is faster, see plan_one_launch.
+//
+// Bound: on small calls latency - in each wave a chain of few round trips to memory: all that a wave needs first
+// is asked for at once (the query, its first codes and parameters; its first value tile, then the
+// extrema), a key block's codes together, a share of the tail together.  On large ones the issue of vector instructions; 16 waves share a CU and hide each other's
 // latency.  Against the shape-agnostic kernels, which dequantize element by element: 64 rows x
 // 3003 tokens, 2 bits, whole-sequence keys and values 618 -> 15.6 us; 64 rows x 3328 tokens of 64
 // channels, 1 bit, 422 -> 14.1 us.  Over key and value groups from 1 to 48 tokens, head_dim 64 to 256
@@ -41,6 +42,7 @@
 #include "cq_internal.h"
 #include "decode_device.h"
 #include "decode_fold.h"
+#include "decode_meet.h"
 
 namespace cq {
 namespace {
@@ -51,6 +53,9 @@ constexpr int kKeyBlock = 128;       // most tokens per key block (8 tiles of 16
 constexpr int kValTile = 64;         // tokens per value tile
 constexpr int kTextShare = 32;       // tokens of the fp16 tail per wave and round
 constexpr int kTextBlock = kWaves * kTextShare;
+// one launch: chunks are whole units of 128 tokens, so many at least and at most; workgroups to aim at
+constexpr int kUnit = 128, kRowMinUnits = 4, kRowMaxUnits = 8, kRowTarget = 768;
+constexpr int kRowMost = 4096, kRowMostAll = 250000, kRowMostChunks = 56;     // see plan_one_launch
 constexpr int kMaxRun = 1024;        // value tiles between two folds of the int32 digit sums (2^20 each)
 
 struct TileArgs {
@@ -61,6 +66,7 @@ struct TileArgs {
   int g, sets, n_vis, n_text, n_text_cap;    // sets = ceil(g / 4)
   const int32_t* n_text_dev;   // NULL, or the tail length in device memory (n_text is then its bound)
   int k_group, k_bpg, k_groups;   // tokens per key group, blocks per group, groups per row
+  int k_block;                    // most tokens per key block
   int v_group, v_tpg, v_groups;   // tokens per value group (token-wise: n_vis), tiles per group, groups per row
   int ca, ca_base, ca_rem;     // logits pass: chunks per row, in key blocks
   int cb, cb_base, cb_rem;     // values pass: chunks per row, in value tiles
@@ -71,6 +77,12 @@ struct TileArgs {
   float* ws_minmax;            // [B*Hq][ca + ct][2]
   float* ws_partial;           // [B*Hq][cb + ct][D + 2]
   int* ws_count;               // [rows][sets] partials stored so far; NULL: no values pass follows
+  // one launch (tile_row_kernel): chunks of cb_base or cb_base + 1 units of 128 tokens
+  int k_bpu, v_tpu, k_blocks, v_tiles;   // key blocks and value tiles per unit, per row
+  int l_stride;                // floats between the logits of two heads in LDS
+  unsigned slots_magic;        // fl(2^32 / (cb + ct)) + 1, or 0 when there is one slot
+  u64* ws_words; u64* ws_tags; // [B*Hq][cb][2] words of the exchange, [rows][sets] counts under the call's tag
+  u64 tag; int patience;
   __half* out;
   int calib_mode; float tau1, tau2, gamma, delta, softmax_scale;
 };
@@ -231,64 +243,32 @@ __device__ inline void text_logits(const TileArgs& a, const TextSpan& x, size_t 
   }
 }
 
-// grid: x = row, y = chunk of the tail, of the visual tokens, of the second set of keys, z = head set
-// (the workgroups of 16-bit keys take all heads and leave the others of their column at once)
+// The wave's share of the key blocks b0 .. b1 of a row: logits of the set's heads, if store, to out (of head kb)
+// from token tok_base on, and their extrema (of head kb).  xb: NP * 1024 bytes of LDS of the wave's own.
 template <int D, int BITS>
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(D == 256 ? 2 : 4)))
-tile_logits_kernel(const TileArgs a) {
+__device__ inline void visual_logits(const TileArgs& a, size_t row, int set, int b0, int b1, int lane, int wave,
+                                     uint8_t* xb, bool store, float* out, int tok_base, float& mn, float& mx) {
   using Op = Operand<D, BITS>;
   constexpr int NP = Op::kProducts;
   // tiles of 16 tokens whose codes are asked for together: a block's, as far as registers go
   constexpr int kFly = Op::kWords <= 4 ? 8 : Op::kWords == 8 ? 4 : 2;
-  __shared__ __align__(16) uint8_t s_x[kWaves][NP * 1024];     // query operand of a wave's key group
-  __shared__ float red[kWaves][16][2];
-  const size_t row = blockIdx.x;
-  if (blockIdx.y == 0 && blockIdx.z == 0 && a.ws_count)          // for the values pass behind this one
-    for (int i = threadIdx.x; i < a.sets; i += kThreads) a.ws_count[row * a.sets + i] = 0;
-  const bool tail = (int)blockIdx.y < a.ct;
-  if (tail || (int)blockIdx.y >= a.ct + a.ca) {
-    if (blockIdx.z != 0) return;
-    const int chunk = (int)blockIdx.y - (tail ? 0 : a.ct + a.ca);
-    const size_t head0 = row * a.g, pitch = (size_t)a.n_vis + a.n_text;
-    TextSpan x;
-    if (tail) {
-      const size_t mm_pitch = (size_t)(a.ca + a.ct) * 2;
-      x = {a.k_text + row * (size_t)a.n_text_cap * D, a.n_text_dev ? min(max(*a.n_text_dev, 0), a.n_text) : a.n_text,
-           a.ct_tokens, a.ws_logits + head0 * pitch + a.n_vis, pitch,
-           a.ws_minmax + head0 * mm_pitch + (size_t)(a.ca + chunk) * 2, mm_pitch};
-    } else {
-      const size_t mm_pitch = (size_t)a.x_ct * 2;
-      x = {a.x_keys + row * (size_t)a.x_tokens * D, a.x_tokens, a.x_ct_tokens,
-           a.x_logits + head0 * a.x_tokens, (size_t)a.x_tokens, a.x_minmax + head0 * mm_pitch + (size_t)chunk * 2,
-           mm_pitch};
-    }
-    text_logits<D>(a, x, row, chunk, red);
-    return;
-  }
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n16 = lane & 15, kb = lane >> 4;
-  const int set = (int)blockIdx.z, chunk = (int)blockIdx.y - a.ct;
-  const int b0 = chunk_first(a.ca_base, a.ca_rem, chunk), b1 = chunk_first(a.ca_base, a.ca_rem, chunk + 1);
   const int gh = min(kHeads, a.g - set * kHeads);              // live heads of the set
   const size_t head0 = row * a.g + (size_t)set * kHeads;
-  const size_t n_all = (size_t)a.n_vis + a.n_text;
 
   // Writer of the query operand: lane l writes row l of every product (lane row l / 16, register
   // (l / 4) % 4, byte l % 4), one channel each; together the lanes cover every channel once.
   int ch[NP];
 #pragma unroll
   for (int i = 0; i < NP; ++i) ch[i] = Op::channel(kb, 4 * i + ((lane >> 2) & 3), lane & 3);
-  uint8_t* xb = s_x[wave];
   const uint8_t* x_rd = xb + (kb * 16 + (n16 >> 1)) * 16 + (n16 & 1) * 8;
   const uint32_t* kc = a.k_codes + row * (size_t)a.n_vis * Op::kRowWords + Op::first_word(kb);
   const int sh = Op::shift(kb);
   const size_t meta0 = row * (size_t)a.k_groups * D;
-  float* out = a.ws_logits + (head0 + min(kb, gh - 1)) * n_all;     // result lane: head kb, token n16
-  const bool live = kb < gh;
+  const bool live = store && kb < gh;                 // result lane: head kb, token n16
 
   v4i A[NP];
   double bias = 0.0, inv_f = 0.0, inv_f16 = 0.0;
-  float mn = FLT_MAX, mx = -FLT_MAX;
   int have = -1;                                               // key group of the operand in A
   int grp, t0, t1;                                             // of the block whose loads are in flight
   uint32_t w[kFly][Op::kWords];
@@ -301,8 +281,8 @@ tile_logits_kernel(const TileArgs a) {
   };
   auto load_block = [&](int blk, int group_loaded) {           // codes, and parameters if they change
     grp = part_of(blk, a.k_bpg);
-    t0 = grp * a.k_group + (blk - grp * a.k_bpg) * kKeyBlock;
-    t1 = min(t0 + kKeyBlock, (grp + 1) * a.k_group);
+    t0 = grp * a.k_group + (blk - grp * a.k_bpg) * a.k_block;
+    t1 = min(t0 + a.k_block, (grp + 1) * a.k_group);
     load_tiles(t0);
     if (grp != group_loaded) {
 #pragma unroll
@@ -312,8 +292,15 @@ tile_logits_kernel(const TileArgs a) {
       }
     }
   };
-  // the first block is asked for before the query, so that a wave waits for memory once
+  // the query and the first block are asked for together, so that a wave waits for memory once
+  uint16_t q_raw[NP][kHeads];
+#pragma unroll
+  for (int i = 0; i < NP; ++i)
+#pragma unroll
+    for (int h = 0; h < kHeads; ++h)
+      q_raw[i][h] = *reinterpret_cast<const uint16_t*>(a.q + (head0 + min(h, gh - 1)) * D + ch[i]);
   if (b0 + wave < b1) load_block(b0 + wave, -1);
+  pin_order();
   float inv_w[NP], qv[NP][kHeads];
 #pragma unroll
   for (int i = 0; i < NP; ++i) {
@@ -321,7 +308,7 @@ tile_logits_kernel(const TileArgs a) {
     inv_w[i] = 1.f / wgt;                                      // exact: powers of two
 #pragma unroll
     for (int h = 0; h < kHeads; ++h)
-      qv[i][h] = h < gh ? __half2float(a.q[(head0 + h) * D + ch[i]]) * wgt : 0.f;      // exact
+      qv[i][h] = h < gh ? __half2float(__ushort_as_half(q_raw[i][h])) * wgt : 0.f;      // exact
   }
   for (int blk = b0 + wave; blk < b1; blk += kWaves) {
     if (blk != b0 + wave) load_block(blk, have);
@@ -382,7 +369,7 @@ tile_logits_kernel(const TileArgs a) {
           const float s = (float)fma((double)hi, inv_f16, fma((double)lo, inv_f, bias));
           const int tok = t + 16 * (u0 + u) + n16;
           if (tok < t1) {
-            if (live) out[tok] = s;
+            if (live) out[tok - tok_base] = s;
             mn = fminf(mn, s);
             mx = fmaxf(mx, s);
           }
@@ -390,6 +377,47 @@ tile_logits_kernel(const TileArgs a) {
       }
     }
   }
+}
+
+// grid: x = row, y = chunk of the tail, of the visual tokens, of the second set of keys, z = head set
+// (the workgroups of 16-bit keys take all heads and leave the others of their column at once)
+template <int D, int BITS>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(D == 256 ? 2 : 4)))
+tile_logits_kernel(const TileArgs a) {
+  __shared__ __align__(16) uint8_t s_x[kWaves][Operand<D, BITS>::kProducts * 1024];     // query operand of a wave's key group
+  __shared__ float red[kWaves][16][2];
+  const size_t row = blockIdx.x;
+  if (blockIdx.y == 0 && blockIdx.z == 0 && a.ws_count)          // for the values pass behind this one
+    for (int i = threadIdx.x; i < a.sets; i += kThreads) a.ws_count[row * a.sets + i] = 0;
+  const bool tail = (int)blockIdx.y < a.ct;
+  if (tail || (int)blockIdx.y >= a.ct + a.ca) {
+    if (blockIdx.z != 0) return;
+    const int chunk = (int)blockIdx.y - (tail ? 0 : a.ct + a.ca);
+    const size_t head0 = row * a.g, pitch = (size_t)a.n_vis + a.n_text;
+    TextSpan x;
+    if (tail) {
+      const size_t mm_pitch = (size_t)(a.ca + a.ct) * 2;
+      x = {a.k_text + row * (size_t)a.n_text_cap * D, a.n_text_dev ? min(max(*a.n_text_dev, 0), a.n_text) : a.n_text,
+           a.ct_tokens, a.ws_logits + head0 * pitch + a.n_vis, pitch,
+           a.ws_minmax + head0 * mm_pitch + (size_t)(a.ca + chunk) * 2, mm_pitch};
+    } else {
+      const size_t mm_pitch = (size_t)a.x_ct * 2;
+      x = {a.x_keys + row * (size_t)a.x_tokens * D, a.x_tokens, a.x_ct_tokens,
+           a.x_logits + head0 * a.x_tokens, (size_t)a.x_tokens, a.x_minmax + head0 * mm_pitch + (size_t)chunk * 2,
+           mm_pitch};
+    }
+    text_logits<D>(a, x, row, chunk, red);
+    return;
+  }
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n16 = lane & 15, kb = lane >> 4;
+  const int set = (int)blockIdx.z, chunk = (int)blockIdx.y - a.ct;
+  const int b0 = chunk_first(a.ca_base, a.ca_rem, chunk), b1 = chunk_first(a.ca_base, a.ca_rem, chunk + 1);
+  const int gh = min(kHeads, a.g - set * kHeads);
+  const size_t head0 = row * a.g + (size_t)set * kHeads;
+  float mn = FLT_MAX, mx = -FLT_MAX;
+  visual_logits<D, BITS>(a, row, set, b0, b1, lane, wave, s_x[wave], true,
+                         a.ws_logits + (head0 + min(kb, gh - 1)) * ((size_t)a.n_vis + a.n_text), 0, mn, mx);
   mn = row_min(mn);
   mx = row_max(mx);
   if (n16 == 0) {
@@ -401,25 +429,14 @@ tile_logits_kernel(const TileArgs a) {
 }
 
 // ===================================================================================== values pass
-// Partials cross from one XCD's L2 to another's inside a launch: stored and loaded at device scope (past
-// L2), eight bytes at a time.
-__device__ inline void store_device(float* p, float a, float b) {
-  __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), __builtin_bit_cast(unsigned long long, (v2f){a, b}),
-                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ inline v2f load_device(const float* p) {
-  return __builtin_bit_cast(v2f, __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED,
-                                                   __HIP_MEMORY_SCOPE_AGENT));
-}
-
 // The end of a workgroup of the values pass: its waves' sums become one partial (m, l, acc[D]) of the
 // joint softmax per head of the set.  The workgroup that finds all other partials of its (row, head
 // set) stored merges them into the output: nobody waits for anybody, and the result does not
 // depend on who comes last.  Each wave's stores have reached memory (vmcnt 0) before the barrier
 // that precedes the workgroup's count.  With a launch of the shared combine kernel in its place
 // the two calls measured at the top of this file took 16.6 and 16.0 us.
-template <int D>
-__device__ inline void finish_chunk(const TileArgs& a, size_t row, int set, size_t head0, int gh, int slot,
+template <int D, bool ROW>
+__device__ inline void finish_chunk(const TileArgs& a, size_t row, int set, size_t head0, int gh, int slot, u64 seen,
                                     const float* m_ref, const float (*s_part)[kHeads][D],
                                     const float (*s_lm)[kHeads][2]) {
   __shared__ int s_last;
@@ -446,80 +463,59 @@ __device__ inline void finish_chunk(const TileArgs& a, size_t row, int set, size
   if (n_slots == 1) return;
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
+  const size_t at = row * a.sets + set;
   if (threadIdx.x == 0)
-    s_last = __hip_atomic_fetch_add(a.ws_count + row * a.sets + set, 1, __ATOMIC_RELAXED,
-                                    __HIP_MEMORY_SCOPE_AGENT) == n_slots - 1;
+    s_last = (ROW ? count_in(a.ws_tags + at, a.tag, seen)
+                  : __hip_atomic_fetch_add(a.ws_count + at, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == n_slots - 1;
   __syncthreads();
   if (!s_last) return;
-  for (int e = threadIdx.x; e < gh * kPairs; e += kThreads) {
-    const int h = e / kPairs, c = 2 * (e % kPairs);
-    const float* base = a.ws_partial + (head0 + h) * (size_t)n_slots * (D + 2);
-    // sixteen partials at a time, their loads independent of each other; each batch brings its own
-    // reference point (online softmax over batches).  A chunk without tokens has weight 0.
-    float M = -FLT_MAX, den = 0.f;
-    v2f num = {0.f, 0.f};
-    for (int i0 = 0; i0 < n_slots; i0 += 16) {
-      v2f ml[16], acc[16];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const float* p = base + (size_t)min(i0 + u, n_slots - 1) * (D + 2);
-        ml[u] = load_device(p);
-        acc[u] = load_device(p + 2 + c);
-      }
-      float Mb = M;
-#pragma unroll
-      for (int u = 0; u < 16; ++u) Mb = fmaxf(Mb, ml[u][0]);     // a repeated partial changes nothing
-      const float keep = __builtin_amdgcn_exp2f((M - Mb) * kLog2e);
-      num *= keep;
-      den *= keep;
-      M = Mb;
-#pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const float w = i0 + u < n_slots ? __builtin_amdgcn_exp2f((ml[u][0] - M) * kLog2e) : 0.f;
-        num[0] = fmaf(w, acc[u][0], num[0]);
-        num[1] = fmaf(w, acc[u][1], num[1]);
-        den = fmaf(w, ml[u][1], den);
-      }
-    }
-    *reinterpret_cast<__half2*>(a.out + (head0 + h) * D + c) = __floats2half2_rn(num[0] / den, num[1] / den);
+  merge_partials<D, kWaves>(a.ws_partial + head0 * n_slots * (D + 2), n_slots, gh, a.out + head0 * D, nullptr);
+  // nobody looks at these any more; a replay of a recorded launch starts from here
+  if constexpr (ROW) {
+    for (int i = threadIdx.x; i < gh * a.cb * 2; i += kThreads) a.ws_words[head0 * a.cb * 2 + i] = 0;
+    if (threadIdx.x == 0) a.ws_tags[at] = 0;
   }
 }
 
-// A chunk of the fp16 tail: weights in fp32 (lane = token), then lane = (token slot, channel octet).
-template <int D>
-__device__ inline void text_values(const TileArgs& a, size_t row, int set, int chunk, float (*s_p)[kHeads],
-                                   float (*s_part)[kHeads][D], float (*s_lm)[kHeads][2]) {
+// Tokens t0 .. t1 of the fp16 tail: weights in fp32 (lane = token), then lane = (token slot, channel octet).
+// lg: logit of the set's first head and token base, pitch floats between two heads.  ready(m_ref), called behind the
+// first loads, leaves the logits in lg and the reference point of every head in m_ref.
+template <int D, bool ROW, typename Ready>
+__device__ inline void text_values(const TileArgs& a, size_t row, int set, int t0, int t1, int slot, u64 seen, int lane,
+                                   int wave, const float* lg, size_t pitch, int base, float (*s_p)[kHeads],
+                                   float (*s_part)[kHeads][D], float (*s_lm)[kHeads][2], Ready ready) {
   constexpr int kOct = D / 8, kSlots = 64 / kOct;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int n_text = a.n_text_dev ? min(max(*a.n_text_dev, 0), a.n_text) : a.n_text;
-  const int t0 = chunk * a.ct_tokens, t1 = min(t0 + a.ct_tokens, n_text);
   const int gh = min(kHeads, a.g - set * kHeads);
   const size_t head0 = row * a.g + (size_t)set * kHeads;
-  const size_t n_all = (size_t)a.n_vis + a.n_text;
   const __half* vals = a.v_text + row * (size_t)a.n_text_cap * D;
+  const int c8 = lane & (kOct - 1), ts = lane / kOct;
+  constexpr int kLoads = kTextShare / kSlots;                  // a share's loads are in flight together
+  v8h v[kLoads];
+  auto load_share = [&](int t) {               // past the end: the last token, which gets weight 0
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i)
+      v[i] = *reinterpret_cast<const v8h*>(vals + (size_t)min(t + i * kSlots + ts, t1 - 1) * D + 8 * c8);
+  };
+  const int first = t0 + kTextShare * wave;
+  constexpr bool kEarly = D == 64;             // (registers)
+  if (kEarly && first < t1) load_share(first);
   float m_ref[kHeads], l[kHeads], acc[kHeads][8];
+  ready(m_ref);
 #pragma unroll
   for (int h = 0; h < kHeads; ++h) {
-    const float* mm = a.ws_minmax + (head0 + min(h, gh - 1)) * (size_t)(a.ca + a.ct) * 2;
-    m_ref[h] = t1 > t0 ? mm[(a.ca + chunk) * 2 + 1] : -FLT_MAX;   // an empty chunk has weight 0
+    if (t1 <= t0) m_ref[h] = -FLT_MAX;         // an empty chunk has weight 0
     l[h] = 0.f;
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[h][j] = 0.f;
   }
-  const int c8 = lane & (kOct - 1), ts = lane / kOct;
-  constexpr int kLoads = kTextShare / kSlots;                  // a share's loads are in flight together
-  for (int t = t0 + kTextShare * wave; t < t1; t += kTextBlock) {
+  for (int t = first; t < t1; t += kTextBlock) {
     const int nt = min(kTextShare, t1 - t);
-    v8h v[kLoads];
-#pragma unroll
-    for (int i = 0; i < kLoads; ++i)           // past the end: the last token, which gets weight 0
-      v[i] = *reinterpret_cast<const v8h*>(vals + (size_t)(t + min(i * kSlots + ts, nt - 1)) * D + 8 * c8);
+    if (!kEarly) load_share(t);
     v4f p = {0.f, 0.f, 0.f, 0.f};
     if (lane < nt) {
 #pragma unroll
       for (int h = 0; h < kHeads; ++h)
-        if (h < gh)
-          p[h] = __builtin_amdgcn_exp2f((a.ws_logits[(head0 + h) * n_all + a.n_vis + t + lane] - m_ref[h]) * kLog2e);
+        if (h < gh) p[h] = __builtin_amdgcn_exp2f((lg[h * pitch + (t - base) + lane] - m_ref[h]) * kLog2e);
     }
 #pragma unroll
     for (int h = 0; h < kHeads; ++h) l[h] += p[h];
@@ -535,6 +531,7 @@ __device__ inline void text_values(const TileArgs& a, size_t row, int set, int c
         for (int u = 0; u < 8; ++u) acc[h][u] = fmaf(w[h], (float)v[i][u], acc[h][u]);
     }
     __builtin_amdgcn_wave_barrier();
+    if (kEarly && t + kTextBlock < t1) load_share(t + kTextBlock);
   }
   // sum over the token slots; the paired folds leave one head per half or row of the wave
   if constexpr (D == 256) {                    // two slots: lanes 0-31 and 32-63
@@ -568,7 +565,10 @@ __device__ inline void text_values(const TileArgs& a, size_t row, int set, int c
   }
   const float lw = head_sums(l, lane);
   if ((lane & 15) == 0) { s_lm[wave][lane >> 4][0] = lw; s_lm[wave][lane >> 4][1] = 0.f; }
-  finish_chunk<D>(a, row, set, head0, gh, a.cb + chunk, m_ref, s_part, s_lm);
+  finish_chunk<D, ROW>(a, row, set, head0, gh, slot, seen, m_ref, s_part, s_lm);
+}
+__device__ inline int text_length(const TileArgs& a) {
+  return a.n_text_dev ? min(max(*a.n_text_dev, 0), a.n_text) : a.n_text;
 }
 
 // a * b + the bias of the four signed base-256 digits: as an integer ^ 0x00808080 its bytes are the digits.
@@ -609,41 +609,40 @@ struct Scales {
   }
 };
 
-// grid: x = row, y = chunk of the tail, then chunk of the visual tokens, z = head set
-template <int D, int BITS, bool VCH>
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(D == 256 || BITS == 8 ? 2 : D == 128 && BITS >= 2 && VCH ? 3 : 4)))
-tile_values_kernel(const TileArgs a) {
-  constexpr int CB = D * BITS / 8;                             // code bytes per token
-  constexpr int kV = 8 / BITS;
-  constexpr int kBlocks = CB >= 16 ? CB / 16 : 1;              // 16-byte column blocks (8 bytes: half of one)
-  constexpr int NACC = kBlocks * kV;
-  constexpr int SW = CB < 128 ? CB : 128;                      // bytes per token staged at a time
-  constexpr int kPasses = CB / SW;
-  constexpr int kPitch = SW >= 64 ? SW + 16 : SW;              // spreads the transposing reads over the banks
-  constexpr int kPieces = SW >= 16 ? SW / 16 : 1;              // 16-byte (8-byte) loads per lane and pass
-  constexpr int kPieceBytes = SW >= 16 ? 16 : 8;
+// What a wave of the values pass stages, and what the workgroup's waves leave for its end.
+template <int D, int BITS>
+struct ValueLds {
+  static constexpr int CB = D * BITS / 8;                      // code bytes per token
+  static constexpr int SW = CB < 128 ? CB : 128;               // bytes per token staged at a time
+  static constexpr int kPitch = SW >= 64 ? SW + 16 : SW;       // spreads the transposing reads over the banks
   struct Stage { uint8_t x[1024]; uint8_t codes[64 * kPitch]; };
   union Mem {
     Stage stage[kWaves];
     float part[kWaves][kHeads][D];
+    uint8_t key_operand[kWaves][Operand<D, BITS>::kProducts * 1024];     // tile_row_kernel: before the values
   };
-  __shared__ __align__(16) Mem mem;
-  __shared__ __align__(16) float s_lm[kWaves][kHeads][2];
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const size_t row = blockIdx.x;
-  const int set = (int)blockIdx.z, chunk = (int)blockIdx.y - a.ct;
-  if (chunk < 0) {
-    __shared__ __align__(16) float s_tp[kTextBlock][kHeads];
-    text_values<D>(a, row, set, (int)blockIdx.y, s_tp, mem.part, s_lm);
-    return;
-  }
+};
+
+// Value tiles u0 .. u1 of a row: weights and values, one partial of the joint softmax.  logits: of the set's first
+// head and token base, pitch floats between two heads (ROW: in LDS).  extrema(lo, hi), called behind the first loads,
+// gives lane row h those of head h; false: not yet, the workgroup has to form them itself.
+template <int D, int BITS, bool VCH, bool ROW, typename Extrema>
+__device__ inline bool visual_values(const TileArgs& a, size_t row, int set, int u0, int u1, int slot, u64 seen, int lane,
+                                     int wave, const float* logits, size_t pitch, int base,
+                                     typename ValueLds<D, BITS>::Mem& mem, float (*s_lm)[kHeads][2], Extrema extrema) {
+  constexpr int CB = D * BITS / 8;                             // code bytes per token
+  constexpr int kV = 8 / BITS;
+  constexpr int kBlocks = CB >= 16 ? CB / 16 : 1;              // 16-byte column blocks (8 bytes: half of one)
+  constexpr int NACC = kBlocks * kV;
+  constexpr int SW = ValueLds<D, BITS>::SW, kPitch = ValueLds<D, BITS>::kPitch;
+  constexpr int kPasses = CB / SW;
+  constexpr int kPieces = SW >= 16 ? SW / 16 : 1;              // 16-byte (8-byte) loads per lane and pass
+  constexpr int kPieceBytes = SW >= 16 ? 16 : 8;
   const int n16 = lane & 15, kb = lane >> 4;
   const int gh = min(kHeads, a.g - set * kHeads);
   const size_t head0 = row * a.g + (size_t)set * kHeads;
-  const size_t n_all = (size_t)a.n_vis + a.n_text;
 
   // the wave's run of tiles
-  const int u0 = chunk_first(a.cb_base, a.cb_rem, chunk), u1 = chunk_first(a.cb_base, a.cb_rem, chunk + 1);
   const int per = (u1 - u0) / kWaves, rem = (u1 - u0) % kWaves;
   const int k0 = u0 + chunk_first(per, rem, wave), k1 = u0 + chunk_first(per, rem, wave + 1);
 
@@ -653,7 +652,7 @@ tile_values_kernel(const TileArgs a) {
   const size_t meta0 = VCH ? row * (size_t)a.v_groups * D : 0;
   const float* lg[kHeads];
 #pragma unroll
-  for (int h = 0; h < kHeads; ++h) lg[h] = a.ws_logits + (head0 + min(h, gh - 1)) * n_all;
+  for (int h = 0; h < kHeads; ++h) lg[h] = logits + min(h, gh - 1) * pitch;
   uint8_t* xbuf = mem.stage[wave].x;
   uint8_t* cbuf = mem.stage[wave].codes;
   const uint8_t* x_rd = xbuf + (kb * 16 + (n16 >> 1)) * 16 + (n16 & 1) * 8;
@@ -711,8 +710,10 @@ tile_values_kernel(const TileArgs a) {
     int grp, tok0, nt;
     tile_at(k, grp, tok0, nt);
     const int j = tok0 + min(lane, nt - 1);
+    if constexpr (!ROW) {
 #pragma unroll
-    for (int h = 0; h < kHeads; ++h) lgv[h] = lg[h][j];
+      for (int h = 0; h < kHeads; ++h) lgv[h] = lg[h][j - base];
+    }
     if constexpr (!VCH) {
       sc = vs[j];
       mi = vm[j];
@@ -735,35 +736,29 @@ tile_values_kernel(const TileArgs a) {
     load_tile(k0);
     load_params(part_of(k0, a.v_tpg));
   }
-  // ---- calibration line and reference point per head (Sec. 3.2): lane 16 h + c folds chunks c,
-  // c + 16, ... of head h
+  // ---- calibration line and reference point per head (Sec. 3.2)
   float a2[kHeads], c2[kHeads], m_ref[kHeads];
   {
-    const float* mm = a.ws_minmax + (head0 + min(kb, gh - 1)) * (size_t)(a.ca + a.ct) * 2;
-    float lo_l = FLT_MAX, hi_l = -FLT_MAX;
-    for (int c = n16; c < a.ca; c += 16) {
-      lo_l = fminf(lo_l, mm[2 * c]);
-      hi_l = fmaxf(hi_l, mm[2 * c + 1]);
+    float lo_l, hi_l;
+    if (!extrema(lo_l, hi_l)) return false;
+    // (the lanes of row h work on head h: one division for all four)
+    float slope = 1.f, gam = 0.f, shift = 0.f;                 // s' = slope * (s - gam) + shift
+    if (a.calib_mode != CQ_CALIB_NONE) {
+      const float glo = a.calib_mode == CQ_CALIB_DYNAMIC ? lo_l : a.gamma;
+      const float ghi = a.calib_mode == CQ_CALIB_DYNAMIC ? hi_l : a.delta;
+      const float width = ghi - glo;
+      slope = width == 0.f ? 1.f : (width + a.tau1 - a.tau2) / width;
+      gam = glo;
+      shift = glo - a.tau1;
     }
-    lo_l = row_min(lo_l);
-    hi_l = row_max(hi_l);
+    // the map is monotone: an end of the row's range is its maximum, every weight is <= 1
+    const float M = fmaxf(slope * (lo_l - gam) + shift, slope * (hi_l - gam) + shift);
+    const float c = (shift - slope * gam - M) * kLog2e;
 #pragma unroll
     for (int h = 0; h < kHeads; ++h) {
-      const float lo = lane_value(lo_l, 16 * h), hi = lane_value(hi_l, 16 * h);
-      float slope = 1.f, gam = 0.f, shift = 0.f;               // s' = slope * (s - gam) + shift
-      if (a.calib_mode != CQ_CALIB_NONE) {
-        const float glo = a.calib_mode == CQ_CALIB_DYNAMIC ? lo : a.gamma;
-        const float ghi = a.calib_mode == CQ_CALIB_DYNAMIC ? hi : a.delta;
-        const float width = ghi - glo;
-        slope = width == 0.f ? 1.f : (width + a.tau1 - a.tau2) / width;
-        gam = glo;
-        shift = glo - a.tau1;
-      }
-      // the map is monotone: an end of the row's range is its maximum, every weight is <= 1
-      const float M = fmaxf(slope * (lo - gam) + shift, slope * (hi - gam) + shift);
-      m_ref[h] = M;
-      a2[h] = h < gh ? slope * kLog2e : 0.f;
-      c2[h] = h < gh ? (shift - slope * gam - M) * kLog2e : -200.f;     // no head: weight 0
+      m_ref[h] = lane_value(M, 16 * h);
+      a2[h] = h < gh ? lane_value(slope, 16 * h) * kLog2e : 0.f;
+      c2[h] = h < gh ? lane_value(c, 16 * h) : -200.f;         // no head: weight 0
     }
   }
 
@@ -789,6 +784,11 @@ tile_values_kernel(const TileArgs a) {
   for (int k = k0; k < k1; ++k) {
     int grp, tok0, nt;
     tile_at(k, grp, tok0, nt);
+    if constexpr (ROW) {                       // (on chip: read when they are needed)
+      const int j = tok0 + min(lane, nt - 1);
+#pragma unroll
+      for (int h = 0; h < kHeads; ++h) lgv[h] = lg[h][j - base];
+    }
     const bool have = lane < nt, next_group = VCH && grp != params_of;         // (the latter wave-uniform)
     float w[kHeads], x[kHeads];
 #pragma unroll
@@ -870,7 +870,200 @@ tile_values_kernel(const TileArgs a) {
   }
   const float l = head_sums(lsum, lane), m = head_sums(msum, lane);      // of head kb
   if (n16 == 0) { s_lm[wave][kb][0] = l; s_lm[wave][kb][1] = m; }
-  finish_chunk<D>(a, row, set, head0, gh, chunk, m_ref, mem.part, s_lm);
+  finish_chunk<D, ROW>(a, row, set, head0, gh, slot, seen, m_ref, mem.part, s_lm);
+  return true;
+}
+
+// grid: x = row, y = chunk of the tail, then chunk of the visual tokens, z = head set
+template <int D, int BITS, bool VCH>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(D == 256 || BITS == 8 ? 2 : D == 128 && BITS >= 2 && VCH ? 3 : 4)))
+tile_values_kernel(const TileArgs a) {
+  __shared__ __align__(16) typename ValueLds<D, BITS>::Mem mem;
+  __shared__ __align__(16) float s_lm[kWaves][kHeads][2];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const size_t row = blockIdx.x;
+  const int set = (int)blockIdx.z, chunk = (int)blockIdx.y - a.ct;
+  const int gh = min(kHeads, a.g - set * kHeads);
+  const size_t head0 = row * a.g + (size_t)set * kHeads, n_all = (size_t)a.n_vis + a.n_text;
+  if (chunk < 0) {
+    __shared__ __align__(16) float s_tp[kTextBlock][kHeads];
+    const int t0 = (int)blockIdx.y * a.ct_tokens, t1 = min(t0 + a.ct_tokens, text_length(a));
+    text_values<D, false>(a, row, set, t0, t1, a.cb + (int)blockIdx.y, 0, lane, wave, a.ws_logits + head0 * n_all + a.n_vis,
+                   n_all, 0, s_tp, mem.part, s_lm, [&](float (&m_ref)[kHeads]) {
+#pragma unroll
+      for (int h = 0; h < kHeads; ++h)
+        m_ref[h] = a.ws_minmax[((head0 + min(h, gh - 1)) * (size_t)(a.ca + a.ct) + a.ca + blockIdx.y) * 2 + 1];
+    });
+    return;
+  }
+  const int u0 = chunk_first(a.cb_base, a.cb_rem, chunk), u1 = chunk_first(a.cb_base, a.cb_rem, chunk + 1);
+  visual_values<D, BITS, VCH, false>(a, row, set, u0, u1, chunk, 0, lane, wave, a.ws_logits + head0 * n_all, n_all, 0, mem,
+                                     s_lm, [&](float& lo, float& hi) {
+    // lane 16 h + c folds chunks c, c + 16, ... of head h
+    const float* mm = a.ws_minmax + (head0 + min(lane >> 4, gh - 1)) * (size_t)(a.ca + a.ct) * 2;
+    lo = FLT_MAX;
+    hi = -FLT_MAX;
+    for (int c = lane & 15; c < a.ca; c += 16) {
+      lo = fminf(lo, mm[2 * c]);
+      hi = fmaxf(hi, mm[2 * c + 1]);
+    }
+    lo = row_min(lo);
+    hi = row_max(hi);
+    return true;
+  });
+}
+
+// ===================================================================================== one launch
+// The logits of a chunk of visual tokens stay in LDS, the workgroups of a row exchange their extrema
+// (decode_meet.h); a chunk of the tail needs nothing from anybody.  Against the two launches above it saves the
+// second one's start, the round trip of the logits through memory and the tail's second query: 64 rows x 3003
+// tokens, 2 bits, whole-sequence keys and values 15.5 -> 13.2 us, 8 such rows 11.5 -> 10.3, 16 rows x 3328 tokens of
+// 256 channels 12.2 -> 11.3, 256 rows x 8001 55.2 -> 47.6.
+// grid: the slots of a (row, head set) one after the other, chunks of the tail first
+extern __shared__ __align__(16) float s_logits[];              // [kHeads][l_stride]
+template <int D, int BITS, bool VCH>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(D == 256 || BITS == 8 ? 2 : D == 128 && BITS >= 2 && VCH ? 3 : 4)))
+tile_row_kernel(const TileArgs args) {
+  __shared__ __align__(16) typename ValueLds<D, BITS>::Mem mem;
+  __shared__ __align__(16) float s_lm[kWaves][kHeads][2];
+  __shared__ float red[kWaves][kHeads][2];
+  __shared__ float s_row[kHeads][2];
+  __shared__ int s_found;
+  float row_lo = FLT_MAX, row_hi = -FLT_MAX;                   // lane row h: extrema of head h, passes so far
+  u64 seen = 0;
+  // one pass over the workgroup's own chunk; if the others' extrema do not turn up, one over each of theirs
+  for (int pass = 0;; ++pass) {
+    int tid = threadIdx.x;                     // (arguments and lane out of the compiler's sight: see decode_fused.hip)
+    auto kernarg = __builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+v"(tid), "+s"(kernarg));
+    const TileArgs& a = *(const TileArgs*)kernarg;
+    // the arguments' cache lines, together
+    asm volatile("" :: "s"(a.q), "s"(a.k_text), "s"(a.k_group), "s"(a.l_stride), "s"(a.patience));
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n16 = lane & 15, kb = lane >> 4;
+    const int n_slots = a.cb + a.ct;
+    const int rs = a.slots_magic ? (int)__umulhi((unsigned)blockIdx.x, a.slots_magic) : (int)blockIdx.x;
+    const int slot = (int)blockIdx.x - rs * n_slots;
+    const size_t row = a.sets == 1 ? rs : rs / a.sets;
+    const int set = a.sets == 1 ? 0 : rs % a.sets;
+    const int gh = min(kHeads, a.g - set * kHeads);
+    const size_t head0 = row * a.g + (size_t)set * kHeads;
+    if (pass == 0 && tid == 0 && n_slots > 1) seen = count_open(a.ws_tags + row * a.sets + set, a.tag);
+    if (slot < a.ct) {
+      __shared__ __align__(16) float s_tp[kTextBlock][kHeads];
+      const int t0 = slot * a.ct_tokens, t1 = min(t0 + a.ct_tokens, text_length(a));
+      text_values<D, true>(a, row, set, t0, t1, slot, seen, lane, wave, s_logits, a.l_stride, t0, s_tp, mem.part, s_lm,
+                     [&](float (&m_ref)[kHeads]) {
+        // the logits of the shares that this wave weights, on the fp16 matrix cores as in text_logits
+        v8h A[D / 32];
+#pragma unroll
+        for (int s = 0; s < D / 32; ++s)       // (matrix rows from gh on repeat the last head)
+          A[s] = *reinterpret_cast<const v8h*>(a.q + (head0 + min(n16, gh - 1)) * D + 32 * s + 8 * kb);
+        float mx[kHeads];
+#pragma unroll
+        for (int h = 0; h < kHeads; ++h) mx[h] = -FLT_MAX;
+        const __half* keys = a.k_text + row * (size_t)a.n_text_cap * D + 8 * kb;
+        constexpr int kFly = kTextShare / 16;
+        for (int t = t0 + kTextShare * wave; t < t1; t += kTextBlock) {
+          v8h kv[kFly][D / 32];
+#pragma unroll
+          for (int u = 0; u < kFly; ++u)
+#pragma unroll
+            for (int s = 0; s < D / 32; ++s)
+              kv[u][s] = *reinterpret_cast<const v8h*>(keys + (size_t)min(t + 16 * u + n16, t1 - 1) * D + 32 * s);
+#pragma unroll
+          for (int u = 0; u < kFly; ++u) {
+            v4f c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < D / 32; ++s) c = __builtin_amdgcn_mfma_f32_16x16x32_f16(A[s], kv[u][s], c, 0, 0, 0);
+            if (kb == 0) {                     // result rows 0..3; past the end: the last token again
+#pragma unroll
+              for (int h = 0; h < kHeads; ++h) {
+                const float x = c[h] * a.softmax_scale;
+                s_logits[h * a.l_stride + t - t0 + 16 * u + n16] = x;
+                mx[h] = fmaxf(mx[h], x);
+              }
+            }
+          }
+        }
+#pragma unroll
+        for (int h = 0; h < kHeads; ++h) {
+          const float m = row_max(mx[h]);
+          if (lane == 0) red[wave][h][1] = m;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int h = 0; h < kHeads; ++h) {
+          m_ref[h] = red[0][h][1];
+#pragma unroll
+          for (int w = 1; w < kWaves; ++w) m_ref[h] = fmaxf(m_ref[h], red[w][h][1]);
+        }
+      });
+      return;
+    }
+    const int own = slot - a.ct;
+    int chunk = own + pass;
+    if (chunk >= a.cb) chunk -= a.cb;
+    const int u0 = chunk_first(a.cb_base, a.cb_rem, chunk), u1 = chunk_first(a.cb_base, a.cb_rem, chunk + 1);
+    if (pass <= a.cb - 1) {                    // (pass cb: all extrema are known, the logits in place)
+      float mn = FLT_MAX, mx = -FLT_MAX;
+      visual_logits<D, BITS>(a, row, set, min(u0 * a.k_bpu, a.k_blocks), min(u1 * a.k_bpu, a.k_blocks), lane, wave,
+                             mem.key_operand[wave], chunk == own, s_logits + kb * a.l_stride, u0 * kUnit, mn, mx);
+      mn = row_min(mn);
+      mx = row_max(mx);
+      __builtin_amdgcn_wave_barrier();
+      if (n16 == 0) {
+        red[wave][kb][0] = mn;
+        red[wave][kb][1] = mx;
+      }
+      __syncthreads();
+      row_lo = fminf(row_lo, row_min(red[n16 & (kWaves - 1)][kb][0]));
+      row_hi = fmaxf(row_hi, row_max(red[n16 & (kWaves - 1)][kb][1]));
+      if (pass > 0) { __syncthreads(); continue; }
+      // stored now: what comes before the others' are needed hides the way there
+      if (a.calib_mode == CQ_CALIB_DYNAMIC && a.cb > 1 && wave == 0 && n16 == 0 && kb < gh)
+        post_extrema(a.ws_words + ((head0 + kb) * (size_t)a.cb + own) * 2, row_lo, row_hi, a.tag);
+    }
+    const bool done = visual_values<D, BITS, VCH, true>(
+        a, row, set, min(u0 * a.v_tpu, a.v_tiles), min(u1 * a.v_tpu, a.v_tiles), slot, seen, lane, wave,
+        s_logits, a.l_stride, u0 * kUnit, mem, s_lm, [&](float& lo, float& hi) {
+      lo = row_lo;
+      hi = row_hi;
+      if (a.calib_mode != CQ_CALIB_DYNAMIC || a.cb == 1 || pass > 0) return true;
+      if (wave == 0) {
+        const u64* words = a.ws_words + (head0 + min(kb, gh - 1)) * (size_t)a.cb * 2;
+        float all_lo = FLT_MAX, all_hi = -FLT_MAX;
+        bool all = false;
+        for (int look = 0; !all && look < a.patience; ++look) {
+          all_lo = lo;
+          all_hi = hi;
+          all = true;
+          for (int c = n16; c < a.cb; c += 16) {
+            if (c == own) continue;
+            float x, y;
+            all = read_extrema(words + 2 * c, &x, &y, a.tag) && all;
+            all_lo = fminf(all_lo, x);
+            all_hi = fmaxf(all_hi, y);
+          }
+          all = __builtin_amdgcn_ballot_w64(!all) == 0;
+          if (!all) __builtin_amdgcn_s_sleep(1);
+        }
+        all_lo = row_min(all_lo);
+        all_hi = row_max(all_hi);
+        if (n16 == 0) {
+          s_row[kb][0] = all_lo;
+          s_row[kb][1] = all_hi;
+        }
+        if (lane == 0) s_found = all;
+      }
+      __syncthreads();
+      if (!s_found) { __syncthreads(); return false; }
+      lo = s_row[kb][0];
+      hi = s_row[kb][1];
+      return true;
+    });
+    if (done) return;
+  }
 }
 
 using TileKernel = void (*)(const TileArgs);
@@ -898,6 +1091,61 @@ TileKernel values_kernel(int bits, bool vch) {
     case 17: return tile_values_kernel<D, 8, true>;
     default: return nullptr;
   }
+}
+
+template <int D>
+TileKernel row_kernel(int bits, bool vch) {
+  switch (bits * 2 + (vch ? 1 : 0)) {
+    case 2: return tile_row_kernel<D, 1, false>;
+    case 3: return tile_row_kernel<D, 1, true>;
+    case 4: return tile_row_kernel<D, 2, false>;
+    case 5: return tile_row_kernel<D, 2, true>;
+    case 8: return tile_row_kernel<D, 4, false>;
+    case 9: return tile_row_kernel<D, 4, true>;
+    case 16: return tile_row_kernel<D, 8, false>;
+    case 17: return tile_row_kernel<D, 8, true>;
+    default: return nullptr;
+  }
+}
+
+}  // namespace
+
+namespace {
+
+// One launch where chunks of whole units can be made of whole key blocks and value tiles, and their logits take
+// little enough LDS for several workgroups per CU.  It is faster on small calls of every head_dim (100 drawn
+// layouts below 100 thousand tokens: 1.06 with 64 channels, 1.2 with 128, 1.17 with 256) and with 128 channels on large
+// ones too (1.3 beyond 600 thousand).  With 64 and 256 channels it is not: all workgroups pass the exchange
+// together, so memory and matrix cores idle in turn (64 rows of 64 channels x 3328 tokens, two / one: 13.6 / 12.8 us,
+// x 8192 17.9 / 18.5; 480 rows of 256 channels x 4352 77 / 99), the more so in key groups of 32, which leave a wave a
+// short block.  768 workgroups: three per CU are resident whatever the registers (256 rows x 2001, 1024 / 768:
+// 21.3 / 18.6); chunks below four units only lengthen the exchange and the merge (64 rows x 3003: 23.6 us with
+// two, 14.9 with four), and more than 56 chunks of a row cost more than they save (8 rows x 60608 25.8 / 31.2).
+void plan_one_launch(const DecodeShape& s, long long rows, long long sets, TilePlan* p) {
+  auto fits_units = [&](int axis, int group) {
+    return axis != CQ_AXIS_CHANNEL || group == s.n_vis || group % kUnit == 0 || kUnit % group == 0;
+  };
+  const int units = ceil_div(s.n_vis, kUnit);
+  p->row_ct = p->ct;
+  if (s.d != 128 && (s.n_vis > kRowMost || rows * sets * s.n_vis > kRowMostAll || (s.k_group < 64 && s.k_group != s.n_vis)))
+    return;
+  if (s.n_vis > 0) {
+    if (!fits_units(s.k_axis, s.k_group) || !fits_units(s.v_axis, s.v_group)) return;
+    const long long want = (kRowTarget + rows * sets - 1) / (rows * sets);
+    const int least = ceil_div(units, kRowMaxUnits), most = ceil_div(units, kRowMinUnits);
+    if (least > kRowMostChunks) return;
+    p->row_cb = (int)(want < least ? least : want > most ? most : want);
+    if (p->row_cb > kRowMostChunks) p->row_cb = kRowMostChunks;
+  }
+  if (p->ct_tokens > kRowMaxUnits * kUnit) return;
+  const long long slots = p->row_cb + p->row_ct;
+  if (slots < 1 || rows * sets * slots * slots >= (1LL << 32)) return;
+  auto align64 = [](size_t x) { return (x + 63) / 64 * 64; };
+  const size_t heads = (size_t)s.B * s.Hq;
+  p->row_tags_floats = align64(heads * (size_t)p->row_cb * 4);
+  p->row_partial_floats = align64(p->row_tags_floats + (size_t)(rows * sets) * 2);
+  const size_t floats = p->row_partial_floats + heads * (size_t)slots * (s.d + 2);
+  p->one_launch = floats * sizeof(float) <= p->ws_bytes;
 }
 
 }  // namespace
@@ -950,6 +1198,7 @@ TilePlan make_tile_plan(const DecodeShape& s, size_t limit) {
     }
     p.ws_bytes = lay_out(p.ct);
   }
+  plan_one_launch(s, rows, sets, &p);
   // grid: rows x chunks x head sets
   p.ok = fits && rows * sets * 2 * kMaxTileChunks < 0x7fffffffLL && sets <= 65535;
   return p;
@@ -974,7 +1223,7 @@ hipError_t start_logits(TileArgs& a, const DecodeShape& s, const TilePlan& plan,
   a.k_text = static_cast<const __half*>(k_text);
   a.g = s.g; a.sets = ceil_div(s.g, kHeads); a.n_vis = s.n_vis; a.n_text = s.n_text;
   a.n_text_cap = s.n_text_cap; a.n_text_dev = n_text_dev;
-  a.k_group = s.k_group; a.k_bpg = ceil_div(s.k_group, kKeyBlock);
+  a.k_group = s.k_group; a.k_block = kKeyBlock; a.k_bpg = ceil_div(s.k_group, kKeyBlock);
   a.ca = plan.ca; a.ct = plan.ct; a.ct_tokens = plan.ct_tokens;
   if (s.n_vis > 0) {
     a.k_groups = s.n_vis / s.k_group;
@@ -1004,10 +1253,63 @@ hipError_t launch_tile_logits(const DecodeShape& s, const TilePlan& plan, const 
   return start_logits(a, s, plan, q, k, k_text, nullptr, softmax_scale, logits, minmax, stream);
 }
 
+namespace {
+
+hipError_t launch_tile_rows(const DecodeShape& s, const TilePlan& plan, const void* q, const cq_qtensor_t& k,
+                            const cq_qtensor_t& v, const void* k_text, const void* v_text, const int32_t* n_text_dev,
+                            const Calib& calib, float softmax_scale, void* out, float* workspace, hipStream_t stream) {
+  TileArgs a{};
+  const bool vch = s.v_axis == CQ_AXIS_CHANNEL;
+  a.q = static_cast<const __half*>(q);
+  a.k_codes = k.codes; a.k_scale = k.scale; a.k_min = k.min;
+  a.v_codes = v.codes; a.v_scale = v.scale; a.v_min = v.min;
+  a.k_text = static_cast<const __half*>(k_text);
+  a.v_text = static_cast<const __half*>(v_text);
+  a.out = static_cast<__half*>(out);
+  a.g = s.g; a.sets = ceil_div(s.g, kHeads); a.n_vis = s.n_vis; a.n_text = s.n_text;
+  a.n_text_cap = s.n_text_cap; a.n_text_dev = n_text_dev;
+  a.cb = plan.row_cb; a.ct = plan.row_ct; a.ct_tokens = plan.ct_tokens;
+  int tokens = plan.ct > 0 ? plan.ct_tokens : 0;               // of the longest chunk
+  if (s.n_vis > 0) {
+    const int units = ceil_div(s.n_vis, kUnit), per_chunk = ceil_div(units, a.cb);
+    a.cb_base = units / a.cb; a.cb_rem = units % a.cb;
+    // a block of keys per wave where a chunk is short
+    a.k_block = per_chunk >= kWaves ? kKeyBlock : per_chunk > 1 ? kKeyBlock / 2 : kKeyBlock / 4;
+    a.k_group = s.k_group; a.k_bpg = ceil_div(s.k_group, a.k_block); a.k_groups = s.n_vis / s.k_group;
+    a.k_blocks = a.k_groups * a.k_bpg;
+    a.k_bpu = s.k_group < kUnit && s.k_group != s.n_vis ? kUnit / s.k_group * a.k_bpg : kUnit / a.k_block;
+    a.v_group = vch ? s.v_group : s.n_vis; a.v_tpg = ceil_div(a.v_group, kValTile); a.v_groups = s.n_vis / a.v_group;
+    a.v_tiles = a.v_groups * a.v_tpg;
+    a.v_tpu = a.v_group < kUnit && a.v_group != s.n_vis ? kUnit / a.v_group * a.v_tpg : kUnit / kValTile;
+    if (per_chunk * kUnit > tokens) tokens = per_chunk * kUnit;
+  }
+  a.l_stride = (tokens + 63) / 64 * 64 + 16;                   // four heads' rows of 16 lanes on different banks
+  a.softmax_scale = softmax_scale;
+  a.calib_mode = calib.mode; a.tau1 = calib.tau1; a.tau2 = calib.tau2;
+  a.gamma = calib.gamma; a.delta = calib.delta;
+  a.ws_words = reinterpret_cast<u64*>(workspace);
+  a.ws_tags = reinterpret_cast<u64*>(workspace + plan.row_tags_floats);
+  a.ws_partial = workspace + plan.row_partial_floats;
+  a.tag = meeting_tag();
+  a.patience = plan.patience;
+  const unsigned slots = (unsigned)(a.cb + a.ct);
+  a.slots_magic = slots == 1 ? 0u : (unsigned)((1ull << 32) / slots + 1);
+  const TileKernel kern = s.d == 64 ? row_kernel<64>(s.bits, vch)
+                          : s.d == 128 ? row_kernel<128>(s.bits, vch) : row_kernel<256>(s.bits, vch);
+  if (!kern) return hipErrorInvalidValue;
+  const size_t blocks = (size_t)s.B * s.Hkv * a.sets * slots;
+  kern<<<dim3((unsigned)blocks), dim3(kThreads), (size_t)kHeads * a.l_stride * sizeof(float), stream>>>(a);
+  return hipGetLastError();
+}
+
+}  // namespace
+
 hipError_t launch_decode_tile(const DecodeShape& s, const TilePlan& plan, const void* q,
                               const cq_qtensor_t& k, const cq_qtensor_t& v, const void* k_text,
                               const void* v_text, const int32_t* n_text_dev, const Calib& calib,
                               float softmax_scale, void* out, float* workspace, hipStream_t stream) {
+  if (plan.ok && plan.one_launch)
+    return launch_tile_rows(s, plan, q, k, v, k_text, v_text, n_text_dev, calib, softmax_scale, out, workspace, stream);
   TileArgs a{};
   a.ws_count = reinterpret_cast<int*>(workspace + plan.ws_count_floats);
   a.out = static_cast<__half*>(out);

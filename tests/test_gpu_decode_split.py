@@ -130,3 +130,43 @@ def test_rows_spread_over_idle_compute_units(args, shared):
         got = cq.cq_decode_attn(lay, dev["q"], k, v, dev["k_text"], dev["v_text"], n_text, calib, 0.0, None, ws)
         err = O.rel_l2(got.cpu().numpy().astype(np.float64), ref)
         assert err <= H.REGRESSION_TOL, (n_bytes, err)
+
+
+# Tile kernels in one launch: (B, Hq, Hkv, head_dim, n_vis, n_text, bits, key group, value axis, value group).  Chunks that
+# end inside a unit of 128 tokens, one unit, one chunk, groups of a part of a unit, several sets of heads, no
+# visual tokens, a tail of several chunks
+TILES = [(2, 8, 2, 128, 3003, 77, 2, 3003, 0, 3003), (1, 4, 4, 64, 4096, 100, 1, 64, 1, 64), (1, 6, 1, 256, 1003, 4, 8, 1003, 1, 256),
+         (1, 4, 1, 64, 100, 0, 4, 100, 0, 100), (2, 10, 2, 128, 1537, 300, 1, 1537, 0, 1537), (1, 2, 2, 64, 0, 700, 1, 64, 1, 64),
+         (1, 3, 1, 64, 1984, 5, 2, 64, 0, 32), (1, 4, 1, 256, 2048, 129, 1, 128, 0, 256), (1, 1, 1, 128, 777, 1, 8, 777, 1, 128)]
+
+
+@pytest.mark.parametrize("shape", TILES)
+def test_tile_kernels_in_one_launch(shape):
+    B, n_q, n_kv, d, n, n_text, bits, k_group, v_axis, v_group = shape
+    w = synth.WORKLOADS[1].replace(batch=B, n_q_heads=n_q, n_kv_heads=n_kv, head_dim=d, n_vis=n, n_text=max(n_text, 1), seed=n + d)
+    x = synth.make_inputs(w, "cpu")
+    lay = cq.make_layout(B, n_q, n_kv, d, n, bits, 0, v_axis, k_group, v_group)
+    dev = {k: t.cuda() for k, t in x.items()}
+    k, v = cq.cq_quantize_kv(lay, dev["k"], dev["v"]) if n else (None, None)
+    kq = O.quantize_tensor(x["k"].numpy(), bits, 0, k_group) if n else None
+    vq = O.quantize_tensor(x["v"].numpy(), bits, v_axis, v_group) if n else None
+    calib = (O.CALIB_DYNAMIC, 1.0, 2.0)
+    if n:
+        ref = O.decode_attn(x["q"].numpy(), kq, vq, x["k_text"].numpy(), x["v_text"].numpy(), n_text, *calib)
+    else:                                                      # the oracle starts from a cache
+        q, kt, vt = (x[t].double().repeat_interleave(n_q // x[t].shape[1], 1) for t in ("q", "k_text", "v_text"))
+        ref = torch.softmax((q[:, :, None] * kt).sum(-1) / d ** 0.5, -1)[..., None].mul(vt).sum(2).numpy()
+    got = []
+    path = cq.cq_bench_set_kernel_path(cq.CQ_PATH_TILE)
+    try:
+        ws = torch.empty(cq.cq_decode_workspace_bytes(lay, n_text, cq.make_calib(*calib)), dtype=torch.uint8, device="cuda")
+        for chunks, fill in ((0, 255), (ALONE, 0), (0, 60)):
+            prev = cq.cq_bench_set_decode_chunks(chunks)
+            got.append(cq.cq_decode_attn(lay, dev["q"], k, v, dev["k_text"], dev["v_text"], n_text, cq.make_calib(*calib), 0.0,
+                                         None, ws.fill_(fill)))
+            cq.cq_bench_set_decode_chunks(prev)
+    finally:
+        cq.cq_bench_set_kernel_path(path)
+    err = O.rel_l2(got[0].cpu().numpy().astype(np.float64), ref)
+    assert err <= H.REGRESSION_TOL, err
+    assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
