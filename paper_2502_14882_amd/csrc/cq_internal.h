@@ -138,6 +138,11 @@ hipError_t launch_quantize_tuned(const QuantizeJob* jobs, int n_jobs, int rows, 
 hipError_t launch_quantize_64(const QuantizeJob* jobs, int n_jobs, size_t n_tokens, int bits, hipStream_t stream);
 hipError_t launch_quantize_256(const QuantizeJob* jobs, int n_jobs, size_t n_tokens, int bits, hipStream_t stream);
 
+// Channel-wise groups that a workgroup's registers hold (quantize_slice.hip): one or two tensors with groups of the
+// same size, in one launch.
+bool quantize_slice_supported(size_t n_tokens, int d, int bits, int axis, int group);
+hipError_t launch_quantize_slices(const QuantizeJob* jobs, int n_jobs, size_t n_tokens, int d, int bits, hipStream_t stream);
+
 // Merge the per-chunk partials [n_rows][n_chunks][d + 2] of the online softmax into out.
 hipError_t launch_combine(int n_rows, int n_chunks, int d, const float* partial, void* out,
                           hipStream_t stream);

@@ -1,0 +1,212 @@
+// Channel-wise groups that a workgroup's registers hold (gfx950): any head_dim, b in {1, 2, 4, 8}, groups of 129 to a
+// few thousand tokens - one pair per channel over the whole sequence, Sec. 3.1 as printed, on an image or two.
+//
+// The tile kernels of quantize_tile.h read such a group twice: once for its extrema, once for its codes, with launches
+// in between.  Here a workgroup owns 32 or 64 channels of a group, all its tokens: it reads them once, 64 or 128
+// bytes per token, keeps them in registers, takes extrema and thresholds in LDS, and forms the codes (steps 1 to
+// 3 of quantize_tile.h, with the same arithmetic: the same bits).  Nothing crosses workgroups, one launch does
+// both tensors, and no output buffer holds intermediate results.
+//
+// Layout.  A thread holds 8 channels (16 bytes) of every kTokens-th token; 4 or 8 lanes hold a token's piece.  The
+// slices of a group lie in the same cache lines, both where they read and where they write their codes, so they get
+// block indices 8 apart: the same XCD, at the same time, and its L2 puts the lines together.
+//
+// Bound: what a CU reads (a workgroup's loads are all out before its arithmetic begins, 16 waves to a CU) and
+// vector issue, one behind the other.  Keys and values, tile kernels / here, us: 64 rows x 3003 tokens, 2 bits
+// 45.1 / 37.8; 256 x 2000 105 / 71; 8 x 1000, 1 bit 12.1 / 4.5; 512 x 300 36.9 / 17.1; 64 x 3003 of 64 channels
+// 27.9 / 16.4.  From 4097 tokens the two are equal.
+#include <hip/hip_fp16.h>
+
+#include "cq_internal.h"
+#include "quantize_tile.h"
+
+namespace cq {
+namespace {
+
+struct SliceArgs {
+  const __half* x;
+  uint32_t* codes;
+  float* scale;
+  uint16_t* minv;
+};
+
+// the value of lane ^ 1 (0xB1) or lane ^ 2 (0x4E)
+template <int CTRL>
+__device__ inline uint32_t other_lane(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xF, 0xF, true);
+}
+
+// grid: ((group / 8) * slices + slice) * 8 + group % 8, first the one tensor's groups, then the other's
+template <int BITS, int LANES, int THREADS, int P>
+__global__ void __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(BITS <= 2 || P <= 12 ? 4 : 1)))
+quantize_slice_kernel(const SliceArgs first, const SliceArgs second, int n_first, int n_groups, int tokens, int d,
+                      int log_slices) {
+  constexpr int L = (1 << BITS) - 1, kTokens = THREADS / LANES, kSlice = 8 * LANES, kWavesQ = THREADS / 64;
+  constexpr bool kWide = BITS > 2;
+  __shared__ __align__(16) _Float16 s_part[2][kWavesQ][kSlice];
+  __shared__ __align__(16) _Float16 s_thr[kWide ? 1 : L][kSlice];
+  __shared__ __align__(16) double s_rinv[kWide ? kSlice : 1];
+  __shared__ __align__(16) _Float16 s_alpha[kSlice];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, oct = lane & (LANES - 1);
+  const int slot = (int)(blockIdx.x >> 3), slice = slot & ((1 << log_slices) - 1);
+  int group = (slot >> log_slices) * 8 + (int)(blockIdx.x & 7);
+  if (group >= n_groups) return;                // the grid is whole eights of groups
+  const bool one = group < n_first;
+  if (!one) group -= n_first;
+  const __half* xb = one ? first.x : second.x;
+  const size_t tok0 = (size_t)group * tokens;
+  const int c0 = slice * kSlice, t_lane = tid / LANES;
+  const char* src = reinterpret_cast<const char*>(xb + tok0 * d + c0 + 8 * oct);
+  v8h x[P];                                     // read exactly once
+#pragma unroll
+  for (int i = 0; i < P; ++i)                   // past the end: the last token, which changes no extremum
+    x[i] = *reinterpret_cast<const v8h*>(src + (unsigned)min(i * kTokens + t_lane, tokens - 1) * (unsigned)(2 * d));
+  // ---- 1. extrema of the slice's channels
+  v8h mn = x[0], mx = x[0];
+#pragma unroll
+  for (int i = 1; i < P; ++i) {
+    mn = __builtin_elementwise_min(mn, x[i]);
+    mx = __builtin_elementwise_max(mx, x[i]);
+  }
+  v4u mnu = __builtin_bit_cast(v4u, mn), mxu = __builtin_bit_cast(v4u, mx);
+#pragma unroll
+  for (int o = LANES; o <= 32; o <<= 1) {
+    v4u on, ox;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      on[r] = __shfl_xor(mnu[r], o);
+      ox[r] = __shfl_xor(mxu[r], o);
+    }
+    mn = __builtin_elementwise_min(mn, __builtin_bit_cast(v8h, on));
+    mx = __builtin_elementwise_max(mx, __builtin_bit_cast(v8h, ox));
+    mnu = __builtin_bit_cast(v4u, mn);
+    mxu = __builtin_bit_cast(v4u, mx);
+  }
+  if (lane < LANES) {
+    *reinterpret_cast<v8h*>(&s_part[0][wave][8 * oct]) = mn;
+    *reinterpret_cast<v8h*>(&s_part[1][wave][8 * oct]) = mx;
+  }
+  __syncthreads();
+  // ---- 2. stored parameters; a thread per (threshold, channel)
+  constexpr int kEach = kWide ? 1 : L;
+  if (tid < kEach * kSlice) {
+    const int c = tid & (kSlice - 1), k = tid / kSlice + 1;
+    _Float16 lo = s_part[0][0][c], hi = s_part[1][0][c];
+#pragma unroll
+    for (int w = 1; w < kWavesQ; ++w) {
+      lo = (_Float16)fminf((float)lo, (float)s_part[0][w][c]);
+      hi = (_Float16)fmaxf((float)hi, (float)s_part[1][w][c]);
+    }
+    const uint16_t mbits = canonical_zero(__builtin_bit_cast(uint16_t, lo));
+    const double alpha = h_to_double(mbits);
+    const double range = ((double)(float)hi - alpha) + 0.0;
+    if (k == 1) {
+      const size_t meta = (size_t)group * d + c0 + c;
+      (one ? first.scale : second.scale)[meta] = (float)(range / (double)L);
+      (one ? first.minv : second.minv)[meta] = mbits;
+    }
+    if constexpr (kWide) {
+      s_alpha[c] = __builtin_bit_cast(_Float16, mbits);
+      s_rinv[c] = range > 0.0 ? (double)L / range : 0.0;
+    } else {
+      s_thr[k - 1][c] = __builtin_bit_cast(_Float16, threshold_bits(alpha, range, k, L));
+    }
+  }
+  __syncthreads();
+  // ---- 3. codes: BITS words per token and slice
+  const int words = d * BITS / 32;
+  uint32_t* dst = (one ? first.codes : second.codes) + tok0 * words + slice * (LANES * BITS / 4);
+  if constexpr (kWide) {
+    double al[8], ri[8];
+    float al32[8], ri32[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      al32[j] = (float)s_alpha[8 * oct + j];
+      al[j] = (double)al32[j];
+      ri[j] = s_rinv[8 * oct + j];
+      ri32[j] = (float)ri[j];
+    }
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      const int t = i * kTokens + t_lane;
+      uint32_t w0, w1;
+      octet_words<BITS>(x[i], al, ri, al32, ri32, w0, w1);
+      if (t < tokens) {
+        if constexpr (BITS == 4) dst[(unsigned)t * (unsigned)words + oct] = w0;
+        else *reinterpret_cast<v2u*>(dst + (unsigned)t * (unsigned)words + 2 * oct) = (v2u){w0, w1};
+      }
+    }
+  } else {
+    v8h thr[L];
+#pragma unroll
+    for (int k = 0; k < L; ++k) thr[k] = *reinterpret_cast<const v8h*>(&s_thr[k][8 * oct]);
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      const int t = i * kTokens + t_lane;
+      uint32_t bits = octet_codes<BITS>(x[i], thr);
+      if constexpr (BITS == 1) {
+        bits <<= 24 - 8 * (oct & 3);
+        bits |= other_lane<0xB1>(bits);
+        bits |= other_lane<0x4E>(bits);
+        if ((oct & 3) == 0 && t < tokens) dst[(unsigned)t * (unsigned)words + (oct >> 2)] = bits;
+      } else {
+        bits <<= 16 - 16 * (oct & 1);
+        bits |= other_lane<0xB1>(bits);
+        if ((oct & 1) == 0 && t < tokens) dst[(unsigned)t * (unsigned)words + (oct >> 1)] = bits;
+      }
+    }
+  }
+}
+
+using SliceKernel = void (*)(const SliceArgs, const SliceArgs, int, int, int, int, int);
+// Whole lines per token (8 lanes) where the group is short; else half of one, with which more workgroups share a CU
+// (us, one-bit keys and values, 8 / 4 lanes: 512 rows x 300 tokens 17.1 / 27.3, 8 x 1000 5.7 / 4.5, 256 x 2000 with two
+// bits 86.6 / 70.6; 8 bits, 256 x 1500 83.5 / 95.1).  Beyond 2048 tokens 1024 threads; 24 registers of data per
+// thread instead are slower (64 x 3003 41.6 / 37.8).
+template <int BITS>
+SliceKernel slice_kernel(int tokens, int* threads, int* lanes) {
+  *lanes = 8;
+  *threads = 512;
+  if (tokens <= 512) return quantize_slice_kernel<BITS, 8, 512, 8>;
+  *lanes = 4;
+  if (tokens <= 1024) return quantize_slice_kernel<BITS, 4, 512, 8>;
+  if constexpr (BITS <= 2) {
+    if (tokens <= 2048) return quantize_slice_kernel<BITS, 4, 512, 16>;
+    *threads = 1024;
+  } else {
+    *threads = 1024;
+    *lanes = 8;
+    if (tokens <= 1536) return quantize_slice_kernel<BITS, 8, 1024, 12>;
+    *lanes = 4;
+  }
+  if (tokens <= 3072) return quantize_slice_kernel<BITS, 4, 1024, 12>;
+  if (tokens <= 4096) return quantize_slice_kernel<BITS, 4, 1024, 16>;
+  return nullptr;
+}
+
+}  // namespace
+
+bool quantize_slice_supported(size_t n_tokens, int d, int bits, int axis, int group) {
+  if (axis != CQ_AXIS_CHANNEL || group <= kTile || group > 4096) return false;
+  if (d != 64 && d != 128 && d != 256) return false;
+  // two tensors of whole eights of groups in one grid of at most 2^32 - 1 threads
+  return (n_tokens / group * 2 + 8) * (d / 32) <= 0xffffffffu / 1024;
+}
+
+hipError_t launch_quantize_slices(const QuantizeJob* jobs, int n_jobs, size_t n_tokens, int d, int bits, hipStream_t stream) {
+  const int tokens = jobs[0].group, n = (int)(n_tokens / tokens);
+  int threads = 0, lanes = 0;
+  const SliceKernel kern = bits == 1 ? slice_kernel<1>(tokens, &threads, &lanes) : bits == 2 ? slice_kernel<2>(tokens, &threads, &lanes)
+                         : bits == 4 ? slice_kernel<4>(tokens, &threads, &lanes) : slice_kernel<8>(tokens, &threads, &lanes);
+  if (!kern) return hipErrorInvalidValue;
+  auto args = [](const QuantizeJob& j) {
+    return SliceArgs{static_cast<const __half*>(j.x_f16), j.out.codes, j.out.scale, j.out.min};
+  };
+  const int log_slices = (d == 64 ? 1 : d == 128 ? 2 : 3) - (lanes == 8 ? 1 : 0), groups = n * n_jobs;
+  const unsigned blocks = (unsigned)((groups + 7) / 8 * 8) << log_slices;
+  kern<<<dim3(blocks), dim3((unsigned)threads), 0, stream>>>(args(jobs[0]), args(jobs[n_jobs - 1]), n, groups, tokens, d,
+                                                             log_slices);
+  return hipGetLastError();
+}
+
+}  // namespace cq

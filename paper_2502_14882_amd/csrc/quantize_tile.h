@@ -24,17 +24,15 @@
 // tokens cut every 128; only the very last tile can be short.  A short tile reads its last token
 // again in place of the missing ones, which changes no extremum, and stores only what exists.
 // Channel-wise groups of any other size are "whole" sequences of their own (Sec. 3.1 as printed
-// when the group is n_vis).  Up to 128 tokens are one short tile.  Longer ones take a pass of their
-// own: row_extrema_kernel leaves `splits` partial (min, max) pairs per channel in the code words of
+// when the group is n_vis).  Up to 128 tokens are one short tile; those that a workgroup's registers hold go to
+// quantize_slice.hip.  Longer ones take a pass of their own: row_extrema_kernel leaves `splits` partial (min, max) pairs per channel in the code words of
 // the sequence's LAST tile (the caller's output buffer: no other memory is needed), the tile
 // kernel reduces them instead of computing tile statistics, and the last tile of every sequence
 // is quantized by a second launch, after all other tiles have read the partials it overwrites.
 // The FIRST tile of a sequence is the short one, so the last one always has room for the partials.
 // Results are bit-identical to evaluating the quantize equation element by element in fp64.
 //
-// Bound: HBM, and the launches of a small call.  Keys and values of 64 rows x 3003 tokens, D = 128, 2
-// bits, whole-sequence statistics (111 MB): 4480 us on the shape-agnostic kernel, one thread per
-// channel walking the sequence, 44.8 us here.  Groups of a few tokens spend a block on little
+// Bound: HBM, and the launches of a small call.  Groups of a few tokens spend a block on little
 // (quantize_tile_is_faster has the line from which these kernels are used).  128 x 8
 // rows x 16384 tokens, 1 bit, groups of 128 (9.33 GB): 1755 us = 5.3 TB/s.
 #ifndef CQ_QUANTIZE_TILE_H_

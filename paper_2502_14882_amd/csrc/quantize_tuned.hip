@@ -28,13 +28,31 @@ bool quantize_tile_is_faster(int d, int bits, int axis, int group) {
   return group >= line * (d == 256 ? 9 : 8) / 8;
 }
 
-hipError_t launch_quantize_tuned(const QuantizeJob* jobs, int n_jobs, int rows, int n_vis, int d, int bits,
-                                 hipStream_t stream) {
-  const size_t n_tokens = (size_t)rows * (size_t)n_vis;
+static hipError_t launch_quantize_tiles(const QuantizeJob* jobs, int n_jobs, size_t n_tokens, int d, int bits,
+                                        hipStream_t stream) {
   if (d == 128) return launch_quantize_dim<128>(jobs, n_jobs, n_tokens, bits, stream);
   if (d == 64) return launch_quantize_64(jobs, n_jobs, n_tokens, bits, stream);
   if (d == 256) return launch_quantize_256(jobs, n_jobs, n_tokens, bits, stream);
   return hipErrorInvalidValue;
+}
+
+hipError_t launch_quantize_tuned(const QuantizeJob* jobs, int n_jobs, int rows, int n_vis, int d, int bits,
+                                 hipStream_t stream) {
+  const size_t n_tokens = (size_t)rows * (size_t)n_vis;
+  // groups that registers hold: both tensors together, or one of them
+  bool slices[2] = {false, false};
+  for (int i = 0; i < n_jobs; ++i) slices[i] = quantize_slice_supported(n_tokens, d, bits, jobs[i].axis, jobs[i].group);
+  if (n_jobs == 2 && slices[0] && slices[1] && jobs[0].group == jobs[1].group)
+    return launch_quantize_slices(jobs, 2, n_tokens, d, bits, stream);
+  if (slices[0] || slices[1]) {
+    for (int i = 0; i < n_jobs; ++i) {
+      const hipError_t e = slices[i] ? launch_quantize_slices(&jobs[i], 1, n_tokens, d, bits, stream)
+                                     : launch_quantize_tiles(&jobs[i], 1, n_tokens, d, bits, stream);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
+  return launch_quantize_tiles(jobs, n_jobs, n_tokens, d, bits, stream);
 }
 
 }  // namespace cq
