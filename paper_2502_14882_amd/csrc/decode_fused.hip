@@ -104,13 +104,16 @@ extern __shared__ __align__(16) uint8_t smem[];
 // token-wise.
 // KW = key statistics over the whole sequence: one parameter group per row, so the query operand,
 // its shift and the additive term are formed once per wave instead of once per 128 tokens.
-template <bool SPLIT, int TILES, int BITS, bool VCH, bool KW = false, bool NT = true, int RK = kRingK>
+// RAG = the row (with KW, and values token-wise or over the whole sequence) may end anywhere: what lies between its end
+// and the next multiple of 128 reads the last token again, which changes no extremum, and has weight 0.
+template <bool SPLIT, int TILES, int BITS, bool VCH, bool KW = false, bool NT = true, int RK = kRingK, bool RAG = false>
 __global__ void __launch_bounds__(kThreads)
 fused_row_kernel(const FusedArgs args) {
   // code words, see stream_load: a key instruction covers whole lines up to b = 4, a value
   // instruction up to b = 2 (wider value codes are read token by token in 16-byte pieces)
   constexpr bool kNtKeys = NT && BITS <= 4, kNtCodes = NT && BITS <= 2;
   static_assert(!KW || TILES == 8, "whole-sequence keys are processed 128 tokens at a time");
+  static_assert(KW || !RAG, "a row that ends inside a processing group has whole-sequence keys");
   // Split rows: one pass over the workgroup's own chunk, unless the other workgroups' extrema do not turn up;
   // then one pass over each of the other chunks for their extrema, and one more over its own.
   u64 count_seen = 0;
@@ -158,7 +161,8 @@ fused_row_kernel(const FusedArgs args) {
   const int unit = a.unit;
   const int ga = chunk_first(a.units_base, a.units_rem, chunk) * unit;
   const int gb = chunk_first(a.units_base, a.units_rem, chunk + 1) * unit;
-  const int n_groups = gb - ga, nv = n_groups * a.k_group, vis0 = ga * a.k_group;
+  const int n_groups = gb - ga, nvp = n_groups * a.k_group, vis0 = ga * a.k_group;
+  const int nv = RAG ? min(nvp, a.n_vis - vis0) : nvp;      // tokens; nvp: with the padding of the last group
   const int ba = chunk_first(a.tblocks_base, a.tblocks_rem, chunk);
   const int bb = chunk_first(a.tblocks_base, a.tblocks_rem, chunk + 1);
   const int txt0 = ba * 64;
@@ -195,16 +199,22 @@ fused_row_kernel(const FusedArgs args) {
   // ring of the first value tiles of the narrow token-wise path (b <= 2): asked for during
   // phase 1, right after the first key groups, so that phase 2 does not start on a cold load
   constexpr bool kPrimeValues = !VCH && BITS <= 2;
+  // word of the e-th KB of a 64-token tile of value codes that this lane takes, from the row's first token
+  auto tile_word = [&](int j0, int e) -> size_t {
+    if constexpr (!RAG) return (size_t)j0 * (4 * BITS) + 256 * e + 4 * lane;
+    const int o = 256 * e + 4 * lane;
+    return (size_t)min(j0 + o / (4 * BITS), nv - 1) * (4 * BITS) + o % (4 * BITS);
+  };
   v4i p2_cg[kRingV][BITS];
   float p2_vsr[kRingV];
   uint16_t p2_vmr[kRingV];       // raw fp16 bits: converting here would wait for the load at once
   const uint32_t* p2_vc_row = a.v_codes + ((size_t)row * a.n_vis + vis0) * (4 * BITS);
   auto p2_load_tile = [&](int slot, int jt) {
-    const int j0 = min(jt, nv - 64), j = j0 + lane;
+    const int j0 = min(jt, nvp - 64), j = RAG ? min(j0 + lane, nv - 1) : j0 + lane;
     // the tile's code bytes are contiguous: instruction e takes the e-th KB, whole cache lines
 #pragma unroll
     for (int e = 0; e < BITS; ++e)
-      p2_cg[slot][e] = stream_load<kNtCodes>(reinterpret_cast<const v4i*>(p2_vc_row + (size_t)j0 * (4 * BITS) + 256 * e + 4 * lane));
+      p2_cg[slot][e] = stream_load<kNtCodes>(reinterpret_cast<const v4i*>(p2_vc_row + tile_word(j0, e)));
     p2_vsr[slot] = stream_load<NT>(vs_row + j);
     p2_vmr[slot] = stream_load<NT>(vm_row + j);
   };
@@ -275,8 +285,8 @@ fused_row_kernel(const FusedArgs args) {
       constexpr int kQuads = kQuadKeys ? TILES / 4 : 1;
       uint32_t w[kQuadKeys ? 1 : kRK][TILES][BITS];
       v4i wq[kQuadKeys ? kRK : 1][kQuads];
-      const uint32_t* kq_lane =
-          a.k_codes + ((size_t)row * a.n_vis + vis0) * 4 + (size_t)(16 * kb + n16) * 4;
+      const uint32_t* kq_row = a.k_codes + ((size_t)row * a.n_vis + vis0) * (4 * BITS);
+      const uint32_t* kq_lane = kq_row + (size_t)(16 * kb + n16) * 4;
       v2f s01[kRK];               // scales of channels wc0, wc1
       uint32_t m01[kRK];          // their minima, two fp16 in one word
       auto load_group = [&](int slot, int t) {
@@ -286,12 +296,14 @@ fused_row_kernel(const FusedArgs args) {
         if constexpr (kQuadKeys) {
 #pragma unroll
           for (int j = 0; j < kQuads; ++j)
-            wq[slot][j] = stream_load<kNtKeys>(
-                reinterpret_cast<const v4i*>(kq_lane + ((size_t)tc * TILES + 4 * j) * 64));
+            wq[slot][j] = stream_load<kNtKeys>(reinterpret_cast<const v4i*>(
+                RAG ? kq_row + (size_t)min(tc * 128 + 64 * j + 16 * kb + n16, nv - 1) * 4
+                    : kq_lane + ((size_t)tc * TILES + 4 * j) * 64));
         }
 #pragma unroll
         for (int i = 0; i < (kQuadKeys ? 0 : TILES); ++i) {
-          const uint32_t* p = kc_lane + ((size_t)tc * TILES + i) * (64 * BITS);
+          const uint32_t* p = RAG ? kq_row + (size_t)min(tc * 128 + 16 * i + n16, nv - 1) * (4 * BITS) + kb * BITS
+                                  : kc_lane + ((size_t)tc * TILES + i) * (64 * BITS);
           if constexpr (BITS == 1) {
             w[slot][i][0] = stream_load<kNtKeys>(p);
           } else if constexpr (BITS == 2) {
@@ -529,7 +541,7 @@ fused_row_kernel(const FusedArgs args) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                   const float sv = c[r] * a.softmax_scale;
-                  logits[r * a.stride + nv + tok] = sv;
+                  logits[r * a.stride + nvp + tok] = sv;
                   tmax[r] = fmaxf(tmax[r], sv);
                 }
               }
@@ -652,7 +664,7 @@ fused_row_kernel(const FusedArgs args) {
       // accumulator layout (column = code byte, head = lane / 16).  A wave owns whole value
       // groups (v_group / 64 consecutive tiles) and folds each finished group into fp32.
       const int VG = a.v_group, tsh = VG == 128 ? 1 : 0, tpg = 1 << tsh;
-      const int n_vg = nv >> (6 + tsh);      // nv / VG, VG = 64 << tsh
+      const int n_vg = nvp >> (6 + tsh);     // nvp / VG, VG = 64 << tsh
       const int n_my = n_vg > wave ? ((n_vg - wave + kVisWaves - 1) / kVisWaves) << tsh : 0;
       const uint32_t* vc_row = a.v_codes + ((size_t)row * a.n_vis + vis0) * (4 * BITS);
       const size_t g0 = (size_t)row * a.v_prow + (size_t)(vis0 >> (6 + tsh)) * a.v_pstride;
@@ -675,7 +687,7 @@ fused_row_kernel(const FusedArgs args) {
         const int j = tile_start(k);
 #pragma unroll
         for (int e = 0; e < BITS; ++e)
-          cg[slot][e] = stream_load<kNtCodes>(reinterpret_cast<const v4i*>(vc_row + (size_t)j * (4 * BITS) + 256 * e + 4 * lane));
+          cg[slot][e] = stream_load<kNtCodes>(reinterpret_cast<const v4i*>(vc_row + tile_word(j, e)));
       };
       v4f gsc[2];
       v2i gmn[2];
@@ -694,7 +706,8 @@ fused_row_kernel(const FusedArgs args) {
         v4i xs;
 #pragma unroll
         for (int h = 0; h < kHeads; ++h) {
-          const float p = __builtin_amdgcn_exp2f(fmaf(lg[h], a2[h], c2v[h]));
+          float p = __builtin_amdgcn_exp2f(fmaf(lg[h], a2[h], c2v[h]));
+          if (RAG) p = jt + lane < nv ? p : 0.f;
           lsum[h] += p;
           xs[h] = product_digits(p, 536870912.f);
         }
@@ -816,7 +829,7 @@ fused_row_kernel(const FusedArgs args) {
       int F_prep = 90, F_acc = 90;
       float fit_below = ldexpf(1.f, 29 - 90);
       const uint32_t* vc_row = a.v_codes + ((size_t)row * a.n_vis + vis0) * (4 * BITS);
-      const int step = kVisWaves * 64, last = nv - 64;
+      const int step = kVisWaves * 64, last = nvp - 64;
       const int x_wr = ((lane >> 4) * a.stride) * 4 + (lane & 15) * 16;
       const int x_rd = (kb * a.stride) * 4 + (n16 >> 1) * 16 + (n16 & 1) * 8;
       const int v_rd = (kb * 16 + (n16 >> 1)) * 32 + (n16 & 1) * 8;     // 32-byte rows: two blocks
@@ -824,7 +837,7 @@ fused_row_kernel(const FusedArgs args) {
       float vsr[2];
       uint16_t vmr[2];
       auto load_tile = [&](int slot, int jt) {
-        const int j = min(jt, last) + lane;
+        const int j = RAG ? min(min(jt, last) + lane, nv - 1) : min(jt, last) + lane;
 #pragma unroll
         for (int e = 0; e < BITS; ++e)
           cg[slot][e] = stream_load<kNtCodes>(reinterpret_cast<const v4i*>(vc_row + (size_t)j * (4 * BITS) + 4 * e));
@@ -851,7 +864,8 @@ fused_row_kernel(const FusedArgs args) {
         v4i xs;
 #pragma unroll
         for (int h = 0; h < kHeads; ++h) {
-          const float p = __builtin_amdgcn_exp2f(fmaf(logits[h * a.stride + jt + lane], a2[h], c2v[h]));
+          float p = __builtin_amdgcn_exp2f(fmaf(logits[h * a.stride + jt + lane], a2[h], c2v[h]));
+          if (RAG) p = jt + lane < nv ? p : 0.f;
           lsum[h] += p;
           msum[h] = fmaf(p, vmf, msum[h]);
           xs[h] = product_digits(p, vsf);
@@ -939,7 +953,8 @@ fused_row_kernel(const FusedArgs args) {
         v4i xs;
 #pragma unroll
         for (int h = 0; h < kHeads; ++h) {
-          const float p = __builtin_amdgcn_exp2f(fmaf(lg[h], a2[h], c2v[h]));
+          float p = __builtin_amdgcn_exp2f(fmaf(lg[h], a2[h], c2v[h]));
+          if (RAG) p = jt + lane < nv ? p : 0.f;
           lsum[h] += p;
           msum[h] = fmaf(p, vmf, msum[h]);
           xs[h] = product_digits(p, vsf);
@@ -1058,11 +1073,11 @@ fused_row_kernel(const FusedArgs args) {
           if (lane < nt) {
 #pragma unroll
             for (int h = 0; h < kHeads; ++h)
-              pv[h] = __builtin_amdgcn_exp2f(fmaf(logits[h * a.stride + nv + t0 + lane], kLog2e, c2t[h]));
+              pv[h] = __builtin_amdgcn_exp2f(fmaf(logits[h * a.stride + nvp + t0 + lane], kLog2e, c2t[h]));
           }
 #pragma unroll
           for (int h = 0; h < kHeads; ++h) tl[h] += pv[h];
-          uint8_t* pb = lbytes + (size_t)(nv + t0) * 4;
+          uint8_t* pb = lbytes + (size_t)(nvp + t0) * 4;
           __builtin_amdgcn_wave_barrier();
           asm volatile("" ::: "memory");     // the records overwrite logits read just above
           if (lane < SH) {                                                  // zero beyond nt
@@ -1250,8 +1265,12 @@ long long device_cu_count() {
 // Returns the shape the kernel works on.
 DecodeShape processing_shape(const DecodeShape& s, bool* k_whole, bool* v_whole) {
   DecodeShape e = s;
-  *k_whole = s.k_axis == CQ_AXIS_CHANNEL && s.k_group == s.n_vis && s.n_vis > 128 && s.n_vis % 128 == 0;
-  *v_whole = s.v_axis == CQ_AXIS_CHANNEL && s.v_group == s.n_vis && s.n_vis > 128 && s.n_vis % 128 == 0;
+  *k_whole = s.k_axis == CQ_AXIS_CHANNEL && s.k_group == s.n_vis && s.n_vis > 128;
+  *v_whole = s.v_axis == CQ_AXIS_CHANNEL && s.v_group == s.n_vis && s.n_vis > 128;
+  if (s.n_vis % 128 != 0) {        // ends inside a processing group: keys and channel-wise values both whole
+    *k_whole = *k_whole && (*v_whole || s.v_axis == CQ_AXIS_TOKEN);
+    *v_whole = *v_whole && *k_whole;
+  }
   if (*k_whole) e.k_group = 128;
   if (*v_whole) e.v_group = 128;
   return e;
@@ -1267,7 +1286,7 @@ int chunk_unit(const DecodeShape& s) {
 
 // largest chunk of a row split into n_chunks (same arithmetic as the kernel): the first one
 void chunk_extent(const DecodeShape& s, int n_chunks, int* nv_max, int* nt_max) {
-  const int unit = chunk_unit(s), n_units = s.n_vis / (s.k_group * unit), n_tblocks = (s.n_text + 63) / 64;
+  const int unit = chunk_unit(s), n_units = ceil_div(s.n_vis, s.k_group * unit), n_tblocks = (s.n_text + 63) / 64;
   *nv_max = ceil_div(n_units, n_chunks) * unit * s.k_group;
   const int nt = ceil_div(n_tblocks, n_chunks) * 64;
   *nt_max = nt < s.n_text ? nt : s.n_text;
@@ -1305,12 +1324,12 @@ FusedPlan make_fused_plan(const DecodeShape& shape, int min_chunks, FusedSplit s
   if (s.k_axis != CQ_AXIS_CHANNEL) return p;
   if (s.v_axis == CQ_AXIS_TOKEN ? s.v_group != kD : (s.v_group != 64 && s.v_group != 128)) return p;
   if (s.k_group != 32 && s.k_group != 64 && s.k_group != 128) return p;
-  if (s.g > 2 * kHeads || s.n_vis % 64 != 0) return p;
-  if (s.v_axis == CQ_AXIS_CHANNEL && s.n_vis % s.v_group != 0) return p;
+  if (s.g > 2 * kHeads || (s.n_vis % 64 != 0 && !k_whole)) return p;
+  if (s.v_axis == CQ_AXIS_CHANNEL && s.n_vis % s.v_group != 0 && !v_whole) return p;
   p.nhb = (s.g + kHeads - 1) / kHeads;
   const long long rows = (long long)s.B * s.Hkv * p.nhb;
   const int unit = chunk_unit(s);
-  const int n_units = s.n_vis / (s.k_group * unit);
+  const int n_units = ceil_div(s.n_vis, s.k_group * unit);
   const int max_chunks = n_units < 64 ? (n_units > 0 ? n_units : 1) : 64;
   // fewest chunks that fit LDS
   int want = min_chunks >= 1 ? min_chunks : 1;                 // > 1: a test's or a tuner's override
@@ -1379,11 +1398,23 @@ namespace {
 
 using FusedKernel = void (*)(const FusedArgs);
 struct FusedChoice { FusedKernel kern; int slot; };
+constexpr int kKernels = 36;       // slots
 
 // SPLIT: rows that several workgroups share.  slot: the kernel's place in the table of LDS limits.
 template <bool SPLIT>
 FusedChoice pick_kernel(const DecodeShape& s, const FusedPlan& plan, bool k_whole) {
   const bool vch = s.v_axis == CQ_AXIS_CHANNEL;
+  if (k_whole && s.n_vis % 128 != 0) {
+    switch (s.bits * 2 + (vch ? 1 : 0)) {
+      case 1 * 2: return {fused_row_kernel<SPLIT, 8, 1, false, true, true, kRingK, true>, 30};
+      case 2 * 2: return {fused_row_kernel<SPLIT, 8, 2, false, true, true, kRingK, true>, 31};
+      case 4 * 2: return {fused_row_kernel<SPLIT, 8, 4, false, true, true, kRingK, true>, 32};
+      case 8 * 2: return {fused_row_kernel<SPLIT, 8, 8, false, true, true, kRingK, true>, 33};
+      case 1 * 2 + 1: return {fused_row_kernel<SPLIT, 8, 1, true, true, true, kRingK, true>, 34};
+      case 2 * 2 + 1: return {fused_row_kernel<SPLIT, 8, 2, true, true, true, kRingK, true>, 35};
+      default: return {nullptr, 0};
+    }
+  }
   if (k_whole) {
     switch (s.bits * 2 + (vch ? 1 : 0)) {
       case 1 * 2: return {fused_row_kernel<SPLIT, 8, 1, false, true>, 18};
@@ -1471,10 +1502,10 @@ hipError_t launch_decode_fused(const DecodeShape& shape, const FusedPlan& plan, 
   const FusedChoice choice = plan.n_chunks == 1 ? pick_kernel<false>(s, plan, k_whole) : pick_kernel<true>(s, plan, k_whole);
   const FusedKernel kern = choice.kern;
   if (!kern) return hipErrorInvalidValue;
-  const int slot = choice.slot + (plan.n_chunks == 1 ? 0 : 30);
+  const int slot = choice.slot + (plan.n_chunks == 1 ? 0 : kKernels);
   // the kernel's dynamic LDS limit is raised once per (device, kernel) and only ever grows;
   // concurrent callers may both raise it, which is harmless
-  static std::atomic<size_t> configured[kMaxDevices][60];
+  static std::atomic<size_t> configured[kMaxDevices][2 * kKernels];
   int dev = 0;
   hipError_t de = hipGetDevice(&dev);
   if (de != hipSuccess) return de;
@@ -1495,7 +1526,7 @@ hipError_t launch_decode_fused(const DecodeShape& shape, const FusedPlan& plan, 
   if (pieces * (size_t)plan.n_chunks >= ((size_t)1 << 32) || plan.nhb > 2) return hipErrorInvalidConfiguration;
   a.chunks_magic = plan.n_chunks == 1 ? 0u : (unsigned)((((unsigned long long)1 << 32) / (unsigned)plan.n_chunks) + 1);
   {
-    const int n_units = s.n_vis / (s.k_group * a.unit), n_tblocks = (s.n_text + 63) / 64;
+    const int n_units = ceil_div(s.n_vis, s.k_group * a.unit), n_tblocks = (s.n_text + 63) / 64;
     a.units_base = n_units / plan.n_chunks;
     a.units_rem = n_units % plan.n_chunks;
     a.tblocks_base = n_tblocks / plan.n_chunks;

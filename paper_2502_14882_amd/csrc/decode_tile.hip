@@ -1,6 +1,6 @@
 // Decode attention over the packed cache for the layouts that the fused and the streaming kernels do
 // not take (gfx950): head_dim 64, 128 or 256, 1-, 2-, 4- or 8-bit codes, channel-wise keys in groups
-// of any number of tokens (Sec. 3.1 as printed: the whole sequence, whatever its length), values
+// of any number of tokens (with 128 channels the whole sequence is the fused kernel's, whatever its length), values
 // token-wise with one group per token or channel-wise in groups of any number of tokens, any
 // number of query heads per KV head.
 //

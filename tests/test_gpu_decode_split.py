@@ -170,3 +170,23 @@ def test_tile_kernels_in_one_launch(shape):
     err = O.rel_l2(got[0].cpu().numpy().astype(np.float64), ref)
     assert err <= H.REGRESSION_TOL, err
     assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
+
+
+# Whole-sequence keys, values token-wise or whole, rows that end inside a group of 128 tokens, on the fused kernel:
+# (B, Hq, Hkv, n_vis, n_text, bits, value axis); one token over a group, one short, inside a value tile's pad, and
+# enough rows or heads for one chunk, several chunks, a last chunk of one token
+RAGGED = [(1, 4, 1, 129, 5, 1, 1), (2, 8, 2, 255, 0, 2, 0), (8, 32, 8, 3003, 77, 2, 0), (1, 6, 1, 2049, 64, 4, 1),
+          (3, 3, 3, 1000, 130, 8, 1), (1, 8, 1, 5185, 33, 1, 0), (16, 16, 16, 193, 70, 1, 1), (1, 1, 1, 12001, 9, 2, 1)]
+
+
+@pytest.mark.parametrize("shape", RAGGED)
+@pytest.mark.parametrize("chunks", [0, 1, 5])
+def test_rows_that_end_inside_a_processing_group(shape, chunks):
+    B, n_q, n_kv, n, n_text, bits, v_axis = shape
+    lay, x, dev, k, v, kq, vq = build(B, n_q, n_kv, n, n_text, bits, n, v_axis, 128 if v_axis else n)
+    calib = (O.CALIB_DYNAMIC, 2.0, 1.0)
+    got = run(lay, dev, k, v, n_text, cq.make_calib(*calib), ONE_LAUNCH + chunks if chunks else 0)
+    ref = O.decode_attn(x["q"].numpy(), kq, vq, x["k_text"].numpy(), x["v_text"].numpy(), n_text, *calib)
+    err = O.rel_l2(got.cpu().numpy().astype(np.float64), ref)
+    assert err <= H.REGRESSION_TOL, err
+    H.assert_elementwise_close(got.cpu().numpy().astype(np.float64), ref)
