@@ -1299,17 +1299,19 @@ void chunk_extent(const DecodeShape& s, int n_chunks, int* nv_max, int* nt_max) 
 // chunk, and 1.3 to 2.2 where the chip is full.  That last figure is set so that two chunks on a full chip are taken
 // where they pay (96 to 128 rows, whole / in 2: 1 bit x 3584 tokens 11.4 / 12.3, x 6016 16.6 / 15.3; 2 bits x 4480
 // 15.5 / 14.9; 4 bits x 3840 18.5 / 19.4, x 4224 18.7 / 16.9).
-int spread_chunks(const DecodeShape& s, long long rows, long long cus, int n_units) {
+int spread_chunks(const DecodeShape& s, bool k_whole, long long rows, long long cus, int n_units) {
+  const bool vch = s.v_axis == CQ_AXIS_CHANNEL;
   const double per_k = (s.bits == 1 ? 1.6 : s.bits == 2 ? 2.1 : 3.1) +
-                       (s.k_group == 32 ? 1.0 : 0.0) + (s.v_axis == CQ_AXIS_CHANNEL ? 0.4 : 0.0);
+                       (s.k_group == 32 ? 1.0 : 0.0) + (vch && !k_whole ? 0.4 : 0.0) - (k_whole && s.bits == 2 ? 0.3 : 0.0);
   const double row = per_k * 1e-3 * s.n_vis + 0.9 * ((s.n_text + 63) / 64), 
                each = 0.1 + (s.bits == 1 ? 1.3 : s.bits == 2 ? 2.1 : 4.6) * (double)rows / (double)cus;
   long long most = cus / rows < n_units ? cus / rows : n_units;
   if (most > 64) most = 64;
   long long c = (long long)(std::sqrt(row / each) + 0.5);
   if (c > most) c = most;
-  // (half a microsecond more than the fit says: short rows scatter, and a shared one needs a larger workspace)
-  if (c < 2 || row * (double)(c - 1) / (double)c < 4.2 + each * (double)(c - 1)) return 1;
+  // (half a microsecond more than the fit says: short rows scatter, and a shared one needs a larger workspace; channel-wise
+  // values of two bits lose another two to registers: 16 rows x 2944 whole / in 8 chunks 10.3 / 11.2, 24 x 6528 15.5 / 12.9)
+  if (c < 2 || row * (double)(c - 1) / (double)c < (vch && s.bits == 2 ? 6.2 : 4.2) + each * (double)(c - 1)) return 1;
   return ceil_div(n_units, ceil_div(n_units, (int)c));         // no more than make the largest chunk smaller
 }
 
@@ -1350,7 +1352,7 @@ FusedPlan make_fused_plan(const DecodeShape& shape, int min_chunks, FusedSplit s
   // Every workgroup on a CU of its own: as many chunks as pay.  (8-bit rows are bound by what the CUs read
   // together, and the tile kernels have them.)
   if (split == FusedSplit::kSpread && !forced && s.n_vis > 0 && s.bits <= 4 && rows * p.n_chunks <= device_cu_count()) {
-    const int c = spread_chunks(s, rows, device_cu_count(), n_units);
+    const int c = spread_chunks(s, k_whole, rows, device_cu_count(), n_units);
     if (c > p.n_chunks) {
       int nv, nt;
       chunk_extent(s, c, &nv, &nt);
