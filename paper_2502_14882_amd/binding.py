@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 from typing import NamedTuple, Optional
 
 import torch
@@ -57,21 +58,21 @@ def lib() -> ctypes.CDLL:
         L = ctypes.CDLL(LIB_PATH)
         P, I, V = ctypes.POINTER, ctypes.c_int32, ctypes.c_void_p
         L.cq_quantize_kv.restype = ctypes.c_int
-        L.cq_quantize_kv.argtypes = [P(CqLayout), V, V, P(CqQTensor), P(CqQTensor), V]
+        L.cq_quantize_kv.argtypes = [P(CqLayout), V, V, V, V, V]          # (cq_qtensor_t: a struct or its bytes)
         L.cq_decode_workspace_bytes.restype = ctypes.c_size_t
         L.cq_decode_workspace_bytes.argtypes = [P(CqLayout), I, P(CqCalib)]
         L.cq_decode_attn.restype = ctypes.c_int
-        L.cq_decode_attn.argtypes = [P(CqLayout), V, P(CqQTensor), P(CqQTensor), V, V, I, I,
+        L.cq_decode_attn.argtypes = [P(CqLayout), V, V, V, V, V, I, I,
                                      P(CqCalib), ctypes.c_float, V, V, ctypes.c_size_t, V]
         L.cq_decode_attn_noalloc.restype = ctypes.c_int
-        L.cq_decode_attn_noalloc.argtypes = [P(CqLayout), V, P(CqQTensor), P(CqQTensor), V, V, I, I,
+        L.cq_decode_attn_noalloc.argtypes = [P(CqLayout), V, V, V, V, V, I, I,
                                              P(CqCalib), ctypes.c_float, V, V]
         L.cq_append_text_kv.restype = ctypes.c_int
         L.cq_append_text_kv.argtypes = [P(CqLayout), V, V, I, I, V, V, V]
         L.cq_append_text_kv_devlen.restype = ctypes.c_int
         L.cq_append_text_kv_devlen.argtypes = [P(CqLayout), V, V, V, I, V, V, V]
         L.cq_decode_attn_devlen.restype = ctypes.c_int
-        L.cq_decode_attn_devlen.argtypes = [P(CqLayout), V, P(CqQTensor), P(CqQTensor), V, V, V, I, I,
+        L.cq_decode_attn_devlen.argtypes = [P(CqLayout), V, V, V, V, V, V, I, I,
                                             P(CqCalib), ctypes.c_float, V, V, ctypes.c_size_t, V]
         L.cq_tau_search_workspace_bytes.restype = ctypes.c_size_t
         L.cq_tau_search_workspace_bytes.argtypes = [P(CqLayout), I, I, I]
@@ -127,6 +128,16 @@ class QTensor(NamedTuple):
         return CqQTensor(self.codes.data_ptr(), self.scale.data_ptr(), self.min.data_ptr())
 
 
+_layout_fields = struct.Struct("10i").unpack_from        # of a CqLayout, in its order
+_three_pointers = struct.Struct("3P").pack
+
+
+def _packed(t: QTensor) -> bytes:
+    """The bytes of the tensor's cq_qtensor_t: cheaper to make and to pass than a ctypes structure."""
+    codes, scale, low = t
+    return _three_pointers(codes.data_ptr(), scale.data_ptr(), low.data_ptr())
+
+
 def make_layout(batch, n_q_heads, n_kv_heads, head_dim, n_vis, bits=1,
                 k_axis=CQ_AXIS_CHANNEL, v_axis=CQ_AXIS_TOKEN, k_group=128, v_group=128) -> CqLayout:
     return CqLayout(batch, n_q_heads, n_kv_heads, head_dim, n_vis, bits, k_axis, v_axis,
@@ -161,12 +172,12 @@ def cq_quantize_kv(layout: CqLayout, k: Optional[torch.Tensor], v: Optional[torc
     for t in (k, v):
         if t is not None:
             assert t.dtype == torch.float16 and t.is_contiguous()
-    ks = k_out.c_struct() if k_out is not None else None
-    vs = v_out.c_struct() if v_out is not None else None
-    _check(lib().cq_quantize_kv(ctypes.byref(layout), _ptr(k), _ptr(v),
-                                ctypes.byref(ks) if ks is not None else None,
-                                ctypes.byref(vs) if vs is not None else None,
-                                _stream(ref) if ref is not None else None))
+    status = lib().cq_quantize_kv(ctypes.byref(layout), _ptr(k), _ptr(v),
+                                  _packed(k_out) if k_out is not None else None,
+                                  _packed(v_out) if v_out is not None else None,
+                                  _stream(ref) if ref is not None else None)
+    if status:
+        _check(status)
     return k_out, v_out
 
 
@@ -175,18 +186,20 @@ def cq_decode_workspace_bytes(layout: CqLayout, n_text: int, calib: Optional[CqC
                                                ctypes.byref(calib) if calib is not None else None))
 
 
-# The checks run on every call, in the time the GPU could already be working: layout fields are read
-# once each, shapes are compared as they are (a torch.Size is a tuple), texts are only made on failure.
+# The checks run on every call, in the time the GPU could already be working: the layout's fields are read
+# all at once, shapes are compared as they are (a torch.Size is a tuple), texts are only made on failure, and
+# what the library takes as a struct of pointers is packed as bytes.  A call whose kernel takes 6.4 us is bound by
+# them: with a ctypes access per field and a ctypes structure per tensor they and the call took 8.0 us.
 
-def _check_decode_tensors(layout: CqLayout, q, k_text, v_text, out) -> int:
+def _check_decode_tensors(fields, q, k_text, v_text, out) -> int:
     """Shapes against the layout (a mismatch would be an out-of-bounds read on the device);
     returns the tail's capacity."""
     f16 = torch.float16
-    batch, d = layout.batch, layout.head_dim
+    batch, n_q_heads, n_kv_heads, d = fields[:4]
     shape = q.shape
     assert q.dtype is f16 and q.is_contiguous()
-    assert shape == (batch, layout.n_q_heads, d), \
-        "q is %s, the layout says %s" % (tuple(shape), (batch, layout.n_q_heads, d))
+    assert shape == (batch, n_q_heads, d), \
+        "q is %s, the layout says %s" % (tuple(shape), (batch, n_q_heads, d))
     assert out.dtype is f16 and out.is_contiguous() and out.shape == shape
     if k_text is None:
         assert v_text is None
@@ -195,20 +208,32 @@ def _check_decode_tensors(layout: CqLayout, q, k_text, v_text, out) -> int:
     assert v_text is not None and v_text.dtype is f16 and v_text.is_contiguous()
     tail = k_text.shape
     assert v_text.shape == tail and len(tail) == 4
-    assert tail[0] == batch and tail[1] == layout.n_kv_heads and tail[3] == d, \
-        "text tail is %s" % (tuple(tail),)
-    return tail[2]
+    cap = tail[2]
+    assert tail == (batch, n_kv_heads, cap, d), "text tail is %s" % (tuple(tail),)
+    return cap
 
 
-def _check_qtensor(layout: CqLayout, t: "QTensor", axis: int, group: int, what: str) -> None:
+def _check_qtensor(fields, t: "QTensor", axis: int, group: int, what: str) -> bytes:
+    """One quantized tensor against the layout; returns its struct."""
     codes, scale, low = t
-    batch, heads, n, d = layout.batch, layout.n_kv_heads, layout.n_vis, layout.head_dim
-    assert codes.shape == (batch, heads, n, d * layout.bits // 32) and codes.is_contiguous(), \
+    batch, _, heads, d, n, bits = fields[:6]
+    assert codes.shape == (batch, heads, n, d * bits // 32) and codes.is_contiguous(), \
         "%s codes are %s" % (what, tuple(codes.shape))
-    meta = _meta_shape_of(batch, heads, n, d, axis, group)
+    if group < 1:
+        group = 1
+    meta = (batch, heads, n // group, d) if axis == CQ_AXIS_CHANNEL else (batch, heads, n, d // group)
     assert scale.shape == meta and low.shape == meta, "%s parameters are %s" % (what, tuple(scale.shape))
     assert scale.dtype is torch.float32 and low.dtype is torch.float16
     assert scale.is_contiguous() and low.is_contiguous()
+    return _three_pointers(codes.data_ptr(), scale.data_ptr(), low.data_ptr())
+
+
+def _check_cache(fields, k: Optional["QTensor"], v: Optional["QTensor"]):
+    """The quantized tensors against the layout; returns their structs."""
+    if fields[4] > 0:
+        return (_check_qtensor(fields, k, fields[6], fields[8], "key"),
+                _check_qtensor(fields, v, fields[7], fields[9], "value"))
+    return None if k is None else _packed(k), None if v is None else _packed(v)
 
 
 def make_calib(mode=CQ_CALIB_NONE, tau1=0.0, tau2=0.0, gamma=0.0, delta=0.0) -> CqCalib:
@@ -223,23 +248,21 @@ def cq_decode_attn(layout: CqLayout, q: torch.Tensor, k: Optional[QTensor], v: O
     """One decode step; returns out [B, Hq, d] fp16 (allocated here unless given)."""
     if out is None:
         out = torch.empty_like(q)
-    n_text_cap = _check_decode_tensors(layout, q, k_text, v_text, out)
+    fields = _layout_fields(layout)
+    n_text_cap = _check_decode_tensors(fields, q, k_text, v_text, out)
     assert 0 <= n_text <= n_text_cap
-    if layout.n_vis > 0:
-        _check_qtensor(layout, k, layout.k_axis, layout.k_group, "key")
-        _check_qtensor(layout, v, layout.v_axis, layout.v_group, "value")
+    ks, vs = _check_cache(fields, k, v)
     if workspace is None:
         workspace = torch.empty(cq_decode_workspace_bytes(layout, n_text, calib), dtype=torch.uint8,
                                 device=q.device)
-    ks = k.c_struct() if k is not None else None
-    vs = v.c_struct() if v is not None else None
-    _check(lib().cq_decode_attn(
-        ctypes.byref(layout), _ptr(q),
-        ctypes.byref(ks) if ks is not None else None,
-        ctypes.byref(vs) if vs is not None else None,
-        _ptr(k_text), _ptr(v_text), int(n_text), int(n_text_cap),
+    status = lib().cq_decode_attn(
+        ctypes.byref(layout), q.data_ptr(),
+        ks, vs,
+        _ptr(k_text), _ptr(v_text), int(n_text), n_text_cap,
         ctypes.byref(calib) if calib is not None else None, float(softmax_scale),
-        _ptr(out), _ptr(workspace), workspace.numel() * workspace.element_size(), _stream(q)))
+        out.data_ptr(), workspace.data_ptr(), workspace.nbytes, _stream(q))
+    if status:
+        _check(status)
     return out
 
 
@@ -255,20 +278,18 @@ def cq_decode_attn_noalloc(layout: CqLayout, q: torch.Tensor, k: Optional[QTenso
     should be given by a caller that must not allocate (it is allocated here otherwise)."""
     if out is None:
         out = torch.empty_like(q)
-    n_text_cap = _check_decode_tensors(layout, q, k_text, v_text, out)
+    fields = _layout_fields(layout)
+    n_text_cap = _check_decode_tensors(fields, q, k_text, v_text, out)
     assert 0 <= n_text <= n_text_cap
-    if layout.n_vis > 0:
-        _check_qtensor(layout, k, layout.k_axis, layout.k_group, "key")
-        _check_qtensor(layout, v, layout.v_axis, layout.v_group, "value")
-    ks = k.c_struct() if k is not None else None
-    vs = v.c_struct() if v is not None else None
-    _check(lib().cq_decode_attn_noalloc(
-        ctypes.byref(layout), _ptr(q),
-        ctypes.byref(ks) if ks is not None else None,
-        ctypes.byref(vs) if vs is not None else None,
-        _ptr(k_text), _ptr(v_text), int(n_text), int(n_text_cap),
+    ks, vs = _check_cache(fields, k, v)
+    status = lib().cq_decode_attn_noalloc(
+        ctypes.byref(layout), q.data_ptr(),
+        ks, vs,
+        _ptr(k_text), _ptr(v_text), int(n_text), n_text_cap,
         ctypes.byref(calib) if calib is not None else None, float(softmax_scale),
-        _ptr(out), _stream(q)))
+        out.data_ptr(), _stream(q))
+    if status:
+        _check(status)
     return out
 
 
@@ -282,24 +303,22 @@ def cq_decode_attn_devlen(layout: CqLayout, q: torch.Tensor, k: Optional[QTensor
     (n_text_max is the host's bound of it)."""
     if out is None:
         out = torch.empty_like(q)
-    n_text_cap = _check_decode_tensors(layout, q, k_text, v_text, out)
+    fields = _layout_fields(layout)
+    n_text_cap = _check_decode_tensors(fields, q, k_text, v_text, out)
     assert n_text_dev.dtype == torch.int32 and n_text_dev.numel() == 1 and n_text_dev.device == q.device
     assert 0 <= n_text_max <= n_text_cap
-    if layout.n_vis > 0:
-        _check_qtensor(layout, k, layout.k_axis, layout.k_group, "key")
-        _check_qtensor(layout, v, layout.v_axis, layout.v_group, "value")
+    ks, vs = _check_cache(fields, k, v)
     if workspace is None:
         workspace = torch.empty(cq_decode_workspace_bytes(layout, n_text_max, calib),
                                 dtype=torch.uint8, device=q.device)
-    ks = k.c_struct() if k is not None else None
-    vs = v.c_struct() if v is not None else None
-    _check(lib().cq_decode_attn_devlen(
-        ctypes.byref(layout), _ptr(q),
-        ctypes.byref(ks) if ks is not None else None,
-        ctypes.byref(vs) if vs is not None else None,
-        _ptr(k_text), _ptr(v_text), _ptr(n_text_dev), int(n_text_max), int(n_text_cap),
+    status = lib().cq_decode_attn_devlen(
+        ctypes.byref(layout), q.data_ptr(),
+        ks, vs,
+        _ptr(k_text), _ptr(v_text), n_text_dev.data_ptr(), int(n_text_max), n_text_cap,
         ctypes.byref(calib) if calib is not None else None, float(softmax_scale),
-        _ptr(out), _ptr(workspace), workspace.numel() * workspace.element_size(), _stream(q)))
+        out.data_ptr(), workspace.data_ptr(), workspace.nbytes, _stream(q))
+    if status:
+        _check(status)
     return out
 
 
