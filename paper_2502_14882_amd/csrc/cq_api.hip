@@ -244,6 +244,21 @@ bool tile_is_faster(cq::DecodeShape s, const cq::FusedPlan& with_tail) {
   return tile < 0.98 * tuned;
 }
 
+// Whether rows too long for one workgroup finish sooner in chunks of the fused kernel than on the streaming kernels, where
+// the chunks take several rounds over the chip.  Microseconds, from 19 measured layouts of 18 to 320 rows x 9 to 63
+// thousand tokens (streaming / fused): 4 heads, 1 bit, 144 rows x 10496 36.4 / 30.0, 100 x 21376 44.1 / 33.8; 2 bits,
+// 64 x 55296 79.3 / 61.4; 7 heads 30 x 48128 54.2 / 39.7; but 8 heads, 216 rows x 18816 99 / 114 and 6 heads, 64 x 65536
+// 81 / 100: six rounds, four rounds, and the streaming kernels expand the codes once for both head sets.  A
+// tail that is half of the bytes counts too: 272 rows x 9088 + 830 in three rounds 55 / 63.
+bool on_chip_is_faster(const cq::DecodeShape& s, const cq::FusedPlan& plan) {
+  const double rows = (double)s.B * s.Hkv, mtok = rows * s.n_vis * 1e-6, c = plan.n_chunks;
+  const double rounds = std::ceil(rows * plan.nhb * c / 256.0);
+  const double chunk = (s.bits == 1 ? 1.6 : 2.1) * 1e-3 * s.n_vis / c + 0.9 * std::ceil(cq::ceil_div(s.n_text, 64) / c);
+  const double fused = 7.8 + 1.25 * rounds * (chunk + 1.3);
+  const double streamed = plan.nhb > 1 ? 38.0 + 11.0 * mtok : 15.5 + 14.5 * mtok;
+  return fused < streamed;
+}
+
 // Scratch of the kernels that run where the tile kernels do not.
 size_t ws_without_tiles(const DecodeCall& c) {
   return c.streamed ? c.stream.ws_bytes : c.tuned ? c.plan.ws_bytes : c.generic_ws.total_bytes;
@@ -270,10 +285,17 @@ int select_kernels(const cq_layout_t* L, int n_text, int n_text_cap, size_t scra
   // so where it is most of the call the streaming kernels stay.
   const bool whole_sets = call->plan.n_chunks == 1 && call->plan.nhb > 1 && L->n_vis >= kTwoSetsOnChip &&
                           L->bits <= 4 && g_decode_chunks == 0;
-  const bool on_chip = whole_sets || (call->plan.spread && (call->plan.nhb == 1 || L->n_vis >= kTwoSetsOnChip));
+  bool on_chip = whole_sets || (call->plan.spread && (call->plan.nhb == 1 || L->n_vis >= kTwoSetsOnChip));
+  size_t reserve = 0;                // scratch that shorter tails may use on other kernels
   if (call->tuned && (call->plan.n_chunks > 1 || call->plan.nhb > 1) && !g_one_launch && !on_chip) {
     call->stream = cq::make_stream_plan(call->shape, g_decode_chunks);
-    call->streamed = call->stream.ok && call->stream.ws_bytes <= scratch_limit;
+    if (call->stream.ok && g_kernel_path == CQ_PATH_AUTO && g_decode_chunks == 0 && call->plan.n_chunks > 1 &&
+        on_chip_is_faster(call->shape, call->plan)) {
+      on_chip = true;
+      reserve = call->stream.ws_bytes;
+    } else {
+      call->streamed = call->stream.ok && call->stream.ws_bytes <= scratch_limit;
+    }
   }
   call->generic_ws = cq::workspace_layout(L->batch, L->n_q_heads, L->head_dim, L->n_vis, n_text);
   call->tiled = false;
@@ -282,7 +304,6 @@ int select_kernels(const cq_layout_t* L, int n_text, int n_text_cap, size_t scra
   // within it too, with fewer chunks if need be; where they would not, that entry point refuses
   // what does not fit.
   const size_t most = (size_t)CQ_NOALLOC_SCRATCH_BYTES;
-  size_t reserve = 0;                // scratch that shorter tails may use on the tile kernels
   if (g_kernel_path == CQ_PATH_TILE) {
     call->tile = cq::make_tile_plan(call->shape);
     call->tiled = call->tile.ok;
