@@ -1115,7 +1115,7 @@ namespace {
 // One launch where chunks of whole units can be made of whole key blocks and value tiles, and their logits take
 // little enough LDS for several workgroups per CU.  It is faster on small calls of every head_dim (100 drawn
 // layouts below 100 thousand tokens: 1.06 with 64 channels, 1.2 with 128, 1.17 with 256) and with 128 channels on large
-// ones too (1.3 beyond 600 thousand).  With 64 and 256 channels it is not: all workgroups pass the exchange
+// ones too (1.3 beyond 600 thousand).  With 64 and 256 channels and with 8 bits it is not: all workgroups pass the exchange
 // together, so memory and matrix cores idle in turn (64 rows of 64 channels x 3328 tokens, two / one: 13.6 / 12.8 us,
 // x 8192 17.9 / 18.5; 480 rows of 256 channels x 4352 77 / 99), the more so in key groups of 32, which leave a wave a
 // short block.  768 workgroups: three per CU are resident whatever the registers (256 rows x 2001, 1024 / 768:
@@ -1127,8 +1127,8 @@ void plan_one_launch(const DecodeShape& s, long long rows, long long sets, TileP
   };
   const int units = ceil_div(s.n_vis, kUnit);
   p->row_ct = p->ct;
-  if (s.d != 128 && (s.n_vis > kRowMost || rows * sets * s.n_vis > kRowMostAll || (s.k_group < 64 && s.k_group != s.n_vis)))
-    return;
+  if (s.k_group < 64 && s.k_group != s.n_vis) return;
+  if ((s.d != 128 || s.bits == 8) && (s.n_vis > kRowMost || rows * sets * s.n_vis > kRowMostAll)) return;
   if (s.n_vis > 0) {
     if (!fits_units(s.k_axis, s.k_group) || !fits_units(s.v_axis, s.v_group)) return;
     const long long want = (kRowTarget + rows * sets - 1) / (rows * sets);
