@@ -30,12 +30,6 @@ struct SliceArgs {
   uint16_t* minv;
 };
 
-// the value of lane ^ 1 (0xB1) or lane ^ 2 (0x4E)
-template <int CTRL>
-__device__ inline uint32_t other_lane(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xF, 0xF, true);
-}
-
 // grid: ((group / 8) * slices + slice) * 8 + group % 8, first the one tensor's groups, then the other's
 template <int BITS, int LANES, int THREADS, int P>
 __global__ void __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(BITS <= 2 || P <= 12 ? 4 : 1)))

@@ -25,10 +25,11 @@
 // again in place of the missing ones, which changes no extremum, and stores only what exists.
 // Channel-wise groups of any other size are "whole" sequences of their own (Sec. 3.1 as printed
 // when the group is n_vis).  Up to 128 tokens are one short tile; those that a workgroup's registers hold go to
-// quantize_slice.hip.  Longer ones take a pass of their own: row_extrema_kernel leaves `splits` partial (min, max) pairs per channel in the code words of
-// the sequence's LAST tile (the caller's output buffer: no other memory is needed), the tile
-// kernel reduces them instead of computing tile statistics, and the last tile of every sequence
-// is quantized by a second launch, after all other tiles have read the partials it overwrites.
+// quantize_slice.hip.  Longer ones take a pass of their own: row_extrema_kernel leaves `splits` partial
+// (min, max) pairs per channel in the code words of the sequence's LAST tile (the caller's output
+// buffer: no other memory is needed), the tile kernel reduces them instead of computing tile statistics,
+// and the last tile of every sequence is quantized by a second launch, after all other tiles have read
+// the partials it overwrites.
 // The FIRST tile of a sequence is the short one, so the last one always has room for the partials.
 // Results are bit-identical to evaluating the quantize equation element by element in fp64.
 //
@@ -53,6 +54,14 @@ typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 
 constexpr int kTile = 128;       // tokens per block
 constexpr int kThreads = 256;
+
+// The value of lane ^ 1 (0xB1), lane ^ 2 (0x4E), of the half row mirrored (0x141) or the row (0x140), moved inside
+// the vector unit; every lane of the wave is active.  A small call is one chain of such steps: with __shfl_xor, an
+// LDS round trip each, 8 rows x 3328 tokens at 2 bits took 8.6 us, now 7.7 (large calls are HBM-bound: the same).
+template <int CTRL>
+__device__ inline uint32_t other_lane(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xF, 0xF, true);
+}
 
 // ---- fp16 bit patterns as an ordered set
 __device__ inline uint16_t h_key(uint16_t u) { return (u & 0x8000u) ? (uint16_t)~u : (uint16_t)(u | 0x8000u); }
@@ -444,12 +453,12 @@ __device__ __forceinline__ void quantize_tile(const QArgs& a, const unsigned blo
       const int tok = 32 * wave + kSlots * i + ts;
       if constexpr (BITS == 1) {
         bits <<= 24 - 8 * (c8 & 3);
-        bits |= __shfl_xor(bits, 1);
-        bits |= __shfl_xor(bits, 2);
+        bits |= other_lane<0xB1>(bits);
+        bits |= other_lane<0x4E>(bits);
         if ((c8 & 3) == 0) s_codes[tok * kWords + (c8 >> 2)] = bits;
       } else {
         bits <<= 16 - 16 * (c8 & 1);
-        bits |= __shfl_xor(bits, 1);
+        bits |= other_lane<0xB1>(bits);
         if ((c8 & 1) == 0) s_codes[tok * kWords + (c8 >> 1)] = bits;
       }
     }
@@ -469,11 +478,14 @@ __device__ __forceinline__ void quantize_tile(const QArgs& a, const unsigned blo
                                                __builtin_shufflevector(hi4, hi4, 2, 3));
       v2h st = {(_Float16)fminf((float)lo[0], (float)lo[1]),
                 (_Float16)(-fmaxf((float)hi[0], (float)hi[1]))};                    // {min, -max}
-#pragma unroll
-      for (int o = 1; o < kLanesPerGroup; o <<= 1) {
-        const uint32_t other = __shfl_xor(__builtin_bit_cast(uint32_t, st), o);
-        st = __builtin_elementwise_min(st, __builtin_bit_cast(v2h, other));
-      }
+      // over 4 to 32 lanes, in the vector unit as far as a row of 16 reaches (each step finds equal values in the
+      // lanes that the ones before it have joined, so a mirror does for a distance of 4 or 8)
+      auto join = [&](uint32_t other) { st = __builtin_elementwise_min(st, __builtin_bit_cast(v2h, other)); };
+      join(other_lane<0xB1>(__builtin_bit_cast(uint32_t, st)));
+      join(other_lane<0x4E>(__builtin_bit_cast(uint32_t, st)));
+      if constexpr (kLanesPerGroup >= 8) join(other_lane<0x141>(__builtin_bit_cast(uint32_t, st)));
+      if constexpr (kLanesPerGroup >= 16) join(other_lane<0x140>(__builtin_bit_cast(uint32_t, st)));
+      if constexpr (kLanesPerGroup >= 32) join(__shfl_xor(__builtin_bit_cast(uint32_t, st), 16));
       if ((c8 % kLanesPerGroup) == 0) {
         const int tok = 32 * wave + kSlots * i + ts;
         s_stat[tok * kPerTok + c8 / kLanesPerGroup][0] = st[0];
@@ -532,12 +544,12 @@ __device__ __forceinline__ void quantize_tile(const QArgs& a, const unsigned blo
       uint32_t bits = octet_codes<BITS>(x[i], thr);
       if constexpr (BITS == 1) {
         bits <<= 24 - 8 * (c8 & 3);
-        bits |= __shfl_xor(bits, 1);
-        bits |= __shfl_xor(bits, 2);
+        bits |= other_lane<0xB1>(bits);
+        bits |= other_lane<0x4E>(bits);
         if ((c8 & 3) == 0) s_codes[tok * kWords + (c8 >> 2)] = bits;
       } else {
         bits <<= 16 - 16 * (c8 & 1);
-        bits |= __shfl_xor(bits, 1);
+        bits |= other_lane<0xB1>(bits);
         if ((c8 & 1) == 0) s_codes[tok * kWords + (c8 >> 1)] = bits;
       }
     }
