@@ -385,8 +385,9 @@ def main() -> int:
 
     # quantizer figures (bytes read + written per call)
     rows = w.batch * w.n_kv_heads
-    # a tensor with whole-sequence statistics is read twice (extrema pass, then codes)
-    q_reads = (2 if k_group == w.n_vis else 1) + (2 if v_group == w.n_vis and args.v_axis == "channel" else 1)
+    # a tensor with whole-sequence statistics of over 4096 tokens is read twice (extrema pass, then codes)
+    q_reads = (2 if k_group == w.n_vis > 4096 else 1) + (
+        2 if v_group == w.n_vis > 4096 and args.v_axis == "channel" else 1)
     q_bytes = rows * w.n_vis * (q_reads * w.head_dim * 2) + rows * w.n_vis * (per_vis)
     q_ms = sorted(quant_ms)[len(quant_ms) // 2]
 
@@ -403,10 +404,10 @@ def main() -> int:
     # (the tile kernels keep their logits in fp32, the streaming ones in 16 bits)
     tiled = args.path == "auto" and ws.numel() >= w.batch * w.n_q_heads * (w.n_vis + w.n_text) * 4
     streamed = split and ws.numel() > w.batch * w.n_q_heads * w.n_vis * 2
-    kernel_name = ("tile_logits_kernel + tile_values_kernel (both launches of one call)" if tiled else
+    kernel_name = ("tile_row_kernel or tile_logits_kernel + tile_values_kernel (all launches of one call)" if tiled else
                    "stream_logits_kernel + stream_values_kernel + combine_kernel (all launches of one call)"
                    if streamed else
-                   "fused_row_kernel, extrema pass + partial pass, + combine_kernel (all launches of one call)"
+                   "fused_row_kernel, several workgroups per row (the call's only launch)"
                    if split else
                    "fused_row_kernel<%d> (the call's only launch)" % (min(k_group, 128) // 16) if fused
                    else "scores_kernel + pv_kernel + combine_kernel (all launches of one call)")

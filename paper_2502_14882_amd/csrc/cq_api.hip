@@ -207,18 +207,18 @@ constexpr int kTwoSetsOnChip = 256;
 // Whether the tile kernels finish a call sooner than the tuned kernels that could take it, asked where the fused kernel
 // does not spread its rows over the chip (8 bits, two head sets of few tokens, more rows than CUs).  The fused
 // kernel gives a row (a chunk of a row) to one CU, which moves about 27 GB/s, and the streaming
-// kernels take three launches; with few rows the tile kernels, two launches over many small
+// kernels take three launches; with few rows the tile kernels, one or two launches over many small
 // workgroups, win.  Microseconds per call inside a recorded graph, fitted to measurements of both sides
-// over 8 to 256 rows (batch x KV heads) of 1024 to 32768 tokens, 1 to 8 bits, key groups of 32 tokens to
-// the whole row, 1 to 6 query heads per KV head; for example (tuned / tile)
+// (two launches of the tile kernels) over 8 to 256 rows (batch x KV heads) of 1024 to 32768 tokens, 1 to
+// 8 bits, key groups of 32 tokens to the whole row, 1 to 6 query heads per KV head; for example (tuned / tile)
 //   1 bit, 4 heads:  8 rows x 3328 tokens 12.5 / 11.8, x 8192 21.8 / 14.4; 32 rows x 8192 22.1 / 19.6;
 //                    8 rows x 1024 9.1 / 11.6 and 64 rows x 8192 22.2 / 27.1 stay fused
 //   1 bit, 6 heads:  8 rows x 3328 20.7 / 12.5, 64 rows 22.6 / 19.5; 128 rows 26.0 / 27.3 stay streamed
 //   4 bits:          32 rows x 3328 17.7 / 14.8;  8 bits: 8 rows x 3328 37.5 / 14.9, 16 x 10240 25.5 / 19.5
 // The tail plays a part in one place: the streaming kernels read it once for two head sets, the tile
 // kernels once for each (112 rows x 128 tokens, 8 heads, 1000 tail tokens: 23.4 / 28.9).  Over 700 drawn
-// layouts of 1 to 500 rows, 3 of the 285 that go to the tile kernels are slower there by more than 2 %,
-// the worst by 8 %.
+// layouts of 1 to 500 rows with the tile kernels in two launches, 3 of the 285 that go to them are slower
+// there by more than 2 %, the worst by 8 %; one launch is taken only where it is faster still.
 bool tile_is_faster(cq::DecodeShape s, const cq::FusedPlan& with_tail) {
   const double rows = (double)s.B * s.Hkv, kn = s.n_vis * 1e-3, mtok = rows * s.n_vis * 1e-6;
   if (mtok > 2.0) return false;

@@ -200,7 +200,7 @@ hipError_t launch_decode_stream(const DecodeShape& s, const StreamPlan& plan, co
 
 // Tile decode (decode_tile.hip) for the layouts the two above do not take: head_dim 64, 128 or 256,
 // channel-wise keys and values in groups of any size or values token-wise over the whole head, any
-// number of query heads per KV head.  Logits pass, values pass.
+// number of query heads per KV head.  Logits pass, values pass, or both in one launch.
 struct TilePlan {
   bool ok = false;
   int ca = 0, cb = 0;              // chunks per row of the visual tokens: logits pass, values pass

@@ -25,8 +25,7 @@
 //                 into one (m, l, acc[128]) per (head, chunk).
 //   combine       the shared kernel of decode_generic.hip (online-softmax merge over chunks).
 //
-// Against recomputing the logits in the second pass (what decode_fused.hip does for split rows)
-// this trades a second read of the packed keys (16b + 6 bytes per token) and all of its
+// Against recomputing the logits in the second pass this trades a second read of the packed keys (16b + 6 bytes per token) and all of its
 // arithmetic for 2g bytes of logits per token written and read once.
 //
 // Logits in 16 bits.  What a weight needs from its logit is absolute accuracy in proportion to the
