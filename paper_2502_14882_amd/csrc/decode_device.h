@@ -85,6 +85,19 @@ __device__ inline float wave_max_nonneg(float v) {
   x = max(x, __builtin_amdgcn_update_dpp(x, x, 0x143, 0xC, 0xF, false));  // row_bcast31 -> rows 2,3
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(x, 63));
 }
+// The same of a float of either sign: the bits of a negative one turned round order like integers.
+__device__ inline float wave_max(float v) {
+  int x = __builtin_bit_cast(int, v);
+  x ^= (x >> 31) & 0x7fffffff;
+  x = max(x, __builtin_amdgcn_update_dpp(x, x, 0xB1, 0xF, 0xF, true));
+  x = max(x, __builtin_amdgcn_update_dpp(x, x, 0x4E, 0xF, 0xF, true));
+  x = max(x, __builtin_amdgcn_update_dpp(x, x, 0x141, 0xF, 0xF, true));
+  x = max(x, __builtin_amdgcn_update_dpp(x, x, 0x140, 0xF, 0xF, true));
+  x = max(x, __builtin_amdgcn_update_dpp(x, x, 0x142, 0xA, 0xF, false));
+  x = max(x, __builtin_amdgcn_update_dpp(x, x, 0x143, 0xC, 0xF, false));
+  x = __builtin_amdgcn_readlane(x, 63);
+  return __builtin_bit_cast(float, x ^ ((x >> 31) & 0x7fffffff));
+}
 // value of four signed base-256 digit accumulators
 __device__ inline float digits_to_float(const v4i& c) {
   return fmaf(fmaf(fmaf((float)c[3], 256.f, (float)c[2]), 256.f, (float)c[1]), 256.f, (float)c[0]);

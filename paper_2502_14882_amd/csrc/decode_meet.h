@@ -107,9 +107,8 @@ __device__ inline void merge_partials(const float* partial, int n_slots, int gh,
         }
       };
       load(first);                                             // before anything is done with (m, l)
-      // the slots' maximum by its distance to the first one's (wave_max_nonneg takes no signs)
-      const float ref = fmaxf(M, lane_value(ml[0], 0));
-      const float Mb = ref + wave_max_nonneg(fmaxf(ml[0] - ref, 0.f));
+      // (any slot may be empty, with -FLT_MAX for its m: nothing is formed by differences to a certain one's)
+      const float Mb = fmaxf(M, wave_max(ml[0]));
       const float keep = __builtin_amdgcn_exp2f((M - Mb) * kLog2e);
       M = Mb;
       const float w = lane < n ? __builtin_amdgcn_exp2f((ml[0] - M) * kLog2e) : 0.f;

@@ -161,6 +161,31 @@ def test_values_that_stand_out(d, bits, tile_path):
             assert err <= least + 1e-4, "%s head %d: rel L2 %.3e, fp16 rounding %.3e" % (what, h, err, least)
 
 
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("level", [150.0, -150.0])
+def test_an_empty_tail_of_a_length_on_the_device(d, level, tile_path):
+    """No token of the tail yet, its bound larger: the partials of the tail's workgroups are empty, and the merge
+    takes its reference from the others.  Logits around 150 and -150, where exp() without a reference leaves
+    fp32's range; rows of one and of several chunks."""
+    for n_vis, bound in ((512, 1), (2048, 300)):
+        gen = torch.Generator().manual_seed(d + n_vis)
+        k = 0.5 + 0.1 * torch.randn(1, 2, n_vis, d, generator=gen)
+        x_cpu = {"q": (2 * level / d ** 0.5 + torch.randn(1, 4, d, generator=gen)).half(), "k": k.half(),
+                 "v": torch.randn(1, 2, n_vis, d, generator=gen).half(),
+                 "k_text": torch.zeros(1, 2, bound, d).half(), "v_text": torch.zeros(1, 2, bound, d).half()}
+        lay = cq.make_layout(1, 4, 2, d, n_vis, 2, 0, 1, 128, d)
+        x = H.to_device(x_cpu)
+        kq, vq = H.oracle_quantize(x_cpu, lay)
+        kd, vd = cq.cq_quantize_kv(lay, x["k"], x["v"])
+        n_dev = torch.zeros(1, dtype=torch.int32, device="cuda")
+        for mode in ("none", "dynamic"):
+            ref = O.decode_attn(x_cpu["q"].numpy(), kq, vq, None, None, 0, *MODES[mode], 0.0)
+            out = cq.cq_decode_attn_devlen(lay, x["q"], kd, vd, x["k_text"], x["v_text"], n_dev, bound,
+                                           cq.make_calib(*MODES[mode]))
+            torch.cuda.synchronize()
+            _check(out, ref, "d %d n_vis %d level %g %s" % (d, n_vis, level, mode))
+
+
 @pytest.mark.parametrize("d,bits,vax", [(64, 1, 1), (128, 2, 0), (256, 1, 1)])
 def test_many_partials(d, bits, vax, tile_path):
     """One row of 32768 tokens is 64 chunks, a tail of 8193 another 33 of 256 tokens (64 of 128 are 8192): the
