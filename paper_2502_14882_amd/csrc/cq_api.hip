@@ -286,6 +286,17 @@ int select_kernels(const cq_layout_t* L, int n_text, int n_text_cap, size_t scra
   const bool whole_sets = call->plan.n_chunks == 1 && call->plan.nhb > 1 && L->n_vis >= kTwoSetsOnChip &&
                           L->bits <= 4 && g_decode_chunks == 0;
   bool on_chip = whole_sets || (call->plan.spread && (call->plan.nhb == 1 || L->n_vis >= kTwoSetsOnChip));
+  // Calls that stay here instead of going to the tile kernels keep the precision of those, or go there.
+  if (on_chip && g_kernel_path == CQ_PATH_AUTO) {
+    const cq::FusedPlan rows = call->plan.n_chunks == 1 ? call->plan : cq::make_fused_plan(call->shape, 0);
+    if (tile_is_faster(call->shape, rows)) {
+      call->plan.fine = call->plan.can_fine;
+      if (!call->plan.fine) {
+        call->plan = rows;
+        on_chip = false;
+      }
+    }
+  }
   size_t reserve = 0;                // scratch that shorter tails may use on other kernels
   if (call->tuned && (call->plan.n_chunks > 1 || call->plan.nhb > 1) && !g_one_launch && !on_chip) {
     call->stream = cq::make_stream_plan(call->shape, g_decode_chunks);

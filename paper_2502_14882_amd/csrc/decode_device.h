@@ -224,6 +224,24 @@ __device__ inline float variant_weight(int v) {     // 1 / (value of a set code-
   else if constexpr (BITS == 2) return v == 0 ? 1.f : v == 1 ? 0.25f : 0.0625f;
   else return 1.f;
 }
+// The same with the upper half of a byte shifted down before it is masked: a code then weighs at most 8 (1 bit) or 4
+// (2 bits), and the other operand, which carries the inverse weight, loses at most 3 of its bits to it (7 with the
+// masks above, which save that shift).
+template <int BITS>
+__device__ inline int operand_low(uint32_t word, int v) {
+  if constexpr (BITS == 8) return operand_variant<8>(word, 0);
+  else {
+    constexpr int kLow = 4 / BITS;                          // variants in the lower half of a byte
+    constexpr uint32_t mask = BITS == 1 ? 0x01010101u : BITS == 2 ? 0x03030303u : 0x0f0f0f0fu;
+    return (int)((v < kLow ? word : word >> 4) & (mask << (BITS * (v % kLow))));
+  }
+}
+template <int BITS>
+__device__ inline float low_weight(int v) {         // 1 / (value of a set code-1 byte)
+  if constexpr (BITS == 1) return ldexpf(1.f, -(v % 4));
+  else if constexpr (BITS == 2) return v % 2 ? 0.25f : 1.f;
+  else return 1.f;
+}
 // Position, inside its 32-bit word, of the code that variant v reads from byte y: the packing is
 // MSB first, so code j sits at bits [32 - b(1 + j), 32 - b j).
 template <int BITS>

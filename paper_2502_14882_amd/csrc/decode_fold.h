@@ -78,6 +78,52 @@ __device__ inline T head_sums(const T (&part)[kHeads], int lane) {
   return fold_rows(fold_halves(h0, h2), fold_halves(h1, h3));
 }
 
+// ---- operands in fixed point that keep fp32's bits
+// The four signed base-256 digits of a * b rounded to the nearest integer (|a b| < 2^30), as the four
+// bytes of the result.  Added to 1.5 * 2^52 a double shows the integer in its low word.
+__device__ inline int rounded_digits(float a, double b) {
+  const double t = fma((double)a, b, 6755399441055744.0 + 8421504.0);
+  return __builtin_bit_cast(v2i, t)[0] ^ 0x00808080;
+}
+
+// a * b + the bias of the four signed base-256 digits: as an integer ^ 0x00808080 its bytes are the digits.
+// Above 2^23 the fma rounds to nearest integers, and fp32 has no more below 2^24.
+__device__ inline float digits_bias(float a, float b) { return fmaf(a, b, 8421504.f); }
+
+// Fixed-point scales of the four heads, powers of two from 2^-90 to 2^90, as the bits of floats.
+struct Scales {
+  static constexpr int kOne = 127 << 23;
+  int up[kHeads];                                              // wave-uniform
+  __device__ explicit Scales(int exponent) {
+#pragma unroll
+    for (int h = 0; h < kHeads; ++h) up[h] = (exponent + 127) << 23;
+  }
+  __device__ float of(int h) const { return __builtin_bit_cast(float, up[h]); }
+  __device__ float inverse(int kb) const {                     // of head kb
+    const int a = kb & 1 ? up[1] : up[0], b = kb & 1 ? up[3] : up[2];
+    return __builtin_bit_cast(float, 2 * kOne - (kb & 2 ? b : a));
+  }
+  // Lowered until w * scale < 2^26 for the heads' w >= 0 of all lanes.  The maxima by a transposing
+  // butterfly, as in head_sums: lane l of a row ends up with head bitrev2(l & 3).  Floats that are not
+  // negative order like their bits, and integer maxima need no second instruction for NaNs.
+  __device__ void lower(const float (&w)[kHeads], int lane) {
+    const bool b0 = lane & 1, b1 = lane & 2;
+    int i[kHeads];
+#pragma unroll
+    for (int h = 0; h < kHeads; ++h) i[h] = __builtin_bit_cast(int, w[h]);
+    const int u0 = max(b0 ? i[2] : i[0], dpp_i32<0xB1>(b0 ? i[0] : i[2]));
+    const int u1 = max(b0 ? i[3] : i[1], dpp_i32<0xB1>(b0 ? i[1] : i[3]));
+    int r = max(b1 ? u1 : u0, dpp_i32<0x4E>(b1 ? u0 : u1));
+    r = max(r, dpp_i32<0x124>(r));
+    r = max_rows(max_halves(max(r, dpp_i32<0x128>(r))));
+    // r < 2^(e - 126) for its exponent field e: the scale 2^(26 - (e - 126)), its field 279 - e
+    const int fits = min(max(279 - (r >> 23), 127 - 90), 127 + 90) << 23;
+    constexpr int kLane[kHeads] = {0, 2, 1, 3};
+#pragma unroll
+    for (int h = 0; h < kHeads; ++h) up[h] = min(up[h], __builtin_amdgcn_readlane(fits, kLane[h]));
+  }
+};
+
 }  // namespace
 }  // namespace cq
 

@@ -46,6 +46,7 @@
 
 #include "cq_internal.h"
 #include "decode_device.h"
+#include "decode_fold.h"
 #include "decode_meet.h"
 
 namespace cq {
@@ -99,14 +100,30 @@ struct FusedArgs {
 
 extern __shared__ __align__(16) uint8_t smem[];
 
-// SPLIT = several workgroups per row.  TILES = 16-token tiles per key group.  VCH = values are
+// Whether one of the wave's operands has outgrown its scale (digits_bias of numbers that are not negative: floats
+// that order like their bits).
+__device__ inline bool over_scale(const float (&x)[kHeads]) {
+  auto bits_of = [](float v) { return __builtin_bit_cast(int, v); };
+  return __builtin_amdgcn_ballot_w64(max(max(bits_of(x[0]), bits_of(x[1])), max(bits_of(x[2]), bits_of(x[3]))) >=
+                                     bits_of(0x1p29f)) != 0;
+}
+
+// SPLIT = several workgroups per row.  FINE = as close as fp32 products and sums, like the tile kernels, whose calls these
+// take over (few rows, two head sets, rows of any length).  Logits: operands of 2^30 steps by the lower masks, put
+// together in fp64; where two channels of +-3e3 in a logit all but cancel, outputs are 3e-4 off otherwise.  Token-wise
+// values: a scale per head that follows weight x token scale; one scale for all heads, set by the largest token
+// scale, lets that token take the bits of the others whether or not a head looks at it, and the tail the bits of
+// all visual tokens (values 3e6 times the others' at weights of 2e-8: 64 of 1000 to 8192 tokens 6e-4 to 1e-2 off, all visual
+// tokens of a short row 100 %; this way below 2e-5 with the rounding of the logits).  Recorded in a graph,
+// otherwise / FINE: 8 rows x 3328 + 128 tokens, 1 bit 11.20 / 11.37 us, 4 bits 12.36 / 12.44; 32 x 8192 + 512, 1 bit 14.10 / 14.45.
+// TILES = 16-token tiles per key group.  VCH = values are
 // quantized channel-wise over groups of tokens (Sec. 3.1, the paper's own choice) instead of
 // token-wise.
 // KW = key statistics over the whole sequence: one parameter group per row, so the query operand,
 // its shift and the additive term are formed once per wave instead of once per 128 tokens.
 // RAG = the row (with KW, and values token-wise or over the whole sequence) may end anywhere: what lies between its end
 // and the next multiple of 128 reads the last token again, which changes no extremum, and has weight 0.
-template <bool SPLIT, int TILES, int BITS, bool VCH, bool KW = false, bool NT = true, int RK = kRingK, bool RAG = false>
+template <bool SPLIT, bool FINE, int TILES, int BITS, bool VCH, bool KW = false, bool NT = true, int RK = kRingK, bool RAG = false>
 __global__ void __launch_bounds__(kThreads)
 fused_row_kernel(const FusedArgs args) {
   // code words, see stream_load: a key instruction covers whole lines up to b = 4, a value
@@ -114,6 +131,7 @@ fused_row_kernel(const FusedArgs args) {
   constexpr bool kNtKeys = NT && BITS <= 4, kNtCodes = NT && BITS <= 2;
   static_assert(!KW || TILES == 8, "whole-sequence keys are processed 128 tokens at a time");
   static_assert(KW || !RAG, "a row that ends inside a processing group has whole-sequence keys");
+  static_assert(FINE || !RAG, "the tile kernels' rows of any length");
   // Split rows: one pass over the workgroup's own chunk, unless the other workgroups' extrema do not turn up;
   // then one pass over each of the other chunks for their extrema, and one more over its own.
   u64 count_seen = 0;
@@ -123,7 +141,10 @@ fused_row_kernel(const FusedArgs args) {
   // address alive from pass to pass (90 scalar and 40 vector registers of them were spilled).
   int tid = threadIdx.x;
   auto kernarg = __builtin_amdgcn_kernarg_segment_ptr();
-  if constexpr (SPLIT) asm volatile("" : "+v"(tid), "+s"(kernarg));
+  if constexpr (SPLIT) {
+    asm volatile("" : "+v"(tid));
+    asm volatile("" : "+s"(kernarg));   // (by itself: next to a vector register it counts as one)
+  }
   const FusedArgs& a = SPLIT ? *(const FusedArgs*)kernarg : args;
   // The arguments fill five cache lines: one word of each now, together, instead of a wait for each of
   // them where it is first used.
@@ -260,8 +281,12 @@ fused_row_kernel(const FusedArgs args) {
       int wvar0, wvar1;
       const int wr0 = row_of(wc0, wvar0), wr1 = row_of(wc1, wvar1);
       float qv0[kHeads], qv1[kHeads], qmax_all;     // set below, behind the first loads
-      const float inv_w0 = 1.f / variant_weight<BITS>(wvar0);   // exact: powers of two
-      const float inv_w1 = 1.f / variant_weight<BITS>(wvar1);
+      float qm0 = 0.f, qm1 = 0.f;                   // FINE: the largest of qv0, of qv1
+      auto key_weight = [](int v) { return FINE ? low_weight<BITS>(v) : variant_weight<BITS>(v); };
+      auto key_operand = [](uint32_t word, int v) { return FINE ? operand_low<BITS>(word, v) : operand_variant<BITS>(word, v); };
+      const float inv_w0 = 1.f / key_weight(wvar0);   // exact: powers of two
+      const float inv_w1 = 1.f / key_weight(wvar1);
+      using Sum = std::conditional_t<FINE, double, float>;
       const uint32_t* kc_lane =
           a.k_codes + ((size_t)row * a.n_vis + vis0) * (4 * BITS) + n16 * (4 * BITS) + kb * BITS;
       float* lrow = logits + (size_t)hres * a.stride + n16;
@@ -325,22 +350,38 @@ fused_row_kernel(const FusedArgs args) {
         }
       };
       // query operand of the key group whose parameters sit in ring slot `slot`, staged at xb
-      auto build_operand = [&](int slot, uint8_t* xb, v4i& A0, v4i& A1, float& bias_h,
-                               float& inv_f, float& inv_f16) {
-        // |q'| <= max|q| * (largest scale of the group): a bound, good to a few bits, that costs
-        // one wave-wide maximum instead of a pass over all scales
+      auto build_operand = [&](int slot, uint8_t* xb, v4i& A0, v4i& A1, Sum& bias_h,
+                               Sum& inv_f, Sum& inv_f16) {
         const float s0 = s01[slot][0], s1 = s01[slot][1];
-        const float smax = wave_max_nonneg(fmaxf(s0, s1));
-        const int F = fixed_point_shift(qmax_all * smax);      // one shift for the four heads
-        const float s0f = ldexpf(s0, F), s1f = ldexpf(s1, F);
         v4i x0, x1;
+        if constexpr (FINE) {
+          // (made here and now from 8 registers: as loop invariants the doubles would occupy 16 more and spill)
 #pragma unroll
-        for (int h = 0; h < kHeads; ++h) {
-          x0[h] = product_digits(qv0[h], s0f);
-          x1[h] = product_digits(qv1[h], s1f);
+          for (int h = 0; h < kHeads; ++h) asm volatile("" : "+v"(qv0[h]), "+v"(qv1[h]));
+          // the largest operand is below 2^30: the top digit of four stays below 64
+          const int F = 1 + fixed_point_shift(wave_max_nonneg(fmaxf(qm0 * s0, qm1 * s1)));
+          const double s0f = ldexp((double)s0, F), s1f = ldexp((double)s1, F);
+#pragma unroll
+          for (int h = 0; h < kHeads; ++h) {
+            x0[h] = rounded_digits(qv0[h], s0f);
+            x1[h] = rounded_digits(qv1[h], s1f);
+          }
+          inv_f = ldexp((Sum)a.softmax_scale, -F);
+          inv_f16 = ldexp((Sum)a.softmax_scale, 16 - F);
+        } else {
+          // |q'| <= max|q| * (largest scale of the group): a bound, good to a few bits, that costs
+          // one wave-wide maximum instead of a pass over all scales
+          const float smax = wave_max_nonneg(fmaxf(s0, s1));
+          const int F = fixed_point_shift(qmax_all * smax);    // one shift for the four heads
+          const float s0f = ldexpf(s0, F), s1f = ldexpf(s1, F);
+#pragma unroll
+          for (int h = 0; h < kHeads; ++h) {
+            x0[h] = product_digits(qv0[h], s0f);
+            x1[h] = product_digits(qv1[h], s1f);
+          }
+          inv_f = ldexpf(1.f, -F);
+          inv_f16 = ldexpf(1.f, 16 - F);
         }
-        inv_f = ldexpf(1.f, -F);
-        inv_f16 = ldexpf(1.f, 16 - F);
         __builtin_amdgcn_wave_barrier();
         *reinterpret_cast<v4i*>(xb + x_wr0) = x0;
         *reinterpret_cast<v4i*>(xb + x_wr1) = x1;
@@ -351,16 +392,25 @@ fused_row_kernel(const FusedArgs args) {
         const v2i r10 = lds_read_tr8(xr + 256), r11 = lds_read_tr8(xr + 384);
         A0 = (v4i){r00[0], r00[1], r01[0], r01[1]};
         A1 = (v4i){r10[0], r10[1], r11[0], r11[1]};
-        bias_h = group_bias(qv0, qv1, (uint16_t)(m01[slot] & 0xffffu), (uint16_t)(m01[slot] >> 16),
-                                        BITS == 8 ? 128.f * s0 : 0.f, BITS == 8 ? 128.f * s1 : 0.f,
-                                        inv_w0, inv_w1, lane);
+        const uint16_t m0 = (uint16_t)(m01[slot] & 0xffffu), m1 = (uint16_t)(m01[slot] >> 16);
+        if constexpr (FINE) {      // 8-bit operand bytes are code - 128: the 128 comes back with the minimum
+          const double f0 = ((double)__half2float(__ushort_as_half(m0)) + (BITS == 8 ? 128.0 * (double)s0 : 0.0)) * (double)inv_w0;
+          const double f1 = ((double)__half2float(__ushort_as_half(m1)) + (BITS == 8 ? 128.0 * (double)s1 : 0.0)) * (double)inv_w1;
+          double part[kHeads];
+#pragma unroll
+          for (int h = 0; h < kHeads; ++h) part[h] = fma((double)qv0[h], f0, (double)qv1[h] * f1);
+          bias_h = head_sums(part, lane) * (double)a.softmax_scale;
+        } else {
+          bias_h = group_bias(qv0, qv1, m0, m1, BITS == 8 ? 128.f * s0 : 0.f, BITS == 8 ? 128.f * s1 : 0.f,
+                              inv_w0, inv_w1, lane);
+        }
         __builtin_amdgcn_wave_barrier();   // operand rows are consumed before logits land there
       };
       v4i A0w = {0, 0, 0, 0}, A1w = {0, 0, 0, 0};
-      float bias_w = 0.f, inv_f_w = 0.f, inv_f16_w = 0.f;
+      Sum bias_w = 0, inv_f_w = 0, inv_f16_w = 0;
       auto do_group = [&](int slot, int t) {
         v4i A0 = A0w, A1 = A1w;
-        float bias_h = bias_w, inv_f = inv_f_w, inv_f16 = inv_f16_w;
+        Sum bias_h = bias_w, inv_f = inv_f_w, inv_f16 = inv_f16_w;
         if constexpr (!KW)
           build_operand(slot, kInPlace ? lbytes + (size_t)t * (TILES * 16 * 4) : stage,
                         A0, A1, bias_h, inv_f, inv_f16);
@@ -386,17 +436,17 @@ fused_row_kernel(const FusedArgs args) {
           for (int v = 0; v < 4; ++v) {
             constexpr int kV = 8 / BITS;            // variants per byte
             if constexpr (kQuadKeys) {
-              B0[v] = operand_variant<BITS>(wt[tile], v);
-              B1[v] = operand_variant<BITS>(wt[tile], 4 + v);
+              B0[v] = key_operand(wt[tile], v);
+              B1[v] = key_operand(wt[tile], 4 + v);
             } else {
-              B0[v] = operand_variant<BITS>(w[slot][tile][v / kV], v % kV);
-              B1[v] = operand_variant<BITS>(w[slot][tile][(4 + v) / kV], (4 + v) % kV);
+              B0[v] = key_operand(w[slot][tile][v / kV], v % kV);
+              B1[v] = key_operand(w[slot][tile][(4 + v) / kV], (4 + v) % kV);
             }
           }
         };
         auto finish_tile = [&](int tile, const v4i& c) {
           const int lo = c[0] + (c[1] << 8), hi = c[2] + (c[3] << 8);
-          const float sv = fmaf((float)hi, inv_f16, fmaf((float)lo, inv_f, bias_h));
+          const float sv = (float)std::fma((Sum)hi, inv_f16, std::fma((Sum)lo, inv_f, bias_h));
           // lanes of unused heads (hres >= g) see q = 0, finish with sv = 0 and write their own
           // (never read) logit row: no branch in the hot loop
           lrow[(t * TILES + tile) * 16] = sv;
@@ -448,10 +498,12 @@ fused_row_kernel(const FusedArgs args) {
           const float x0 = h < gh ? __half2float(__ushort_as_half((uint16_t)(q01[h] & 0xffffu))) : 0.f;
           const float x1 = h < gh ? __half2float(__ushort_as_half((uint16_t)(q01[h] >> 16))) : 0.f;
           most = fmaxf(most, fmaxf(fabsf(x0), fabsf(x1)));
-          qv0[h] = x0 * (a.softmax_scale * variant_weight<BITS>(wvar0));
-          qv1[h] = x1 * (a.softmax_scale * variant_weight<BITS>(wvar1));
+          qv0[h] = x0 * (FINE ? key_weight(wvar0) : a.softmax_scale * key_weight(wvar0));      // FINE: exact
+          qv1[h] = x1 * (FINE ? key_weight(wvar1) : a.softmax_scale * key_weight(wvar1));
+          qm0 = fmaxf(qm0, fabsf(qv0[h]));
+          qm1 = fmaxf(qm1, fabsf(qv1[h]));
         }
-        qmax_all = wave_max_nonneg(most) * a.softmax_scale;
+        if constexpr (!FINE) qmax_all = wave_max_nonneg(most) * a.softmax_scale;
       }
       if constexpr (KW) {
         build_operand(0, stage, A0w, A1w, bias_w, inv_f_w, inv_f16_w);
@@ -579,7 +631,7 @@ fused_row_kernel(const FusedArgs args) {
   }
   // ---- split row: gamma, delta are the extrema of all its chunks (Sec. 3.2)
   if constexpr (SPLIT) {
-    if (a.calib_mode == CQ_CALIB_DYNAMIC && a.n_chunks > 1 && pass < a.n_chunks) {
+    if (a.calib_mode == CQ_CALIB_DYNAMIC && pass < a.n_chunks) {
       row_lo = fminf(row_lo, lo_l);
       row_hi = fmaxf(row_hi, hi_l);
       if (pass > 0) { __syncthreads(); continue; }             // (red is written again)
@@ -618,13 +670,14 @@ fused_row_kernel(const FusedArgs args) {
   }
   // (the lanes of row h work on head h: one division for all four)
   float a2[kHeads], c2v[kHeads], c2t[kHeads], mref[kHeads];
+  float vis_unit = 1.f;      // of head kb: what a weight of the visual tokens is worth
   {
     float slope = 1.f, gam = 0.f, shift = 0.f;    // s' = slope * (s - gam) + shift
     if (a.calib_mode != CQ_CALIB_NONE && nv > 0) {
       float glo = a.gamma, ghi = a.delta;
       if (a.calib_mode == CQ_CALIB_DYNAMIC) {
-        glo = SPLIT && a.n_chunks > 1 ? row_lo : lo_l;      // of the whole row
-        ghi = SPLIT && a.n_chunks > 1 ? row_hi : hi_l;
+        glo = SPLIT ? row_lo : lo_l;      // of the whole row
+        ghi = SPLIT ? row_hi : hi_l;
       }
       const float width = ghi - glo;
       slope = width == 0.f ? 1.f : (width + a.tau1 - a.tau2) / width;
@@ -636,7 +689,13 @@ fused_row_kernel(const FusedArgs args) {
       M = fmaxf(M, slope * (lo_l - gam) + shift);
       M = fmaxf(M, slope * (hi_l - gam) + shift);
     }
-    const float c = (shift - slope * gam - M) * kLog2e;
+    // (FINE: weights of the visual tokens beside their own largest, however small that is beside the tail's)
+    float M_vis = M;
+    if (FINE && nv > 0) {
+      M_vis = fmaxf(slope * (lo_l - gam) + shift, slope * (hi_l - gam) + shift);
+      vis_unit = __builtin_amdgcn_exp2f((M_vis - M) * kLog2e);
+    }
+    const float c = (shift - slope * gam - M_vis) * kLog2e;
 #pragma unroll
     for (int h = 0; h < kHeads; ++h) {
       mref[h] = lane_value(M, 16 * h);
@@ -650,6 +709,7 @@ fused_row_kernel(const FusedArgs args) {
   v4i acc[8];
   float facc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};   // banked part, already unscaled
   int Fv = 0;          // shift of this wave's accumulators at the end of phase 2
+  float inv_fine = 0.f;      // FINE, token-wise: what they are worth there, of head kb
 #pragma unroll
   for (int p = 0; p < 8; ++p) acc[p] = (v4i){0, 0, 0, 0};
   float lsum[kHeads] = {0.f, 0.f, 0.f, 0.f}, msum[kHeads] = {0.f, 0.f, 0.f, 0.f};
@@ -794,7 +854,7 @@ fused_row_kernel(const FusedArgs args) {
         static_assert(kRingV == 2, "the loops below pair a ring slot with a tile of a 128-token group");
         const std::integral_constant<bool, true> fold_yes;
         const std::integral_constant<bool, false> fold_no;
-        if (a.v_pstride == 0) {
+        if (RAG || a.v_pstride == 0) {
           // whole-sequence statistics: every group has the row's parameters, so the wave folds
           // once, after its last tile (an int32 accumulator takes 2^20 per tile at most: 2047
           // tiles, a workgroup's LDS holds ~140)
@@ -844,31 +904,52 @@ fused_row_kernel(const FusedArgs args) {
         vsr[slot] = stream_load<NT>(vs_row + j);
         vmr[slot] = stream_load<NT>(vm_row + j);
       };
-      auto tile_step = [&](int jt, int slot) {
-        if (__builtin_amdgcn_ballot_w64(vsr[slot] >= fit_below) != 0) {
-          F_prep = min(F_prep, fixed_point_shift(wave_max_nonneg(vsr[slot])));
-          fit_below = ldexpf(1.f, 29 - F_prep);
-        }
-        if (F_prep < F_acc) {                     // bank before a tile with a lower shift is added
-          const float w_old = ldexpf(1.f, -F_acc);
+      Scales scales(90);
+      auto bank = [&](float w_old) {
 #pragma unroll
-          for (int p = 0; p < 8; ++p) {
-            facc[p] = fmaf(digits_to_float(acc[p]), w_old, facc[p]);
-            acc[p] = (v4i){0, 0, 0, 0};
+        for (int p = 0; p < 8; ++p) {
+          facc[p] = fmaf(digits_to_float(acc[p]), w_old, facc[p]);
+          acc[p] = (v4i){0, 0, 0, 0};
+        }
+      };
+      auto tile_step = [&](int jt, int slot) {
+        if constexpr (!FINE) {
+          if (__builtin_amdgcn_ballot_w64(vsr[slot] >= fit_below) != 0) {
+            F_prep = min(F_prep, fixed_point_shift(wave_max_nonneg(vsr[slot])));
+            fit_below = ldexpf(1.f, 29 - F_prep);
           }
-          F_acc = F_prep;
+          if (F_prep < F_acc) {                   // bank before a tile with a lower shift is added
+            bank(ldexpf(1.f, -F_acc));
+            F_acc = F_prep;
+          }
         }
         const float vsf = ldexpf(vsr[slot], F_prep);
         // 8-bit operands are code - 128: the 128 comes back with the token's minimum
         const float vmf = __half2float(__ushort_as_half(vmr[slot])) + (BITS == 8 ? 128.f * vsr[slot] : 0.f);
         v4i xs;
+        float w[kHeads], x[kHeads];
 #pragma unroll
         for (int h = 0; h < kHeads; ++h) {
           float p = __builtin_amdgcn_exp2f(fmaf(logits[h * a.stride + jt + lane], a2[h], c2v[h]));
           if (RAG) p = jt + lane < nv ? p : 0.f;
           lsum[h] += p;
           msum[h] = fmaf(p, vmf, msum[h]);
-          xs[h] = product_digits(p, vsf);
+          if constexpr (FINE) {
+            w[h] = p * vsr[slot];
+            x[h] = digits_bias(w[h], scales.of(h));
+          } else {
+            xs[h] = product_digits(p, vsf);
+          }
+        }
+        if constexpr (FINE) {
+          if (over_scale(x)) {
+            bank(scales.inverse(kb));
+            scales.lower(w, lane);
+#pragma unroll
+            for (int h = 0; h < kHeads; ++h) x[h] = digits_bias(w[h], scales.of(h));
+          }
+#pragma unroll
+          for (int h = 0; h < kHeads; ++h) xs[h] = (int)x[h] ^ 0x00808080;
         }
         __builtin_amdgcn_wave_barrier();
         *reinterpret_cast<v4i*>(lbytes + (size_t)jt * 4 + x_wr) = xs;
@@ -912,6 +993,7 @@ fused_row_kernel(const FusedArgs args) {
       }
       if (j0 < nv) tile_step(j0, 0);
       Fv = F_acc;
+      if constexpr (FINE) inv_fine = scales.inverse(kb);
     } }
     if constexpr (!VCH && BITS <= 2) { if (nv > 0) {
       // Pipeline over 64-token tiles (tile k of this wave starts at token (wave + 8k) * 64):
@@ -926,6 +1008,11 @@ fused_row_kernel(const FusedArgs args) {
       // it, the integer accumulators are banked into fp32 before that tile is added
       int F_prep = 90, F_acc = 90, F_tile[2] = {90, 90};
       float fit_below = ldexpf(1.f, 29 - 90);   // scales below this fit the shift F_prep
+      // FINE: the same with a scale per head that follows weight x scale; what a step of it is worth of head kb, for
+      // the tile prepared in each buffer and in the accumulators, and the number of times it was lowered
+      Scales scales(90);
+      float inv_prep = 0.f, inv_tile[2] = {0.f, 0.f}, inv_acc = 0.f;
+      int n_prep = 0, n_tile[2] = {0, 0}, n_acc = 0;
       const int step = kVisWaves * 64;
       const int x_wr = ((lane >> 4) * a.stride) * 4 + (lane & 15) * 16;          // row of token lane
       const int x_rd = (kb * a.stride) * 4 + (n16 >> 1) * 16 + (n16 & 1) * 8;   // tr rows 16kb+k
@@ -935,12 +1022,14 @@ fused_row_kernel(const FusedArgs args) {
       auto& vmr = p2_vmr;
       auto& load_tile = p2_load_tile;
       auto prep_tile = [&](int slot, int jt, int buf) {
-        if (__builtin_amdgcn_ballot_w64(vsr[slot] >= fit_below) != 0) {
-          // some token's scale does not fit the running shift (rare after the first tiles)
-          F_prep = min(F_prep, fixed_point_shift(wave_max_nonneg(vsr[slot])));
-          fit_below = ldexpf(1.f, 29 - F_prep);
+        if constexpr (!FINE) {
+          if (__builtin_amdgcn_ballot_w64(vsr[slot] >= fit_below) != 0) {
+            // some token's scale does not fit the running shift (rare after the first tiles)
+            F_prep = min(F_prep, fixed_point_shift(wave_max_nonneg(vsr[slot])));
+            fit_below = ldexpf(1.f, 29 - F_prep);
+          }
+          F_tile[buf] = F_prep;
         }
-        F_tile[buf] = F_prep;
         const float vsf = ldexpf(vsr[slot], F_prep);
         // converted here and now: folded into the multiply-adds below, the raw 16 bits would stay
         // live past the ring's next load into this slot, the compiler would give that load another
@@ -951,13 +1040,32 @@ fused_row_kernel(const FusedArgs args) {
 #pragma unroll
         for (int h = 0; h < kHeads; ++h) lg[h] = logits[h * a.stride + jt + lane];
         v4i xs;
+        float w[kHeads], x[kHeads];
 #pragma unroll
         for (int h = 0; h < kHeads; ++h) {
           float p = __builtin_amdgcn_exp2f(fmaf(lg[h], a2[h], c2v[h]));
           if (RAG) p = jt + lane < nv ? p : 0.f;
           lsum[h] += p;
           msum[h] = fmaf(p, vmf, msum[h]);
-          xs[h] = product_digits(p, vsf);
+          if constexpr (FINE) {
+            w[h] = p * vsr[slot];
+            x[h] = digits_bias(w[h], scales.of(h));
+          } else {
+            xs[h] = product_digits(p, vsf);
+          }
+        }
+        if constexpr (FINE) {
+          if (over_scale(x)) {
+            scales.lower(w, lane);
+            inv_prep = scales.inverse(kb);
+            ++n_prep;
+#pragma unroll
+            for (int h = 0; h < kHeads; ++h) x[h] = digits_bias(w[h], scales.of(h));
+          }
+          inv_tile[buf] = inv_prep;
+          n_tile[buf] = n_prep;
+#pragma unroll
+          for (int h = 0; h < kHeads; ++h) xs[h] = (int)x[h] ^ 0x00808080;
         }
         __builtin_amdgcn_wave_barrier();
         *reinterpret_cast<v4i*>(lbytes + (size_t)jt * 4 + x_wr) = xs;
@@ -996,16 +1104,18 @@ fused_row_kernel(const FusedArgs args) {
         pin_order();
         load_tile(nslot, jt + step + kRingV * step);
         pin_order();
-        if (F_tile[buf] < F_acc) {              // wave-uniform, rare
-          // a larger scale lowered the shift: bank what was accumulated so far in fp32 (the
+        if (FINE ? n_tile[buf] != n_acc : F_tile[buf] < F_acc) {              // wave-uniform, rare
+          // a larger scale (product) lowered the shift: bank what was accumulated so far in fp32 (the
           // four digit accumulators of a value cannot be shifted independently)
-          const float w_old = ldexpf(1.f, -F_acc);
+          const float w_old = FINE ? inv_acc : ldexpf(1.f, -F_acc);
 #pragma unroll
           for (int p = 0; p < 8; ++p) {
             facc[p] = fmaf(digits_to_float(acc[p]), w_old, facc[p]);
             acc[p] = (v4i){0, 0, 0, 0};
           }
           F_acc = F_tile[buf];
+          n_acc = n_tile[buf];
+          inv_acc = inv_tile[buf];
         }
         // p = mask variant (b = 1) or 4 * block + variant; the operand of product p + 1 is formed
         // before product p is issued, so no product waits on the ANDs right in front of it
@@ -1035,6 +1145,7 @@ fused_row_kernel(const FusedArgs args) {
       for (int d = 0; d < kRingV; ++d)                            // the wave's last 1..kRingV tiles
         if (j0 + d * step < nv) m_step(j0 + d * step, d, false);
       Fv = F_acc;
+      inv_fine = inv_acc;
     } }
   } else {
     // text tail.  lane = (token slot kb, channels 8 * n16 .. +7): one 16-byte load covers 8 channels
@@ -1043,8 +1154,8 @@ fused_row_kernel(const FusedArgs args) {
     // tokens; fp16 operands, fp32 sums): a 4 x 4 transpose over the wave's four rows of lanes
     // (two lane swaps each way) and four byte permutes leave every lane with the four tokens of
     // its two channels 8 n16 + 2 kb, + 1, and the weights come as fp16 pairs hi + lo / 2^11 of
-    // 2^10 p (p <= 1; products of fp16 numbers are exact in fp32), so the sum carries the weights
-    // to 2^-22 as the fp32 multiply-adds it replaces did to 2^-24.  The tail is handed to the text
+    // 2^15 p (p <= 1; products of fp16 numbers are exact in fp32), so the sum carries every weight down to
+    // 2^-29 of the largest to 2^-22 of itself, as the fp32 multiply-adds it replaces did to 2^-24.  The tail is handed to the text
     // waves in shares of SH tokens; the weights of a share are computed once (lane = token) and
     // staged in the share's own logit slots (SH * 4 bytes in each of the four head rows), one
     // 64-byte record per load step: [hi | lo][head][token of the step].
@@ -1083,7 +1194,7 @@ fused_row_kernel(const FusedArgs args) {
           if (lane < SH) {                                                  // zero beyond nt
 #pragma unroll
             for (int h = 0; h < kHeads; ++h) {
-              const float ps = pv[h] * 1024.f;
+              const float ps = pv[h] * 32768.f;
               const _Float16 hi = (_Float16)ps;
               const _Float16 lo = (_Float16)((ps - (float)hi) * 2048.f);
               *reinterpret_cast<_Float16*>(pb + rec_wr + 8 * h) = hi;
@@ -1127,7 +1238,7 @@ fused_row_kernel(const FusedArgs args) {
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int h = 0; h < kHeads; ++h)
-          ttot[2 * h + i] = fmaf(acc_lo[i][h], 0x1p-11f, acc_hi[i][h]) * 0x1p-10f;
+          ttot[2 * h + i] = fmaf(acc_lo[i][h], 0x1p-11f, acc_hi[i][h]) * 0x1p-15f;
     }
 #pragma unroll
     for (int h = 0; h < kHeads; ++h) lsum[h] = tl[h];
@@ -1137,7 +1248,15 @@ fused_row_kernel(const FusedArgs args) {
   float* partial = reinterpret_cast<float*>(smem) + (size_t)wave * kHeads * kD;   // [head][channel]
   if (vis_wave) {
     // matrix result lane: column n16 = code byte index, head = kb; accumulator p = bit position
-    const float inv_fv = ldexpf(1.f, -Fv);
+    const float inv_fv = FINE && !VCH ? inv_fine : ldexpf(1.f, -Fv);
+    if constexpr (FINE) {
+#pragma unroll
+      for (int h = 0; h < kHeads; ++h) {
+        const float unit = lane_value(vis_unit, 16 * h);
+        lsum[h] *= unit;
+        msum[h] *= unit;
+      }
+    }
 #pragma unroll
     for (int p = 0; p < 8; ++p) {
       const float v = fmaf(digits_to_float(acc[p]), inv_fv, facc[p]);
@@ -1147,7 +1266,8 @@ fused_row_kernel(const FusedArgs args) {
       const int tb = 16 * (p / kV) + n16;
       const int ch = (32 / BITS) * (tb >> 2) + code_in_word<BITS>(tb & 3, p % kV);
       // channel-wise values are accumulated in units of 2^-29 (the weights' fixed point)
-      partial[kb * kD + ch] = VCH ? v * 0x1p-29f : v * variant_weight<BITS>(p % kV);
+      const float x = VCH ? v * 0x1p-29f : v * variant_weight<BITS>(p % kV);
+      partial[kb * kD + ch] = FINE ? x * vis_unit : x;
     }
   } else {      // text wave: lane (kb, n16) holds heads 0..3, channels 8 n16 + 2 kb and + 1
 #pragma unroll
@@ -1196,7 +1316,7 @@ fused_row_kernel(const FusedArgs args) {
 #pragma unroll
       for (int w = 0; w < kWaves; ++w)
         num += reinterpret_cast<float*>(smem)[((size_t)w * kHeads + h) * kD + c];
-      if (!SPLIT || a.n_chunks == 1) {
+      if constexpr (!SPLIT) {
         a.out[(head0 + h) * kD + c] = __float2half_rn((num + m) / l);
       } else {          // one (m, l, acc[d]) partial of the joint softmax per (head, chunk)
         float* part = a.ws_partial + ((head0 + h) * a.n_chunks + own) * (size_t)(kD + 2);
@@ -1206,7 +1326,6 @@ fused_row_kernel(const FusedArgs args) {
     }
   }
   if constexpr (SPLIT) {
-    if (a.n_chunks == 1) return;
     u64* count = a.ws_count + (size_t)row * a.nhb + hb;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // this wave's partials have reached memory
     __syncthreads();
@@ -1215,7 +1334,7 @@ fused_row_kernel(const FusedArgs args) {
     __syncthreads();
     if (last[0] == 0.f) return;
     merge_partials<kD, kWaves>(a.ws_partial + head0 * a.n_chunks * (kD + 2), a.n_chunks, gh, a.out + head0 * kD,
-                               reinterpret_cast<float*>(smem));
+                               reinterpret_cast<float*>(smem), tid);
     for (int i = tid; i < gh * a.n_chunks * 2; i += kThreads) a.ws_words[head0 * a.n_chunks * 2 + i] = 0;
     if (tid == 0) *count = 0;
   }
@@ -1329,6 +1448,7 @@ FusedPlan make_fused_plan(const DecodeShape& shape, int min_chunks, FusedSplit s
   if (s.g > 2 * kHeads || (s.n_vis % 64 != 0 && !k_whole)) return p;
   if (s.v_axis == CQ_AXIS_CHANNEL && s.n_vis % s.v_group != 0 && !v_whole) return p;
   p.nhb = (s.g + kHeads - 1) / kHeads;
+  p.can_fine = s.bits <= 4 && (s.v_axis == CQ_AXIS_TOKEN || (k_whole && v_whole));
   const long long rows = (long long)s.B * s.Hkv * p.nhb;
   const int unit = chunk_unit(s);
   const int n_units = ceil_div(s.n_vis, s.k_group * unit);
@@ -1403,63 +1523,68 @@ struct FusedChoice { FusedKernel kern; int slot; };
 constexpr int kKernels = 36;       // slots
 
 // SPLIT: rows that several workgroups share.  slot: the kernel's place in the table of LDS limits.
-template <bool SPLIT>
+template <bool SPLIT, bool FINE>
 FusedChoice pick_kernel(const DecodeShape& s, const FusedPlan& plan, bool k_whole) {
   const bool vch = s.v_axis == CQ_AXIS_CHANNEL;
   if (k_whole && s.n_vis % 128 != 0) {
     switch (s.bits * 2 + (vch ? 1 : 0)) {
-      case 1 * 2: return {fused_row_kernel<SPLIT, 8, 1, false, true, true, kRingK, true>, 30};
-      case 2 * 2: return {fused_row_kernel<SPLIT, 8, 2, false, true, true, kRingK, true>, 31};
-      case 4 * 2: return {fused_row_kernel<SPLIT, 8, 4, false, true, true, kRingK, true>, 32};
-      case 8 * 2: return {fused_row_kernel<SPLIT, 8, 8, false, true, true, kRingK, true>, 33};
-      case 1 * 2 + 1: return {fused_row_kernel<SPLIT, 8, 1, true, true, true, kRingK, true>, 34};
-      case 2 * 2 + 1: return {fused_row_kernel<SPLIT, 8, 2, true, true, true, kRingK, true>, 35};
+      case 1 * 2: return {fused_row_kernel<SPLIT, true, 8, 1, false, true, true, kRingK, true>, 30};
+      case 2 * 2: return {fused_row_kernel<SPLIT, true, 8, 2, false, true, true, kRingK, true>, 31};
+      case 4 * 2: return {fused_row_kernel<SPLIT, true, 8, 4, false, true, true, kRingK, true>, 32};
+      case 8 * 2: return {fused_row_kernel<SPLIT, true, 8, 8, false, true, true, kRingK, true>, 33};
+      case 1 * 2 + 1: return {fused_row_kernel<SPLIT, true, 8, 1, true, true, true, kRingK, true>, 34};
+      case 2 * 2 + 1: return {fused_row_kernel<SPLIT, true, 8, 2, true, true, true, kRingK, true>, 35};
       default: return {nullptr, 0};
     }
   }
   if (k_whole) {
     switch (s.bits * 2 + (vch ? 1 : 0)) {
-      case 1 * 2: return {fused_row_kernel<SPLIT, 8, 1, false, true>, 18};
-      case 2 * 2: return {fused_row_kernel<SPLIT, 8, 2, false, true>, 19};
-      case 4 * 2: return {fused_row_kernel<SPLIT, 8, 4, false, true>, 20};
-      case 8 * 2: return {fused_row_kernel<SPLIT, 8, 8, false, true>, 21};
-      case 1 * 2 + 1: return {fused_row_kernel<SPLIT, 8, 1, true, true>, 22};
-      case 2 * 2 + 1: return {fused_row_kernel<SPLIT, 8, 2, true, true>, 23};
+      case 1 * 2: return {fused_row_kernel<SPLIT, FINE, 8, 1, false, true>, 18};
+      case 2 * 2: return {fused_row_kernel<SPLIT, FINE, 8, 2, false, true>, 19};
+      case 4 * 2: return {fused_row_kernel<SPLIT, FINE, 8, 4, false, true>, 20};
+      case 8 * 2: return {fused_row_kernel<SPLIT, false, 8, 8, false, true>, 21};
+      case 1 * 2 + 1: return {fused_row_kernel<SPLIT, FINE, 8, 1, true, true>, 22};
+      case 2 * 2 + 1: return {fused_row_kernel<SPLIT, FINE, 8, 2, true, true>, 23};
       default: return {nullptr, 0};
     }
   }
   // two head blocks per KV head: the twin workgroups share their lines through L2 (ordinary loads)
-  if (plan.nhb > 1 && !vch && s.k_group == 128 && s.bits == 1) return {fused_row_kernel<SPLIT, 8, 1, false, false, false>, 24};
-  if (plan.nhb > 1 && !vch && s.k_group == 128 && s.bits == 2) return {fused_row_kernel<SPLIT, 8, 2, false, false, false>, 25};
+  if (plan.nhb > 1 && !vch && s.k_group == 128 && s.bits == 1) return {fused_row_kernel<SPLIT, FINE, 8, 1, false, false, false>, 24};
+  if (plan.nhb > 1 && !vch && s.k_group == 128 && s.bits == 2) return {fused_row_kernel<SPLIT, FINE, 8, 2, false, false, false>, 25};
   // long whole rows: three key groups in flight per wave
-  if constexpr (!SPLIT) {
+  if constexpr (!SPLIT && !FINE) {
     if (plan.nhb == 1 && !vch && s.n_vis >= 48 * 128) switch (s.k_group * 4 + s.bits) {
-      case 128 * 4 + 1: return {fused_row_kernel<SPLIT, 8, 1, false, false, true, 3>, 26};
-      case 128 * 4 + 2: return {fused_row_kernel<SPLIT, 8, 2, false, false, true, 3>, 27};
-      case 32 * 4 + 1: return {fused_row_kernel<SPLIT, 2, 1, false, false, true, 3>, 28};
-      case 32 * 4 + 2: return {fused_row_kernel<SPLIT, 2, 2, false, false, true, 3>, 29};
+      case 128 * 4 + 1: return {fused_row_kernel<SPLIT, FINE, 8, 1, false, false, true, 3>, 26};
+      case 128 * 4 + 2: return {fused_row_kernel<SPLIT, FINE, 8, 2, false, false, true, 3>, 27};
+      case 32 * 4 + 1: return {fused_row_kernel<SPLIT, FINE, 2, 1, false, false, true, 3>, 28};
+      case 32 * 4 + 2: return {fused_row_kernel<SPLIT, FINE, 2, 2, false, false, true, 3>, 29};
+      default: break;
+    }
+  }
+  if constexpr (!FINE) {
+    switch ((s.k_group * 4 + s.bits) * 2 + (vch ? 1 : 0)) {
+      case (32 * 4 + 1) * 2 + 1: return {fused_row_kernel<SPLIT, false, 2, 1, true>, 6};
+      case (64 * 4 + 1) * 2 + 1: return {fused_row_kernel<SPLIT, false, 4, 1, true>, 7};
+      case (128 * 4 + 1) * 2 + 1: return {fused_row_kernel<SPLIT, false, 8, 1, true>, 8};
+      case (32 * 4 + 2) * 2 + 1: return {fused_row_kernel<SPLIT, false, 2, 2, true>, 9};
+      case (64 * 4 + 2) * 2 + 1: return {fused_row_kernel<SPLIT, false, 4, 2, true>, 10};
+      case (128 * 4 + 2) * 2 + 1: return {fused_row_kernel<SPLIT, false, 8, 2, true>, 11};
+      case (32 * 4 + 8) * 2: return {fused_row_kernel<SPLIT, false, 2, 8, false>, 15};
+      case (64 * 4 + 8) * 2: return {fused_row_kernel<SPLIT, false, 4, 8, false>, 16};
+      case (128 * 4 + 8) * 2: return {fused_row_kernel<SPLIT, false, 8, 8, false>, 17};
       default: break;
     }
   }
   switch ((s.k_group * 4 + s.bits) * 2 + (vch ? 1 : 0)) {
-    case (32 * 4 + 1) * 2: return {fused_row_kernel<SPLIT, 2, 1, false>, 0};
-    case (64 * 4 + 1) * 2: return {fused_row_kernel<SPLIT, 4, 1, false>, 1};
-    case (128 * 4 + 1) * 2: return {fused_row_kernel<SPLIT, 8, 1, false>, 2};
-    case (32 * 4 + 2) * 2: return {fused_row_kernel<SPLIT, 2, 2, false>, 3};
-    case (64 * 4 + 2) * 2: return {fused_row_kernel<SPLIT, 4, 2, false>, 4};
-    case (128 * 4 + 2) * 2: return {fused_row_kernel<SPLIT, 8, 2, false>, 5};
-    case (32 * 4 + 1) * 2 + 1: return {fused_row_kernel<SPLIT, 2, 1, true>, 6};
-    case (64 * 4 + 1) * 2 + 1: return {fused_row_kernel<SPLIT, 4, 1, true>, 7};
-    case (128 * 4 + 1) * 2 + 1: return {fused_row_kernel<SPLIT, 8, 1, true>, 8};
-    case (32 * 4 + 2) * 2 + 1: return {fused_row_kernel<SPLIT, 2, 2, true>, 9};
-    case (64 * 4 + 2) * 2 + 1: return {fused_row_kernel<SPLIT, 4, 2, true>, 10};
-    case (128 * 4 + 2) * 2 + 1: return {fused_row_kernel<SPLIT, 8, 2, true>, 11};
-    case (32 * 4 + 4) * 2: return {fused_row_kernel<SPLIT, 2, 4, false>, 12};
-    case (64 * 4 + 4) * 2: return {fused_row_kernel<SPLIT, 4, 4, false>, 13};
-    case (128 * 4 + 4) * 2: return {fused_row_kernel<SPLIT, 8, 4, false>, 14};
-    case (32 * 4 + 8) * 2: return {fused_row_kernel<SPLIT, 2, 8, false>, 15};
-    case (64 * 4 + 8) * 2: return {fused_row_kernel<SPLIT, 4, 8, false>, 16};
-    case (128 * 4 + 8) * 2: return {fused_row_kernel<SPLIT, 8, 8, false>, 17};
+    case (32 * 4 + 1) * 2: return {fused_row_kernel<SPLIT, FINE, 2, 1, false>, 0};
+    case (64 * 4 + 1) * 2: return {fused_row_kernel<SPLIT, FINE, 4, 1, false>, 1};
+    case (128 * 4 + 1) * 2: return {fused_row_kernel<SPLIT, FINE, 8, 1, false>, 2};
+    case (32 * 4 + 2) * 2: return {fused_row_kernel<SPLIT, FINE, 2, 2, false>, 3};
+    case (64 * 4 + 2) * 2: return {fused_row_kernel<SPLIT, FINE, 4, 2, false>, 4};
+    case (128 * 4 + 2) * 2: return {fused_row_kernel<SPLIT, FINE, 8, 2, false>, 5};
+    case (32 * 4 + 4) * 2: return {fused_row_kernel<SPLIT, FINE, 2, 4, false>, 12};
+    case (64 * 4 + 4) * 2: return {fused_row_kernel<SPLIT, FINE, 4, 4, false>, 13};
+    case (128 * 4 + 4) * 2: return {fused_row_kernel<SPLIT, FINE, 8, 4, false>, 14};
     default: return {nullptr, 0};
   }
 }
@@ -1501,13 +1626,15 @@ hipError_t launch_decode_fused(const DecodeShape& shape, const FusedPlan& plan, 
   a.ws_partial = workspace ? workspace + plan.ws_partial_floats : nullptr;
   a.tag = 0;
   a.patience = plan.patience;
-  const FusedChoice choice = plan.n_chunks == 1 ? pick_kernel<false>(s, plan, k_whole) : pick_kernel<true>(s, plan, k_whole);
+  const bool split = plan.n_chunks > 1;
+  const FusedChoice choice = split ? plan.fine ? pick_kernel<true, true>(s, plan, k_whole) : pick_kernel<true, false>(s, plan, k_whole)
+                                   : plan.fine ? pick_kernel<false, true>(s, plan, k_whole) : pick_kernel<false, false>(s, plan, k_whole);
   const FusedKernel kern = choice.kern;
   if (!kern) return hipErrorInvalidValue;
-  const int slot = choice.slot + (plan.n_chunks == 1 ? 0 : kKernels);
+  const int slot = choice.slot + (split ? kKernels : 0) + (plan.fine ? 2 * kKernels : 0);
   // the kernel's dynamic LDS limit is raised once per (device, kernel) and only ever grows;
   // concurrent callers may both raise it, which is harmless
-  static std::atomic<size_t> configured[kMaxDevices][2 * kKernels];
+  static std::atomic<size_t> configured[kMaxDevices][4 * kKernels];
   int dev = 0;
   hipError_t de = hipGetDevice(&dev);
   if (de != hipSuccess) return de;

@@ -76,9 +76,9 @@ __device__ inline int count_in(u64* count, u64 tag, u64 seen) {
 // any more.  (One thread per pair of channels over all slots, sixteen at a time whether there are sixteen or not,
 // took 1.0 to 1.5 us of a call; this takes 0.5.)
 template <int D, int WAVES>
-__device__ inline void merge_partials(const float* partial, int n_slots, int gh, __half* out, float* lds) {
+__device__ inline void merge_partials(const float* partial, int n_slots, int gh, __half* out, float* lds, int tid) {
   constexpr int kGroups = WAVES / kHeads, kPer = D / 64;       // channels per lane
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = wave % kHeads, first = wave / kHeads;
   float num[kPer], den = 0.f;
 #pragma unroll
@@ -138,7 +138,7 @@ __device__ inline void merge_partials(const float* partial, int n_slots, int gh,
   }
   if constexpr (kGroups > 1) {
     __syncthreads();
-    for (int e = threadIdx.x; e < gh * D; e += WAVES * 64) {
+    for (int e = tid; e < gh * D; e += WAVES * 64) {
       float sum = 0.f;
 #pragma unroll
       for (int f = 0; f < kGroups; ++f) sum += lds[f * kHeads * D + e];

@@ -92,9 +92,7 @@ struct TileArgs {
 // `words` consecutive words of its token, register p is variant p % kV (code of every byte) of word
 // p / kV.  One-bit codes of 64 channels are the exception: two words for four lane rows, so a lane
 // row holds half a word, the lower or the upper half of every byte.
-// The upper half of a byte is shifted down before it is masked: a code then weighs 1 to 8 (1 bit) or
-// 1 or 4 (2 bits), and the query operand, which carries the inverse weight, loses at most 3 of its
-// bits to it (7 with the masks of decode_device.h, which save that shift).
+// Codes by the lower masks of decode_device.h.
 template <int D, int BITS>
 struct Operand {
   static constexpr int kProducts = D / 64;
@@ -102,7 +100,6 @@ struct Operand {
   static constexpr bool kHalf = D * BITS < 128;             // half a word per lane row
   static constexpr int kWords = kHalf ? 1 : D * BITS / 128; // words per lane
   static constexpr int kRowWords = D * BITS / 32;           // words per token
-  static constexpr int kLow = 4 / BITS;                     // variants in the lower half of a byte (b < 8)
   __device__ static int first_word(int kb) { return kHalf ? kb >> 1 : kb * kWords; }
   __device__ static int shift(int kb) { return kHalf ? 4 * (kb & 1) : 0; }
   // channel of operand byte y of register p in lane row kb
@@ -112,18 +109,10 @@ struct Operand {
   }
   // 1 / (what a code of 1 is worth in register p)
   __device__ static float weight(int p) {
-    if constexpr (BITS == 1) return ldexpf(1.f, -(p % 4));
-    else if constexpr (BITS == 2) return p % 2 ? 0.25f : 1.f;
-    else return 1.f;
+    return low_weight<BITS>(p % kV);
   }
   __device__ static int reg(const uint32_t (&w)[kWords], int p, int sh) {
-    if constexpr (BITS == 8) return operand_variant<8>(w[p], 0);
-    else {
-      const int v = kHalf ? p : p % kV;
-      const uint32_t word = kHalf ? w[0] >> sh : w[p / kV];
-      constexpr uint32_t mask = BITS == 1 ? 0x01010101u : BITS == 2 ? 0x03030303u : 0x0f0f0f0fu;
-      return (int)((v < kLow ? word : word >> 4) & (mask << (BITS * (v % kLow))));
-    }
+    return kHalf ? operand_low<BITS>(w[0] >> sh, p) : operand_low<BITS>(w[p / kV], p % kV);
   }
 };
 
@@ -148,13 +137,6 @@ __device__ inline void load_words(uint32_t (&w)[N], const uint32_t* p) {
 // k / per without a division where there is nothing to divide: one part, or parts of one (a division
 // by a value that is only known at run time takes about 40 instructions)
 __device__ inline int part_of(int k, int per) { return per == 1 ? k : k < per ? 0 : k / per; }
-
-// The four signed base-256 digits of a * b rounded to the nearest integer (|a b| < 2^30), as the four
-// bytes of the result.  Added to 1.5 * 2^52 a double shows the integer in its low word.
-__device__ inline int rounded_digits(float a, double b) {
-  const double t = fma((double)a, b, 6755399441055744.0 + 8421504.0);
-  return __builtin_bit_cast(v2i, t)[0] ^ 0x00808080;
-}
 
 // min and max of the workgroup's waves for the 16 heads of a text workgroup or the 4 of a head set:
 // lane h of wave 0 stores head h
@@ -469,7 +451,7 @@ __device__ inline void finish_chunk(const TileArgs& a, size_t row, int set, size
                   : __hip_atomic_fetch_add(a.ws_count + at, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == n_slots - 1;
   __syncthreads();
   if (!s_last) return;
-  merge_partials<D, kWaves>(a.ws_partial + head0 * n_slots * (D + 2), n_slots, gh, a.out + head0 * D, nullptr);
+  merge_partials<D, kWaves>(a.ws_partial + head0 * n_slots * (D + 2), n_slots, gh, a.out + head0 * D, nullptr, threadIdx.x);
   // nobody looks at these any more; a replay of a recorded launch starts from here
   if constexpr (ROW) {
     for (int i = threadIdx.x; i < gh * a.cb * 2; i += kThreads) a.ws_words[head0 * a.cb * 2 + i] = 0;
@@ -570,44 +552,6 @@ __device__ inline void text_values(const TileArgs& a, size_t row, int set, int t
 __device__ inline int text_length(const TileArgs& a) {
   return a.n_text_dev ? min(max(*a.n_text_dev, 0), a.n_text) : a.n_text;
 }
-
-// a * b + the bias of the four signed base-256 digits: as an integer ^ 0x00808080 its bytes are the digits.
-// Above 2^23 the fma rounds to nearest integers, and fp32 has no more below 2^24.
-__device__ inline float digits_bias(float a, float b) { return fmaf(a, b, 8421504.f); }
-
-// Fixed-point scales of the four heads, powers of two from 2^-90 to 2^90, as the bits of floats.
-struct Scales {
-  static constexpr int kOne = 127 << 23;
-  int up[kHeads];                                              // wave-uniform
-  __device__ explicit Scales(int exponent) {
-#pragma unroll
-    for (int h = 0; h < kHeads; ++h) up[h] = (exponent + 127) << 23;
-  }
-  __device__ float of(int h) const { return __builtin_bit_cast(float, up[h]); }
-  __device__ float inverse(int kb) const {                     // of head kb
-    const int a = kb & 1 ? up[1] : up[0], b = kb & 1 ? up[3] : up[2];
-    return __builtin_bit_cast(float, 2 * kOne - (kb & 2 ? b : a));
-  }
-  // Lowered until w * scale < 2^26 for the heads' w >= 0 of all lanes.  The maxima by a transposing
-  // butterfly, as in head_sums: lane l of a row ends up with head bitrev2(l & 3).  Floats that are not
-  // negative order like their bits, and integer maxima need no second instruction for NaNs.
-  __device__ void lower(const float (&w)[kHeads], int lane) {
-    const bool b0 = lane & 1, b1 = lane & 2;
-    int i[kHeads];
-#pragma unroll
-    for (int h = 0; h < kHeads; ++h) i[h] = __builtin_bit_cast(int, w[h]);
-    const int u0 = max(b0 ? i[2] : i[0], dpp_i32<0xB1>(b0 ? i[0] : i[2]));
-    const int u1 = max(b0 ? i[3] : i[1], dpp_i32<0xB1>(b0 ? i[1] : i[3]));
-    int r = max(b1 ? u1 : u0, dpp_i32<0x4E>(b1 ? u0 : u1));
-    r = max(r, dpp_i32<0x124>(r));
-    r = max_rows(max_halves(max(r, dpp_i32<0x128>(r))));
-    // r < 2^(e - 126) for its exponent field e: the scale 2^(26 - (e - 126)), its field 279 - e
-    const int fits = min(max(279 - (r >> 23), 127 - 90), 127 + 90) << 23;
-    constexpr int kLane[kHeads] = {0, 2, 1, 3};
-#pragma unroll
-    for (int h = 0; h < kHeads; ++h) up[h] = min(up[h], __builtin_amdgcn_readlane(fits, kLane[h]));
-  }
-};
 
 // What a wave of the values pass stages, and what the workgroup's waves leave for its end.
 template <int D, int BITS>

@@ -190,3 +190,70 @@ def test_rows_that_end_inside_a_processing_group(shape, chunks):
     err = O.rel_l2(got.cpu().numpy().astype(np.float64), ref)
     assert err <= H.REGRESSION_TOL, err
     H.assert_elementwise_close(got.cpu().numpy().astype(np.float64), ref)
+
+
+# Calls that the library takes from the tile kernels to the fused one: rows of any length with whole-sequence keys, few
+# rows, two head sets: (q heads of the KV head, n_vis, key group, value axis, value group); values in groups stay
+STAND_OUT = [(4, 1000, 1000, 1, 128), (4, 3003, 3003, 1, 128), (4, 3003, 3003, 0, 3003), (4, 4096, 128, 1, 128), (4, 8192, 32, 1, 128),
+             (4, 8192, 8192, 0, 8192), (8, 3328, 64, 1, 128), (7, 2001, 2001, 0, 2001), (4, 8192, 128, 0, 64)]
+
+
+@pytest.mark.parametrize("shape", STAND_OUT)
+@pytest.mark.parametrize("bits", [1, 2, 4, 8])
+@pytest.mark.parametrize("where", ["group", "tail", "all"])
+def test_values_that_stand_out_by_default(shape, bits, where):
+    """As test_values_that_stand_out for the tile kernels, with what the library selects by itself: the values of some tokens
+    (64 of the visual ones, the tail, all visual ones) are 3e6 times the others' and their weights, for the first
+    query head, 2e-8 of theirs, so both parts count alike and each has to keep fp32's bits.  The bar is what
+    rounding the exact result to fp16 gives for that head, plus 1e-4: weights are within 17.5 x 2^-22 = 4e-6 (fp32
+    logits), sums of 8192 terms in fp32, by lane and wave, within 4e-5."""
+    g, n, k_group, v_axis, v_group = shape
+    n_text, d = 5, 128
+    gen = torch.Generator().manual_seed(n + bits)
+    q0 = torch.randn(d, generator=gen)
+    q = torch.stack([q0 * (1.0, 0.5, 0.1, 0.0)[h % 4] for h in range(g)]).half().view(1, g, d)
+    k, kt = (0.05 * torch.randn(1, 1, m, d, generator=gen) for m in (n, n_text))
+    v, vt = (0.01 * torch.randn(1, 1, m, d, generator=gen) for m in (n, n_text))
+    low = -17.5 * d ** 0.5 * q0 / q0.square().sum()
+    high = lambda m: 30000.0 * torch.randn(1, 1, m, d, generator=gen).clamp(-2, 2)
+    if where == "group":
+        k[:, :, 128:192], v[:, :, 128:192] = low, high(64)
+    elif where == "tail":
+        kt[:], vt[:] = low, high(n_text)
+    else:
+        k[:], v[:] = low, high(n)
+    x = {"q": q, "k": k.half(), "v": v.half(), "k_text": kt.half(), "v_text": vt.half()}
+    dev = H.to_device(x)
+    lay = cq.make_layout(1, g, 1, d, n, bits, 0, v_axis, k_group, v_group)
+    kq, vq = H.oracle_quantize(x, lay)
+    kd, vd = cq.cq_quantize_kv(lay, dev["k"], dev["v"])
+    ref = O.decode_attn(x["q"].numpy(), kq, vq, x["k_text"].numpy(), x["v_text"].numpy(), n_text, O.CALIB_NONE)
+    got = cq.cq_decode_attn(lay, dev["q"], kd, vd, dev["k_text"], dev["v_text"], n_text).cpu().numpy()
+    for h in range(g):
+        err, least = H.row_rel_l2(got[:, h], ref[:, h]), H.row_rel_l2(ref[:, h].astype(np.float16), ref[:, h])
+        assert err <= least + 1e-4, "head %d: rel L2 %.3e, fp16 rounding %.3e" % (h, err, least)
+
+
+@pytest.mark.parametrize("shape", [(4, 4096, 64, 1, 128), (8, 3328, 128, 1, 128), (4, 3003, 3003, 1, 128), (4, 3003, 3003, 0, 3003)])
+@pytest.mark.parametrize("bits", [1, 4])
+def test_logits_that_cancel_by_default(shape, bits):
+    """Two channels add +-3e3 to every logit and all but cancel: 2^-24 of either is 2e-4 of a weight, a few of which an
+    assembly in fp32 loses.  The same bar as above: what is left is the rounding of the finished logit (2^-24 of 20)."""
+    g, n, k_group, v_axis, v_group = shape
+    gen = torch.Generator().manual_seed(n + bits)
+    q, k = torch.randn(1, g, 128, generator=gen), 0.1 * torch.randn(1, 1, n, 128, generator=gen)
+    v, vt = torch.randn(1, 1, n, 128, generator=gen), torch.randn(1, 1, 3, 128, generator=gen)
+    q[..., 3], q[..., 90] = 1.0, -0.9
+    k[..., 3] = 36000.0 + 32 * torch.randint(0, 4, (1, 1, n), generator=gen)
+    k[..., 90] = 40000.0 + 32 * torch.randint(0, 4, (1, 1, n), generator=gen)
+    kt = torch.zeros(1, 1, 3, 128)
+    x = {"q": q.half(), "k": k.half(), "v": v.half(), "k_text": kt.half(), "v_text": vt.half()}
+    dev = H.to_device(x)
+    lay = cq.make_layout(1, g, 1, 128, n, bits, 0, v_axis, k_group, v_group)
+    kq, vq = H.oracle_quantize(x, lay)
+    kd, vd = cq.cq_quantize_kv(lay, dev["k"], dev["v"])
+    ref = O.decode_attn(x["q"].numpy(), kq, vq, x["k_text"].numpy(), x["v_text"].numpy(), 3, O.CALIB_NONE)
+    got = cq.cq_decode_attn(lay, dev["q"], kd, vd, dev["k_text"], dev["v_text"], 3).cpu().numpy()
+    for h in range(g):
+        err, least = H.row_rel_l2(got[:, h], ref[:, h]), H.row_rel_l2(ref[:, h].astype(np.float16), ref[:, h])
+        assert err <= least + 1e-4, "head %d: rel L2 %.3e, fp16 rounding %.3e" % (h, err, least)
