@@ -165,7 +165,7 @@ struct FusedPlan {
   int stride = 0;             // floats between the logit rows of two heads in LDS
   size_t lds = 0;             // dynamic LDS bytes per workgroup
   int patience = kPatience;
-  size_t ws_count_floats = 0, ws_partial_floats = 0;   // split rows: [words | counts | partials], offsets in floats
+  size_t ws_partial_floats = 0;   // split rows: [counts | partials], offset in floats
   size_t ws_bytes = 256;      // workspace the launches touch (a multiple of 256, >= 256)
 };
 // min_chunks: 0 = as split says, n >= 1 = at least n (test override)

@@ -90,9 +90,9 @@ struct FusedArgs {
   unsigned chunks_magic;     // fl(2^32 / n_chunks) + 1, or 0 when n_chunks == 1
   int units_base, units_rem;       // units of visual tokens per chunk: quotient and remainder
   int tblocks_base, tblocks_rem;   // 64-token text blocks per chunk, likewise
-  // split rows (decode_meet.h): [B*Hq][n_chunks][2] words of the exchange, [rows][nhb] counts,
-  // [B*Hq][n_chunks][d + 2] partials (m, l, acc)
-  u64* ws_words; u64* ws_count; float* ws_partial;
+  // split rows (decode_meet.h): [rows][nhb] counts, [B*Hq][n_chunks][d + 2] partials (m, l, acc); until the partial is
+  // there, its first four floats are the words of the exchange
+  u64* ws_count; float* ws_partial;
   u64 tag; int patience;     // of the call; looks at the words before a workgroup goes on alone
   int calib_mode; float tau1, tau2, gamma, delta, softmax_scale;
 };
@@ -637,23 +637,30 @@ fused_row_kernel(const FusedArgs args) {
       if (pass > 0) { __syncthreads(); continue; }             // (red is written again)
       float* found = red + kVisWaves * kHeads * kRedPerHead;   // slots of the first text wave
       if (wave == 0) {
-        u64* words = a.ws_words + (head0 + min(kb, gh - 1)) * (size_t)a.n_chunks * 2;
-        if (n16 == 0 && kb < gh) post_extrema(words + 2 * own, lo_l, hi_l, a.tag);
+        float* const slots = a.ws_partial + (head0 + min(kb, gh - 1)) * (size_t)a.n_chunks * (kD + 2);
+        auto words = [&](int c) { return reinterpret_cast<u64*>(slots + (size_t)c * (kD + 2)); };
+        if (n16 == 0 && kb < gh) post_extrema(words(own), lo_l, hi_l, a.tag);
         bool all = false;
         float lo = FLT_MAX, hi = -FLT_MAX;
-        for (int look = 0; !all && look < a.patience; ++look) {
+        for (int looks = a.patience; !all && looks > 0; --looks) {
           lo = FLT_MAX;
           hi = -FLT_MAX;
           all = true;
+          // (asked for in every sixteenth look, not the first: in each one it takes 0.1 us of a call)
+          const bool finished = looks % 16 == 1 && any_counted(a.ws_count + (size_t)row * a.nhb + hb, a.tag);
           for (int c = n16; c < a.n_chunks; c += 16) {
             float x = lo_l, y = hi_l;
-            if (c != own) all = read_extrema(words + 2 * c, &x, &y, a.tag) && all;
+            if (c != own) all = read_extrema(words(c), &x, &y, a.tag) && all;
             lo = fminf(lo, x);
             hi = fmaxf(hi, y);
           }
           all = __builtin_amdgcn_ballot_w64(!all) == 0;
+          // who has finished has found all words, so they were there, and put a partial in the place of its own
+          if (!all && finished) looks = min(looks, 2);
           if (!all) __builtin_amdgcn_s_sleep(1);
         }
+        // the words have arrived before another wave stores the partial in their place
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         lo = row_min(lo);
         hi = row_max(hi);
         if (n16 == 0) {
@@ -1335,7 +1342,6 @@ fused_row_kernel(const FusedArgs args) {
     if (last[0] == 0.f) return;
     merge_partials<kD, kWaves>(a.ws_partial + head0 * a.n_chunks * (kD + 2), a.n_chunks, gh, a.out + head0 * kD,
                                reinterpret_cast<float*>(smem), tid);
-    for (int i = tid; i < gh * a.n_chunks * 2; i += kThreads) a.ws_words[head0 * a.n_chunks * 2 + i] = 0;
     if (tid == 0) *count = 0;
   }
   return;
@@ -1505,10 +1511,9 @@ FusedPlan make_fused_plan(const DecodeShape& shape, int min_chunks, FusedSplit s
   }
   if (p.n_chunks > 1 || p.nhb > 1) {
     if (s.n_vis == 0) return p;
-    // two words per (head, chunk), a count per (row, head block), one (m, l, acc[d]) partial per (head, chunk)
+    // a count per (row, head block), one (m, l, acc[d]) partial per (head, chunk)
     const size_t heads = (size_t)s.B * s.Hq;
-    p.ws_count_floats = (heads * p.n_chunks * 4 + 63) / 64 * 64;
-    p.ws_partial_floats = (p.ws_count_floats + (size_t)rows * 2 + 63) / 64 * 64;
+    p.ws_partial_floats = ((size_t)rows * 2 + 63) / 64 * 64;
     const size_t floats = p.ws_partial_floats + heads * p.n_chunks * (size_t)(kD + 2);
     p.ws_bytes = (floats * sizeof(float) + 255) / 256 * 256;
   }
@@ -1621,8 +1626,7 @@ hipError_t launch_decode_fused(const DecodeShape& shape, const FusedPlan& plan, 
   a.stride = plan.stride;
   a.n_chunks = plan.n_chunks;
   a.nhb = plan.nhb;
-  a.ws_words = reinterpret_cast<u64*>(workspace);
-  a.ws_count = reinterpret_cast<u64*>(workspace ? workspace + plan.ws_count_floats : nullptr);
+  a.ws_count = reinterpret_cast<u64*>(workspace);
   a.ws_partial = workspace ? workspace + plan.ws_partial_floats : nullptr;
   a.tag = 0;
   a.patience = plan.patience;

@@ -13,9 +13,9 @@
 // extrema of the whole row itself.  No workgroup's end depends on another's start.
 //
 // Merge.  Every workgroup counts itself when its partial has reached memory; the one that counts last
-// merges, in the order of the chunks, so the result does not depend on who that is.  It also clears the words
-// and the count, which nobody reads any more: a recorded launch finds them clear when it is replayed with the
-// same tag.
+// merges, in the order of the chunks, so the result does not depend on who that is.  It also clears the
+// count, and the words where no partials have taken their place, which nobody reads any more: a recorded launch
+// finds nothing of its own when it is replayed with the same tag.
 #ifndef CQ_DECODE_MEET_H_
 #define CQ_DECODE_MEET_H_
 
@@ -61,6 +61,11 @@ __device__ inline bool read_extrema(const u64* w, float* lo, float* hi, u64 tag)
 // Asked for at the start of a workgroup; clear memory (0) becomes the tag.
 __device__ inline u64 count_open(u64* count, u64 tag) {
   return atomicCAS(count, (u64)0, tag);
+}
+// Whether a workgroup of the call has been counted.
+__device__ inline bool any_counted(const u64* count, u64 tag) {
+  const u64 c = __hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return __builtin_amdgcn_readfirstlane((int)((c & ~(u64)0xff) == tag && (c & 0xff) != 0)) != 0;
 }
 // The workgroups counted before this one.  seen: what count_open returned.  Memory that held something
 // else takes a second exchange; whoever's succeeds, the word then counts for the call.

@@ -105,3 +105,17 @@ def test_a_long_tail_for_two_head_sets_stays_on_the_streaming_kernels():
     cq.cq_bench_set_kernel_path(prev)
     assert needed(lay, 1000) == tuned[1] and needed(lay, 100) != tuned[0]
     assert cq.cq_decode_workspace_bytes(lay, 1000, calib) >= needed(lay, 100)
+
+
+# (layout, tail) of shared rows, and the scratch of one (min, max) pair and one partial per (head, chunk) that
+# workspaces for them were first made with
+SHARED = [((120, 16, 16, 128, 10752, 8, 0, 1, 128, 128), 0), ((131, 64, 8, 128, 1920, 2, 0, 1, 64, 128), 33),
+          ((154, 32, 8, 128, 63744, 4, 0, 1, 64, 128), 0), ((31, 64, 8, 128, 65536, 4, 0, 1, 128, 128), 0),
+          ((62, 64, 8, 128, 32448, 1, 0, 1, 64, 128), 221), ((165, 16, 16, 128, 46592, 1, 0, 1, 64, 128), 3485)]
+SHARED_BYTES = [2027520, 4426752, 20815872, 8380416, 8380416, 8363520]
+
+
+@pytest.mark.parametrize("case,size", zip(SHARED, SHARED_BYTES))
+def test_words_of_the_exchange_take_no_scratch_of_their_own(case, size):
+    args, n_text = case
+    assert needed(cq.make_layout(*args), n_text) <= size
