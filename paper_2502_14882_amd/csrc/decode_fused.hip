@@ -1509,8 +1509,8 @@ FusedPlan make_fused_plan(const DecodeShape& shape, int min_chunks, FusedSplit s
       p.stride = stride;
     }
   }
-  if (p.n_chunks > 1 || p.nhb > 1) {
-    if (s.n_vis == 0) return p;
+  if ((p.n_chunks > 1 || p.nhb > 1) && s.n_vis == 0) return p;
+  if (p.n_chunks > 1) {
     // a count per (row, head block), one (m, l, acc[d]) partial per (head, chunk)
     const size_t heads = (size_t)s.B * s.Hq;
     p.ws_partial_floats = ((size_t)rows * 2 + 63) / 64 * 64;

@@ -119,3 +119,10 @@ SHARED_BYTES = [2027520, 4426752, 20815872, 8380416, 8380416, 8363520]
 def test_words_of_the_exchange_take_no_scratch_of_their_own(case, size):
     args, n_text = case
     assert needed(cq.make_layout(*args), n_text) <= size
+
+
+@pytest.mark.parametrize("args", [(82, 48, 8, 128, 1024, 2, 0, 1, 32, 128), (20, 64, 8, 128, 3328, 4, 0, 1, 128, 128),
+                                  (600, 64, 8, 128, 512, 1, 0, 0, 128, 128)])
+def test_whole_rows_of_two_head_sets_take_the_least_scratch(args):
+    """One workgroup owns a row (of each set): 256 bytes, also of the entry point that allocates nothing."""
+    assert needed(cq.make_layout(*args), 20) == 256
