@@ -259,6 +259,20 @@ bool on_chip_is_faster(const cq::DecodeShape& s, const cq::FusedPlan& plan) {
   return fused < streamed;
 }
 
+// The same for two head sets whose rows fit a workgroup each: one launch that shares a row's lines through an XCD's L2 but reads
+// the tail twice, in rounds over the chip, against three that read it once.  One round is always faster (64 rows x 3328
+// tokens, 6 heads: 12.0 / 22.9 us).  Beyond, microseconds fitted to 28 measured layouts of 136 to 512 rows x 256 to
+// 4608 + 31 to 1000 tokens (3 and 5 % rms; on chip / streaming): 224 rows x 768 + 38, 2 bits 15.6 / 22.3; 512 x 3328 + 128
+// 46.2 / 60.9; but 512 x 256 + 1000 89.1 / 73.8, 424 x 768 + 804 76.9 / 56.0.  Three of the 28 go to the slower one, by 1, 2
+// and 7 %.
+bool whole_sets_are_faster(const cq::DecodeShape& s, const cq::FusedPlan& plan) {
+  const double rows = (double)s.B * s.Hkv, rounds = std::ceil(rows * plan.nhb / 256.0);
+  if (rounds <= 1.0 || !cq::make_stream_plan(s, 0).ok) return true;
+  const double on_chip = -1.9 + rounds * (6.0 + (s.bits == 1 ? 1.3 : 1.7) * 1e-3 * s.n_vis + 1.0 * cq::ceil_div(s.n_text, 64));
+  const double streamed = 15.1 + 24.6e-6 * rows * s.n_vis + 101e-6 * rows * s.n_text;
+  return on_chip < streamed;
+}
+
 // Scratch of the kernels that run where the tile kernels do not.
 size_t ws_without_tiles(const DecodeCall& c) {
   return c.streamed ? c.stream.ws_bytes : c.tuned ? c.plan.ws_bytes : c.generic_ws.total_bytes;
@@ -280,11 +294,8 @@ int select_kernels(const cq_layout_t* L, int n_text, int n_text_cap, size_t scra
     return fail(CQ_ERR_UNSUPPORTED, "no tuned decode kernel for this layout");
   call->tuned = g_kernel_path != CQ_PATH_GENERIC && call->plan.ok;
   call->streamed = false;
-  // Two head blocks of a whole row share its lines through one XCD's L2, and one launch takes half the time of the
-  // streaming kernels' three (64 rows of 3328 tokens, 6 heads: 11.4 / 22.2 us).  They read the tail twice, though,
-  // so where it is most of the call the streaming kernels stay.
   const bool whole_sets = call->plan.n_chunks == 1 && call->plan.nhb > 1 && L->n_vis >= kTwoSetsOnChip &&
-                          L->bits <= 4 && g_decode_chunks == 0;
+                          L->bits <= 4 && g_decode_chunks == 0 && whole_sets_are_faster(call->shape, call->plan);
   bool on_chip = whole_sets || (call->plan.spread && (call->plan.nhb == 1 || L->n_vis >= kTwoSetsOnChip));
   // Calls that stay here instead of going to the tile kernels keep the precision of those, or go there.
   if (on_chip && g_kernel_path == CQ_PATH_AUTO) {

@@ -126,3 +126,13 @@ def test_words_of_the_exchange_take_no_scratch_of_their_own(case, size):
 def test_whole_rows_of_two_head_sets_take_the_least_scratch(args):
     """One workgroup owns a row (of each set): 256 bytes, also of the entry point that allocates nothing."""
     assert needed(cq.make_layout(*args), 20) == 256
+
+
+@pytest.mark.parametrize("batch,tails,streamed", [(64, (1000, 128, 128), (True, False, False)), (53, (804, 300, 20), (True, True, False)),
+                                                  (16, (1000, 700, 10), (False, False, False))])
+def test_two_head_sets_on_chip_unless_rounds_of_a_long_tail(batch, tails, streamed):
+    """768 tokens of 8 KV heads, 8 query heads each: 128 rows are one round of workgroups, more of them read a long tail
+    more slowly than the streaming kernels, which need scratch."""
+    lay = cq.make_layout(batch, 64, 8, 128, 768, 1)
+    for n_text, expect in zip(tails, streamed):
+        assert (needed(lay, n_text) > batch * 64 * 768 * 2) == expect, n_text
