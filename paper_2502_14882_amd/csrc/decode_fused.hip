@@ -210,7 +210,7 @@ fused_row_kernel(const FusedArgs args) {
   // Nothing is staged ahead of phase 1: every wave asks for its own piece of the query (2 KB that all share)
   // together with its first keys.  The fixed-point shifts and the additive post-scaling term q . min_t are
   // formed on the fly from the scales and minima that the streaming loads bring in anyway, so every
-  // parameter is read exactly once.  What this and the text waves' early loads save is latency: 1 row x 1024 tokens
+  // parameter is read exactly once.  What this saves is latency: 1 row x 1024 tokens
   // 7.9 -> 6.4 us, 128 rows x 3328 12.9 -> 11.9 (1 bit) and 19.6 -> 18.1 (4 bits).  (The rows of unused heads (g < 4) are computed along on a zero query and
   // never output; their text slots are never read.)
   const float* ks_row = a.k_scale + (size_t)row * a.k_prow + (size_t)ga * a.k_pstride;
@@ -239,16 +239,6 @@ fused_row_kernel(const FusedArgs args) {
     p2_vsr[slot] = stream_load<NT>(vs_row + j);
     p2_vmr[slot] = stream_load<NT>(vm_row + j);
   };
-
-  // ring of the first text values, asked for behind the first text keys: a tail's waves have little to do, and
-  // what they do is a chain of waits.  The tail goes out in shares of 64 tokens, a short one in shares of 16
-  // that still occupy all text waves (rounds over the waves; a share of 16 costs ~1.1 quarters of one of 64).
-  v8h tv_ring[kRingTV];
-  const bool small_shares = 11 * (((ntx + 15) / 16 + kTextWaves - 1) / kTextWaves) <
-                            40 * (((ntx + 63) / 64 + kTextWaves - 1) / kTextWaves);
-  const __amdgpu_buffer_rsrc_t vt_buf =
-      stream_buffer(a.v_text + ((size_t)row * a.n_text_cap + txt0) * kD, (unsigned)ntx * kD * 2);
-  const int vt_lane = (kb * kD + 8 * n16) * 2;
 
   // =================================================================== phase 1: logits
   if (vis_wave) {
@@ -564,10 +554,6 @@ fused_row_kernel(const FusedArgs args) {
       };
 #pragma unroll
       for (int d = 0; d < kRingT; ++d) load_tile(d, tw + d * kTextWaves);
-      pin_order();
-#pragma unroll
-      for (int s = 0; s < kRingTV; ++s)
-        tv_ring[s] = buffer_load_v8h<NT>(vt_buf, vt_lane, (tw * (small_shares ? 16 : 64) + 4 * s) * (kD * 2));
       pin_order();
       for (int t = tw; t < n_tiles; t += kRingT * kTextWaves) {
 #pragma unroll
@@ -1172,6 +1158,13 @@ fused_row_kernel(const FusedArgs args) {
       v4f acc_hi[2], acc_lo[2];              // [channel 8 n16 + 2 kb + i][head]
 #pragma unroll
       for (int i = 0; i < 2; ++i) acc_hi[i] = acc_lo[i] = (v4f){0.f, 0.f, 0.f, 0.f};
+      // The tail goes out in shares of 64 tokens, a short one in shares of 16 that still occupy all text waves (rounds
+      // over the waves; a share of 16 costs ~1.1 quarters of one of 64).
+      const bool small_shares = 11 * (((ntx + 15) / 16 + kTextWaves - 1) / kTextWaves) <
+                                40 * (((ntx + 63) / 64 + kTextWaves - 1) / kTextWaves);
+      const __amdgpu_buffer_rsrc_t vt_buf =
+          stream_buffer(a.v_text + ((size_t)row * a.n_text_cap + txt0) * kD, (unsigned)ntx * kD * 2);
+      const int vt_lane = (kb * kD + 8 * n16) * 2;
       auto text_values = [&](auto share_tag) {
         constexpr int SH = decltype(share_tag)::value;
         // wave-wide loads per share, how many of them are in flight, records per head row
@@ -1180,10 +1173,15 @@ fused_row_kernel(const FusedArgs args) {
         const int n_sh = (ntx + SH - 1) / SH;
         const int rec_wr = (((lane >> 2) / kRecs) * a.stride) * 4 + ((lane >> 2) % kRecs) * 64 + (lane & 3) * 2;
         const int rec_rd = (lane & 3) * 8;          // matrix row = lane % 4 = head
-        auto& ring = tv_ring;                       // holds the first steps of the wave's first share
+        v8h ring[kDepth];
         auto load_step = [&](int slot, int sh, int s) {
           ring[slot] = buffer_load_v8h<NT>(vt_buf, vt_lane, (sh * SH + 4 * s) * (kD * 2));
         };
+        // (asked for in phase 1 already, behind the first text keys, the ring makes calls with long tails 0.1 to 2.5 us
+        // slower: 120 rows x 256 + 572, 4 bits 19.1 / 16.4, 16 x 700 + 400, 2 bits 15.9 / 14.0; and up to 41 registers spill)
+#pragma unroll
+        for (int s = 0; s < kDepth; ++s) load_step(s, tw, s);
+        pin_order();
         for (int sh = tw; sh < n_sh; sh += kTextWaves) {
           const int t0 = sh * SH;
           const int nt = min(SH, ntx - t0);
