@@ -121,15 +121,16 @@ typedef struct {
 
 /* Bytes of scratch cq_decode_attn needs for this shape and calibration (a multiple of 256,
  * > 0): what the kernels that the call will select use.  A batch whose rows are each owned by one
- * workgroup (the tuned kernel) needs the minimum of 256 bytes; a row split over several
- * workgroups needs one (m, l, acc[d]) partial of the online softmax per (batch, query head,
- * chunk), plus the chunks' logit extrema; the tile kernels (few rows, and
- * layouts the tuned ones do not take) and the shape-agnostic kernels also keep one float per
+ * workgroup (the tuned kernel) needs the minimum of 256 bytes (with 5 to 8 query heads per KV head and
+ * few rows a partial per head in any case); a row split over several workgroups needs a count and one
+ * (m, l, acc[d]) partial of the online softmax per (batch, query head, chunk); the tile kernels (few
+ * rows, and layouts the tuned ones do not take) and the shape-agnostic kernels also keep one float per
  * (batch, query head, token).  n_text is the largest tail length the
  * workspace has to serve; `calib` may be NULL (= CQ_CALIB_NONE).  Returns 0 if the layout,
  * n_text or the calibration mode is invalid.
- * A decode call also accepts less where it would run the tile kernels and the workspace holds what
- * the tuned (else the shape-agnostic) kernels need: those run then, slower. */
+ * A decode call also accepts less where other kernels, or fewer workgroups per row, need no more than the
+ * workspace holds: the tuned (else the shape-agnostic) kernels in place of the tile kernels, whole rows in
+ * place of the streaming kernels, the fewest chunks of a row in place of more.  Those run then, slower. */
 size_t cq_decode_workspace_bytes(const cq_layout_t *layout, int32_t n_text,
                                  const cq_calib_t *calib);
 

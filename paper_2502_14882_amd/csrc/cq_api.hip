@@ -172,6 +172,7 @@ struct DecodeCall {
   bool tuned;               // a layout of the tuned kernels (else of the shape-agnostic ones)
   bool streamed;            // tuned, split rows: the streaming kernels with logits kept in scratch
   bool tiled;               // the tile kernels run, in place of either
+  bool sets_fit;            // two head sets whose rows fit a workgroup each: the fused kernel can run, without scratch
   cq::FusedPlan plan;       // valid when tuned
   cq::StreamPlan stream;    // valid when streamed
   cq::TilePlan tile;        // valid when tiled
@@ -201,7 +202,8 @@ int check_calib(const cq_calib_t* calib, cq::Calib* c) {
   return CQ_OK;
 }
 
-// Two sets of query heads: visual tokens from which their whole rows stay on chip (see select_kernels).
+// Two sets of query heads: visual tokens from which their whole rows stay on chip (see select_kernels).  Below, calls with
+// many rows would lose: 256 rows x 128 + 100 tokens, 8 heads 12.7 us on the other kernels, 13.6 on chip.
 constexpr int kTwoSetsOnChip = 256;
 
 // Whether the tile kernels finish a call sooner than the tuned kernels that could take it, asked where the fused kernel
@@ -273,6 +275,24 @@ bool whole_sets_are_faster(const cq::DecodeShape& s, const cq::FusedPlan& plan) 
   return on_chip < streamed;
 }
 
+// Whether the tile kernels finish a call sooner than the fused kernel on rows with compute units to themselves, spread over them or
+// whole: short rows with a long tail, which the chunks of a row share (each has four waves for it) while the tile kernels
+// give it workgroups of its own.  Microseconds, fitted to 56 layouts of 1 to 83 rows x 157 to 4516 + 8 to 991 tokens (5 and
+// 8 % rms; tile / fused): 8 rows x 446 + 511, 2 bits 9.4 / 12.5; 4 x 214 + 460, 4 bits 9.0 / 12.5; 8 x 1372 + 971, 2
+// bits 11.4 / 13.2; but 40 x 846 + 902 19.2 / 15.4, 44 x 2304 + 160 13.5 / 11.2.  By less than 7 % neither is sure: of the
+// layouts at issue two stay 2 % slower than they could be, and none moves to the slower side.
+bool tiles_beat_spread_rows(const cq::DecodeShape& s, const cq::FusedPlan& plan) {
+  const double rows = (double)s.B * s.Hkv, kn = s.n_vis * 1e-3, c = plan.n_chunks, sets = s.g > 4 ? 2.0 : 1.0;
+  const int i = s.bits == 1 ? 0 : s.bits == 2 ? 1 : 2;
+  static const double kTilePerM[] = {25.0, 27.0, 34.5}, kRowPerK[] = {1.35, 1.75, 2.6};
+  const double group = s.k_axis == CQ_AXIS_CHANNEL && s.k_group == 32 ? 0.85 : 0.0;
+  const double tile = 9.1 + 0.57 * kn + (sets > 1 ? 1.6 : 1.0) * kTilePerM[i] * rows * kn * 1e-3 +
+                      0.104e-3 * sets * rows * s.n_text + (sets > 1 ? 0.3 : 0.0);
+  const double fused = 5.1 + (c > 1 ? 3.8 + 0.05 * c : 0.0) + (kRowPerK[i] + group) * kn / c +
+                       0.96 * std::ceil(cq::ceil_div(s.n_text, 64) / c) + 1.7 * rows * plan.nhb * c / 256.0;
+  return tile < 0.93 * fused;
+}
+
 // Scratch of the kernels that run where the tile kernels do not.
 size_t ws_without_tiles(const DecodeCall& c) {
   return c.streamed ? c.stream.ws_bytes : c.tuned ? c.plan.ws_bytes : c.generic_ws.total_bytes;
@@ -294,20 +314,25 @@ int select_kernels(const cq_layout_t* L, int n_text, int n_text_cap, size_t scra
     return fail(CQ_ERR_UNSUPPORTED, "no tuned decode kernel for this layout");
   call->tuned = g_kernel_path != CQ_PATH_GENERIC && call->plan.ok;
   call->streamed = false;
-  const bool whole_sets = call->plan.n_chunks == 1 && call->plan.nhb > 1 && L->n_vis >= kTwoSetsOnChip &&
-                          L->bits <= 4 && g_decode_chunks == 0 && whole_sets_are_faster(call->shape, call->plan);
+  auto sets_fit = [&] {
+    return call->plan.n_chunks == 1 && call->plan.nhb > 1 && L->n_vis >= kTwoSetsOnChip && L->bits <= 4 && g_decode_chunks == 0;
+  };
+  const bool whole_sets = sets_fit() && whole_sets_are_faster(call->shape, call->plan);
   bool on_chip = whole_sets || (call->plan.spread && (call->plan.nhb == 1 || L->n_vis >= kTwoSetsOnChip));
   // Calls that stay here instead of going to the tile kernels keep the precision of those, or go there.
+  bool to_tiles = false;
   if (on_chip && g_kernel_path == CQ_PATH_AUTO) {
     const cq::FusedPlan rows = call->plan.n_chunks == 1 ? call->plan : cq::make_fused_plan(call->shape, 0);
-    if (tile_is_faster(call->shape, rows)) {
-      call->plan.fine = call->plan.can_fine;
-      if (!call->plan.fine) {
+    if (call->plan.ragged || tile_is_faster(call->shape, rows)) {
+      to_tiles = !call->plan.can_fine || (call->plan.spread && tiles_beat_spread_rows(call->shape, call->plan));
+      call->plan.fine = !to_tiles;
+      if (to_tiles) {
         call->plan = rows;
         on_chip = false;
       }
     }
   }
+  call->sets_fit = sets_fit();
   size_t reserve = 0;                // scratch that shorter tails may use on other kernels
   if (call->tuned && (call->plan.n_chunks > 1 || call->plan.nhb > 1) && !g_one_launch && !on_chip) {
     call->stream = cq::make_stream_plan(call->shape, g_decode_chunks);
@@ -339,7 +364,7 @@ int select_kernels(const cq_layout_t* L, int n_text, int n_text_cap, size_t scra
   } else if (g_kernel_path == CQ_PATH_AUTO && L->n_vis > 0 && g_decode_chunks == 0 && !on_chip) {
     cq::DecodeShape no_tail = call->shape;
     no_tail.n_text = 0;
-    const bool faster = tile_is_faster(call->shape, call->plan);
+    const bool faster = to_tiles || tile_is_faster(call->shape, call->plan);
     if (faster || (no_tail.g > 4 && tile_is_faster(no_tail, call->plan))) {
       // Not beyond the scratch of the allocation-free entry point: both entry points run the same kernels.
       // By the size that never falls as the tail grows: where a tail stays here, so does every shorter one.
@@ -441,11 +466,17 @@ int noalloc_scratch(void** out) {
 }
 
 // The kernels that the tile kernels stand in for need less scratch (256 bytes where one workgroup owns
-// a row): a workspace that holds what they need, but not more, is accepted, and they run.
+// a row), and so does the fused kernel in place of the streaming ones: a workspace that holds what they need,
+// but not more, is accepted, and they run.
 int check_workspace(DecodeCall* call, const void* workspace, size_t workspace_bytes) {
   if (!workspace) return fail(CQ_ERR_WORKSPACE, "workspace is NULL");
   if ((reinterpret_cast<uintptr_t>(workspace) & 255u) != 0)
     return fail(CQ_ERR_WORKSPACE, "workspace must be 256-byte aligned");
+  if (call->streamed && call->sets_fit && g_kernel_path == CQ_PATH_AUTO && workspace_bytes < call->stream.ws_bytes &&
+      workspace_bytes >= call->plan.ws_bytes) {
+    call->streamed = false;
+    if (!call->tiled) call->ws_bytes = ws_without_tiles(*call);
+  }
   if (call->tiled && g_kernel_path == CQ_PATH_AUTO && workspace_bytes < call->ws_bytes &&
       workspace_bytes >= ws_without_tiles(*call)) {
     call->tiled = false;

@@ -1419,7 +1419,8 @@ void chunk_extent(const DecodeShape& s, int n_chunks, int* nv_max, int* nt_max) 
 // exchange, the merge and each further partial cost.  Microseconds, fitted to 4000 measurements of 570 layouts
 // with 1 to 256 workgroups, head_dim 128 (6 % rms): a call takes 4.1, 3.7 more for a shared row, per thousand tokens
 // of a chunk 1.6 / 2.1 / 3.1 (1 / 2 / 4 bits; key groups of 32 another 1.0), 0.9 per 64 tokens of the tail, 0.1 per
-// chunk, and 1.3 to 2.2 where the chip is full.  That last figure is set so that two chunks on a full chip are taken
+// chunk, and 1.3 to 2.2 where the chip is full (the corrections for channel-wise values and whole-sequence keys are of the
+// same fit).  That last figure is set so that two chunks on a full chip are taken
 // where they pay (96 to 128 rows, whole / in 2: 1 bit x 3584 tokens 11.4 / 12.3, x 6016 16.6 / 15.3; 2 bits x 4480
 // 15.5 / 14.9; 4 bits x 3840 18.5 / 19.4, x 4224 18.7 / 16.9).
 int spread_chunks(const DecodeShape& s, bool k_whole, long long rows, long long cus, int n_units) {
@@ -1452,6 +1453,7 @@ FusedPlan make_fused_plan(const DecodeShape& shape, int min_chunks, FusedSplit s
   if (s.g > 2 * kHeads || (s.n_vis % 64 != 0 && !k_whole)) return p;
   if (s.v_axis == CQ_AXIS_CHANNEL && s.n_vis % s.v_group != 0 && !v_whole) return p;
   p.nhb = (s.g + kHeads - 1) / kHeads;
+  p.ragged = k_whole && s.n_vis % 128 != 0;
   p.can_fine = s.bits <= 4 && (s.v_axis == CQ_AXIS_TOKEN || (k_whole && v_whole));
   const long long rows = (long long)s.B * s.Hkv * p.nhb;
   const int unit = chunk_unit(s);
@@ -1508,7 +1510,9 @@ FusedPlan make_fused_plan(const DecodeShape& shape, int min_chunks, FusedSplit s
     }
   }
   if ((p.n_chunks > 1 || p.nhb > 1) && s.n_vis == 0) return p;
-  if (p.n_chunks > 1) {
+  // Whole rows touch none.  (Two head sets with compute units to spare are shared between workgroups where their tail is
+  // longer; a workspace for them holds a partial per head in any case.)
+  if (p.n_chunks > 1 || (p.nhb > 1 && rows <= device_cu_count())) {
     // a count per (row, head block), one (m, l, acc[d]) partial per (head, chunk)
     const size_t heads = (size_t)s.B * s.Hq;
     p.ws_partial_floats = ((size_t)rows * 2 + 63) / 64 * 64;

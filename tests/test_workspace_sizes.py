@@ -128,11 +128,13 @@ def test_whole_rows_of_two_head_sets_take_the_least_scratch(args):
     assert needed(cq.make_layout(*args), 20) == 256
 
 
-@pytest.mark.parametrize("batch,tails,streamed", [(64, (1000, 128, 128), (True, False, False)), (53, (804, 300, 20), (True, True, False)),
-                                                  (16, (1000, 700, 10), (False, False, False))])
-def test_two_head_sets_on_chip_unless_rounds_of_a_long_tail(batch, tails, streamed):
-    """768 tokens of 8 KV heads, 8 query heads each: 128 rows are one round of workgroups, more of them read a long tail
-    more slowly than the streaming kernels, which need scratch."""
-    lay = cq.make_layout(batch, 64, 8, 128, 768, 1)
-    for n_text, expect in zip(tails, streamed):
-        assert (needed(lay, n_text) > batch * 64 * 768 * 2) == expect, n_text
+# batch, n_vis, tail; whether the streaming kernels take it: rounds of long tails, rows that are long beside them, 128 rows
+# (one round)
+SETS = [(64, 768, 1000, True), (53, 768, 804, True), (64, 3328, 128, False), (28, 768, 38, False), (16, 768, 1000, False)]
+
+
+@pytest.mark.parametrize("batch,n_vis,n_text,streamed", SETS)
+def test_two_head_sets_on_chip_unless_rounds_of_a_long_tail(batch, n_vis, n_text, streamed):
+    """8 KV heads of 8 query heads.  The streaming kernels keep 16-bit logits in scratch."""
+    lay = cq.make_layout(batch, 64, 8, 128, n_vis, 1)
+    assert (needed(lay, n_text) > batch * 64 * n_vis * 2) == streamed
