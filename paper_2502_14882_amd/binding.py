@@ -58,21 +58,21 @@ def lib() -> ctypes.CDLL:
         L = ctypes.CDLL(LIB_PATH)
         P, I, V = ctypes.POINTER, ctypes.c_int32, ctypes.c_void_p
         L.cq_quantize_kv.restype = ctypes.c_int
-        L.cq_quantize_kv.argtypes = [P(CqLayout), V, V, V, V, V]          # (cq_qtensor_t: a struct or its bytes)
+        L.cq_quantize_kv.argtypes = [P(CqLayout), V, V, P(CqQTensor), P(CqQTensor), V]
         L.cq_decode_workspace_bytes.restype = ctypes.c_size_t
         L.cq_decode_workspace_bytes.argtypes = [P(CqLayout), I, P(CqCalib)]
         L.cq_decode_attn.restype = ctypes.c_int
-        L.cq_decode_attn.argtypes = [P(CqLayout), V, V, V, V, V, I, I,
+        L.cq_decode_attn.argtypes = [P(CqLayout), V, P(CqQTensor), P(CqQTensor), V, V, I, I,
                                      P(CqCalib), ctypes.c_float, V, V, ctypes.c_size_t, V]
         L.cq_decode_attn_noalloc.restype = ctypes.c_int
-        L.cq_decode_attn_noalloc.argtypes = [P(CqLayout), V, V, V, V, V, I, I,
+        L.cq_decode_attn_noalloc.argtypes = [P(CqLayout), V, P(CqQTensor), P(CqQTensor), V, V, I, I,
                                              P(CqCalib), ctypes.c_float, V, V]
         L.cq_append_text_kv.restype = ctypes.c_int
         L.cq_append_text_kv.argtypes = [P(CqLayout), V, V, I, I, V, V, V]
         L.cq_append_text_kv_devlen.restype = ctypes.c_int
         L.cq_append_text_kv_devlen.argtypes = [P(CqLayout), V, V, V, I, V, V, V]
         L.cq_decode_attn_devlen.restype = ctypes.c_int
-        L.cq_decode_attn_devlen.argtypes = [P(CqLayout), V, V, V, V, V, V, I, I,
+        L.cq_decode_attn_devlen.argtypes = [P(CqLayout), V, P(CqQTensor), P(CqQTensor), V, V, V, I, I,
                                             P(CqCalib), ctypes.c_float, V, V, ctypes.c_size_t, V]
         L.cq_tau_search_workspace_bytes.restype = ctypes.c_size_t
         L.cq_tau_search_workspace_bytes.argtypes = [P(CqLayout), I, I, I]
@@ -98,6 +98,30 @@ def lib() -> ctypes.CDLL:
         L.cq_version.argtypes = []
         _lib = L
     return _lib
+
+
+class _PackedCalls:
+    """The entry points that the functions below call with cq_qtensor_t packed as bytes, as function objects of their
+    own: those of lib() take the struct, by value or by reference, and refuse anything else."""
+    __slots__ = ("quantize_kv", "decode_attn", "decode_attn_noalloc", "decode_attn_devlen")
+
+    def __init__(self, L: ctypes.CDLL):
+        struct = ctypes.POINTER(CqQTensor)
+        for name in self.__slots__:
+            typed, call = getattr(L, "cq_" + name), L["cq_" + name]
+            call.restype = typed.restype
+            call.argtypes = [ctypes.c_void_p if t is struct else t for t in typed.argtypes]
+            setattr(self, name, call)
+
+
+_packed_calls: Optional[_PackedCalls] = None
+
+
+def _calls() -> _PackedCalls:
+    global _packed_calls
+    if _packed_calls is None or _lib is None:
+        _packed_calls = _PackedCalls(lib())
+    return _packed_calls
 
 
 def _check(status: int) -> None:
@@ -172,7 +196,7 @@ def cq_quantize_kv(layout: CqLayout, k: Optional[torch.Tensor], v: Optional[torc
     for t in (k, v):
         if t is not None:
             assert t.dtype == torch.float16 and t.is_contiguous()
-    status = lib().cq_quantize_kv(ctypes.byref(layout), _ptr(k), _ptr(v),
+    status = _calls().quantize_kv(ctypes.byref(layout), _ptr(k), _ptr(v),
                                   _packed(k_out) if k_out is not None else None,
                                   _packed(v_out) if v_out is not None else None,
                                   _stream(ref) if ref is not None else None)
@@ -255,7 +279,7 @@ def cq_decode_attn(layout: CqLayout, q: torch.Tensor, k: Optional[QTensor], v: O
     if workspace is None:
         workspace = torch.empty(cq_decode_workspace_bytes(layout, n_text, calib), dtype=torch.uint8,
                                 device=q.device)
-    status = lib().cq_decode_attn(
+    status = _calls().decode_attn(
         ctypes.byref(layout), q.data_ptr(),
         ks, vs,
         _ptr(k_text), _ptr(v_text), int(n_text), n_text_cap,
@@ -282,7 +306,7 @@ def cq_decode_attn_noalloc(layout: CqLayout, q: torch.Tensor, k: Optional[QTenso
     n_text_cap = _check_decode_tensors(fields, q, k_text, v_text, out)
     assert 0 <= n_text <= n_text_cap
     ks, vs = _check_cache(fields, k, v)
-    status = lib().cq_decode_attn_noalloc(
+    status = _calls().decode_attn_noalloc(
         ctypes.byref(layout), q.data_ptr(),
         ks, vs,
         _ptr(k_text), _ptr(v_text), int(n_text), n_text_cap,
@@ -311,7 +335,7 @@ def cq_decode_attn_devlen(layout: CqLayout, q: torch.Tensor, k: Optional[QTensor
     if workspace is None:
         workspace = torch.empty(cq_decode_workspace_bytes(layout, n_text_max, calib),
                                 dtype=torch.uint8, device=q.device)
-    status = lib().cq_decode_attn_devlen(
+    status = _calls().decode_attn_devlen(
         ctypes.byref(layout), q.data_ptr(),
         ks, vs,
         _ptr(k_text), _ptr(v_text), n_text_dev.data_ptr(), int(n_text_max), n_text_cap,

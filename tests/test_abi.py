@@ -318,3 +318,19 @@ def test_quantizer_kernels_stop_where_a_launch_does():
             assert _quant(lay) == cq.CQ_ERR_UNSUPPORTED, (d, n, group)
     finally:
         cq.cq_bench_set_kernel_path(cq.CQ_PATH_AUTO)
+
+
+def test_quantized_tensors_are_passed_as_structs_only():
+    """By value or by reference; what is neither is refused before the call."""
+    lay, t = cq.make_layout(1, 4, 1, 128, 128), cq.CqQTensor(FAKE, FAKE, FAKE)
+    L = cq.lib()
+    cq._calls()                              # the functions that take packed bytes are others
+    for arg in (t, ctypes.byref(t), ctypes.pointer(t)):
+        assert L.cq_quantize_kv(ctypes.byref(lay), None, None, arg, arg, None) == cq.CQ_ERR_NULL
+        for call in (L.cq_decode_attn, L.cq_decode_attn_devlen):
+            head = (ctypes.byref(lay), None, arg, arg, None, None) + ((None,) if call is L.cq_decode_attn_devlen else ())
+            assert call(*head, 0, 0, None, 0.0, None, None, 0, None) == cq.CQ_ERR_NULL
+        assert L.cq_decode_attn_noalloc(ctypes.byref(lay), None, arg, arg, None, None, 0, 0, None, 0.0, None, None) == cq.CQ_ERR_NULL
+    for arg in (bytes(24), FAKE):
+        with pytest.raises(ctypes.ArgumentError):
+            L.cq_quantize_kv(ctypes.byref(lay), None, None, arg, arg, None)
