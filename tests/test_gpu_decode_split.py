@@ -124,6 +124,10 @@ def test_rows_spread_over_idle_compute_units(args, shared):
     cq.cq_bench_set_kernel_path(prev)
     if args[5] <= 4:
         assert (size > whole) == shared, (size, whole)
+    else:                                                      # the tile kernels' scratch, which keeps the logits
+        prev = cq.cq_bench_set_kernel_path(cq.CQ_PATH_TILE)
+        assert size == cq.cq_decode_workspace_bytes(lay, n_text, calib) >= args[0] * args[1] * (args[3] + n_text) * 4
+        cq.cq_bench_set_kernel_path(prev)
     ref = O.decode_attn(x["q"].numpy(), kq, vq, x["k_text"].numpy(), x["v_text"].numpy(), n_text, O.CALIB_DYNAMIC, 1.0, 2.0)
     for n_bytes in {size, whole}:
         ws = torch.empty(n_bytes, dtype=torch.uint8, device="cuda").fill_(255)
@@ -165,6 +169,9 @@ def test_tile_kernels_in_one_launch(shape):
             got.append(cq.cq_decode_attn(lay, dev["q"], k, v, dev["k_text"], dev["v_text"], n_text, cq.make_calib(*calib), 0.0,
                                          None, ws.fill_(fill)))
             cq.cq_bench_set_decode_chunks(prev)
+            # one launch it was: two keep an fp32 logit of every (head, token) at the start of the scratch
+            logits = ws[:B * n_q * (n + n_text) * 4]
+            assert (logits == fill).float().mean() > 0.05, "the logits went through memory"
     finally:
         cq.cq_bench_set_kernel_path(path)
     err = O.rel_l2(got[0].cpu().numpy().astype(np.float64), ref)
