@@ -206,13 +206,16 @@ int check_calib(const cq_calib_t* calib, cq::Calib* c) {
 // many rows would lose: 256 rows x 128 + 100 tokens, 8 heads 12.7 us on the other kernels, 13.6 on chip.
 constexpr int kTwoSetsOnChip = 256;
 
-// Whether the tile kernels finish a call sooner than the tuned kernels that could take it, asked where the fused kernel
-// does not spread its rows over the chip (8 bits, two head sets of few tokens, more rows than CUs).  The fused
-// kernel gives a row (a chunk of a row) to one CU, which moves about 27 GB/s, and the streaming
-// kernels take three launches; with few rows the tile kernels, one or two launches over many small
-// workgroups, win.  Microseconds per call inside a recorded graph, fitted to measurements of both sides
+// Whether the tile kernels finish a call sooner than the tuned kernels that could take it on whole rows or the fewest
+// chunks.  Decides where the fused kernel does not spread its rows over the chip (8 bits, two head sets of few
+// tokens, more rows than CUs); of the calls that it does spread, says which would be the tile kernels' and keep their
+// precision (select_kernels).  The fused kernel gives a row (a chunk of a row) to one CU, which moves about
+// 27 GB/s, and the streaming kernels take three launches; with few rows the tile kernels, one or two launches
+// over many small workgroups, win.  Microseconds per call inside a recorded graph, fitted to measurements of both sides
 // (two launches of the tile kernels) over 8 to 256 rows (batch x KV heads) of 1024 to 32768 tokens, 1 to
-// 8 bits, key groups of 32 tokens to the whole row, 1 to 6 query heads per KV head; for example (tuned / tile)
+// 8 bits, key groups of 32 tokens to the whole row, 1 to 6 query heads per KV head, none of them spread (the streaming
+// kernels with two head sets: below 2 million tokens; longer rows have on_chip_is_faster, rows of more than one
+// round whole_sets_are_faster); for example (tuned / tile)
 //   1 bit, 4 heads:  8 rows x 3328 tokens 12.5 / 11.8, x 8192 21.8 / 14.4; 32 rows x 8192 22.1 / 19.6;
 //                    8 rows x 1024 9.1 / 11.6 and 64 rows x 8192 22.2 / 27.1 stay fused
 //   1 bit, 6 heads:  8 rows x 3328 20.7 / 12.5, 64 rows 22.6 / 19.5; 128 rows 26.0 / 27.3 stay streamed
