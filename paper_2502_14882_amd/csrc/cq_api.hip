@@ -327,7 +327,7 @@ int select_kernels(const cq_layout_t* L, int n_text, int n_text_cap, size_t scra
   if (on_chip && g_kernel_path == CQ_PATH_AUTO) {
     const cq::FusedPlan rows = call->plan.n_chunks == 1 ? call->plan : cq::make_fused_plan(call->shape, 0);
     if (call->plan.ragged || tile_is_faster(call->shape, rows)) {
-      to_tiles = !call->plan.can_fine || (call->plan.spread && tiles_beat_spread_rows(call->shape, call->plan));
+      to_tiles = call->plan.spread && tiles_beat_spread_rows(call->shape, call->plan);
       call->plan.fine = !to_tiles;
       if (to_tiles) {
         call->plan = rows;

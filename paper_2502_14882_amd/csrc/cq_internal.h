@@ -164,7 +164,6 @@ struct FusedPlan {
   bool spread = false;        // every workgroup has a CU of its own, and as many chunks as pay
   bool fine = false;          // at the precision of the tile kernels (set by the caller; rows that end inside a group always are)
   bool ragged = false;        // rows that end inside a group
-  bool can_fine = false;      // a kernel has it for the layout: up to 4 bits, values not channel-wise in groups
   int stride = 0;             // floats between the logit rows of two heads in LDS
   size_t lds = 0;             // dynamic LDS bytes per workgroup
   int patience = kPatience;

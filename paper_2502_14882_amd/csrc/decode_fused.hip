@@ -114,7 +114,8 @@ __device__ inline bool over_scale(const float (&x)[kHeads]) {
 // values: a scale per head that follows weight x token scale; one scale for all heads, set by the largest token
 // scale, lets that token take the bits of the others whether or not a head looks at it, and the tail the bits of
 // all visual tokens (values 3e6 times the others' at weights of 2e-8: 64 of 1000 to 8192 tokens 6e-4 to 1e-2 off, all visual
-// tokens of a short row 100 %; this way below 2e-5 with the rounding of the logits).  Recorded in a graph,
+// tokens of a short row 100 %; this way below 2e-5 with the rounding of the logits).  Channel-wise values in groups: a
+// scale per head and tile (8 rows x 8192 + 128 tokens, 1 bit 12.0 / 12.4 us, the tile kernels 14.6).  Recorded in a graph,
 // otherwise / FINE: 8 rows x 3328 + 128 tokens, 1 bit 11.20 / 11.37 us, 4 bits 12.36 / 12.44; 32 x 8192 + 512, 1 bit 14.10 / 14.45.
 // TILES = 16-token tiles per key group.  VCH = values are
 // quantized channel-wise over groups of tokens (Sec. 3.1, the paper's own choice) instead of
@@ -712,7 +713,8 @@ fused_row_kernel(const FusedArgs args) {
     if constexpr (VCH) { if (nv > 0) {
       // Channel-wise values: out_c = sum over value groups G of
       //     scale_{G,c} * sum_{j in G} p_j code_{j,c}  +  min_{G,c} * sum_{j in G} p_j.
-      // The weights p_j <= 1 go into the matrix operand with one fixed shift (2^29); an extra
+      // The weights p_j <= 1 go into the matrix operand with one fixed shift (2^29; FINE, where a group has parameters of
+      // its own: with a scale per head and tile, and every tile is folded); an extra
       // product with an all-ones operand yields sum_j p_j in the same fixed point and in the
       // accumulator layout (column = code byte, head = lane / 16).  A wave owns whole value
       // groups (v_group / 64 consecutive tiles) and folds each finished group into fp32.
@@ -751,18 +753,31 @@ fused_row_kernel(const FusedArgs args) {
         gmn[0] = *reinterpret_cast<const v2i*>(vmn + (size_t)grp * a.v_pstride + c_lo);
         gmn[1] = *reinterpret_cast<const v2i*>(vmn + (size_t)grp * a.v_pstride + c_hi);
       };
+      const bool whole = RAG || a.v_pstride == 0;
+      float inv_tile[2] = {0x1p-29f, 0x1p-29f};       // FINE: what a step of the tile in each buffer is worth, of head kb
       auto prep_tile = [&](int slot, int k, int buf) {
         const int jt = tile_start(k);
         float lg[kHeads];
 #pragma unroll
         for (int h = 0; h < kHeads; ++h) lg[h] = logits[h * a.stride + jt + lane];
         v4i xs;
+        float w[kHeads];
 #pragma unroll
         for (int h = 0; h < kHeads; ++h) {
           float p = __builtin_amdgcn_exp2f(fmaf(lg[h], a2[h], c2v[h]));
           if (RAG) p = jt + lane < nv ? p : 0.f;
           lsum[h] += p;
-          xs[h] = product_digits(p, 536870912.f);
+          w[h] = p;
+        }
+        if (FINE && !RAG && !whole) {
+          Scales scales(90);
+          scales.lower(w, lane);
+          inv_tile[buf] = scales.inverse(kb);
+#pragma unroll
+          for (int h = 0; h < kHeads; ++h) xs[h] = (int)digits_bias(w[h], scales.of(h)) ^ 0x00808080;
+        } else {
+#pragma unroll
+          for (int h = 0; h < kHeads; ++h) xs[h] = product_digits(w[h], 536870912.f);
         }
         __builtin_amdgcn_wave_barrier();
         *reinterpret_cast<v4i*>(lbytes + (size_t)jt * 4 + x_wr) = xs;
@@ -774,8 +789,8 @@ fused_row_kernel(const FusedArgs args) {
       v4i acc_w = {0, 0, 0, 0};
       const v4i ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
       // folds the finished value group into fp32 and asks for the parameters of group `next_group`
-      auto fold_group = [&](int next_group) {
-        const float wsum = digits_to_float(acc_w);
+      auto fold_group = [&](int next_group, int buf) {
+        const float unit = FINE ? inv_tile[buf] : 1.f, wsum = digits_to_float(acc_w) * unit;
         acc_w = (v4i){0, 0, 0, 0};
 #pragma unroll
         for (int p = 0; p < 8; ++p) {
@@ -786,7 +801,7 @@ fused_row_kernel(const FusedArgs args) {
           const float mn = __half2float(__ushort_as_half((uint16_t)((el & 1) ? mpair >> 16 : mpair & 0xffffu)));
           // the operand byte of a set code is 2^p (b = 1) resp. code * {1, 4, 16, 16}: take that out
           const float sc = gsc[vec][el] * variant_weight<BITS>(p % (8 / BITS));
-          facc[p] = fmaf(digits_to_float(acc[p]), sc, fmaf(wsum, mn, facc[p]));
+          facc[p] = fmaf(digits_to_float(acc[p]) * unit, sc, fmaf(wsum, mn, facc[p]));
           acc[p] = (v4i){0, 0, 0, 0};
         }
         pin_order();
@@ -833,7 +848,7 @@ fused_row_kernel(const FusedArgs args) {
           acc[p] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A, B, acc[p], 0, 0, 0);
         }
         acc_w = __builtin_amdgcn_mfma_i32_16x16x64_i8(A, ones, acc_w, 0, 0, 0);
-        if constexpr (FOLD) fold_group((k >> tsh) + 1);
+        if constexpr (FOLD) fold_group(FINE ? (k + 1) >> tsh : (k >> tsh) + 1, buf);
         lds_publish();
       };
       if (n_my > 0) {
@@ -847,7 +862,7 @@ fused_row_kernel(const FusedArgs args) {
         static_assert(kRingV == 2, "the loops below pair a ring slot with a tile of a 128-token group");
         const std::integral_constant<bool, true> fold_yes;
         const std::integral_constant<bool, false> fold_no;
-        if (RAG || a.v_pstride == 0) {
+        if (whole) {
           // whole-sequence statistics: every group has the row's parameters, so the wave folds
           // once, after its last tile (an int32 accumulator takes 2^20 per tile at most: 2047
           // tiles, a workgroup's LDS holds ~140)
@@ -857,13 +872,13 @@ fused_row_kernel(const FusedArgs args) {
             m_step(k + 1, 1, fold_no);
           }
           if (k < n_my) m_step(k, 0, fold_no);
-          fold_group(0);
-        } else if (tpg == 2) {              // groups of 128 tokens: two tiles, the second one folds
+          fold_group(0, 0);
+        } else if (!FINE && tpg == 2) {              // groups of 128 tokens: two tiles, the second one folds
           for (int k = 0; k < n_my; k += 2) {
             m_step(k, 0, fold_no);
             m_step(k + 1, 1, fold_yes);
           }
-        } else {                            // groups of 64 tokens: every tile folds
+        } else {                            // groups of 64 tokens, FINE: every tile folds
           int k = 0;
           for (; k + 2 <= n_my; k += 2) {
             m_step(k, 0, fold_yes);
@@ -1270,8 +1285,8 @@ fused_row_kernel(const FusedArgs args) {
       constexpr int kV = 8 / BITS;
       const int tb = 16 * (p / kV) + n16;
       const int ch = (32 / BITS) * (tb >> 2) + code_in_word<BITS>(tb & 3, p % kV);
-      // channel-wise values are accumulated in units of 2^-29 (the weights' fixed point)
-      const float x = VCH ? v * 0x1p-29f : v * variant_weight<BITS>(p % kV);
+      // channel-wise values are accumulated in units of 2^-29 (the weights' fixed point; FINE: already without)
+      const float x = VCH ? (FINE ? v : v * 0x1p-29f) : v * variant_weight<BITS>(p % kV);
       partial[kb * kD + ch] = FINE ? x * vis_unit : x;
     }
   } else {      // text wave: lane (kb, n16) holds heads 0..3, channels 8 n16 + 2 kb and + 1
@@ -1454,7 +1469,6 @@ FusedPlan make_fused_plan(const DecodeShape& shape, int min_chunks, FusedSplit s
   if (s.v_axis == CQ_AXIS_CHANNEL && s.n_vis % s.v_group != 0 && !v_whole) return p;
   p.nhb = (s.g + kHeads - 1) / kHeads;
   p.ragged = k_whole && s.n_vis % 128 != 0;
-  p.can_fine = s.bits <= 4 && (s.v_axis == CQ_AXIS_TOKEN || (k_whole && v_whole));
   const long long rows = (long long)s.B * s.Hkv * p.nhb;
   const int unit = chunk_unit(s);
   const int n_units = ceil_div(s.n_vis, s.k_group * unit);
@@ -1568,20 +1582,6 @@ FusedChoice pick_kernel(const DecodeShape& s, const FusedPlan& plan, bool k_whol
       default: break;
     }
   }
-  if constexpr (!FINE) {
-    switch ((s.k_group * 4 + s.bits) * 2 + (vch ? 1 : 0)) {
-      case (32 * 4 + 1) * 2 + 1: return {fused_row_kernel<SPLIT, false, 2, 1, true>, 6};
-      case (64 * 4 + 1) * 2 + 1: return {fused_row_kernel<SPLIT, false, 4, 1, true>, 7};
-      case (128 * 4 + 1) * 2 + 1: return {fused_row_kernel<SPLIT, false, 8, 1, true>, 8};
-      case (32 * 4 + 2) * 2 + 1: return {fused_row_kernel<SPLIT, false, 2, 2, true>, 9};
-      case (64 * 4 + 2) * 2 + 1: return {fused_row_kernel<SPLIT, false, 4, 2, true>, 10};
-      case (128 * 4 + 2) * 2 + 1: return {fused_row_kernel<SPLIT, false, 8, 2, true>, 11};
-      case (32 * 4 + 8) * 2: return {fused_row_kernel<SPLIT, false, 2, 8, false>, 15};
-      case (64 * 4 + 8) * 2: return {fused_row_kernel<SPLIT, false, 4, 8, false>, 16};
-      case (128 * 4 + 8) * 2: return {fused_row_kernel<SPLIT, false, 8, 8, false>, 17};
-      default: break;
-    }
-  }
   switch ((s.k_group * 4 + s.bits) * 2 + (vch ? 1 : 0)) {
     case (32 * 4 + 1) * 2: return {fused_row_kernel<SPLIT, FINE, 2, 1, false>, 0};
     case (64 * 4 + 1) * 2: return {fused_row_kernel<SPLIT, FINE, 4, 1, false>, 1};
@@ -1589,11 +1589,24 @@ FusedChoice pick_kernel(const DecodeShape& s, const FusedPlan& plan, bool k_whol
     case (32 * 4 + 2) * 2: return {fused_row_kernel<SPLIT, FINE, 2, 2, false>, 3};
     case (64 * 4 + 2) * 2: return {fused_row_kernel<SPLIT, FINE, 4, 2, false>, 4};
     case (128 * 4 + 2) * 2: return {fused_row_kernel<SPLIT, FINE, 8, 2, false>, 5};
+    case (32 * 4 + 1) * 2 + 1: return {fused_row_kernel<SPLIT, FINE, 2, 1, true>, 6};
+    case (64 * 4 + 1) * 2 + 1: return {fused_row_kernel<SPLIT, FINE, 4, 1, true>, 7};
+    case (128 * 4 + 1) * 2 + 1: return {fused_row_kernel<SPLIT, FINE, 8, 1, true>, 8};
+    case (32 * 4 + 2) * 2 + 1: return {fused_row_kernel<SPLIT, FINE, 2, 2, true>, 9};
+    case (64 * 4 + 2) * 2 + 1: return {fused_row_kernel<SPLIT, FINE, 4, 2, true>, 10};
+    case (128 * 4 + 2) * 2 + 1: return {fused_row_kernel<SPLIT, FINE, 8, 2, true>, 11};
     case (32 * 4 + 4) * 2: return {fused_row_kernel<SPLIT, FINE, 2, 4, false>, 12};
     case (64 * 4 + 4) * 2: return {fused_row_kernel<SPLIT, FINE, 4, 4, false>, 13};
     case (128 * 4 + 4) * 2: return {fused_row_kernel<SPLIT, FINE, 8, 4, false>, 14};
-    default: return {nullptr, 0};
+    default: break;
   }
+  if constexpr (!FINE) switch (s.k_group * 4 + s.bits) {
+    case 32 * 4 + 8: return {fused_row_kernel<SPLIT, false, 2, 8, false>, 15};
+    case 64 * 4 + 8: return {fused_row_kernel<SPLIT, false, 4, 8, false>, 16};
+    case 128 * 4 + 8: return {fused_row_kernel<SPLIT, false, 8, 8, false>, 17};
+    default: break;
+  }
+  return {nullptr, 0};
 }
 
 }  // namespace

@@ -200,9 +200,10 @@ def test_rows_that_end_inside_a_processing_group(shape, chunks):
 
 
 # Calls that the library takes from the tile kernels to the fused one: rows of any length with whole-sequence keys, few
-# rows, two head sets: (q heads of the KV head, n_vis, key group, value axis, value group); values in groups stay
+# rows, two head sets: (q heads of the KV head, n_vis, key group, value axis, value group)
 STAND_OUT = [(4, 1000, 1000, 1, 128), (4, 3003, 3003, 1, 128), (4, 3003, 3003, 0, 3003), (4, 4096, 128, 1, 128), (4, 8192, 32, 1, 128),
-             (4, 8192, 8192, 0, 8192), (8, 3328, 64, 1, 128), (7, 2001, 2001, 0, 2001), (4, 8192, 128, 0, 64)]
+             (4, 8192, 8192, 0, 8192), (8, 3328, 64, 1, 128), (7, 2001, 2001, 0, 2001), (4, 8192, 128, 0, 64),
+             (8, 5120, 32, 0, 128), (4, 4096, 4096, 0, 64)]
 
 
 @pytest.mark.parametrize("shape", STAND_OUT)
