@@ -1,5 +1,6 @@
 // Channel-wise groups that a workgroup's registers hold (gfx950): any head_dim, b in {1, 2, 4, 8}, groups of 129 to a
-// few thousand tokens - one pair per channel over the whole sequence, Sec. 3.1 as printed, on an image or two.
+// few thousand tokens - one pair per channel over the whole sequence, Sec. 3.1 as printed, on an image or two - where
+// that is faster (quantize_slice_supported).
 //
 // The tile kernels of quantize_tile.h read such a group twice: once for its extrema, once for its codes, with launches
 // in between.  Here a workgroup owns 32 or 64 channels of a group, all its tokens: it reads them once, 64 or 128
@@ -174,15 +175,26 @@ SliceKernel slice_kernel(int tokens, int* threads, int* lanes) {
     *lanes = 4;
   }
   if (tokens <= 3072) return quantize_slice_kernel<BITS, 4, 1024, 12>;
-  if (tokens <= 4096) return quantize_slice_kernel<BITS, 4, 1024, 16>;
+  if constexpr (BITS <= 2) {
+    if (tokens <= 4096) return quantize_slice_kernel<BITS, 4, 1024, 16>;
+  }
   return nullptr;
 }
 
 }  // namespace
 
+// A workgroup's own time grows with the tokens it owns and the width of the codes, so long groups take the tile kernels'
+// many workgroups unless there are enough of them, and beyond 3072 tokens 4- and 8-bit codes always do (their registers
+// spilled there).  us, keys and values whole, tile kernels / here: 2 bits 4000 tokens, 128 channels in all 13.6 / 15.5, 1024
+// 19.2 / 16.3; 4 bits 1500 tokens 64 channels 10.5 / 11.9, 128 12.7 / 12.2; 3000 tokens 128 13.2 / 14.6, 1024 18.6 / 15.6;
+// 8 bits 4000 tokens 128 14.7 / 21.9, 1024 21.9 / 23.9, 8192 74.6 / 76.0 (but 4096 43.6 / 36.0).  One bit always wins.
 bool quantize_slice_supported(size_t n_tokens, int d, int bits, int axis, int group) {
-  if (axis != CQ_AXIS_CHANNEL || group <= kTile || group > 4096) return false;
+  if (axis != CQ_AXIS_CHANNEL || group <= kTile || group > (bits <= 2 ? 4096 : 3072)) return false;
   if (d != 64 && d != 128 && d != 256) return false;
+  const size_t channels = n_tokens / group * d;                // of all groups
+  const size_t least = bits == 1 ? 0 : bits == 2 ? (group <= 2048 ? 0 : group <= 3072 ? 128 : 512) : group <= 1024 ? 0
+                       : group <= 1536 ? 128 : 512;
+  if (channels < least) return false;
   // two tensors of whole eights of groups in one grid of at most 2^32 - 1 threads
   return (n_tokens / group * 2 + 8) * (d / 32) <= 0xffffffffu / 1024;
 }
