@@ -55,7 +55,8 @@ constexpr int kTextShare = 32;       // tokens of the fp16 tail per wave and rou
 constexpr int kTextBlock = kWaves * kTextShare;
 // one launch: chunks are whole units of 128 tokens, so many at least and at most; workgroups to aim at
 constexpr int kUnit = 128, kRowMinUnits = 4, kRowMaxUnits = 8, kRowTarget = 768;
-constexpr int kRowMost = 4096, kRowMostAll = 250000, kRowMostChunks = 56;     // see plan_one_launch
+constexpr int kRowMost = 4096, kRowMostShort = 512, kRowMostChunks = 56;      // see plan_one_launch
+constexpr int kRowMostAll = 250000, kRowMostWide = 100000, kRowLeast64 = 150000;
 constexpr int kMaxRun = 1024;        // value tiles between two folds of the int32 digit sums (2^20 each)
 
 struct TileArgs {
@@ -1061,8 +1062,10 @@ namespace {
 // layouts below 100 thousand tokens: 1.06 with 64 channels, 1.2 with 128, 1.17 with 256) and with 128 channels on large
 // ones too (1.3 beyond 600 thousand).  With 64 and 256 channels and with 8 bits it is not: all workgroups pass the exchange
 // together, so memory and matrix cores idle in turn (64 rows of 64 channels x 3328 tokens, two / one: 13.6 / 12.8 us,
-// x 8192 17.9 / 18.5; 480 rows of 256 channels x 4352 77 / 99), the more so in key groups of 32, which leave a wave a
-// short block.  768 workgroups: three per CU are resident whatever the registers (256 rows x 2001, 1024 / 768:
+// x 8192 17.9 / 18.5; 480 rows of 256 channels x 4352 77 / 99; 144 x 1198, 4 bits 25.3 / 30.1), the more so in key groups of
+// 32, and with 256 channels, 8 bits, or 64 channels of few rows in groups of 64, which leave a wave short blocks (128 x 640, 6
+// heads, 2 bits, 256 channels 17.4 / 25.0; 16 x 1536, 8 bits 12.1 / 13.9; 8 x 3328, 4 bits, 64 channels 9.5 / 10.9; but 157 x
+// 256, 8 bits 15.3 / 13.0).  768 workgroups: three per CU are resident whatever the registers (256 rows x 2001, 1024 / 768:
 // 21.3 / 18.6); chunks below four units only lengthen the exchange and the merge (64 rows x 3003: 23.6 us with
 // two, 14.9 with four), and more than 56 chunks of a row cost more than they save (8 rows x 60608 25.8 / 31.2).
 void plan_one_launch(const DecodeShape& s, long long rows, long long sets, TilePlan* p) {
@@ -1072,7 +1075,10 @@ void plan_one_launch(const DecodeShape& s, long long rows, long long sets, TileP
   const int units = ceil_div(s.n_vis, kUnit);
   p->row_ct = p->ct;
   if (s.k_group < 64 && s.k_group != s.n_vis) return;
-  if ((s.d != 128 || s.bits == 8) && (s.n_vis > kRowMost || rows * sets * s.n_vis > kRowMostAll)) return;
+  if ((s.d != 128 || s.bits == 8) &&
+      (s.n_vis > kRowMost || rows * sets * s.n_vis > (s.d == 256 ? kRowMostWide : kRowMostAll))) return;
+  if (s.k_group == 64 && s.n_vis > kRowMostShort &&
+      (s.d == 256 || s.bits == 8 || (s.d == 64 && rows * sets * s.n_vis < kRowLeast64))) return;
   if (s.n_vis > 0) {
     if (!fits_units(s.k_axis, s.k_group) || !fits_units(s.v_axis, s.v_group)) return;
     const long long want = (kRowTarget + rows * sets - 1) / (rows * sets);

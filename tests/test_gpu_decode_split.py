@@ -141,7 +141,8 @@ def test_rows_spread_over_idle_compute_units(args, shared):
 # visual tokens, a tail of several chunks
 TILES = [(2, 8, 2, 128, 3003, 77, 2, 3003, 0, 3003), (1, 4, 4, 64, 4096, 100, 1, 64, 1, 64), (1, 6, 1, 256, 1003, 4, 8, 1003, 1, 256),
          (1, 4, 1, 64, 100, 0, 4, 100, 0, 100), (2, 10, 2, 128, 1537, 300, 1, 1537, 0, 1537), (1, 2, 2, 64, 0, 700, 1, 64, 1, 64),
-         (1, 3, 1, 64, 1984, 5, 2, 64, 0, 32), (1, 4, 1, 256, 2048, 129, 1, 128, 0, 256), (1, 1, 1, 128, 777, 1, 8, 777, 1, 128)]
+         (1, 3, 1, 64, 1984, 5, 2, 64, 0, 32), (1, 4, 1, 256, 2048, 129, 1, 128, 0, 256), (1, 1, 1, 128, 777, 1, 8, 777, 1, 128),
+         (5, 8, 8, 64, 4096, 100, 1, 64, 1, 64), (10, 24, 8, 64, 1984, 5, 2, 64, 0, 32)]
 
 
 @pytest.mark.parametrize("shape", TILES)
@@ -169,9 +170,11 @@ def test_tile_kernels_in_one_launch(shape):
             got.append(cq.cq_decode_attn(lay, dev["q"], k, v, dev["k_text"], dev["v_text"], n_text, cq.make_calib(*calib), 0.0,
                                          None, ws.fill_(fill)))
             cq.cq_bench_set_decode_chunks(prev)
-            # one launch it was: two keep an fp32 logit of every (head, token) at the start of the scratch
+            # one launch it was: two keep an fp32 logit of every (head, token) at the start of the scratch (key groups of
+            # 64 tokens with 64 channels: from 150 thousand tokens)
             logits = ws[:B * n_q * (n + n_text) * 4]
-            assert (logits == fill).float().mean() > 0.05, "the logits went through memory"
+            one = not (k_group == d == 64 and n > 512 and B * n_kv * n < 150000)
+            assert ((logits == fill).float().mean() > 0.05) == one, "whether the logits went through memory"
     finally:
         cq.cq_bench_set_kernel_path(path)
     err = O.rel_l2(got[0].cpu().numpy().astype(np.float64), ref)
