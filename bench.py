@@ -385,9 +385,11 @@ def main() -> int:
 
     # quantizer figures (bytes read + written per call)
     rows = w.batch * w.n_kv_heads
-    # a tensor with whole-sequence statistics of over 4096 tokens is read twice (extrema pass, then codes)
-    q_reads = (2 if k_group == w.n_vis > 4096 else 1) + (
-        2 if v_group == w.n_vis > 4096 and args.v_axis == "channel" else 1)
+    # a tensor with whole-sequence statistics of over 4096 tokens (3072 with 4 and 8 bits) is read twice (extrema
+    # pass, then codes)
+    q_once = 4096 if args.bits <= 2 else 3072
+    q_reads = (2 if k_group == w.n_vis > q_once else 1) + (
+        2 if v_group == w.n_vis > q_once and args.v_axis == "channel" else 1)
     q_bytes = rows * w.n_vis * (q_reads * w.head_dim * 2) + rows * w.n_vis * (per_vis)
     q_ms = sorted(quant_ms)[len(quant_ms) // 2]
 

@@ -1449,7 +1449,8 @@ int spread_chunks(const DecodeShape& s, bool k_whole, long long rows, long long 
   long long c = (long long)(std::sqrt(row / each) + 0.5);
   if (c > most) c = most;
   // (half a microsecond more than the fit says: short rows scatter, and a shared one needs a larger workspace; channel-wise
-  // values of two bits lose another two to registers: 16 rows x 2944 whole / in 8 chunks 10.3 / 11.2, 24 x 6528 15.5 / 12.9)
+  // values of two bits another two, from when their shared kernel spilled 57 registers: 16 rows x 2944 whole / in 8 chunks
+  // 10.3 / 11.2, 24 x 6528 15.5 / 12.9)
   if (c < 2 || row * (double)(c - 1) / (double)c < (vch && s.bits == 2 ? 6.2 : 4.2) + each * (double)(c - 1)) return 1;
   return ceil_div(n_units, ceil_div(n_units, (int)c));         // no more than make the largest chunk smaller
 }
