@@ -212,7 +212,8 @@ struct TilePlan {
   size_t ws_minmax_floats = 0;     // workspace: [logits | extrema | partials | counts], offsets in floats
   size_t ws_partial_floats = 0, ws_count_floats = 0;
   // one launch instead of two, in a part of the same workspace: [words | counts | partials]
-  bool one_launch = false;
+  bool one_launch = false;         // where the workgroups of a row exchange extrema
+  bool one_launch_free = false;    // where they do not (no calibration, or a given range)
   int row_cb = 0, row_ct = 0;      // chunks per row of the visual tokens, of the tail
   size_t row_tags_floats = 0, row_partial_floats = 0;
   int patience = kPatience;

@@ -1065,7 +1065,8 @@ namespace {
 // x 8192 17.9 / 18.5; 480 rows of 256 channels x 4352 77 / 99; 144 x 1198, 4 bits 25.3 / 30.1), the more so in key groups of
 // 32, and with 256 channels, 8 bits, or 64 channels of few rows in groups of 64, which leave a wave short blocks (128 x 640, 6
 // heads, 2 bits, 256 channels 17.4 / 25.0; 16 x 1536, 8 bits 12.1 / 13.9; 8 x 3328, 4 bits, 64 channels 9.5 / 10.9; but 157 x
-// 256, 8 bits 15.3 / 13.0).  768 workgroups: three per CU are resident whatever the registers (256 rows x 2001, 1024 / 768:
+// 256, 8 bits 15.3 / 13.0; and without a calibration range to find there is no exchange: 32 x 1472, 1 bit, 64 channels
+// 10.2 / 9.3).  768 workgroups: three per CU are resident whatever the registers (256 rows x 2001, 1024 / 768:
 // 21.3 / 18.6); chunks below four units only lengthen the exchange and the merge (64 rows x 3003: 23.6 us with
 // two, 14.9 with four), and more than 56 chunks of a row cost more than they save (8 rows x 60608 25.8 / 31.2).
 void plan_one_launch(const DecodeShape& s, long long rows, long long sets, TilePlan* p) {
@@ -1075,10 +1076,10 @@ void plan_one_launch(const DecodeShape& s, long long rows, long long sets, TileP
   const int units = ceil_div(s.n_vis, kUnit);
   p->row_ct = p->ct;
   if (s.k_group < 64 && s.k_group != s.n_vis) return;
-  if ((s.d != 128 || s.bits == 8) &&
-      (s.n_vis > kRowMost || rows * sets * s.n_vis > (s.d == 256 ? kRowMostWide : kRowMostAll))) return;
-  if (s.k_group == 64 && s.n_vis > kRowMostShort &&
-      (s.d == 256 || s.bits == 8 || (s.d == 64 && rows * sets * s.n_vis < kRowLeast64))) return;
+  if ((s.d != 128 || s.bits == 8) && (s.n_vis > kRowMost || rows * sets * s.n_vis > kRowMostAll)) return;
+  const bool exchange_pays = !(s.d == 256 && rows * sets * s.n_vis > kRowMostWide) &&
+                             !(s.k_group == 64 && s.n_vis > kRowMostShort &&
+                               (s.d == 256 || s.bits == 8 || (s.d == 64 && rows * sets * s.n_vis < kRowLeast64)));
   if (s.n_vis > 0) {
     if (!fits_units(s.k_axis, s.k_group) || !fits_units(s.v_axis, s.v_group)) return;
     const long long want = (kRowTarget + rows * sets - 1) / (rows * sets);
@@ -1095,7 +1096,8 @@ void plan_one_launch(const DecodeShape& s, long long rows, long long sets, TileP
   p->row_tags_floats = align64(heads * (size_t)p->row_cb * 4);
   p->row_partial_floats = align64(p->row_tags_floats + (size_t)(rows * sets) * 2);
   const size_t floats = p->row_partial_floats + heads * (size_t)slots * (s.d + 2);
-  p->one_launch = floats * sizeof(float) <= p->ws_bytes;
+  p->one_launch_free = floats * sizeof(float) <= p->ws_bytes;
+  p->one_launch = p->one_launch_free && exchange_pays;
 }
 
 }  // namespace
@@ -1258,7 +1260,7 @@ hipError_t launch_decode_tile(const DecodeShape& s, const TilePlan& plan, const 
                               const cq_qtensor_t& k, const cq_qtensor_t& v, const void* k_text,
                               const void* v_text, const int32_t* n_text_dev, const Calib& calib,
                               float softmax_scale, void* out, float* workspace, hipStream_t stream) {
-  if (plan.ok && plan.one_launch)
+  if (plan.ok && (calib.mode == CQ_CALIB_DYNAMIC ? plan.one_launch : plan.one_launch_free))
     return launch_tile_rows(s, plan, q, k, v, k_text, v_text, n_text_dev, calib, softmax_scale, out, workspace, stream);
   TileArgs a{};
   a.ws_count = reinterpret_cast<int*>(workspace + plan.ws_count_floats);

@@ -182,6 +182,29 @@ def test_tile_kernels_in_one_launch(shape):
     assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
 
 
+# The first of TILES that takes two launches because of the exchange, and one of 256 channels
+@pytest.mark.parametrize("shape", [TILES[1], (1, 4, 1, 256, 1024, 5, 2, 64, 0, 256)])
+def test_tile_kernels_without_an_exchange_take_one_launch(shape):
+    """Without calibration no workgroup waits for another's extrema."""
+    B, n_q, n_kv, d, n, n_text, bits, k_group, v_axis, v_group = shape
+    w = synth.WORKLOADS[1].replace(batch=B, n_q_heads=n_q, n_kv_heads=n_kv, head_dim=d, n_vis=n, n_text=n_text, seed=n + d)
+    x = synth.make_inputs(w, "cpu")
+    lay = cq.make_layout(B, n_q, n_kv, d, n, bits, 0, v_axis, k_group, v_group)
+    dev = {k: t.cuda() for k, t in x.items()}
+    k, v = cq.cq_quantize_kv(lay, dev["k"], dev["v"])
+    kq, vq = H.oracle_quantize(x, lay)
+    prev = cq.cq_bench_set_kernel_path(cq.CQ_PATH_TILE)
+    try:
+        ws = torch.empty(cq.cq_decode_workspace_bytes(lay, n_text, None), dtype=torch.uint8, device="cuda").fill_(255)
+        got = cq.cq_decode_attn(lay, dev["q"], k, v, dev["k_text"], dev["v_text"], n_text, None, 0.0, None, ws)
+    finally:
+        cq.cq_bench_set_kernel_path(prev)
+    assert (ws[:B * n_q * (n + n_text) * 4] == 255).float().mean() > 0.05, "the logits went through memory"
+    ref = O.decode_attn(x["q"].numpy(), kq, vq, x["k_text"].numpy(), x["v_text"].numpy(), n_text, O.CALIB_NONE)
+    err = O.rel_l2(got.cpu().numpy().astype(np.float64), ref)
+    assert err <= H.REGRESSION_TOL, err
+
+
 # Whole-sequence keys, values token-wise or whole, rows that end inside a group of 128 tokens, on the fused kernel:
 # (B, Hq, Hkv, n_vis, n_text, bits, value axis); one token over a group, one short, inside a value tile's pad, and
 # enough rows or heads for one chunk, several chunks, a last chunk of one token
