@@ -10,15 +10,24 @@
 // kernels' logits pass where it takes the layout, else the shape-agnostic one; the exact keys pass
 // as a 16-bit tail), the weights in fp64.
 //
-// The grid costs n1 + n2 + 2 exponentials per token and pass (4 where the taus are evenly spaced
-// from 0) instead of one per pair: with u = (s - gamma) / (delta - gamma),  g(s) = s + tau1 (u - 1) -
-// tau2 u,  so a weight is e^s e^(tau1 (u - 1)) e^(-tau2 u).  Blocks of 4 x 4 pairs stay in registers;
-// a row is cut into chunks so that every CU works, and two passes (normalizers, then squared
-// differences) meet in memory.
+// The grid costs n1 + n2 + 2 exponentials per token (4 where the taus are evenly spaced from 0) instead of
+// one per pair: with u = (s - gamma) / (delta - gamma),  g(s) = s + tau1 (u - 1) - tau2 u,  so a weight is
+// e^s e^(tau1 (u - 1)) e^(-tau2 u).  Blocks of 4 x 4 pairs stay in registers; a row is cut into chunks so
+// that every CU works.
+//
+// One pass over the tokens.  With w and q the weights of the calibrated and of the exact keys before they are
+// normalized, Z and Q their sums, the squared differences of the normalized ones need Z and Q, which are
+// known only behind the last token.  But for any constant r of a row and pair, d = w - r q and S = sum d,
+//     sum (w / Z - q / Q)^2 = (sum d^2 - 2 (S / Q) sum d q + (S / Q)^2 sum q^2) / Z^2,   Z = r Q + S,
+// so three sums per pair and two per row, formed with Z and Q unknown, do.  r is the largest w (the largest q is
+// 1): d is then as small as the difference that is asked for, equal weights give exactly 0, and
+// what cancels in the bracket is the part of d along q only.
 // Bound: fp64 arithmetic.  128 query rows x 3456 tokens, 4 x 4 grid: 416 us at first (one exponential
 // per pair, a block per row), 55.6 us with factors and chunks, 42.8 with the sums folded by lane swaps,
 // 32.9 with even spacing and the normalizers loaded eight at a time, 29.4 with both sets of logits in
-// one launch; against 64 bits 2e-7 -> 3e-8.
+// one launch (28.6 on another box), 20.2 in one pass instead of two (normalizers, then squared differences; 7.3 and
+// 9.4 us of kernels).  Other sizes, two passes / one: 1 row x 256 + 8 tokens 14.1 / 10.8, 4096 x 2048 + 64 227 / 175.
+// Against 64 bits 1e-8 to 8e-7, the same with one pass as with two: that is what the fp32 logits leave.
 #include <cfloat>
 #include <cmath>
 
@@ -48,8 +57,9 @@ struct TauArgs {
   const float* logits_x;                 // [rows][n_vis]: exact visual
   const float* minmax_q;                 // [rows][ca + ct][2]
   const float* minmax_x;                 // [rows][cx][2]
-  double* z_part;                        // [rows][n_chunks][n1 n2 + 1] normalizers, the last one exact
-  double* err_part;                      // [rows][n_chunks][n1 n2] squared differences
+  size_t n_parts;                        // rows * n_chunks
+  double* sums;                          // [3 n1 n2 + 2][rows][n_chunks]: S, sum d^2, sum d q per pair, then Q, sum q^2
+  double* ratio;                         // [n1 n2][rows]: r;  one chunk per row: [rows][n1 n2] squared differences
 };
 
 // sum over each row of 16 lanes, every lane of the row gets it
@@ -102,9 +112,20 @@ __device__ inline Row row_extrema(const TauArgs& a, size_t row) {
   return r;
 }
 
+// The largest calibrated logit of a pair: g is monotone, so an end of [gamma, delta] or a text token has it.
+__device__ inline double largest_logit(const Row& r, double tau1, double tau2) {
+  const double at_lo = r.gamma - tau1;
+  const double at_hi = r.width == 0.0 ? at_lo : r.gamma + r.width - tau2;
+  return fmax(fmax(at_lo, at_hi), r.top_text);
+}
+__device__ inline double lane_value(double v, int lane) {      // wave-uniform copy of one lane's value
+  const v2i x = __builtin_bit_cast(v2i, v);
+  return __builtin_bit_cast(double, (v2i){__builtin_amdgcn_readlane(x[0], lane), __builtin_amdgcn_readlane(x[1], lane)});
+}
+
 // Weights (up to a factor per pair) of one token for the pairs (i0 + i, j0 + j), and of the exact keys.
 // With factors: common reference m0 for all pairs.  Else pair by pair, with each pair's own reference,
-// the largest calibrated logit (g is monotone: an end of [gamma, delta] or a text token).
+// the largest calibrated logit.
 template <int MODE>
 __device__ inline void token_weights(const TauArgs& a, const Row& r, const double (&t1)[kGrid],
                                      const double (&t2)[kGrid], double s, double sx, bool vis,
@@ -139,116 +160,140 @@ __device__ inline void token_weights(const TauArgs& a, const Row& r, const doubl
 #pragma unroll
     for (int i = 0; i < kGrid; ++i)
 #pragma unroll
-      for (int j = 0; j < kGrid; ++j) {
-        const double at_lo = r.gamma - t1[i];
-        const double at_hi = r.width == 0.0 ? at_lo : r.gamma + r.width - t2[j];
-        const double m = fmax(fmax(at_lo, at_hi), r.top_text);
-        w[i * kGrid + j] = exp((vis ? s + t1[i] * (u - 1.0) - t2[j] * u : s) - m);
-      }
+      for (int j = 0; j < kGrid; ++j)
+        w[i * kGrid + j] = exp((vis ? s + t1[i] * (u - 1.0) - t2[j] * u : s) - largest_logit(r, t1[i], t2[j]));
   }
 }
 
-// grid.x = rows * n_chunks.  ERR = false: normalizers of the chunk; true: squared differences.
-template <int MODE, bool ERR>
+// (sum d^2 - 2 (S / Q) sum d q + (S / Q)^2 sum q^2) / Z^2, see above; never below 0 by rounding, NaN stays NaN
+__device__ inline double squared_difference(double S, double dd, double dq, double r, double Q, double qq) {
+  const double Z = fma(r, Q, S), f = S / Q;
+  const double v = fma(f, fma(f, qq, -2.0 * dq), dd) / (Z * Z);
+  return v < 0.0 ? 0.0 : v;
+}
+
+// grid.x = rows * n_chunks.  ONE: a row is one chunk, whose block goes on to the squared differences.
+template <int MODE, bool ONE>
 __global__ void __launch_bounds__(kThreads)
 tau_grid_kernel(const TauArgs a) {
-  __shared__ double red[kThreads / 64][kPairs + 1];
-  __shared__ double inv_z[kMaxTauPairs + 1];
-  const size_t row = blockIdx.x / (unsigned)a.n_chunks;
-  const int chunk = (int)(blockIdx.x - row * a.n_chunks);
+  constexpr int kSums = 3 * kPairs + 2;
+  __shared__ double red[kThreads / 64][kSums + 2];
+  const size_t row = ONE ? blockIdx.x : blockIdx.x / (unsigned)a.n_chunks;
+  const int chunk = ONE ? 0 : (int)(blockIdx.x - row * a.n_chunks);
   const int n_all = a.n_vis + a.n_text, n_pairs = a.n1 * a.n2;
   const int c0 = chunk * a.chunk_tokens, c1 = min(c0 + a.chunk_tokens, n_all);
   const float* sq = a.logits_q + row * (size_t)n_all;
   const float* sx = a.logits_x + row * (size_t)a.n_vis;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  auto logit_of = [&](int t) { return sq[min(t, n_all - 1)]; };
+  auto exact_of = [&](int t) { return sx[min(t, a.n_vis - 1)]; };       // (of a text token: not used)
+  const int t_first = c0 + (int)threadIdx.x;
+  const float s_first = logit_of(t_first), x_first = exact_of(t_first); // asked for before the extrema are known
   const Row r = row_extrema(a, row);
-  if constexpr (ERR) {
-    for (int p = threadIdx.x; p <= n_pairs; p += kThreads) {
-      double z = 0.0;
-      const double* zp = a.z_part + row * a.n_chunks * (size_t)(n_pairs + 1) + p;
-      for (int c0 = 0; c0 < a.n_chunks; c0 += 8) {           // eight loads in flight
-        double v[8];
-#pragma unroll
-        for (int c = 0; c < 8; ++c) v[c] = zp[(size_t)min(c0 + c, a.n_chunks - 1) * (n_pairs + 1)];
-#pragma unroll
-        for (int c = 0; c < 8; ++c) z += c0 + c < a.n_chunks ? v[c] : 0.0;
-      }
-      inv_z[p] = 1.0 / z;
-    }
-    __syncthreads();
-  }
   for (int i0 = 0; i0 < a.n1; i0 += kGrid)
     for (int j0 = 0; j0 < a.n2; j0 += kGrid) {
-      double t1[kGrid], t2[kGrid], acc[kPairs + 1], iz[kPairs];
+      double t1[kGrid], t2[kGrid], S[kPairs], dd[kPairs], dq[kPairs], Q = 0.0, qq = 0.0;
 #pragma unroll
       for (int i = 0; i < kGrid; ++i) {        // beyond the grid: its last value again, not stored
         t1[i] = a.tau1[min(i0 + i, a.n1 - 1)];
         t2[i] = a.tau2[min(j0 + i, a.n2 - 1)];
       }
 #pragma unroll
-      for (int p = 0; p <= kPairs; ++p) acc[p] = 0.0;
-      double iz_ref = 0.0;
-      if constexpr (ERR) {
-#pragma unroll
-        for (int p = 0; p < kPairs; ++p)
-          iz[p] = inv_z[min(i0 + p / kGrid, a.n1 - 1) * a.n2 + min(j0 + p % kGrid, a.n2 - 1)];
-        iz_ref = inv_z[n_pairs];
+      for (int p = 0; p < kPairs; ++p) S[p] = dd[p] = dq[p] = 0.0;
+      // the largest weight of pair lane % 16, then of every pair in scalar registers
+      double own_ratio = 1.0, ratio[kPairs];
+      if constexpr (MODE != kPairwise) {
+        const double x1 = a.tau1[min(i0 + ((lane >> 2) & 3), a.n1 - 1)], x2 = a.tau2[min(j0 + (lane & 3), a.n2 - 1)];
+        own_ratio = exp(largest_logit(r, x1, x2) - r.m0);
       }
-      for (int t = c0 + (int)threadIdx.x; t < c1; t += kThreads) {
+#pragma unroll
+      for (int p = 0; p < kPairs; ++p) ratio[p] = MODE == kPairwise ? 1.0 : lane_value(own_ratio, p);
+      float s_next = s_first, x_next = x_first;
+      for (int t = t_first; t < c1; t += kThreads) {
         const bool vis = t < a.n_vis;
-        const double s = sq[t], x = vis ? sx[t] : sq[t];
-        double w[kPairs], ref;
-        token_weights<MODE>(a, r, t1, t2, s, x, vis, w, ref);
-        if constexpr (ERR) {
-          const double q = ref * iz_ref;
+        const double s = s_next, x = vis ? x_next : s_next;
+        s_next = logit_of(t + kThreads);
+        x_next = exact_of(t + kThreads);
+        double w[kPairs], q;
+        token_weights<MODE>(a, r, t1, t2, s, x, vis, w, q);
+        Q += q;
+        qq = fma(q, q, qq);
 #pragma unroll
-          for (int p = 0; p < kPairs; ++p) {
-            const double d = w[p] * iz[p] - q;
-            acc[p] += d * d;
-          }
-        } else {
-#pragma unroll
-          for (int p = 0; p < kPairs; ++p) acc[p] += w[p];
-          acc[kPairs] += ref;
+        for (int p = 0; p < kPairs; ++p) {
+          const double d = fma(-ratio[p], q, w[p]);
+          S[p] += d;
+          dd[p] = fma(d, d, dd[p]);
+          dq[p] = fma(d, q, dq[p]);
         }
       }
-      const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
       __syncthreads();                         // the sums of the block of pairs before this one are out
       // four sums at a time: paired lane swaps leave one per row of 16 lanes (17 sums through LDS
       // exchanges took a third of the kernel)
+      auto fold = [&](int at, double v0, double v1, double v2, double v3) {
+        const double v = row_total(fold_rows(fold_halves(v0, v2), fold_halves(v1, v3)));
+        if ((lane & 15) == 0) red[wave][at + (lane >> 4)] = v;
+      };
 #pragma unroll
       for (int p = 0; p < kPairs; p += 4) {
-        const double v = row_total(fold_rows(fold_halves(acc[p], acc[p + 2]), fold_halves(acc[p + 1], acc[p + 3])));
-        if ((lane & 15) == 0) red[wave][p + (lane >> 4)] = v;
+        fold(p, S[p], S[p + 1], S[p + 2], S[p + 3]);
+        fold(kPairs + p, dd[p], dd[p + 1], dd[p + 2], dd[p + 3]);
+        fold(2 * kPairs + p, dq[p], dq[p + 1], dq[p + 2], dq[p + 3]);
       }
-      if constexpr (!ERR) {
-        const double v = wave_total(acc[kPairs]);
-        if (lane == 0) red[wave][kPairs] = v;
-      }
+      fold(3 * kPairs, Q, qq, 0.0, 0.0);
       __syncthreads();
-      const int p = threadIdx.x;
-      if (p <= (ERR ? kPairs - 1 : kPairs)) {
+      auto total = [&](int e) {
         double v = 0.0;
 #pragma unroll
-        for (int wv = 0; wv < kThreads / 64; ++wv) v += red[wv][p];
-        const int i = i0 + p / kGrid, j = j0 + p % kGrid;
+        for (int wv = 0; wv < kThreads / 64; ++wv) v += red[wv][e];
+        return v;
+      };
+      const int e = threadIdx.x, p = e % kPairs, i = i0 + p / kGrid, j = j0 + p % kGrid;
+      const bool exists = i < a.n1 && j < a.n2;
+      if constexpr (ONE) {
+        if (e < kPairs && exists)
+          a.ratio[row * n_pairs + i * a.n2 + j] = squared_difference(total(p), total(kPairs + p), total(2 * kPairs + p), own_ratio,
+                                                                     total(3 * kPairs), total(3 * kPairs + 1));
+      } else {
         const size_t at = row * a.n_chunks + chunk;
-        if (p == kPairs) {
-          a.z_part[at * (n_pairs + 1) + n_pairs] = v;
-        } else if (i < a.n1 && j < a.n2) {
-          if constexpr (ERR) a.err_part[at * n_pairs + i * a.n2 + j] = v;
-          else a.z_part[at * (n_pairs + 1) + i * a.n2 + j] = v;
+        if (e < 3 * kPairs) {
+          if (exists) a.sums[((size_t)(e / kPairs) * n_pairs + i * a.n2 + j) * a.n_parts + at] = total(e);
+          if (e < kPairs && exists && chunk == 0) a.ratio[(size_t)(i * a.n2 + j) * (a.n_parts / a.n_chunks) + row] = own_ratio;
+        } else if (e < kSums) {
+          a.sums[((size_t)3 * n_pairs + (e - 3 * kPairs)) * a.n_parts + at] = total(e);
         }
       }
     }
 }
 
-// One block per pair: the squared differences over all rows and chunks, in a fixed order.
+// One block per pair: the squared differences of all rows, in a fixed order.
+template <bool ONE>
 __global__ void __launch_bounds__(kThreads)
-tau_reduce_kernel(size_t n_parts, int n_pairs, double n_terms, const double* __restrict__ err_part,
-                  double* __restrict__ mse_out) {
+tau_reduce_kernel(const TauArgs a, size_t rows, double n_terms, double* __restrict__ mse_out) {
   __shared__ double red[kThreads / 64];
+  const int n_pairs = a.n1 * a.n2, pair = blockIdx.x;
   double acc = 0.0;
-  for (size_t r = threadIdx.x; r < n_parts; r += kThreads) acc += err_part[r * n_pairs + blockIdx.x];
+  for (size_t r = threadIdx.x; r < rows; r += kThreads) {
+    if constexpr (ONE) {
+      acc += a.ratio[r * n_pairs + pair];
+    } else {
+      const size_t of[5] = {(size_t)pair, (size_t)n_pairs + pair, 2 * (size_t)n_pairs + pair, 3 * (size_t)n_pairs,
+                            3 * (size_t)n_pairs + 1};
+      double sum[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+      const double ratio = a.ratio[(size_t)pair * rows + r];
+      for (int c0 = 0; c0 < a.n_chunks; c0 += 4) {             // twenty loads in flight
+        double v[5][4];
+#pragma unroll
+        for (int k = 0; k < 5; ++k)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) v[k][c] = a.sums[of[k] * a.n_parts + r * a.n_chunks + min(c0 + c, a.n_chunks - 1)];
+#pragma unroll
+        for (int k = 0; k < 5; ++k)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) sum[k] += c0 + c < a.n_chunks ? v[k][c] : 0.0;
+      }
+      acc += squared_difference(sum[0], sum[1], sum[2], ratio, sum[3], sum[4]);
+    }
+  }
   acc = wave_total(acc);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
   __syncthreads();
@@ -256,7 +301,7 @@ tau_reduce_kernel(size_t n_parts, int n_pairs, double n_terms, const double* __r
     double v = 0.0;
 #pragma unroll
     for (int w = 0; w < kThreads / 64; ++w) v += red[w];
-    mse_out[blockIdx.x] = v / n_terms;
+    mse_out[pair] = v / n_terms;
   }
 }
 
@@ -307,8 +352,9 @@ hipError_t launch_tau_search(const DecodeShape& s, const void* q, const void* k_
   a.chunk_tokens = ceil_div(ceil_div(n_all, kThreads), wl.n_chunks) * kThreads;
   a.logits_q = logits_q; a.logits_x = logits_x;
   a.minmax_q = minmax_q; a.minmax_x = minmax_x;
-  a.z_part = reinterpret_cast<double*>(workspace + wl.z_part);
-  a.err_part = reinterpret_cast<double*>(workspace + wl.err_part);
+  a.n_parts = rows * wl.n_chunks;
+  a.ratio = reinterpret_cast<double*>(workspace + wl.sums);
+  a.sums = a.ratio + rows * n_pairs;
   const dim3 grid((unsigned)(rows * wl.n_chunks)), block(kThreads);
   auto spacing = [](const float* t, int n, double* step) {     // whether t is evenly spaced, exactly
     *step = n > 1 ? (double)t[1] - (double)t[0] : 0.0;
@@ -318,18 +364,16 @@ hipError_t launch_tau_search(const DecodeShape& s, const void* q, const void* k_
   };
   const bool even = spacing(tau1, n_tau1, &a.step1) && spacing(tau2, n_tau2, &a.step2);
   const int mode = !factored ? kPairwise : even ? kEven : kFactors;
-  if (mode == kEven) tau_grid_kernel<kEven, false><<<grid, block, 0, stream>>>(a);
-  else if (mode == kFactors) tau_grid_kernel<kFactors, false><<<grid, block, 0, stream>>>(a);
-  else tau_grid_kernel<kPairwise, false><<<grid, block, 0, stream>>>(a);
-  hipError_t e = hipGetLastError();
+  using GridKernel = void (*)(const TauArgs);
+  static const GridKernel kern[3][2] = {{tau_grid_kernel<kPairwise, false>, tau_grid_kernel<kPairwise, true>},
+                                        {tau_grid_kernel<kFactors, false>, tau_grid_kernel<kFactors, true>},
+                                        {tau_grid_kernel<kEven, false>, tau_grid_kernel<kEven, true>}};
+  const bool one = wl.n_chunks == 1;
+  kern[mode][one]<<<grid, block, 0, stream>>>(a);
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (mode == kEven) tau_grid_kernel<kEven, true><<<grid, block, 0, stream>>>(a);
-  else if (mode == kFactors) tau_grid_kernel<kFactors, true><<<grid, block, 0, stream>>>(a);
-  else tau_grid_kernel<kPairwise, true><<<grid, block, 0, stream>>>(a);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  tau_reduce_kernel<<<dim3((unsigned)n_pairs), block, 0, stream>>>(
-      rows * wl.n_chunks, n_pairs, (double)n_all * (double)rows, a.err_part, mse_out);
+  (one ? tau_reduce_kernel<true> : tau_reduce_kernel<false>)<<<dim3((unsigned)n_pairs), block, 0, stream>>>(
+      a, rows, (double)n_all * (double)rows, mse_out);
   return hipGetLastError();
 }
 

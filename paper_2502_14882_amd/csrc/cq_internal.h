@@ -83,9 +83,8 @@ struct TauWorkspace {
   size_t logits_x;   // [B*Hq][n_vis]           logits on the exact 16-bit keys
   size_t minmax_q;   // [B*Hq][chunks of n_vis + chunks of n_text][2]
   size_t minmax_x;   // [B*Hq][chunks of n_vis][2]
-  size_t z_part;     // [B*Hq][n_chunks][n_pairs + 1] doubles
-  size_t err_part;   // [B*Hq][n_chunks][n_pairs] doubles
-  int n_chunks;      // chunks per query row of the grid kernels
+  size_t sums;       // doubles: [n_pairs][B*Hq] and, with several chunks, [3 n_pairs + 2][B*Hq][n_chunks]
+  int n_chunks;      // chunks per query row of the grid kernel
   size_t total_bytes;
   size_t reserve_bytes;   // the most that a tail of up to n_text tokens needs (never falls with n_text)
 };
@@ -97,23 +96,26 @@ inline TauWorkspace tau_workspace_layout(int B, int Hq, int n_vis, int n_text, i
   const int nvc = most(ceil_div(n_vis, kVisChunk)), ntc = most(ceil_div(n_text, kTextChunk));
   const int nxc = most(ceil_div(n_vis, kTextChunk));
   const size_t rows = (size_t)B * (size_t)Hq;
-  // about four blocks per CU, each of them whole rounds of one token per thread
+  // About four blocks per CU, each of them whole rounds of one token per thread, have a share of scratch per
+  // row; the grid kernel takes as many chunks as their sums fit it.
   const int want = (int)((1024 + rows - 1) / rows), rounds = ceil_div(n_vis + n_text, 256);
-  w.n_chunks = rounds > 0 ? ceil_div(rounds, ceil_div(rounds, want)) : 1;
+  const int shares = rounds > 0 ? ceil_div(rounds, ceil_div(rounds, want)) : 1;
+  const int fit = (shares * (2 * n_pairs + 1) - n_pairs) / (3 * n_pairs + 2);
+  w.n_chunks = fit > 1 ? ceil_div(rounds, ceil_div(rounds, fit)) : 1;
   auto align64 = [](size_t x) { return (x + 63) / 64 * 64; };
   w.logits_q = 0;
   w.logits_x = align64(w.logits_q + rows * ((size_t)n_vis + (size_t)n_text));
   w.minmax_q = align64(w.logits_x + rows * (size_t)n_vis);
   w.minmax_x = align64(w.minmax_q + rows * (size_t)(nvc + ntc) * 2);
-  w.z_part = align64(w.minmax_x + rows * (size_t)nxc * 2);
-  auto lay_out = [&](int n_chunks) {
-    w.err_part = align64(w.z_part + rows * (size_t)n_chunks * (size_t)(n_pairs + 1) * 2);
-    const size_t end = align64(w.err_part + rows * (size_t)n_chunks * (size_t)n_pairs * 2);
+  w.sums = align64(w.minmax_x + rows * (size_t)nxc * 2);
+  auto lay_out = [&](int n) {
+    const size_t half = align64(w.sums + rows * (size_t)n * (size_t)(n_pairs + 1) * 2);
+    const size_t end = align64(half + rows * (size_t)n * (size_t)n_pairs * 2);
     return (end * sizeof(float) + 255) / 256 * 256;
   };
   // whole rounds per chunk: one round more can mean fewer chunks, but never more than these
   w.reserve_bytes = lay_out(rounds > want ? want : rounds > 0 ? rounds : 1);
-  w.total_bytes = lay_out(w.n_chunks);
+  w.total_bytes = lay_out(shares);
   return w;
 }
 hipError_t launch_tau_search(const DecodeShape& s, const void* q, const void* k_exact,
