@@ -90,33 +90,41 @@ __device__ inline uint16_t threshold_bits(double alpha, double D, int k, int L) 
 
 __device__ inline uint16_t canonical_zero(uint16_t bits) { return (bits & 0x7fffu) == 0 ? (uint16_t)0 : bits; }
 
-// sign bits of (t - x) for 8 channels -> 0x80 per channel, channels 0..3 in xa, 4..7 in xb
-__device__ inline void sign_bytes(const v8h& t, const v8h& x, uint32_t& xa, uint32_t& xb) {
-  const v8h d = t - x;
-  const v4u u = __builtin_bit_cast(v4u, d);
-  xa = __builtin_amdgcn_perm(u[1], u[0], 0x07050301u) & 0x80808080u;
-  xb = __builtin_amdgcn_perm(u[3], u[2], 0x07050301u) & 0x80808080u;
+// t - x for 8 channels, two to a register: its sign bits say x > t.  (Written out because the compiler takes a packed
+// subtraction apart, into two subtractions and a third instruction that joins them.)
+__device__ inline v4u differences(const v8h& t, const v8h& x) {
+  const v4u a = __builtin_bit_cast(v4u, t), b = __builtin_bit_cast(v4u, x);
+  v4u d;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    unsigned v;
+    asm("v_pk_add_f16 %0, %1, %2 neg_lo:[0,1] neg_hi:[0,1]" : "=v"(v) : "v"(a[r]), "v"(b[r]));
+    d[r] = v;
+  }
+  return d;
 }
+// the sign bits of four 16-bit numbers as bytes, 0 or -1, first number in the low byte
+__device__ inline int sign_bytes(uint32_t d01, uint32_t d23) { return (int)__builtin_amdgcn_perm(d23, d01, 0x0b0a0908u); }
 
-// code bits of one octet of one token: 8 bits (b = 1) or 16 bits (b = 2), first channel highest
+// Code bits of one octet of one token: 8 bits (b = 1) or 16 bits (b = 2), first channel highest.  Four signs at a
+// time become bits by a product of bytes whose other factors are minus the powers of two they stand for: 8 and 25
+// instructions for the octet (19 and 56 with the differences as the compiler forms them, masks and unsigned products).
+// us, before / now, keys and values: 64 rows x 3003 tokens, 2 bits, whole-sequence groups 36.0 / 32.6, 1 bit 27.7 / 26.2;
+// 8 rows x 3328, 2 bits, groups of 128 7.8 / 7.2; 128 rows x 3328, 2 bits, groups of 32 50.3 / 45.8 (large calls of one bit are
+// HBM-bound: the same).
 template <int BITS>
 __device__ inline uint32_t octet_codes(const v8h& x, const v8h* thr) {
   if constexpr (BITS == 1) {
-    uint32_t xa, xb;
-    sign_bytes(thr[0], x, xa, xb);
-    const uint32_t s = __builtin_amdgcn_udot4(xa, 0x10204080u, 0u, false);
-    return __builtin_amdgcn_udot4(xb, 0x01020408u, s, false) >> 7;
+    const v4u d = differences(thr[0], x);
+    const int s = __builtin_amdgcn_sdot4(sign_bytes(d[0], d[1]), (int)0xf0e0c080u, 0, false);
+    return (uint32_t)__builtin_amdgcn_sdot4(sign_bytes(d[2], d[3]), (int)0xfffefcf8u, s, false);
   } else {
-    uint32_t a1, b1, a2, b2, a3, b3;
-    sign_bytes(thr[0], x, a1, b1);
-    sign_bytes(thr[1], x, a2, b2);
-    sign_bytes(thr[2], x, a3, b3);
-    const uint32_t la = a1 ^ a2 ^ a3, lb = b1 ^ b2 ^ b3;     // low code bit; high bit is [x > t2]
-    uint32_t up = __builtin_amdgcn_udot4(a2, 0x02082080u, 0u, false);
-    up = __builtin_amdgcn_udot4(la, 0x01041040u, up, false);
-    uint32_t lo = __builtin_amdgcn_udot4(b2, 0x02082080u, 0u, false);
-    lo = __builtin_amdgcn_udot4(lb, 0x01041040u, lo, false);
-    return ((up >> 7) << 8) | (lo >> 7);
+    const v4u d2 = differences(thr[1], x);                   // high code bit: x > t2
+    const v4u dl = differences(thr[0], x) ^ d2 ^ differences(thr[2], x);      // low one
+    int s = __builtin_amdgcn_sdot4(sign_bytes(d2[0], d2[1]), (int)0xfef8e080u, 0, false);
+    s = __builtin_amdgcn_sdot4(sign_bytes(dl[0], dl[1]), (int)0xfffcf0c0u, s, false);
+    s = __builtin_amdgcn_sdot4(sign_bytes(d2[2], d2[3]), (int)0xfef8e080u, s << 8, false);
+    return (uint32_t)__builtin_amdgcn_sdot4(sign_bytes(dl[2], dl[3]), (int)0xfffcf0c0u, s, false);
   }
 }
 
