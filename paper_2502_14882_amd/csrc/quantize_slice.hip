@@ -63,24 +63,7 @@ quantize_slice_kernel(const SliceArgs first, const SliceArgs second, int n_first
     mn = __builtin_elementwise_min(mn, x[i]);
     mx = __builtin_elementwise_max(mx, x[i]);
   }
-  v4u mnu = __builtin_bit_cast(v4u, mn), mxu = __builtin_bit_cast(v4u, mx);
-#pragma unroll
-  for (int o = LANES; o <= 32; o <<= 1) {
-    v4u on, ox;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      on[r] = __shfl_xor(mnu[r], o);
-      ox[r] = __shfl_xor(mxu[r], o);
-    }
-    mn = __builtin_elementwise_min(mn, __builtin_bit_cast(v8h, on));
-    mx = __builtin_elementwise_max(mx, __builtin_bit_cast(v8h, ox));
-    mnu = __builtin_bit_cast(v4u, mn);
-    mxu = __builtin_bit_cast(v4u, mx);
-  }
-  if (lane < LANES) {
-    *reinterpret_cast<v8h*>(&s_part[0][wave][8 * oct]) = mn;
-    *reinterpret_cast<v8h*>(&s_part[1][wave][8 * oct]) = mx;
-  }
+  store_extrema<LANES>(mn, mx, lane, s_part[0][wave], s_part[1][wave]);
   __syncthreads();
   // ---- 2. stored parameters; a thread per (threshold, channel)
   constexpr int kEach = kWide ? 1 : L;

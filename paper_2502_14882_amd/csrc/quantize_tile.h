@@ -83,12 +83,68 @@ __device__ inline uint16_t threshold_bits(double alpha, double D, int k, int L) 
   // candidate: the real-valued boundary, good to an fp16 step (the reciprocal of 2L is a compile-time
   // constant at every call site; the loops below make the result exact whatever the candidate)
   uint16_t t = __half_as_ushort(__float2half_rn((float)(alpha + rhs * (1.0 / twoL))));
-  for (int it = 0; it < 4 && pred(t); ++it) t = h_prev(t);
-  for (int it = 0; it < 4 && !pred(h_next(t)); ++it) t = h_next(t);
+  // (its neighbours are tried along with it, not one behind the other, each a chain of fp64 instructions and a branch)
+  const uint16_t below = h_prev(t);
+  const bool over = pred(t), over_below = pred(below), over_above = pred(h_next(t));
+  if (over ? over_below : !over_above) {     // more than a step off
+    for (int it = 0; it < 4 && pred(t); ++it) t = h_prev(t);
+    for (int it = 0; it < 4 && !pred(h_next(t)); ++it) t = h_next(t);
+  } else if (over) {
+    t = below;
+  }
   return t == 0x8000u ? (uint16_t)0 : t;     // -0 would break the sign test against +0
 }
 
 __device__ inline uint16_t canonical_zero(uint16_t bits) { return (bits & 0x7fffu) == 0 ? (uint16_t)0 : bits; }
+
+// Extrema over the tokens of a wave whose lanes hold 8 channels each, STRIDE lanes to a token: lo[c], hi[c] of the
+// wave's channels.  In the vector unit: lane rotations within a row of 16 lanes, then paired swaps of registers
+// over halves and rows of the wave, each of which leaves half as many registers.  With LDS exchanges, eight registers at each
+// distance, and the threshold's candidates one behind the other, 64 rows x 3003 tokens, 2 bits took 32.6 us, now 31.5; 80 x
+// 3003 46.1 / 44.2; 64 rows x 2500 tokens of 256 channels, 1 bit 48.4 / 45.9.
+template <int STRIDE>
+__device__ inline void store_extrema(v8h mn, v8h mx, int lane, _Float16* lo, _Float16* hi) {
+  v4u a = __builtin_bit_cast(v4u, mn), b = __builtin_bit_cast(v4u, mx);
+  auto least = [](uint32_t x, uint32_t y) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(v2h, x), __builtin_bit_cast(v2h, y)));
+  };
+  auto most = [](uint32_t x, uint32_t y) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(v2h, x), __builtin_bit_cast(v2h, y)));
+  };
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    if constexpr (STRIDE <= 4) {
+      a[r] = least(a[r], other_lane<0x124>(a[r]));           // row_ror 4
+      b[r] = most(b[r], other_lane<0x124>(b[r]));
+    }
+    if constexpr (STRIDE <= 8) {
+      a[r] = least(a[r], other_lane<0x128>(a[r]));           // row_ror 8
+      b[r] = most(b[r], other_lane<0x128>(b[r]));
+    }
+  }
+  // registers 0, 1 of the whole wave in lanes 0-31, registers 2, 3 in lanes 32-63
+#pragma unroll
+  for (int r = 0; r < 2; ++r) {
+    const auto x = __builtin_amdgcn_permlane32_swap(a[r], a[r + 2], false, false);
+    const auto y = __builtin_amdgcn_permlane32_swap(b[r], b[r + 2], false, false);
+    a[r] = least(x[0], x[1]);
+    b[r] = most(y[0], y[1]);
+  }
+  const int oct = lane & (STRIDE - 1);
+  if constexpr (STRIDE == 32) {
+    const int at = 8 * oct + 4 * (lane >> 5);
+    *reinterpret_cast<v2u*>(lo + at) = (v2u){a[0], a[1]};
+    *reinterpret_cast<v2u*>(hi + at) = (v2u){b[0], b[1]};
+  } else {                                                   // register r in the r-th row of lanes
+    const auto x = __builtin_amdgcn_permlane16_swap(a[0], a[1], false, false);
+    const auto y = __builtin_amdgcn_permlane16_swap(b[0], b[1], false, false);
+    if ((lane & 15) < STRIDE) {
+      const int at = 8 * oct + 2 * (lane >> 4);
+      *reinterpret_cast<uint32_t*>(lo + at) = least(x[0], x[1]);
+      *reinterpret_cast<uint32_t*>(hi + at) = most(y[0], y[1]);
+    }
+  }
+}
 
 // t - x for 8 channels, two to a register: its sign bits say x > t.  (Written out because the compiler takes a packed
 // subtraction apart, into two subtractions and a third instruction that joins them.)
@@ -231,24 +287,7 @@ row_extrema_kernel(const QArgs first, const QArgs second, unsigned n_first) {
       mx = __builtin_elementwise_max(mx, x[i]);
     }
   }
-  v4u mnu = __builtin_bit_cast(v4u, mn), mxu = __builtin_bit_cast(v4u, mx);
-#pragma unroll
-  for (int o = kOct; o <= 32; o <<= 1) {
-    v4u on, ox;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      on[r] = __shfl_xor(mnu[r], o);
-      ox[r] = __shfl_xor(mxu[r], o);
-    }
-    mn = __builtin_elementwise_min(mn, __builtin_bit_cast(v8h, on));
-    mx = __builtin_elementwise_max(mx, __builtin_bit_cast(v8h, ox));
-    mnu = __builtin_bit_cast(v4u, mn);
-    mxu = __builtin_bit_cast(v4u, mx);
-  }
-  if (ts == 0) {
-    *reinterpret_cast<v8h*>(&s_part[0][wave][c8 * 8]) = mn;
-    *reinterpret_cast<v8h*>(&s_part[1][wave][c8 * 8]) = mx;
-  }
+  store_extrema<kOct>(mn, mx, lane, s_part[0][wave], s_part[1][wave]);
   __syncthreads();
   if (tid < D) {
     _Float16 lo = s_part[0][0][tid], hi = s_part[1][0][tid];
@@ -291,6 +330,7 @@ __device__ __forceinline__ void quantize_tile(const QArgs& a, const unsigned blo
   constexpr int L = Mem::L, kG = Mem::kG, NG = Mem::NG, kPerTok = Mem::kPerTok;
   constexpr int kWords = D * BITS / 32;                   // words per token
   constexpr bool kWhole = GROUP == 0, kWide = Mem::kWide;
+  constexpr int kParts = BITS == 2 ? 2 : 1;               // threads per group slot in step 2, three thresholds shared: 8 rows x 3328, 7.1 / 6.7 us
   static_assert(!kWhole || AXIS == CQ_AXIS_CHANNEL, "long groups are channel-wise");
   auto& s_part = sm.s_part;
   auto& s_stat = sm.s_stat;
@@ -377,29 +417,12 @@ __device__ __forceinline__ void quantize_tile(const QArgs& a, const unsigned blo
       mn = __builtin_elementwise_min(mn, x[i]);
       mx = __builtin_elementwise_max(mx, x[i]);
     }
-    v4u mnu = __builtin_bit_cast(v4u, mn), mxu = __builtin_bit_cast(v4u, mx);
-#pragma unroll
-    for (int o = kOct; o <= 32; o <<= 1) {
-      v4u on, ox;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        on[r] = __shfl_xor(mnu[r], o);
-        ox[r] = __shfl_xor(mxu[r], o);
-      }
-      mn = __builtin_elementwise_min(mn, __builtin_bit_cast(v8h, on));
-      mx = __builtin_elementwise_max(mx, __builtin_bit_cast(v8h, ox));
-      mnu = __builtin_bit_cast(v4u, mn);
-      mxu = __builtin_bit_cast(v4u, mx);
-    }
-    if (ts == 0) {
-      *reinterpret_cast<v8h*>(&s_part[0][wave][c8 * 8]) = mn;
-      *reinterpret_cast<v8h*>(&s_part[1][wave][c8 * 8]) = mx;
-    }
+    store_extrema<kOct>(mn, mx, lane, s_part[0][wave], s_part[1][wave]);
     __syncthreads();
-    // ---- 2. one thread per (group, channel): stored parameters and thresholds
+    // ---- 2. one thread per (group, channel), two where there are three thresholds: stored parameters and thresholds
     constexpr int kWavesPerGroup = GROUP / 32;
-    for (int item = tid; item < NG * D; item += kThreads) {
-      const int g = item / D, c = item % D;
+    for (int at = tid; at < kParts * NG * D; at += kThreads) {
+      const int part = at / (NG * D), item = at % (NG * D), g = item / D, c = item % D;
       _Float16 lo = s_part[0][g * kWavesPerGroup][c], hi = s_part[1][g * kWavesPerGroup][c];
 #pragma unroll
       for (int w = 1; w < kWavesPerGroup; ++w) {
@@ -409,7 +432,7 @@ __device__ __forceinline__ void quantize_tile(const QArgs& a, const unsigned blo
       const uint16_t mbits = canonical_zero(__builtin_bit_cast(uint16_t, lo));
       const double alpha = h_to_double(mbits);
       const double range = ((double)(float)hi - alpha) + 0.0;
-      if (g * GROUP < nt) {                    // a short last tile holds whole groups only
+      if (part == 0 && g * GROUP < nt) {       // a short last tile holds whole groups only
         const size_t meta = ((size_t)block * NG + g) * D + c;
         a.scale[meta] = (float)(range / (double)L);
         a.minv[meta] = mbits;
@@ -420,8 +443,9 @@ __device__ __forceinline__ void quantize_tile(const QArgs& a, const unsigned blo
       } else {
 #pragma unroll
         for (int k = 1; k <= L; ++k)
-          s_thr[(g * L + (k - 1)) * D + c] =
-              __builtin_bit_cast(_Float16, threshold_bits(alpha, range, k, L));
+          if (kParts == 1 || (k > 1) == (part == 1))
+            s_thr[(g * L + (k - 1)) * D + c] =
+                __builtin_bit_cast(_Float16, threshold_bits(alpha, range, k, L));
       }
     }
     __syncthreads();
@@ -501,13 +525,14 @@ __device__ __forceinline__ void quantize_tile(const QArgs& a, const unsigned blo
       }
     }
     __syncthreads();
-    // ---- 2. one thread per (token, channel group)
-    for (int item = tid; item < kTile * NG; item += kThreads) {
+    // ---- 2. one thread per (token, channel group), or two
+    for (int both = tid; both < kParts * kTile * NG; both += kThreads) {
+      const int part = both / (kTile * NG), item = both % (kTile * NG);
       const int at = item / NG * kPerTok + item % NG;
       const uint16_t mbits = canonical_zero(__builtin_bit_cast(uint16_t, s_stat[at][0]));
       const double alpha = h_to_double(mbits);
       const double range = ((double)(float)s_stat[at][1] - alpha) + 0.0;
-      if (item < nt * NG) {
+      if (part == 0 && item < nt * NG) {
         const size_t meta = tok0 * NG + item;
         a.scale[meta] = (float)(range / (double)L);
         a.minv[meta] = mbits;
@@ -518,7 +543,7 @@ __device__ __forceinline__ void quantize_tile(const QArgs& a, const unsigned blo
       } else {
 #pragma unroll
         for (int k = 1; k <= L; ++k)
-          s_thr[at * 4 + (k - 1)] = __builtin_bit_cast(_Float16, threshold_bits(alpha, range, k, L));
+          if (kParts == 1 || (k > 1) == (part == 1)) s_thr[at * 4 + (k - 1)] = __builtin_bit_cast(_Float16, threshold_bits(alpha, range, k, L));
       }
     }
     __syncthreads();
