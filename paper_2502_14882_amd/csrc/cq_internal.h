@@ -56,6 +56,10 @@ struct Calib {
   float tau1, tau2, gamma, delta;
 };
 
+// Compute units of the current device (cached per device; 256, the MI355X count, when there is
+// no device, as in host-only checks of the plans).
+long long device_cu_count();
+
 // ---- launchers (each returns the hipError_t of its launches) -----------------------
 hipError_t launch_quantize_generic(const void* x_f16, const cq_qtensor_t& out, int rows,
                                    int n_vis, int d, int bits, int axis, int group,

@@ -1383,8 +1383,8 @@ namespace {
 
 constexpr int kMaxDevices = 64;
 
-// Compute units of the current device (cached per device; 256, the MI355X count, when there is
-// no device, as in host-only checks of the plan).
+}  // namespace
+
 long long device_cu_count() {
   static std::atomic<int> n_cus[kMaxDevices];
   int dev = 0;
@@ -1397,6 +1397,8 @@ long long device_cu_count() {
   }
   return v;
 }
+
+namespace {
 
 // Channel-wise statistics over the whole sequence (group = n_vis, the scheme of Sec. 3.1 as
 // printed) run as processing groups of 128 tokens that share the row's one parameter group.

@@ -13,8 +13,8 @@
 // block indices 8 apart: the same XCD, at the same time, and its L2 puts the lines together.
 //
 // Bound: what a CU reads (a workgroup's loads are all out before its arithmetic begins, 16 waves to a CU) and
-// vector issue, one behind the other.  Keys and values, tile kernels / here, us: 64 rows x 3003 tokens, 2 bits
-// 45.1 / 37.8; 256 x 2000 105 / 71; 8 x 1000, 1 bit 12.1 / 4.5; 512 x 300 36.9 / 17.1; 64 x 3003 of 64 channels
+// vector issue, one behind the other unless a workgroup takes several blocks (slice_kernel).  Keys and values, tile
+// kernels / here, us: 64 rows x 3003 tokens, 2 bits 45.1 / 29.6; 256 x 2000 105 / 71; 8 x 1000, 1 bit 12.1 / 4.5; 512 x 300 36.9 / 17.1; 64 x 3003 of 64 channels
 // 27.9 / 16.4.  From 4097 tokens the two are equal.
 #include <hip/hip_fp16.h>
 
@@ -32,10 +32,12 @@ struct SliceArgs {
 };
 
 // grid: ((group / 8) * slices + slice) * 8 + group % 8, first the one tensor's groups, then the other's
-template <int BITS, int LANES, int THREADS, int P>
+// ROUNDS: a workgroup has a CU to itself and takes every gridDim.x-th block, one behind the other; as soon as a piece of x
+// has become codes, the same piece of the next block is asked for.
+template <int BITS, int LANES, int THREADS, int P, bool ROUNDS>
 __global__ void __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(BITS <= 2 || P <= 12 ? 4 : 1)))
 quantize_slice_kernel(const SliceArgs first, const SliceArgs second, int n_first, int n_groups, int tokens, int d,
-                      int log_slices) {
+                      int log_slices, int n_blocks) {
   constexpr int L = (1 << BITS) - 1, kTokens = THREADS / LANES, kSlice = 8 * LANES, kWavesQ = THREADS / 64;
   constexpr bool kWide = BITS > 2;
   __shared__ __align__(16) _Float16 s_part[2][kWavesQ][kSlice];
@@ -43,19 +45,45 @@ quantize_slice_kernel(const SliceArgs first, const SliceArgs second, int n_first
   __shared__ __align__(16) double s_rinv[kWide ? kSlice : 1];
   __shared__ __align__(16) _Float16 s_alpha[kSlice];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, oct = lane & (LANES - 1);
-  const int slot = (int)(blockIdx.x >> 3), slice = slot & ((1 << log_slices) - 1);
-  int group = (slot >> log_slices) * 8 + (int)(blockIdx.x & 7);
-  if (group >= n_groups) return;                // the grid is whole eights of groups
-  const bool one = group < n_first;
-  if (!one) group -= n_first;
-  const __half* xb = one ? first.x : second.x;
-  const size_t tok0 = (size_t)group * tokens;
-  const int c0 = slice * kSlice, t_lane = tid / LANES;
-  const char* src = reinterpret_cast<const char*>(xb + tok0 * d + c0 + 8 * oct);
+  int t_lane = tid / LANES;
+  struct Piece { bool one; int group, c0; };
+  auto piece_of = [&](int block) {
+    const int slot = block >> 3, group = (slot >> log_slices) * 8 + (block & 7);
+    return Piece{group < n_first, group < n_first ? group : group - n_first, (slot & ((1 << log_slices) - 1)) * kSlice};
+  };
+  auto exists = [&](int block) {                // the blocks are whole eights of groups
+    return block < n_blocks && (block >> 3 >> log_slices) * 8 + (block & 7) < n_groups;
+  };
+  auto source = [&](const Piece& p) {
+    return reinterpret_cast<const char*>((p.one ? first.x : second.x) + (size_t)p.group * tokens * d + p.c0);
+  };
+  auto load = [&](const char* src, int i) {     // past the end: the last token, which changes no extremum
+    const int t0 = min(i * kTokens, tokens - 1);
+    return *reinterpret_cast<const v8h*>(src + (size_t)t0 * (unsigned)(2 * d) +
+                                         ((unsigned)min(t_lane, tokens - 1 - t0) * (unsigned)(2 * d) + 16u * oct));
+  };
+  int block = (int)blockIdx.x;
+  if (!exists(block)) return;
+  Piece piece = piece_of(block);
   v8h x[P];                                     // read exactly once
+  {
+    const char* src = source(piece);
 #pragma unroll
-  for (int i = 0; i < P; ++i)                   // past the end: the last token, which changes no extremum
-    x[i] = *reinterpret_cast<const v8h*>(src + (unsigned)min(i * kTokens + t_lane, tokens - 1) * (unsigned)(2 * d));
+    for (int i = 0; i < P; ++i) x[i] = load(src, i);
+  }
+  for (;;) {
+  // (offsets of loads and stores are made anew in every round: kept from round to round they spill)
+  if constexpr (ROUNDS) asm volatile("" : "+v"(t_lane));
+  const bool one = piece.one;
+  const int group = piece.group, c0 = piece.c0;
+  const size_t tok0 = (size_t)group * tokens;
+  bool more = false;
+  if constexpr (ROUNDS) {
+    block += (int)gridDim.x;
+    more = exists(block);
+    if (more) piece = piece_of(block);
+  }
+  const char* next = source(piece);
   // ---- 1. extrema of the slice's channels
   v8h mn = x[0], mx = x[0];
 #pragma unroll
@@ -93,7 +121,7 @@ quantize_slice_kernel(const SliceArgs first, const SliceArgs second, int n_first
   __syncthreads();
   // ---- 3. codes: BITS words per token and slice
   const int words = d * BITS / 32;
-  uint32_t* dst = (one ? first.codes : second.codes) + tok0 * words + slice * (LANES * BITS / 4);
+  uint32_t* dst = (one ? first.codes : second.codes) + tok0 * words + c0 / 32 * BITS;
   if constexpr (kWide) {
     double al[8], ri[8];
     float al32[8], ri32[8];
@@ -104,64 +132,83 @@ quantize_slice_kernel(const SliceArgs first, const SliceArgs second, int n_first
       ri[j] = s_rinv[8 * oct + j];
       ri32[j] = (float)ri[j];
     }
+    static_assert(!ROUNDS, "one and two bits: with wider codes the loop spills");
 #pragma unroll
     for (int i = 0; i < P; ++i) {
-      const int t = i * kTokens + t_lane;
+      uint32_t* to = dst + (size_t)(i * kTokens) * (unsigned)words;
+      const unsigned at = (unsigned)t_lane * (unsigned)words;
       uint32_t w0, w1;
       octet_words<BITS>(x[i], al, ri, al32, ri32, w0, w1);
-      if (t < tokens) {
-        if constexpr (BITS == 4) dst[(unsigned)t * (unsigned)words + oct] = w0;
-        else *reinterpret_cast<v2u*>(dst + (unsigned)t * (unsigned)words + 2 * oct) = (v2u){w0, w1};
+      if (t_lane < tokens - i * kTokens) {
+        if constexpr (BITS == 4) to[at + oct] = w0;
+        else *reinterpret_cast<v2u*>(to + (at + 2 * oct)) = (v2u){w0, w1};
       }
     }
   } else {
     v8h thr[L];
 #pragma unroll
     for (int k = 0; k < L; ++k) thr[k] = *reinterpret_cast<const v8h*>(&s_thr[k][8 * oct]);
-#pragma unroll
-    for (int i = 0; i < P; ++i) {
-      const int t = i * kTokens + t_lane;
+    auto put = [&](int i) {
+      uint32_t* to = dst + (size_t)(i * kTokens) * (unsigned)words;
+      const unsigned at = (unsigned)t_lane * (unsigned)words;
       uint32_t bits = octet_codes<BITS>(x[i], thr);
       if constexpr (BITS == 1) {
         bits <<= 24 - 8 * (oct & 3);
         bits |= other_lane<0xB1>(bits);
         bits |= other_lane<0x4E>(bits);
-        if ((oct & 3) == 0 && t < tokens) dst[(unsigned)t * (unsigned)words + (oct >> 2)] = bits;
+        if ((oct & 3) == 0 && t_lane < tokens - i * kTokens) to[at + (oct >> 2)] = bits;
       } else {
         bits <<= 16 - 16 * (oct & 1);
         bits |= other_lane<0xB1>(bits);
-        if ((oct & 1) == 0 && t < tokens) dst[(unsigned)t * (unsigned)words + (oct >> 1)] = bits;
+        if ((oct & 1) == 0 && t_lane < tokens - i * kTokens) to[at + (oct >> 1)] = bits;
       }
+    };
+    if (more) {
+#pragma unroll
+      for (int i = 0; i < P; ++i) {
+        put(i);
+        x[i] = load(next, i);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < P; ++i) put(i);
     }
+  }
+  if (!more) return;
   }
 }
 
-using SliceKernel = void (*)(const SliceArgs, const SliceArgs, int, int, int, int, int);
+using SliceKernel = void (*)(const SliceArgs, const SliceArgs, int, int, int, int, int, int);
 // Whole lines per token (8 lanes) where the group is short; else half of one, with which more workgroups share a CU
 // (us, one-bit keys and values, 8 / 4 lanes: 512 rows x 300 tokens 17.1 / 27.3, 8 x 1000 5.7 / 4.5, 256 x 2000 with two
 // bits 86.6 / 70.6; 8 bits, 256 x 1500 83.5 / 95.1).  Beyond 2048 tokens 1024 threads; 24 registers of data per
 // thread instead are slower (64 x 3003 41.6 / 37.8).
+// Where such a workgroup leaves no room for another (1024 threads) and there are more of them than CUs, one to a CU takes
+// its blocks in rounds: us, a workgroup per block / in rounds: 2 bits 64 x 3003 31.5 / 29.6, 256 x 3003 122 / 113, 96 x 2049
+// 36.0 / 32.0, 64 channels 128 x 3003 32.1 / 28.8; 1 bit 64 x 3003 24.8 / 24.5, 128 x 4000 67.0 / 63.3.  Not with 256 channels, eight
+// slices to a line of tokens: 160 x 2500 127 / 138, 160 x 4000, 1 bit 161 / 178.
 template <int BITS>
-SliceKernel slice_kernel(int tokens, int* threads, int* lanes) {
+SliceKernel slice_kernel(int tokens, int d, long long blocks_of_4_lanes, int* threads, int* lanes, bool* rounds) {
   *lanes = 8;
   *threads = 512;
-  if (tokens <= 512) return quantize_slice_kernel<BITS, 8, 512, 8>;
+  *rounds = false;
+  if (tokens <= 512) return quantize_slice_kernel<BITS, 8, 512, 8, false>;
   *lanes = 4;
-  if (tokens <= 1024) return quantize_slice_kernel<BITS, 4, 512, 8>;
+  if (tokens <= 1024) return quantize_slice_kernel<BITS, 4, 512, 8, false>;
   if constexpr (BITS <= 2) {
-    if (tokens <= 2048) return quantize_slice_kernel<BITS, 4, 512, 16>;
+    if (tokens <= 2048) return quantize_slice_kernel<BITS, 4, 512, 16, false>;
     *threads = 1024;
+    if (tokens > 4096) return nullptr;
+    *rounds = d <= 128 && blocks_of_4_lanes > device_cu_count();
+    if (tokens <= 3072) return *rounds ? quantize_slice_kernel<BITS, 4, 1024, 12, true> : quantize_slice_kernel<BITS, 4, 1024, 12, false>;
+    return *rounds ? quantize_slice_kernel<BITS, 4, 1024, 16, true> : quantize_slice_kernel<BITS, 4, 1024, 16, false>;
   } else {
     *threads = 1024;
     *lanes = 8;
-    if (tokens <= 1536) return quantize_slice_kernel<BITS, 8, 1024, 12>;
+    if (tokens <= 1536) return quantize_slice_kernel<BITS, 8, 1024, 12, false>;
     *lanes = 4;
+    return tokens <= 3072 ? quantize_slice_kernel<BITS, 4, 1024, 12, false> : nullptr;
   }
-  if (tokens <= 3072) return quantize_slice_kernel<BITS, 4, 1024, 12>;
-  if constexpr (BITS <= 2) {
-    if (tokens <= 4096) return quantize_slice_kernel<BITS, 4, 1024, 16>;
-  }
-  return nullptr;
 }
 
 }  // namespace
@@ -184,17 +231,22 @@ bool quantize_slice_supported(size_t n_tokens, int d, int bits, int axis, int gr
 
 hipError_t launch_quantize_slices(const QuantizeJob* jobs, int n_jobs, size_t n_tokens, int d, int bits, hipStream_t stream) {
   const int tokens = jobs[0].group, n = (int)(n_tokens / tokens);
+  const int groups = n * n_jobs, log_slices_4 = d == 64 ? 1 : d == 128 ? 2 : 3;
+  const unsigned eights = (unsigned)((groups + 7) / 8 * 8);
+  const long long blocks_4 = (long long)eights << log_slices_4;
   int threads = 0, lanes = 0;
-  const SliceKernel kern = bits == 1 ? slice_kernel<1>(tokens, &threads, &lanes) : bits == 2 ? slice_kernel<2>(tokens, &threads, &lanes)
-                         : bits == 4 ? slice_kernel<4>(tokens, &threads, &lanes) : slice_kernel<8>(tokens, &threads, &lanes);
+  bool rounds = false;
+  const auto pick = bits == 1 ? slice_kernel<1> : bits == 2 ? slice_kernel<2> : bits == 4 ? slice_kernel<4> : slice_kernel<8>;
+  const SliceKernel kern = pick(tokens, d, blocks_4, &threads, &lanes, &rounds);
   if (!kern) return hipErrorInvalidValue;
   auto args = [](const QuantizeJob& j) {
     return SliceArgs{static_cast<const __half*>(j.x_f16), j.out.codes, j.out.scale, j.out.min};
   };
-  const int log_slices = (d == 64 ? 1 : d == 128 ? 2 : 3) - (lanes == 8 ? 1 : 0), groups = n * n_jobs;
-  const unsigned blocks = (unsigned)((groups + 7) / 8 * 8) << log_slices;
-  kern<<<dim3(blocks), dim3((unsigned)threads), 0, stream>>>(args(jobs[0]), args(jobs[n_jobs - 1]), n, groups, tokens, d,
-                                                             log_slices);
+  const int log_slices = log_slices_4 - (lanes == 8 ? 1 : 0);
+  const unsigned blocks = eights << log_slices;
+  const unsigned grid = rounds ? (unsigned)device_cu_count() & ~7u : blocks;      // whole eights: a block stays on its XCD
+  kern<<<dim3(grid), dim3((unsigned)threads), 0, stream>>>(args(jobs[0]), args(jobs[n_jobs - 1]), n, groups, tokens, d,
+                                                           log_slices, (int)blocks);
   return hipGetLastError();
 }
 
