@@ -305,6 +305,10 @@ fused_row_kernel(const FusedArgs args) {
       const uint32_t* kq_lane = kq_row + (size_t)(16 * kb + n16) * 4;
       v2f s01[kRK];               // scales of channels wc0, wc1
       uint32_t m01[kRK];          // their minima, two fp16 in one word
+      // Eight bits: past the last group, where the ring asks along, all lanes read the same bytes, not a line each (and past
+      // the last value tile in phase 2).  us, lines / same bytes: 256 rows x 3328 49.7 / 46.4, 256 x 1024 in groups of 32
+      // 18.9 / 16.2, 512 x 8192 218 / 212.  (With four bits small calls gain 5 % and 128 rows x 3328 lose 2; with fewer
+      // it is the same.)
       auto load_group = [&](int slot, int t) {
         const int tc = min(t, n_groups - 1);      // clamped, never a branch around a load
         // a lane's b words of a tile are adjacent: one load of 4b bytes (two of 16 for b = 8), so
@@ -319,6 +323,7 @@ fused_row_kernel(const FusedArgs args) {
 #pragma unroll
         for (int i = 0; i < (kQuadKeys ? 0 : TILES); ++i) {
           const uint32_t* p = RAG ? kq_row + (size_t)min(tc * 128 + 16 * i + n16, nv - 1) * (4 * BITS) + kb * BITS
+                      : BITS == 8 ? kq_row + ((size_t)tc * TILES + i) * (64 * BITS) + (t < n_groups ? n16 * (4 * BITS) + kb * BITS : 0)
                                   : kc_lane + ((size_t)tc * TILES + i) * (64 * BITS);
           if constexpr (BITS == 1) {
             w[slot][i][0] = stream_load<kNtKeys>(p);
@@ -905,7 +910,7 @@ fused_row_kernel(const FusedArgs args) {
       float vsr[2];
       uint16_t vmr[2];
       auto load_tile = [&](int slot, int jt) {
-        const int j = RAG ? min(min(jt, last) + lane, nv - 1) : min(jt, last) + lane;
+        const int j = RAG ? min(min(jt, last) + lane, nv - 1) : min(jt, last) + (BITS == 8 && jt > last ? 0 : lane);
 #pragma unroll
         for (int e = 0; e < BITS; ++e)
           cg[slot][e] = stream_load<kNtCodes>(reinterpret_cast<const v4i*>(vc_row + (size_t)j * (4 * BITS) + 4 * e));
