@@ -606,7 +606,16 @@ template <int D, int AXIS, int BITS, int GROUP, bool SHORT = true>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(D <= 128 && BITS <= 2 ? 8 : 1)))
 quantize_tile_kernel(const QArgs a) {
   __shared__ TileMem<D, AXIS, BITS, GROUP> sm;
-  quantize_tile<D, AXIS, BITS, GROUP, SHORT>(a, blockIdx.x, sm);
+  // An XCD (every eighth block) takes eight tiles in a row, a quarter of a megabyte at 128 channels, not every eighth tile:
+  // us, keys and values, every eighth / eight in a row: 1024 rows x 16384 tokens, 1 bit 1760 / 1674, 512 x 8192 427 / 419, 256 x
+  // 8192, 4 bits 255 / 247.  (Runs of 2: 1760; 4: 1687; 64: 1687; 256: 1663, but 2 bits in groups of 32 only as fast as
+  // without; 4096: slower there.  8 bits lose: 256 x 16384 552 / 562.)
+  unsigned block = blockIdx.x;
+  if constexpr (GROUP != 0 && BITS != 8) {                 // (long groups: neighbours share extrema, their order stays)
+    const unsigned base = block & ~63u;
+    if (base + 64 <= gridDim.x) block = base + ((block & 7) << 3) + ((block >> 3) & 7);
+  }
+  quantize_tile<D, AXIS, BITS, GROUP, SHORT>(a, block, sm);
 }
 
 // Keys and values in one launch, the first n_first blocks on the keys (channel-wise, KGROUP).
