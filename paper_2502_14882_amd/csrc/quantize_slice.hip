@@ -14,7 +14,7 @@
 //
 // Bound: what a CU reads (a workgroup's loads are all out before its arithmetic begins, 16 waves to a CU) and
 // vector issue, one behind the other unless a workgroup takes several blocks (slice_kernel).  Keys and values, tile
-// kernels / here, us: 64 rows x 3003 tokens, 2 bits 45.1 / 29.6; 256 x 2000 105 / 71; 8 x 1000, 1 bit 12.1 / 4.5; 512 x 300 36.9 / 17.1; 64 x 3003 of 64 channels
+// kernels / here, us: 64 rows x 3003 tokens, 2 bits 45.1 / 29.6; 256 x 2000 105 / 66; 8 x 1000, 1 bit 12.1 / 4.5; 512 x 300 36.9 / 15.4; 64 x 3003 of 64 channels
 // 27.9 / 16.4.  From 4097 tokens the two are equal.
 #include <hip/hip_fp16.h>
 
