@@ -609,9 +609,13 @@ quantize_tile_kernel(const QArgs a) {
   // An XCD (every eighth block) takes eight tiles in a row, a quarter of a megabyte at 128 channels, not every eighth tile:
   // us, keys and values, every eighth / eight in a row: 1024 rows x 16384 tokens, 1 bit 1760 / 1674, 512 x 8192 427 / 419, 256 x
   // 8192, 4 bits 255 / 247.  (Runs of 2: 1760; 4: 1687; 64: 1687; 256: 1663, but 2 bits in groups of 32 only as fast as
-  // without; 4096: slower there.  8 bits lose: 256 x 16384 552 / 562.)
+  // without; 4096: slower there.)  Not with 8 bits, which lose: 256 x 16384 552 / 562.  Not with 64 channels, half the bytes
+  // to a run: one tensor, 1 bit, loses 3 to 7 % below 64 MB (256 x 4096 23.4 / 24.5) and gains nothing above, 2 and 4 bits
+  // are the same.  Not for long groups, the same within 1.5 %.  (The pair kernel below keeps every eighth tile: with 128
+  // channels the same within 2 %, but for 64 x 3328, 4 bits, 3 % less; with 256 channels runs take 1 to 5 % less; with 64 up to
+  // 8 % more.)
   unsigned block = blockIdx.x;
-  if constexpr (GROUP != 0 && BITS != 8) {                 // (long groups: neighbours share extrema, their order stays)
+  if constexpr (GROUP != 0 && D > 64 && BITS != 8) {
     const unsigned base = block & ~63u;
     if (base + 64 <= gridDim.x) block = base + ((block & 7) << 3) + ((block >> 3) & 7);
   }
