@@ -35,7 +35,7 @@
 //
 // Bound: HBM, and the launches of a small call.  Groups of a few tokens spend a block on little
 // (quantize_tile_is_faster has the line from which these kernels are used).  128 x 8
-// rows x 16384 tokens, 1 bit, groups of 128 (9.33 GB): 1755 us = 5.3 TB/s.
+// rows x 16384 tokens, 1 bit, groups of 128 (9.33 GB): 1669 us = 5.6 TB/s.
 #ifndef CQ_QUANTIZE_TILE_H_
 #define CQ_QUANTIZE_TILE_H_
 
@@ -607,8 +607,8 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(D
 quantize_tile_kernel(const QArgs a) {
   __shared__ TileMem<D, AXIS, BITS, GROUP> sm;
   // An XCD (every eighth block) takes eight tiles in a row, a quarter of a megabyte at 128 channels, not every eighth tile:
-  // us, keys and values, every eighth / eight in a row: 1024 rows x 16384 tokens, 1 bit 1760 / 1674, 512 x 8192 427 / 419, 256 x
-  // 8192, 4 bits 255 / 247.  (Runs of 2: 1760; 4: 1687; 64: 1687; 256: 1663, but 2 bits in groups of 32 only as fast as
+  // us, keys and values, every eighth / eight in a row: 1024 rows x 16384 tokens, 1 bit 1764 / 1669, 2 bits 1838 / 1809, 512 x
+  // 8192, 1 bit 389 / 389, 4 bits 480 / 475.  (Runs of 2: 1760; 4: 1687; 64: 1687; 256: 1663, but 2 bits in groups of 32 only as fast as
   // without; 4096: slower there.)  Not with 8 bits, which lose: 256 x 16384 552 / 562.  Not with 64 channels, half the bytes
   // to a run: one tensor, 1 bit, loses 3 to 7 % below 64 MB (256 x 4096 23.4 / 24.5) and gains nothing above, 2 and 4 bits
   // are the same.  Not for long groups, the same within 1.5 %.  (The pair kernel below keeps every eighth tile: with 128

@@ -28,7 +28,8 @@ __global__ void __launch_bounds__(256) stream_copy_kernel(const v4f* __restrict_
 }
 // The tile quantizer's memory traffic without its arithmetic: a 256-thread block reads a tile of
 // 128 tokens x 128 fp16 (32 KB, eight 16-byte loads per lane, as the quantizer does), folds it with
-// a handful of instructions and writes `code_bytes` + `meta_bytes` per tile.
+// a handful of instructions and writes `code_bytes` + `meta_bytes` per tile.  Tiles go to the XCDs in the
+// quantizer's order, eight in a row to each.
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 __global__ void __launch_bounds__(256) tile_traffic_kernel(const v8h* __restrict__ x,
@@ -36,7 +37,10 @@ __global__ void __launch_bounds__(256) tile_traffic_kernel(const v8h* __restrict
                                                            float* __restrict__ meta, int code_v4,
                                                            int meta_f) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const size_t tile = blockIdx.x;
+  unsigned block = blockIdx.x;
+  const unsigned base = block & ~63u;
+  if (base + 64 <= gridDim.x) block = base + ((block & 7) << 3) + ((block >> 3) & 7);
+  const size_t tile = block;
   const v8h* src = x + (tile * 128 + 32 * wave + (lane >> 4)) * 16 + (lane & 15);
   v8h r[8];
 #pragma unroll
