@@ -12,8 +12,8 @@
 //
 // The grid costs n1 + n2 + 2 exponentials per token (4 where the taus are evenly spaced from 0) instead of
 // one per pair: with u = (s - gamma) / (delta - gamma),  g(s) = s + tau1 (u - 1) - tau2 u,  so a weight is
-// e^s e^(tau1 (u - 1)) e^(-tau2 u).  Blocks of 4 x 4 pairs stay in registers; a row is cut into chunks so
-// that every CU works.
+// e^s e^(tau1 (u - 1)) e^(-tau2 u).  Blocks of 4 x 4 pairs stay in registers; rows are cut into chunks
+// where there are fewer than blocks that the chip holds (tau_workspace_layout has the number).
 //
 // One pass over the tokens.  With w and q the weights of the calibrated and of the exact keys before they are
 // normalized, Z and Q their sums, the squared differences of the normalized ones need Z and Q, which are
@@ -26,7 +26,10 @@
 // per pair, a block per row), 55.6 us with factors and chunks, 42.8 with the sums folded by lane swaps,
 // 32.9 with even spacing and the normalizers loaded eight at a time, 29.4 with both sets of logits in
 // one launch (28.6 on another box), 20.2 in one pass instead of two (normalizers, then squared differences; 7.3 and
-// 9.4 us of kernels).  Other sizes, two passes / one: 1 row x 256 + 8 tokens 14.1 / 10.8, 4096 x 2048 + 64 227 / 175.
+// 9.4 us of kernels).  Other sizes, two passes / one: 1 row x 256 + 8 tokens 14.1 / 10.8, 4096 x 2048 + 64 227 / 175, 1 row x 65536
+// 35.2 / 30.8.
+// The three sums per pair cost registers: 191 to 238 and two waves per SIMD (104 to 229 and two to four in the two passes),
+// 9 to 97 scalar registers spilled (none with unevenly spaced factors).
 // Against 64 bits 1e-8 to 8e-7, the same with one pass as with two: that is what the fp32 logits leave.
 #include <cfloat>
 #include <cmath>
@@ -265,7 +268,8 @@ tau_grid_kernel(const TauArgs a) {
     }
 }
 
-// One block per pair: the squared differences of all rows, in a fixed order.
+// One block per pair: the squared differences of all rows, in a fixed order.  A thread takes a row: with one row of 65536 tokens
+// one thread reads 129 chunks, 14 of that call's 31 us (2.0 us with 128 rows of 4 chunks).
 template <bool ONE>
 __global__ void __launch_bounds__(kThreads)
 tau_reduce_kernel(const TauArgs a, size_t rows, double n_terms, double* __restrict__ mse_out) {
