@@ -14,8 +14,9 @@
 //
 // Bound: what a CU reads (a workgroup's loads are all out before its arithmetic begins, 16 waves to a CU) and
 // vector issue, one behind the other unless a workgroup takes several blocks (slice_kernel).  Keys and values, tile
-// kernels / here, us: 64 rows x 3003 tokens, 2 bits 45.1 / 29.6; 256 x 2000 105 / 66; 8 x 1000, 1 bit 12.1 / 4.5; 512 x 300 36.9 / 15.4; 64 x 3003 of 64 channels
-// 27.9 / 16.4.  From 4097 tokens the two are equal.
+// kernels / here, us, call after call on the same tensors: 64 rows x 3003 tokens, 2 bits 42.9 / 22.3 (here 29.6 where the tensors
+// change from call to call); 256 x 2000 101 / 57.6; 8 x 1000, 1 bit 8.8 / 3.8; 512 x 300 34.5 / 15.5; 64 x 3003 of 64 channels, 2 bits
+// 25.6 / 13.5; at the longest, 4096 tokens, 64 x, 1 bit 49.1 / 25.2, 2 bits 55.1 / 29.9, 256 x, 2 bits 205 / 158.
 #include <hip/hip_fp16.h>
 
 #include "cq_internal.h"
@@ -182,7 +183,8 @@ using SliceKernel = void (*)(const SliceArgs, const SliceArgs, int, int, int, in
 // Whole lines per token (8 lanes) where the group is short; else half of one, with which more workgroups share a CU
 // (us, one-bit keys and values, 8 / 4 lanes: 512 rows x 300 tokens 17.1 / 27.3, 8 x 1000 5.7 / 4.5, 256 x 2000 with two
 // bits 86.6 / 70.6; 8 bits, 256 x 1500 83.5 / 95.1).  Beyond 2048 tokens 1024 threads; 24 registers of data per
-// thread instead are slower (64 x 3003 41.6 / 37.8).
+// thread instead are slower (64 x 3003 41.6 / 37.8).  (These are from before the codes took half the instructions; the kernels
+// chosen have since become faster by a tenth, the others were not measured again.)
 // Where such a workgroup leaves no room for another (1024 threads) and there are more of them than CUs, one to a CU takes
 // its blocks in rounds: us, a workgroup per block / in rounds: 2 bits 64 x 3003 31.5 / 29.6, 256 x 3003 122 / 113, 96 x 2049
 // 36.0 / 32.0, 64 channels 128 x 3003 32.1 / 28.8; 1 bit 64 x 3003 24.8 / 24.5, 128 x 4000 67.0 / 63.3.  Not with 256 channels, eight
@@ -215,9 +217,12 @@ SliceKernel slice_kernel(int tokens, int d, long long blocks_of_4_lanes, int* th
 
 // A workgroup's own time grows with the tokens it owns and the width of the codes, so long groups take the tile kernels'
 // many workgroups unless there are enough of them, and beyond 3072 tokens 4- and 8-bit codes always do (their registers
-// spilled there).  us, keys and values whole, tile kernels / here: 2 bits 4000 tokens, 128 channels in all 13.6 / 15.5, 1024
-// 19.2 / 16.3; 4 bits 1500 tokens 64 channels 10.5 / 11.9, 128 12.7 / 12.2; 3000 tokens 128 13.2 / 14.6, 1024 18.6 / 15.6;
-// 8 bits 4000 tokens 128 14.7 / 21.9, 1024 21.9 / 23.9, 8192 74.6 / 76.0 (but 4096 43.6 / 36.0).  One bit always wins.
+// spilled there: 8 bits, 4000 tokens, 128 channels in all 14.7 / 21.9, 8192 74.6 / 76.0).  us, keys and values whole, tile
+// kernels / here: 4 bits 1500 tokens, 64 channels in all 9.3 / 10.3, 128 11.4 / 10.6; 3000 tokens 1024 15.0 / 11.9; 8 bits 1500
+// tokens 64 10.5 / 10.8, 128 13.8 / 12.2; 3000 tokens 1024 17.8 / 14.2.  One bit always wins.  The lines for the longest groups
+// were drawn when a block here took half as long again (2 bits 4000 tokens 128 channels 13.6 / 15.5, 4 bits 3000 13.2 / 14.6); now
+// they keep calls from the faster kernel: 2 bits 4000 tokens 128 and 256 channels 11.3 / 9.4, 3003 tokens 64 channels 9.3 /
+// 7.7, 4 bits 3000 tokens 128 and 256 channels 11.9 / 11.3, 12.4 / 11.3, 8 bits 128 13.2 / 12.8.
 bool quantize_slice_supported(size_t n_tokens, int d, int bits, int axis, int group) {
   if (axis != CQ_AXIS_CHANNEL || group <= kTile || group > (bits <= 2 ? 4096 : 3072)) return false;
   if (d != 64 && d != 128 && d != 256) return false;

@@ -17,11 +17,14 @@ bool quantize_tuned_supported(int rows, int n_vis, int d, int bits, int axis, in
 // tokens: a group under 128 tokens other than 32 and 64 is a block of 256 threads of its own, which
 // derives the parameters and thresholds of every channel for a few tokens, while the other kernel spends
 // one thread per channel on it.  Microseconds, one tensor of 128 rows x 4096 tokens, shape-agnostic / tile:
-//   128 channels, 1 bit:   4 tokens 161 / 348, 12: 118 / 121, 16: 114 / 96, 31: 114 / 52
-//                 2 bits:  4 tokens 144 / 600, 16: 109 / 154, 24: 112 / 105, 31: 114 / 84
-//                 8 bits:  1 token 299 / 2691, 16: 115 / 194, 24: 118 / 135, 31: 122 / 109
-//   256 channels, 2 bits:  16 tokens 287 / 286; 8 rows: 14.0 / 22.6, 24: 16.4 / 18.2, 31: 17.8 / 15.9
-// The line is where the slower of 8, 64 and 256 rows breaks even.
+//   128 channels, 1 bit:   4 tokens 161 / 287, 12: 119 / 99, 16: 114 / 77, 31: 114 / 44
+//                 2 bits:  4 tokens 144 / 481, 16: 109 / 124, 20: 111 / 100, 24: 112 / 84, 31: 114 / 69
+//                 4 bits:  24 tokens 112 / 128, 28: 113 / 111, 31: 116 / 102
+//                 8 bits:  1 token 302 / 2605, 16: 115 / 193, 24: 117 / 135, 28: 118 / 118, 31: 122 / 108
+//   256 channels, 2 bits:  16 tokens 286 / 260; 8 rows: 13.6 / 19.7, 24: 16.1 / 15.2, 31: 17.5 / 13.1
+// The line is where the slower of 8, 64 and 256 rows broke even when 1 and 2 bits took a quarter longer on the tile
+// kernels (1 bit 12 tokens 118 / 121, 2 bits 20: 111 / 127); since then groups of 12 to 15 tokens of 1 bit and of 20 to 23 of 2 bits stay
+// with the slower kernel (8 rows x 14 tokens, 1 bit 10.7 / 8.0, x 20, 2 bits 11.6 / 9.2).
 bool quantize_tile_is_faster(int d, int bits, int axis, int group) {
   if (axis == CQ_AXIS_TOKEN) return true;
   const int line = bits == 1 ? 16 : bits == 2 ? 24 : 28;
