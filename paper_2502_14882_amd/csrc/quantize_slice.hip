@@ -73,109 +73,109 @@ quantize_slice_kernel(const SliceArgs first, const SliceArgs second, int n_first
     for (int i = 0; i < P; ++i) x[i] = load(src, i);
   }
   for (;;) {
-  // (offsets of loads and stores are made anew in every round: kept from round to round they spill)
-  if constexpr (ROUNDS) asm volatile("" : "+v"(t_lane));
-  const bool one = piece.one;
-  const int group = piece.group, c0 = piece.c0;
-  const size_t tok0 = (size_t)group * tokens;
-  bool more = false;
-  if constexpr (ROUNDS) {
-    block += (int)gridDim.x;
-    more = exists(block);
-    if (more) piece = piece_of(block);
-  }
-  const char* next = source(piece);
-  // ---- 1. extrema of the slice's channels
-  v8h mn = x[0], mx = x[0];
-#pragma unroll
-  for (int i = 1; i < P; ++i) {
-    mn = __builtin_elementwise_min(mn, x[i]);
-    mx = __builtin_elementwise_max(mx, x[i]);
-  }
-  store_extrema<LANES>(mn, mx, lane, s_part[0][wave], s_part[1][wave]);
-  __syncthreads();
-  // ---- 2. stored parameters; a thread per (threshold, channel)
-  constexpr int kEach = kWide ? 1 : L;
-  if (tid < kEach * kSlice) {
-    const int c = tid & (kSlice - 1), k = tid / kSlice + 1;
-    _Float16 lo = s_part[0][0][c], hi = s_part[1][0][c];
-#pragma unroll
-    for (int w = 1; w < kWavesQ; ++w) {
-      lo = (_Float16)fminf((float)lo, (float)s_part[0][w][c]);
-      hi = (_Float16)fmaxf((float)hi, (float)s_part[1][w][c]);
+    // (offsets of loads and stores are made anew in every round: kept from round to round they spill)
+    if constexpr (ROUNDS) asm volatile("" : "+v"(t_lane));
+    const bool one = piece.one;
+    const int group = piece.group, c0 = piece.c0;
+    const size_t tok0 = (size_t)group * tokens;
+    bool more = false;
+    if constexpr (ROUNDS) {
+      block += (int)gridDim.x;
+      more = exists(block);
+      if (more) piece = piece_of(block);
     }
-    const uint16_t mbits = canonical_zero(__builtin_bit_cast(uint16_t, lo));
-    const double alpha = h_to_double(mbits);
-    const double range = ((double)(float)hi - alpha) + 0.0;
-    if (k == 1) {
-      const size_t meta = (size_t)group * d + c0 + c;
-      (one ? first.scale : second.scale)[meta] = (float)(range / (double)L);
-      (one ? first.minv : second.minv)[meta] = mbits;
-    }
-    if constexpr (kWide) {
-      s_alpha[c] = __builtin_bit_cast(_Float16, mbits);
-      s_rinv[c] = range > 0.0 ? (double)L / range : 0.0;
-    } else {
-      s_thr[k - 1][c] = __builtin_bit_cast(_Float16, threshold_bits(alpha, range, k, L));
-    }
-  }
-  __syncthreads();
-  // ---- 3. codes: BITS words per token and slice
-  const int words = d * BITS / 32;
-  uint32_t* dst = (one ? first.codes : second.codes) + tok0 * words + c0 / 32 * BITS;
-  if constexpr (kWide) {
-    double al[8], ri[8];
-    float al32[8], ri32[8];
+    const char* next = source(piece);
+    // ---- 1. extrema of the slice's channels
+    v8h mn = x[0], mx = x[0];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      al32[j] = (float)s_alpha[8 * oct + j];
-      al[j] = (double)al32[j];
-      ri[j] = s_rinv[8 * oct + j];
-      ri32[j] = (float)ri[j];
+    for (int i = 1; i < P; ++i) {
+      mn = __builtin_elementwise_min(mn, x[i]);
+      mx = __builtin_elementwise_max(mx, x[i]);
     }
-    static_assert(!ROUNDS, "one and two bits: with wider codes the loop spills");
+    store_extrema<LANES>(mn, mx, lane, s_part[0][wave], s_part[1][wave]);
+    __syncthreads();
+    // ---- 2. stored parameters; a thread per (threshold, channel)
+    constexpr int kEach = kWide ? 1 : L;
+    if (tid < kEach * kSlice) {
+      const int c = tid & (kSlice - 1), k = tid / kSlice + 1;
+      _Float16 lo = s_part[0][0][c], hi = s_part[1][0][c];
 #pragma unroll
-    for (int i = 0; i < P; ++i) {
-      uint32_t* to = dst + (size_t)(i * kTokens) * (unsigned)words;
-      const unsigned at = (unsigned)t_lane * (unsigned)words;
-      uint32_t w0, w1;
-      octet_words<BITS>(x[i], al, ri, al32, ri32, w0, w1);
-      if (t_lane < tokens - i * kTokens) {
-        if constexpr (BITS == 4) to[at + oct] = w0;
-        else *reinterpret_cast<v2u*>(to + (at + 2 * oct)) = (v2u){w0, w1};
+      for (int w = 1; w < kWavesQ; ++w) {
+        lo = (_Float16)fminf((float)lo, (float)s_part[0][w][c]);
+        hi = (_Float16)fmaxf((float)hi, (float)s_part[1][w][c]);
       }
-    }
-  } else {
-    v8h thr[L];
-#pragma unroll
-    for (int k = 0; k < L; ++k) thr[k] = *reinterpret_cast<const v8h*>(&s_thr[k][8 * oct]);
-    auto put = [&](int i) {
-      uint32_t* to = dst + (size_t)(i * kTokens) * (unsigned)words;
-      const unsigned at = (unsigned)t_lane * (unsigned)words;
-      uint32_t bits = octet_codes<BITS>(x[i], thr);
-      if constexpr (BITS == 1) {
-        bits <<= 24 - 8 * (oct & 3);
-        bits |= other_lane<0xB1>(bits);
-        bits |= other_lane<0x4E>(bits);
-        if ((oct & 3) == 0 && t_lane < tokens - i * kTokens) to[at + (oct >> 2)] = bits;
+      const uint16_t mbits = canonical_zero(__builtin_bit_cast(uint16_t, lo));
+      const double alpha = h_to_double(mbits);
+      const double range = ((double)(float)hi - alpha) + 0.0;
+      if (k == 1) {
+        const size_t meta = (size_t)group * d + c0 + c;
+        (one ? first.scale : second.scale)[meta] = (float)(range / (double)L);
+        (one ? first.minv : second.minv)[meta] = mbits;
+      }
+      if constexpr (kWide) {
+        s_alpha[c] = __builtin_bit_cast(_Float16, mbits);
+        s_rinv[c] = range > 0.0 ? (double)L / range : 0.0;
       } else {
-        bits <<= 16 - 16 * (oct & 1);
-        bits |= other_lane<0xB1>(bits);
-        if ((oct & 1) == 0 && t_lane < tokens - i * kTokens) to[at + (oct >> 1)] = bits;
+        s_thr[k - 1][c] = __builtin_bit_cast(_Float16, threshold_bits(alpha, range, k, L));
       }
-    };
-    if (more) {
+    }
+    __syncthreads();
+    // ---- 3. codes: BITS words per token and slice
+    const int words = d * BITS / 32;
+    uint32_t* dst = (one ? first.codes : second.codes) + tok0 * words + c0 / 32 * BITS;
+    if constexpr (kWide) {
+      double al[8], ri[8];
+      float al32[8], ri32[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        al32[j] = (float)s_alpha[8 * oct + j];
+        al[j] = (double)al32[j];
+        ri[j] = s_rinv[8 * oct + j];
+        ri32[j] = (float)ri[j];
+      }
+      static_assert(!ROUNDS, "one and two bits: with wider codes the loop spills");
 #pragma unroll
       for (int i = 0; i < P; ++i) {
-        put(i);
-        x[i] = load(next, i);
+        uint32_t* to = dst + (size_t)(i * kTokens) * (unsigned)words;
+        const unsigned at = (unsigned)t_lane * (unsigned)words;
+        uint32_t w0, w1;
+        octet_words<BITS>(x[i], al, ri, al32, ri32, w0, w1);
+        if (t_lane < tokens - i * kTokens) {
+          if constexpr (BITS == 4) to[at + oct] = w0;
+          else *reinterpret_cast<v2u*>(to + (at + 2 * oct)) = (v2u){w0, w1};
+        }
       }
     } else {
+      v8h thr[L];
 #pragma unroll
-      for (int i = 0; i < P; ++i) put(i);
+      for (int k = 0; k < L; ++k) thr[k] = *reinterpret_cast<const v8h*>(&s_thr[k][8 * oct]);
+      auto put = [&](int i) {
+        uint32_t* to = dst + (size_t)(i * kTokens) * (unsigned)words;
+        const unsigned at = (unsigned)t_lane * (unsigned)words;
+        uint32_t bits = octet_codes<BITS>(x[i], thr);
+        if constexpr (BITS == 1) {
+          bits <<= 24 - 8 * (oct & 3);
+          bits |= other_lane<0xB1>(bits);
+          bits |= other_lane<0x4E>(bits);
+          if ((oct & 3) == 0 && t_lane < tokens - i * kTokens) to[at + (oct >> 2)] = bits;
+        } else {
+          bits <<= 16 - 16 * (oct & 1);
+          bits |= other_lane<0xB1>(bits);
+          if ((oct & 1) == 0 && t_lane < tokens - i * kTokens) to[at + (oct >> 1)] = bits;
+        }
+      };
+      if (more) {
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+          put(i);
+          x[i] = load(next, i);
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < P; ++i) put(i);
+      }
     }
-  }
-  if (!more) return;
+    if (!more) return;
   }
 }
 
@@ -184,7 +184,7 @@ using SliceKernel = void (*)(const SliceArgs, const SliceArgs, int, int, int, in
 // (us, one-bit keys and values, 8 / 4 lanes: 512 rows x 300 tokens 17.1 / 27.3, 8 x 1000 5.7 / 4.5, 256 x 2000 with two
 // bits 86.6 / 70.6; 8 bits, 256 x 1500 83.5 / 95.1).  Beyond 2048 tokens 1024 threads; 24 registers of data per
 // thread instead are slower (64 x 3003 41.6 / 37.8).  (These are from before the codes took half the instructions; the kernels
-// chosen have since become faster by a tenth, the others were not measured again.)
+// chosen have since become faster by a tenth to a fifth, the others were not measured again.)
 // Where such a workgroup leaves no room for another (1024 threads) and there are more of them than CUs, one to a CU takes
 // its blocks in rounds: us, a workgroup per block / in rounds: 2 bits 64 x 3003 31.5 / 29.6, 256 x 3003 122 / 113, 96 x 2049
 // 36.0 / 32.0, 64 channels 128 x 3003 32.1 / 28.8; 1 bit 64 x 3003 24.8 / 24.5, 128 x 4000 67.0 / 63.3.  Not with 256 channels, eight

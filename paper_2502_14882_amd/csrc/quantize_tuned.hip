@@ -22,7 +22,7 @@ bool quantize_tuned_supported(int rows, int n_vis, int d, int bits, int axis, in
 //                 4 bits:  24 tokens 112 / 128, 28: 113 / 111, 31: 116 / 102
 //                 8 bits:  1 token 302 / 2605, 16: 115 / 193, 24: 117 / 135, 28: 118 / 118, 31: 122 / 108
 //   256 channels, 2 bits:  16 tokens 286 / 260; 8 rows: 13.6 / 19.7, 24: 16.1 / 15.2, 31: 17.5 / 13.1
-// The line is where the slower of 8, 64 and 256 rows broke even when 1 and 2 bits took a quarter longer on the tile
+// The line is where the slower of 8, 64 and 256 rows broke even when 1 and 2 bits took a fifth to a quarter longer on the tile
 // kernels (1 bit 12 tokens 118 / 121, 2 bits 20: 111 / 127); since then groups of 12 to 15 tokens of 1 bit and of 20 to 23 of 2 bits stay
 // with the slower kernel (8 rows x 14 tokens, 1 bit 10.7 / 8.0, x 20, 2 bits 11.6 / 9.2).
 bool quantize_tile_is_faster(int d, int bits, int axis, int group) {
