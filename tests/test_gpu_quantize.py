@@ -246,10 +246,11 @@ def test_random_layouts_on_the_tuned_quantizer(kernel_path):
 
 
 @pytest.mark.tuned_only
-def test_traffic_measurement_aid_runs(kernel_path):
+@pytest.mark.parametrize("n_tiles", [37, 64, 165])       # tiles change their order by spans of 64
+def test_traffic_measurement_aid_runs(kernel_path, n_tiles):
     """The quantizer's traffic skeleton (measurement aid) reads its tiles and writes the byte counts
     it is asked for, and nothing beyond them."""
-    n_tiles, cb, mb = 37, 2048, 768
+    cb, mb = 2048, 768
     x = torch.randn(n_tiles * 128, 128, device="cuda").half()
     codes = torch.full((n_tiles * cb + 64,), 0xA5, dtype=torch.uint8, device="cuda")
     meta = torch.full((n_tiles * mb + 64,), 0xA5, dtype=torch.uint8, device="cuda")
